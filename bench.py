@@ -49,20 +49,17 @@ FP64_PEAK_TFLOPS = 78.6
 # path (each datum read or written once; the packed half spectrum of nine
 # components is 9 x n^3/2 complex = 36 B per voxel)
 PASS_BYTES_F32 = {
-    # K (81 floats), r, p_old, x in; p, K:p, x out (the previous iteration's
-    # x += alpha p_old rides on the direction kernel)
-    "matvec_kp": 4 * (81 + 9 + 9 + 9 + 9 + 9 + 9),
+    "matvec_kp": 4 * (81 + 9 + 9),                  # K, p in; K:p out
     "matvec_pass_a": 4 * 9 + 36,                    # K:p in, half spectrum out
-    "matvec_pass_b": 36 + 36,                       # spectrum in and out
-    "matvec_pass_c": 36 + 4 * 9 + 4 * 9,            # spectrum, r in; r out
+    "matvec_pass_b": 36 + 2 * 12,                   # spectrum in, rho in and out
+    "matvec_pass_c": 24 + 4 * 9,                    # six planes in, p out
+    # direction: rho in, pi and xi in and out, six planes out
+    "cg_update": 12 + 2 * 12 + 2 * 12 + 24,
 }
-# the same with the direction step and K:p folded into pass A (fused
-# schedule): K, r, p_old, x in; p, x, half spectrum out; no K:p round trip
-PASS_BYTES_F32_FUSED = {
-    "matvec_pass_a": 4 * (81 + 9 + 9 + 9 + 9 + 9) + 36,
-    "matvec_pass_b": 36 + 36,
-    "matvec_pass_c": 36 + 4 * 9 + 4 * 9,
-}
+# the same with K:p folded into pass A (fused schedule): no K:p round trip
+PASS_BYTES_F32_FUSED = dict(
+    {k: v for k, v in PASS_BYTES_F32.items() if k != "matvec_kp"},
+    matvec_pass_a=4 * (81 + 9) + 36)
 
 
 def pass_bytes(fused):
@@ -84,7 +81,7 @@ def live_classes(fused):
 # P) and per particle voxel
 RM_FLOPS = {"eval64": 1206, "eval32": 72, "step64": 60, "step32": 2350,
             "crystal64": 825, "particle64": 90}
-# kernel classes timed live in the timed region: the K:p direction kernel
+# kernel classes timed live in the timed region: the K:p kernel
 # (the dominant kernel, on a sample of its launches) and the return mapping
 # (every launch: its ALU roofline needs the local Newton steps of the same
 # launches).  Every class, the tangent, the FP64 residual and the three FFT
@@ -312,13 +309,13 @@ def cg_pass_report(kern, N, fused=False):
         gbs = N * b / (ms * 1e-3) / 1e9
         out[k] = dict(us=round(1e3 * ms, 2), bytes_per_voxel=b,
                       gbps=round(gbs, 1), frac=round(gbs / HBM_PEAK_GBS, 3))
-    mv = ("matvec_pass_a", "matvec_pass_b", "matvec_pass_c")
+    mv = ("matvec_pass_a", "matvec_pass_b", "matvec_pass_c", "cg_update")
     ms = sum(kern[k] for k in mv)
     gbs = N * sum(pb[k] for k in mv) / (ms * 1e-3) / 1e9
     out["fft_projection_passes"] = dict(us=round(1e3 * ms, 2), gbps=round(gbs, 1),
                                         frac=round(gbs / HBM_PEAK_GBS, 3))
     if fused:
-        out["fft_projection_passes"]["includes"] = "direction step and K:p (pass A)"
+        out["fft_projection_passes"]["includes"] = "K:p (pass A)"
     ms_all = sum(kern[k] for k in pb)
     out["cg_iteration_us"] = round(1e3 * ms_all, 2)
     return out
@@ -967,7 +964,8 @@ def live_report(live, rmc, N, cg_total, sample=None, fused=False, seen=None):
     # matvec passes: bytes actually streamed = per-voxel bytes x voxels x
     # CG iterations done (launches past convergence in a replayed chunk
     # return at once and move nothing)
-    mv = ("matvec_pass_a", "matvec_pass_b", "matvec_pass_c")  # FFT passes
+    mv = ("matvec_pass_a", "matvec_pass_b", "matvec_pass_c",  # FFT passes
+          "cg_update")
     mv_ms = sum(total_ms[k] for k in mv)
     fft_gbs = (N * cg_total * sum(pb[k] for k in mv)
                / (mv_ms * 1e-3) / 1e9) if all(launches[k] for k in mv) else None

@@ -392,17 +392,17 @@ rve_status rve_debug_set_field(rve_t h, int32_t field, const double* src,
    (needs at least one committed increment).  ms_out[count], count <= 8,
    indexed by kernel class:
      0 matvec pass A (forward z/y FFTs of K:p; publishes the CG step
-       alpha = r.r / p.(K:p), equal to r.r / p.G(K:p) since p lies in the
+       alpha = r.z / p.(K:p), equal to r.z / p.G(K:p) since p lies in the
        range of the orthogonal projection G),
-     1 pass B (x FFTs and the projection of Sec. 2.2),
-     2 pass C (inverse y/z FFTs, r -= alpha G(K:p) and the new r.r),
-     3 unused (the CG vector update rides on classes 2 and 7; reported
-       as 0),
+     1 pass B (forward x FFT, r -= alpha G(K:p) in Fourier space and the
+       norms r.r and r.z),
+     2 pass C (inverse y/z FFTs of the direction p),
+     3 CG direction (z = M r, p = z + beta p, the previous iteration's
+       x += alpha p, inverse x FFT),
      4 FP64 return mapping (Sec. 3.2, Eq. 22),
      5 tangent (Eq. 13),
      6 FP64 residual G(P) (Eq. 11; three kernels),
-     7 CG direction, the previous iteration's x += alpha p and K:p
-       (Eqs. 15-16).
+     7 K:p (Eqs. 15-16; 0 when it is folded into pass A).
    Only scratch buffers are written; the committed state is untouched. */
 rve_status rve_bench_kernels(rve_t h, int32_t reps, double* ms_out,
                              int32_t count);
@@ -441,14 +441,13 @@ rve_status rve_get_return_map_counts(rve_t h, int64_t out[4], int32_t reset);
 
 /* Schedule of the CG matvec G(K : p) (Sec. 2.1, Eqs. 15-16): cpb
    components of the tensor field per slab block in the z/y-transform
-   passes (1 or 3), tt kz columns per block in the x-transform and
-   projection pass (4, 8 or 16), and fused (0 or 1): whether the CG
-   direction step and K : p run in their own streaming kernel (0) or inside
-   the first transform pass (1), which then forms p = r + beta p_old for
-   all nine components of each voxel of its slab and transforms its own
-   rows of K : p.  Both give the same CG up to the order of the FP64 sum of
-   p . (K:p).  By default (0, 0, -) the handle times every valid schedule
-   once on its own buffers at the first CG solve and keeps the fastest.
+   passes (1 or 3), tt kz columns per block in the x-transform passes (4, 8
+   or 16), and fused (0 or 1): whether K : p runs in its own streaming
+   kernel (0) or inside the forward z/y transform (1), each block of which
+   then forms its own rows of K : p.  All give the same CG up to the order
+   of the FP64 sums.  By default (0, 0, -) the handle times the schedules of
+   its grid edge (both cpb, both fused) once on its own buffers at the first
+   CG solve and keeps the fastest.
    rve_set_fft_schedule forces one (or (0, 0, -) to tune again);
    RVE_EINVAL when the schedule does not exist for the grid and precision or
    fused is not 0 or 1.  rve_get_fft_schedule writes (cpb, tt, fused) in use
@@ -595,10 +594,10 @@ rve_status rve_batch_debug_apply_G(rve_batch_t h, const double* in,
                                    double* out);
 /* Per-grid-edge schedule of the batched CG matvec (Sec. 2.1, Eqs. 15-16):
    cpb components per slab block (1 or 3) and tt kz columns per pencil block
-   (4, 8 or 16), as for a single RVE (the direction step is always part of
-   the first pass in a batch).  Unless forced, every edge of the batch is
+   (4, 8 or 16), as for a single RVE (K : p is always formed inside the
+   forward transform in a batch).  Unless forced, every edge of the batch is
    tuned at the first increment (or by rve_batch_tune_fft_schedule): each
-   valid candidate times one matvec of that edge's RVEs alone through the
+   candidate times one CG iteration of that edge's RVEs alone through the
    batched passes, and the fastest is kept.  rve_batch_set_fft_schedule
    forces edge's schedule, or with (0, 0) tunes it again at the next
    increment; rve_batch_get_fft_schedule writes edge's (cpb, tt) and in *ms

@@ -4,6 +4,7 @@
 // once with per-RVE convergence: an RVE that has converged (or failed)
 // leaves the work of the following iterations.
 #include "batch.hpp"
+#include "cg_scalars.hpp"
 #include "newton.hpp"
 
 #include <algorithm>
@@ -82,11 +83,10 @@ BatchEngine::BatchEngine(const rve_config& cfg, int count, const int32_t* n)
   r64_ = (double*)alloc(f9);
   dFt_ = (double*)alloc(f9);
   K_ = alloc(81 * Nt_ * tsz);
-  x_ = alloc(9 * Nt_ * tsz);
-  r_ = alloc(9 * Nt_ * tsz);
-  p0_ = alloc(9 * Nt_ * tsz);
-  p1_ = alloc(9 * Nt_ * tsz);
-  Ap_ = alloc(9 * Nt_ * tsz);
+  rho_ = alloc(3 * Nt_ * tsz);
+  pi_ = alloc(3 * Nt_ * tsz);
+  xi_ = alloc(3 * Nt_ * tsz);
+  p_ = alloc(9 * Nt_ * tsz);
   spec_ = alloc(St_ * 2 * tsz);
   spec64_ = fp64_ ? spec_ : alloc(St_ * 2 * sizeof(double));
   phase_ = (int32_t*)alloc(Nt_ * sizeof(int32_t));
@@ -122,47 +122,27 @@ BatchEngine::BatchEngine(const rve_config& cfg, int count, const int32_t* n)
   for (int b = 0; b < B_; ++b) psn += 9 * n_[b];
   psum_ = (double*)alloc(psn * sizeof(double));
   psq_ = (double*)alloc(psn * sizeof(double));
-  // partial arenas: pass-C partials per RVE (room for one component per
-  // slab block, any schedule), then elementwise partials
-  int64_t ppass = 0;
-  for (int b = 0; b < B_; ++b) ppass += 9 * n_[b];
-  std::vector<SegItem> seg(B_);
-  int segb = 0;
-  for (int b = 0; b < B_; ++b) {
-    const int64_t n9 = 9 * (int64_t)n_[b] * n_[b] * n_[b];
-    int nb = (int)((n9 + kBlock * 8 - 1) / (kBlock * 8));
-    nb = nb < 1 ? 1 : (nb > 512 ? 512 : nb);
-    seg[b].off = off_[b];
-    seg[b].n9 = n9;
-    seg[b].blk0 = segb;
-    seg[b].nblk = nb;
-    segb += nb;
-  }
-  seg_blocks_ = segb;
-  partials_ = (double*)alloc((ppass + segb) * sizeof(double));
-  std::vector<RedItem> rseg(B_);
-  for (int b = 0; b < B_; ++b) {
-    seg[b].partial = partials_ + ppass + seg[b].blk0;
-    seg[b].sc = sc_ + b;
-    rseg[b] = RedItem{seg[b].partial, seg[b].nblk, nullptr, nullptr, 0, 0.0};
-  }
+  // partials per RVE, room for any schedule: pass A's p.(K:p) (one component
+  // per slab block), the CG pencils' (four kz columns per block), those of
+  // the FP64 residual
+  int64_t pp = 0;
+  for (int b = 0; b < B_; ++b)
+    pp += 9 * n_[b] + 3 * cg_pencil_blocks(n_[b], 4) + 3 * residual_blocks(n_[b]);
+  partials_ = (double*)alloc(pp * sizeof(double));
   items32_ = alloc(B_ * sizeof(SpecItem<float>));
   items64_ = alloc(B_ * sizeof(SpecItem<double>));
   tune_items_ = alloc(B_ * std::max(sizeof(SpecItem<float>), sizeof(SpecItem<double>)));
-  seg_ = (SegItem*)alloc(B_ * sizeof(SegItem));
-  red_inv32_ = (RedItem*)alloc(B_ * sizeof(RedItem));
-  red_inv64_ = (RedItem*)alloc(B_ * sizeof(RedItem));
-  red_seg_ = (RedItem*)alloc(B_ * sizeof(RedItem));
-  RVE_HIP(hipMemcpyAsync(seg_, seg.data(), B_ * sizeof(SegItem), hipMemcpyHostToDevice, st_));
-  RVE_HIP(hipMemcpyAsync(red_seg_, rseg.data(), B_ * sizeof(RedItem), hipMemcpyHostToDevice, st_));
+  red_ = (RedItem*)alloc(B_ * sizeof(RedItem));
   std::vector<uint8_t> vr(Nt_);
   for (int b = 0; b < B_; ++b)
     std::memset(vr.data() + off_[b], b, (size_t)n_[b] * n_[b] * n_[b]);
   RVE_HIP(hipMemcpyAsync(vrve_, vr.data(), Nt_, hipMemcpyHostToDevice, st_));
-  // the timed matvecs of the schedule tuner read these before the solver
+  // the timed iterations of the schedule tuner read these before the solver
   // writes them: start from zeros
-  for (void* f : {K_, r_, p0_, p1_})
-    RVE_HIP(hipMemsetAsync(f, 0, (f == K_ ? 81 : 9) * Nt_ * tsz, st_));
+  RVE_HIP(hipMemsetAsync(K_, 0, 81 * Nt_ * tsz, st_));
+  for (void* f : {rho_, pi_, xi_})
+    RVE_HIP(hipMemsetAsync(f, 0, 3 * Nt_ * tsz, st_));
+  RVE_HIP(hipMemsetAsync(p_, 0, 9 * Nt_ * tsz, st_));
   RVE_HIP(hipStreamSynchronize(st_));
 
   if (cfg_.use_graph) {
@@ -200,69 +180,72 @@ BatchEngine::BatchEngine(const rve_config& cfg, int count, const int32_t* n)
 void BatchEngine::build_tables() {
   std::vector<SpecItem<float>> it32(B_);
   std::vector<SpecItem<double>> it64(B_);
-  std::vector<RedItem> ri32(B_), ri64(B_);
-  int a32 = 0, b32 = 0, a64 = 0, b64 = 0;
+  std::vector<RedItem> red(B_);
   int64_t pp = 0, pso = 0;
-  ldsA32_ = ldsB32_ = ldsA64_ = ldsB64_ = 0;
+  grid32_ = grid64_ = BatchGrid{};
   cpbs32_ = cpbs64_ = 0;
   for (int b = 0; b < B_; ++b) {
     const int nb = n_[b];
-    const int64_t Nb = (int64_t)nb * nb * nb;
-    auto fill = [&](auto& it, int& accA, int& accB, bool dbl, size_t& la,
-                    size_t& lb, RedItem& ri, int& cpbs) {
+    auto fill = [&](auto& it, BatchGrid& g, bool dbl, int& cpbs) {
       using T = std::remove_reference_t<decltype(it.tw[0].x)>;
       int cpb = 0, tt = 0;
       default_schedule(nb, dbl, cpb, tt);
       if (dbl == fp64_) {
+        tt = cg_tile(nb);
         auto f = sched_.find(nb);
         if (f != sched_.end() && f->second[0]) {
           cpb = f->second[0];
           tt = f->second[1];
         }
       }
-      const int sA = slab_blocks(nb, dbl, cpb);
       cpbs |= cpb == 3 ? 2 : 1;
       it.n = nb;
       it.cpb = cpb;
       it.tt = tt;
-      it.blk[0] = accA;
-      it.blk[1] = accB;
+      it.npen = cg_pencil_blocks(nb, tt);
+      it.blk[0] = g.A;
+      it.blk[1] = g.B;
+      it.blk[2] = 3 * g.B;
       it.off = off_[b];
       it.soff = soff_[b];
       it.sc = sc_ + b;
-      it.partial = partials_ + pp;
       it.psum = psum_ + pso;
       it.psq = psq_ + pso;
       it.tw = (const cplx<T>*)(dbl ? tw64_ : tw32_) + twoff_[b];
       it.vt = (const T*)(dbl ? vt64_ : vt32_) + vtoff_[b];
-      accA += sA;
-      accB += pencil_blocks(nb, dbl, tt);
+      it.pkp = partials_ + pp;
+      it.prr = it.pkp + 9 * nb;
+      g.A += slab_blocks(nb, dbl, cpb);
+      g.B += it.npen;
       size_t s1, s2;
       batch_lds<T>(nb, cpb, tt, s1, s2);
-      la = std::max(la, s1);
-      lb = std::max(lb, s2);
-      ri = RedItem{partials_ + pp, sA, psum_ + pso, psq_ + pso, nb,
-                   1.0 / (double)Nb};
+      g.ldsA = std::max(g.ldsA, s1);
+      g.ldsB = std::max(g.ldsB, s2);
     };
-    fill(it32[b], a32, b32, false, ldsA32_, ldsB32_, ri32[b], cpbs32_);
-    fill(it64[b], a64, b64, true, ldsA64_, ldsB64_, ri64[b], cpbs64_);
-    pp += 9 * nb;
+    fill(it32[b], grid32_, false, cpbs32_);
+    fill(it64[b], grid64_, true, cpbs64_);
+    // the residual's partials: the start of a solve (rr0, rz0) is reduced
+    // from them before the CG passes write theirs, in FP64 mode in the same
+    // place
+    if (!fp64_)
+      it64[b].prr = partials_ + pp + 9 * nb + 3 * cg_pencil_blocks(nb, 4);
+    red[b] = RedItem{it64[b].prr, it64[b].npen, it64[b].psum, it64[b].psq, nb,
+                     1.0 / ((double)nb * nb * nb)};
+    pp += 9 * nb + 3 * cg_pencil_blocks(nb, 4) + 3 * residual_blocks(nb);
     pso += 9 * nb;
   }
-  if (ldsA32_ > 65536 || ldsB32_ > 65536) batch_allow_lds<float>(ldsA32_, ldsB32_);
-  if (ldsA64_ > 65536 || ldsB64_ > 65536) batch_allow_lds<double>(ldsA64_, ldsB64_);
-  blocksA32_ = a32;
-  blocksB32_ = b32;
-  blocksA64_ = a64;
-  blocksB64_ = b64;
+  if (grid32_.ldsA > 65536 || grid32_.ldsB > 65536)
+    batch_allow_lds<float>(grid32_.ldsA, grid32_.ldsB);
+  if (grid64_.ldsA > 65536 || grid64_.ldsB > 65536)
+    batch_allow_lds<double>(grid64_.ldsA, grid64_.ldsB);
   host_it32_ = it32;
   host_it64_ = it64;
   RVE_HIP(hipMemcpyAsync(items32_, it32.data(), B_ * sizeof(SpecItem<float>), hipMemcpyHostToDevice, st_));
   RVE_HIP(hipMemcpyAsync(items64_, it64.data(), B_ * sizeof(SpecItem<double>), hipMemcpyHostToDevice, st_));
-  RVE_HIP(hipMemcpyAsync(red_inv32_, ri32.data(), B_ * sizeof(RedItem), hipMemcpyHostToDevice, st_));
-  RVE_HIP(hipMemcpyAsync(red_inv64_, ri64.data(), B_ * sizeof(RedItem), hipMemcpyHostToDevice, st_));
+  RVE_HIP(hipMemcpyAsync(red_, red.data(), B_ * sizeof(RedItem), hipMemcpyHostToDevice, st_));
   if (cfg_.use_graph) {
-    persist_lds_ = fp64_ ? std::max(ldsA64_, ldsB64_) : std::max(ldsA32_, ldsB32_);
+    const BatchGrid& g = fp64_ ? grid64_ : grid32_;
+    persist_lds_ = std::max(g.ldsA, g.ldsB);
     persist_grid_ = fp64_ ? cg_batch_persistent_grid<double>(persist_lds_)
                           : cg_batch_persistent_grid<float>(persist_lds_);
   }
@@ -280,13 +263,14 @@ void BatchEngine::build_tables() {
 }
 
 // Per grid edge of the batch (edges with a forced schedule excepted), the
-// fastest schedule of the CG matvec G(K : p) (components per slab block,
-// kz columns per pencil block): every valid candidate times one matvec of
+// fastest schedule of the CG iteration (components per slab block; the kz
+// columns per pencil block follow cg_tile): every candidate times one
+// iteration of
 // this edge's RVEs alone, through the batched passes, with every RVE
-// active and beta = 0 (p = r + 0 p_old: the traffic of an iteration after
-// the first); three interleaved rounds, the best of each.  The scalars are
-// restored afterwards; the passes overwrite only the direction, the
-// spectrum, G(K:p) and the partials, all rewritten by the next solve.
+// active and alpha = beta = 0; three interleaved rounds, the best of each.
+// The scalars are restored afterwards; the passes keep the residual and
+// overwrite only the direction, the iterate, the spectrum and the partials,
+// all rewritten by the next solve.
 template <typename T>
 void BatchEngine::autotune() {
   const bool dbl = sizeof(T) == sizeof(double);
@@ -295,7 +279,7 @@ void BatchEngine::autotune() {
   for (int b = 0; b < B_; ++b) {
     sc_host_[b].done = 0;
     sc_host_[b].inactive = 0;
-    sc_host_[b].first = 0;
+    sc_host_[b].alpha = 0.0;
     sc_host_[b].beta = 0.0;
   }
   upload_scalars();
@@ -313,27 +297,28 @@ void BatchEngine::autotune() {
     struct Cand {
       int cpb, tt;
       std::vector<SpecItem<T>> items;
-      int bA, bB;
-      size_t lA, lB;
+      BatchGrid g;
     };
     std::vector<Cand> cand;
     for (int cpb : {1, 3})
-      for (int tt : {4, 8, 16}) {
+      for (int tt : {cg_tile(e)}) {
         if (!schedule_valid(e, dbl, cpb, tt)) continue;
-        Cand c{cpb, tt, {}, 0, 0, 0, 0};
+        Cand c{cpb, tt, {}, {}};
         for (int b = 0; b < B_; ++b) {
           if (n_[b] != e) continue;
           SpecItem<T> it = full[b];
           it.cpb = cpb;
           it.tt = tt;
-          it.blk[0] = c.bA;
-          it.blk[1] = c.bB;
-          c.bA += slab_blocks(e, dbl, cpb);
-          c.bB += pencil_blocks(e, dbl, tt);
+          it.npen = cg_pencil_blocks(e, tt);
+          it.blk[0] = c.g.A;
+          it.blk[1] = c.g.B;
+          c.g.A += slab_blocks(e, dbl, cpb);
+          c.g.B += it.npen;
           c.items.push_back(it);
         }
-        batch_lds<T>(e, cpb, tt, c.lA, c.lB);
-        if (c.lA > 65536 || c.lB > 65536) batch_allow_lds<T>(c.lA, c.lB);
+        batch_lds<T>(e, cpb, tt, c.g.ldsA, c.g.ldsB);
+        if (c.g.ldsA > 65536 || c.g.ldsB > 65536)
+          batch_allow_lds<T>(c.g.ldsA, c.g.ldsB);
         cand.push_back(std::move(c));
       }
     std::vector<float> best(cand.size(), 0.f);
@@ -347,10 +332,8 @@ void BatchEngine::autotune() {
         bs.items = (const SpecItem<T>*)tune_items_;
         bs.nitems = (int)cand[c].items.size();
         bs.cpbs = cand[c].cpb == 3 ? 2 : 1;
-        auto matvec = [&] {
-          launch_G_batch<T>(bs, SRC_KP, (T*)Ap_, nullptr, cand[c].bA,
-                            cand[c].bB, cand[c].lA, cand[c].lB, st_);
-        };
+        bs.timing = 1;
+        auto matvec = [&] { launch_cg_batch<T>(bs, cand[c].g, st_); };
         matvec();  // untimed first launch
         RVE_HIP(hipEventRecord(ev[0], st_));
         for (int i = 0; i < reps; ++i) matvec();
@@ -505,6 +488,7 @@ void BatchEngine::set_microstructure(int b, const int32_t* phase, int32_t G,
   } else {
     for (int i = 0; i < RVE_NPARAMS; ++i) params_[i] = params[i];
     have_params_ = true;
+    prec_ = cg_preconditioner(params_);
   }
   // the label table concatenates the RVEs' tables: labels of RVE k start
   // at label_off_[k]
@@ -579,12 +563,16 @@ BatchSpec<T> BatchEngine::spec(bool cg, int parity) const {
   b.nitems = B_;
   b.cpbs = dbl ? cpbs64_ : cpbs32_;
   b.cs = Nt_;
+  b.prec = prec_;
   if (cg) {
     b.K = (const T*)K_;
-    b.r = (const T*)r_;
-    b.p_old = (const T*)(parity ? p1_ : p0_);
-    b.p_new = (T*)(parity ? p0_ : p1_);
+    b.field = (const T*)p_;
+    b.p = (T*)p_;
     b.spec = (cplx<T>*)spec_;
+    b.rho = (cplx<T>*)rho_;
+    b.pi = (cplx<T>*)pi_;
+    b.xi = (cplx<T>*)xi_;
+    b.parity = parity;
   } else {
     b.field = (const T*)P_;
     b.spec = (cplx<T>*)spec64_;
@@ -594,15 +582,8 @@ BatchSpec<T> BatchEngine::spec(bool cg, int parity) const {
 
 template <typename T>
 void BatchEngine::cg_iteration(int parity) {
-  const bool dbl = sizeof(T) == sizeof(double);
-  BatchSpec<T> b = spec<T>(true, parity);
-  launch_G_batch<T>(b, SRC_KP, (T*)Ap_, nullptr, dbl ? blocksA64_ : blocksA32_,
-                    dbl ? blocksB64_ : blocksB32_, dbl ? ldsA64_ : ldsA32_,
-                    dbl ? ldsB64_ : ldsB32_, st_);
-  launch_reduce_batch(RED_ALPHA, dbl ? red_inv64_ : red_inv32_, B_, sc_, st_);
-  launch_cg_update_batch<T>(seg_, B_, seg_blocks_, Nt_, (T*)x_, (T*)r_,
-                            (const T*)b.p_new, (const T*)Ap_, st_);
-  launch_reduce_batch(RED_BETA, red_seg_, B_, sc_, st_);
+  launch_cg_batch<T>(spec<T>(true, parity), sizeof(T) == 8 ? grid64_ : grid32_,
+                     st_);
 }
 
 template <typename T>
@@ -612,14 +593,10 @@ void BatchEngine::cg_solve(std::vector<int>& iters) {
     // equilibrium tolerance needs from this RVE's residual)
     const double eta = forcing_eta(cfg_.cg_forcing, cfg_.cg_tol,
                                    cfg_.newton_tol, rel_[b]);
-    sc_host_[b].max_iters = cfg_.cg_max_iter;
-    sc_host_[b].eta2bb = eta * eta;
+    cg_start(&sc_host_[b], cfg_.cg_max_iter, eta);
     sc_host_[b].done = sc_host_[b].inactive;
   }
   upload_scalars();
-  launch_cg_init_batch<T>(seg_, B_, seg_blocks_, Nt_, r64_, (T*)r_, (T*)x_, st_);
-  launch_reduce_batch(RED_INIT, red_seg_, B_, sc_, st_);
-  RVE_HIP(hipGetLastError());
   int parity = 0;
   for (;;) {
     for (int j = 0; j < cfg_.cg_chunk; ++j) {
@@ -632,7 +609,35 @@ void BatchEngine::cg_solve(std::vector<int>& iters) {
     for (int b = 0; b < B_; ++b) all = all && sc_host_[b].done;
     if (all) break;
   }
+  launch_cg_final_batch<T>(spec<T>(true, 0), F_,
+                           sizeof(T) == 8 ? grid64_ : grid32_, st_);
   for (int b = 0; b < B_; ++b) iters[b] = sc_host_[b].inactive ? 0 : sc_host_[b].iters;
+}
+
+void BatchEngine::evaluate(const LawParams& lp, const double* dg_start) {
+  ConstArgs a{};
+  a.F = F_;
+  a.Fpi0 = Fpi_c_;
+  a.chi0 = chi_c_;
+  a.dg0 = dg_start;
+  a.phase = phase_;
+  a.table = table_;
+  a.P = P_;
+  a.Fpi = Fpi_t_;
+  a.chi = chi_t_;
+  a.dg = dg_t_;
+  a.fails = nullptr;
+  a.lp = lp;
+  a.N = Nt_;
+  a.vrve = vrve_;
+  a.scs = sc_;
+  launch_return_map(a, st_);
+  const BatchSpec<double> rs = spec<double>(false, 0);
+  if (fp64_)
+    launch_residual_batch<double>(rs, (cplx<double>*)rho_, grid64_, st_);
+  else
+    launch_residual_batch<float>(rs, (cplx<float>*)rho_, grid64_, st_);
+  launch_reduce_batch(red_, B_, sc_, st_);
 }
 
 int BatchEngine::increment(const double* Fbar_all, double dt,
@@ -670,27 +675,7 @@ int BatchEngine::increment(const double* Fbar_all, double dt,
   for (int it = 0; it <= cfg_.newton_max_iter; ++it) {
     for (int b = 0; b < B_; ++b) sc_host_[b].fails = 0;
     upload_scalars();
-    ConstArgs a{};
-    a.F = F_;
-    a.Fpi0 = Fpi_c_;
-    a.chi0 = chi_c_;
-    a.dg0 = dg_start;
-    a.phase = phase_;
-    a.table = table_;
-    a.P = P_;
-    a.Fpi = Fpi_t_;
-    a.chi = chi_t_;
-    a.dg = dg_t_;
-    a.fails = nullptr;
-    a.lp = lp;
-    a.N = Nt_;
-    a.vrve = vrve_;
-    a.scs = sc_;
-    launch_return_map(a, st_);
-    BatchSpec<double> rs = spec<double>(false, 0);
-    launch_G_batch<double>(rs, SRC_FIELD, nullptr, r64_, blocksA64_, blocksB64_,
-                           ldsA64_, ldsB64_, st_);
-    launch_reduce_batch(RED_RESID, red_inv64_, B_, sc_, st_);
+    evaluate(lp, dg_start);
     RVE_HIP(hipGetLastError());
     read_scalars();
     bool any = false;
@@ -723,12 +708,10 @@ int BatchEngine::increment(const double* Fbar_all, double dt,
       TangentArgs<double> t{F_, Fpi_c_, chi_c_, dg_t_, phase_, table_, (double*)K_, lp, Nt_, vrve_, sc_};
       launch_tangent<double>(t, st_);
       cg_solve<double>(iters);
-      launch_add_to_F<double>(F_, (const double*)x_, 9 * Nt_, st_);
     } else {
       TangentArgs<float> t{F_, Fpi_c_, chi_c_, dg_t_, phase_, table_, (float*)K_, lp, Nt_, vrve_, sc_};
       launch_tangent<float>(t, st_);
       cg_solve<float>(iters);
-      launch_add_to_F<float>(F_, (const float*)x_, 9 * Nt_, st_);
     }
     RVE_HIP(hipGetLastError());
     for (int b = 0; b < B_; ++b) {
@@ -800,27 +783,7 @@ int BatchEngine::increment(const double* Fbar_all, double dt,
 // (slips from dg_start), FP64 residual G(P) and norms, the device decision.
 void BatchEngine::newton_eval_device(int it, const LawParams& lp,
                                      const double* dg_start) {
-  ConstArgs a{};
-  a.F = F_;
-  a.Fpi0 = Fpi_c_;
-  a.chi0 = chi_c_;
-  a.dg0 = dg_start;
-  a.phase = phase_;
-  a.table = table_;
-  a.P = P_;
-  a.Fpi = Fpi_t_;
-  a.chi = chi_t_;
-  a.dg = dg_t_;
-  a.fails = nullptr;
-  a.lp = lp;
-  a.N = Nt_;
-  a.vrve = vrve_;
-  a.scs = sc_;
-  launch_return_map(a, st_);
-  BatchSpec<double> rs = spec<double>(false, 0);
-  launch_G_batch<double>(rs, SRC_FIELD, nullptr, r64_, blocksA64_, blocksB64_,
-                         ldsA64_, ldsB64_, st_);
-  launch_reduce_batch(RED_RESID, red_inv64_, B_, sc_, st_);
+  evaluate(lp, dg_start);
   NewtonCtl ctl{cfg_.newton_tol, cfg_.cg_tol, cfg_.newton_max_iter,
                 cfg_.cg_max_iter, cfg_.cg_forcing};
   launch_newton_control_batch(sc_, log_, B_, it, ctl, st_);
@@ -831,34 +794,24 @@ void BatchEngine::newton_eval_device(int it, const LawParams& lp,
 template <typename T>
 void BatchEngine::newton_solve_device(int it, const LawParams& lp) {
   (void)it;
-  const bool dbl = sizeof(T) == sizeof(double);
+  const BatchGrid& g = sizeof(T) == sizeof(double) ? grid64_ : grid32_;
   TangentArgs<T> t{F_, Fpi_c_, chi_c_, dg_t_, phase_, table_, (T*)K_, lp, Nt_,
                    vrve_, sc_};
   launch_tangent<T>(t, st_);
-  launch_cg_init_batch<T>(seg_, B_, seg_blocks_, Nt_, r64_, (T*)r_, (T*)x_, st_);
-  launch_reduce_batch(RED_INIT, red_seg_, B_, sc_, st_);
   BatchCG<T> c{};
   c.even = spec<T>(true, 0);
   c.odd = spec<T>(true, 1);
-  c.seg = seg_;
-  c.seg_blocks = seg_blocks_;
-  c.red_inv = dbl ? red_inv64_ : red_inv32_;
-  c.red_seg = red_seg_;
   c.scs = sc_;
   c.nitems = B_;
-  c.blocksA = dbl ? blocksA64_ : blocksA32_;
-  c.blocksB = dbl ? blocksB64_ : blocksB32_;
-  c.cs = Nt_;
-  c.x = (T*)x_;
-  c.r = (T*)r_;
-  c.Ap = (T*)Ap_;
+  c.blocksA = g.A;
+  c.blocksB = g.B;
   c.max_iters = cfg_.cg_max_iter + 1;
   c.bar = bar_;
   c.err = (int*)(bar_ + kBatchBarWords);
   // arrival counts to zero (the generation may keep its value; the flag too)
   launch_fill_i32((int32_t*)bar_ + 1, 0, kBatchBarWords - 1, st_);
   launch_cg_batch_persistent<T>(c, persist_grid_, persist_lds_, st_);
-  launch_add_to_F<T>(F_, (const T*)x_, 9 * Nt_, st_);
+  launch_cg_final_batch<T>(c.even, F_, g, st_);
 }
 
 void BatchEngine::read_logs() {
@@ -1028,19 +981,17 @@ void BatchEngine::debug_apply_G(const double* in, double* out) {
     rs.cs = Nt_;
     rs.field = r64_;
     rs.spec = (cplx<double>*)spec64_;
-    launch_G_batch<double>(rs, SRC_FIELD, nullptr, P_, blocksA64_, blocksB64_,
-                           ldsA64_, ldsB64_, st_);
+    launch_G_batch<double>(rs, P_, grid64_, st_);
   } else {
-    launch_convert<float>(r64_, (float*)x_, 9 * Nt_, st_);
+    launch_convert<float>(r64_, (float*)p_, 9 * Nt_, st_);
     BatchSpec<float> rs{};
     rs.items = (const SpecItem<float>*)items32_;
     rs.nitems = B_;
     rs.cpbs = cpbs32_;
     rs.cs = Nt_;
-    rs.field = (const float*)x_;
+    rs.field = (const float*)p_;
     rs.spec = (cplx<float>*)spec_;
-    launch_G_batch<float>(rs, SRC_FIELD, nullptr, P_, blocksA32_, blocksB32_,
-                          ldsA32_, ldsB32_, st_);
+    launch_G_batch<float>(rs, P_, grid32_, st_);
   }
   RVE_HIP(hipGetLastError());
   pos = 0;

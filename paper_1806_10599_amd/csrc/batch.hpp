@@ -58,6 +58,8 @@ class BatchEngine {
   template <typename T>
   void newton_solve_device(int it, const LawParams& lp);
   void newton_eval_device(int it, const LawParams& lp, const double* dg_start);
+  // P, trial state and FP64 residual of the active RVEs at F_
+  void evaluate(const LawParams& lp, const double* dg_start);
   void read_logs();
   void build_tables();
   template <typename T>
@@ -76,7 +78,9 @@ class BatchEngine {
   // arena fields
   double *Fprev_, *Pc_, *Fpi_c_, *chi_c_, *dg_c_, *pcyc_, *pcyc_lit_, *wcyc_;
   double *F_, *P_, *Fpi_t_, *chi_t_, *dg_t_, *r64_, *dFt_;
-  void *K_, *x_, *r_, *p0_, *p1_, *Ap_, *spec_, *spec64_;
+  void *K_, *p_, *spec_, *spec64_;
+  void *rho_, *pi_, *xi_;   // CG vectors in Fourier space (pencil passes)
+  double prec_ = 0.0;       // the preconditioner's (lambda + mu)/(lambda + 2 mu)
   int32_t* phase_;
   uint8_t* vrve_;
   double* table_ = nullptr;
@@ -96,13 +100,10 @@ class BatchEngine {
   double* dF_dev_;
   // spectral descriptors (device) and grid sizes
   void *items32_, *items64_;
-  int blocksA32_, blocksB32_, blocksA64_, blocksB64_;
-  size_t ldsA32_, ldsB32_, ldsA64_, ldsB64_;
+  BatchGrid grid32_, grid64_;
   int cpbs32_ = 3, cpbs64_ = 3;  // slab schedules present (BatchSpec::cpbs)
   double* partials_;
-  SegItem* seg_;
-  int seg_blocks_;
-  RedItem *red_inv32_, *red_inv64_, *red_seg_;
+  RedItem* red_;
   void *tw32_, *tw64_, *vt32_, *vt64_;  // per RVE, concatenated
   std::vector<int64_t> twoff_, vtoff_;  // each RVE's offsets in them
   std::vector<SpecItem<float>> host_it32_;

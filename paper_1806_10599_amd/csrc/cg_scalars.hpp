@@ -1,7 +1,8 @@
-// Device-side CG scalar logic (text after Eq. 16: alpha = r.r / p.Ap,
-// beta = r_new.r_new / r.r, stop at ||r|| <= eta ||b|| or p.Ap <= 0; the
-// single-RVE path forms p.Ap as p.(K:p), see cg_alpha_publish) and the
-// fixed-order reductions of the per-block partial sums.
+// Device-side CG scalar logic (text after Eq. 16: alpha = r.z / p.Ap,
+// beta = r_new.z_new / r.z, z the preconditioned residual, stop at
+// ||r|| <= eta ||b|| or p.Ap <= 0; the single-RVE path forms p.Ap as
+// p.(K:p), see cg_alpha_publish) and the fixed-order reductions of the
+// per-block partial sums.
 #pragma once
 
 #include "common.hpp"
@@ -24,49 +25,22 @@ __device__ __forceinline__ double cg_sum_partials(const double* partial,
   return cg_block_reduce(acc, red);
 }
 
-// the scalar update of RED_INIT / RED_ALPHA / RED_BETA given the total
-__device__ __forceinline__ void cg_scalar_update(int op, double tot,
-                                                 Scalars* sc) {
-  if (op == RED_INIT) {
-    sc->rrs[0] = tot;
-    sc->rrs[1] = 0.0;
-    sc->its[0] = 0;
-    sc->its[1] = -1;  // iteration 0 has no previous update
-    sc->bb = tot;
-    sc->rr = tot;
-    sc->eta2bb = sc->eta2bb * tot;  // eta^2 was stored by the init kernel
-    sc->iters = 0;
-    sc->first = 1;
-    sc->breakdown = 0;
-    sc->converged = (tot == 0.0) ? 1 : 0;
-    sc->done = sc->converged;
-    sc->alpha = 0.0;
-    sc->beta = 0.0;
-    sc->alphas[0] = sc->alphas[1] = 0.0;
-    sc->halt[0] = sc->halt[1] = 0;
-  } else if (op == RED_ALPHA) {
-    sc->pAp = tot;
-    if (!(tot > 0.0) || !isfinite(tot)) {
-      sc->breakdown = 1;
-      sc->done = 1;
-      sc->iters += 1;
-    } else {
-      sc->alpha = sc->rr / tot;
-    }
-  } else if (op == RED_BETA) {
-    sc->iters += 1;
-    sc->rr_new = tot;
-    sc->first = 0;
-    if (tot <= sc->eta2bb) {
-      sc->converged = 1;
-      sc->done = 1;
-    } else if (sc->iters >= sc->max_iters || !isfinite(tot)) {
-      sc->done = 1;
-    } else {
-      sc->beta = tot / sc->rr;
-      sc->rr = tot;
-    }
-  }
+// The scalars at the start of a CG run (rr0 and rz0 are set)
+__host__ __device__ inline void cg_start(Scalars* sc, int max_iters,
+                                         double eta) {
+  sc->max_iters = max_iters;
+  sc->eta2 = eta * eta;
+  sc->done = 0;
+  sc->converged = 0;
+  sc->breakdown = 0;
+  sc->iters = 0;
+  sc->fails = 0;
+  sc->its[0] = 0;
+  sc->its[1] = -1;  // iteration 0 has no previous update
+  sc->halt[0] = sc->halt[1] = 0;
+  sc->alphas[0] = sc->alphas[1] = 0.0;
+  sc->xalpha = 0.0;
+  sc->xvalid = 0;
 }
 
 // Copies the scalars into the host's coherent pinned buffer pub (plain
@@ -102,14 +76,14 @@ struct BetaStep {
   double beta;
 };
 
-// The r.r partials of the last inverse pass are summed by every wavefront
-// of the consumer on its own: lane l adds partial[l], partial[l + 64], ...
-// in index order, then a butterfly over the wavefront (both lanes of a pair
-// add the same two numbers), so every wavefront of every consuming kernel
-// gets the same bits, with no barrier or LDS.  The first PU loads of each
-// lane can be issued early (load), away from the sum (sum).
+// The r.r and r.z partials of the last pencil pass are summed by every
+// wavefront of the consumer on its own: lane l adds partial[l],
+// partial[l + 64], ... in index order, then a butterfly over the wavefront
+// (both lanes of a pair add the same two numbers), so every wavefront of
+// every consuming kernel gets the same bits, with no barrier or LDS.  The
+// first PU loads of each lane can be issued early (load), away from the sum.
 template <int PU>
-struct RrPartials {
+struct WavePartials {
   double v[PU];
   __device__ __forceinline__ void load(const double* __restrict__ partial,
                                        int count) {
@@ -133,72 +107,105 @@ struct RrPartials {
   }
 };
 
-// The CG decision of the direction kernel of parity p (RED_BETA's
-// decision) from rr, the sum of the last inverse pass's r.r partials;
-// prev = its[p ^ 1] >= 0 (not iteration 0).
+// The decision of the direction pass of parity p from the r.r and r.z sums
+// of the last pencil pass (or, in iteration 0, prev < 0, from the start's).
+// k = prev + 1 updates are complete; the thread with pub publishes.
 __device__ __forceinline__ BetaStep cg_beta_step(Scalars* sc, int p, int prev,
-                                                 double rr) {
-  BetaStep d{false, false, 0.0};
+                                                 double rr, double rz,
+                                                 bool pub) {
   const int q = p ^ 1;
   const int k = prev + 1;
-  const double rr_prev = sc->rrs[q];
-  const bool conv = rr <= sc->eta2bb;
-  d.stop = conv || k >= sc->max_iters || !isfinite(rr);
-  d.beta = d.stop ? 0.0 : rr / rr_prev;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  const bool first = prev < 0;
+  const double e2bb = first ? sc->eta2 * rr : sc->eta2bb;
+  const bool conv = first ? rr == 0.0 : rr <= e2bb;
+  BetaStep d{first, conv, 0.0};
+  if (!first) d.stop = conv || k >= sc->max_iters || !isfinite(rr);
+  if (!first && !d.stop) d.beta = rz / sc->rzs[q];
+  if (pub) {
     sc->rrs[p] = rr;
+    sc->rzs[p] = rz;
     sc->its[p] = k;
     sc->iters = k;
     sc->rr_new = rr;
-    sc->first = 0;
+    if (first) {
+      sc->bb = rr;
+      sc->eta2bb = e2bb;
+    }
     if (conv) sc->converged = 1;
     if (d.stop) {
       sc->done = 1;
       sc->halt[p] = 1;
+      if (first) sc->xalpha = 0.0;
     } else {
       sc->beta = d.beta;
-      sc->rr = rr;
+      if (first) sc->xvalid = 1;
     }
   }
   return d;
 }
 
-// In the direction kernel of parity p (and in the chunk-closing kernel and
-// the fused forward pass): reduce the r.r partials of the last inverse pass
-// and take the decision, unless this is iteration 0.
-__device__ __forceinline__ BetaStep cg_beta_consume(const double* partial,
+// reduce the partials of the last pencil pass and take the decision (the
+// chunk-closing kernel)
+__device__ __forceinline__ BetaStep cg_beta_consume(const double* prr,
+                                                    const double* prz,
                                                     int count, Scalars* sc,
                                                     int p) {
   const int prev = sc->its[p ^ 1];
-  if (prev < 0) return BetaStep{true, false, 0.0};
-  RrPartials<8> rp;
-  rp.load(partial, count);
-  return cg_beta_step(sc, p, prev, rp.sum(partial, count));
+  const bool pub = threadIdx.x == 0;
+  if (prev < 0) return cg_beta_step(sc, p, prev, sc->rr0, sc->rz0, pub);
+  WavePartials<8> a, b;
+  a.load(prr, count);
+  b.load(prz, count);
+  return cg_beta_step(sc, p, prev, a.sum(prr, count), b.sum(prz, count), pub);
+}
+
+// alpha_k = r.z / p.(K:p), published by one thread.  Since p lies in the
+// range of the projection G and G is an orthogonal projection,
+// p.G(K:p) = p.(K:p): alpha is known before the transforms of K:p end, and
+// the pencil pass applies r -= alpha G(K:p) as it forms G(K:p).
+__device__ __forceinline__ void cg_alpha_set(double pAp, Scalars* sc, int p) {
+  if (threadIdx.x != 0) return;
+  sc->pAp = pAp;
+  if (!(pAp > 0.0) || !isfinite(pAp)) {
+    sc->breakdown = 1;
+    sc->done = 1;
+    sc->halt[p] = 1;
+    sc->iters = sc->its[p] + 1;
+    sc->xalpha = 0.0;
+  } else {
+    const double al = sc->rzs[p] / pAp;
+    sc->alpha = al;
+    sc->alphas[p] = al;
+    sc->xalpha = al;
+  }
 }
 
 // In block 0 of the forward pass of parity p: reduce the p.(K:p) partials of
-// the direction kernel and publish alpha_k = r.r / p.(K:p).  Since p lies in
-// the range of the projection G (r and every direction are outputs of G, up
-// to rounding) and G is an orthogonal projection, p.G(K:p) = p.(K:p): alpha
-// is known before the FFT passes, and the inverse pass can apply
-// r -= alpha G(K:p) itself.
+// the K:p kernel and publish alpha
 __device__ __forceinline__ void cg_alpha_publish(const double* partial,
                                                  int count, Scalars* sc,
                                                  int p, double* red) {
-  const double pAp = cg_sum_partials(partial, count, red);
-  if (threadIdx.x == 0) {
-    sc->pAp = pAp;
-    if (!(pAp > 0.0) || !isfinite(pAp)) {
-      sc->breakdown = 1;
-      sc->done = 1;
-      sc->halt[p] = 1;
-      sc->iters = sc->its[p] + 1;
-    } else {
-      const double al = sc->rrs[p] / pAp;
-      sc->alpha = al;
-      sc->alphas[p] = al;
-    }
-  }
+  cg_alpha_set(cg_sum_partials(partial, count, red), sc, p);
+}
+
+// The residual pass forms alpha itself from pass A's partials when K:p is
+// folded into pass A: every block the same bits, the one with `pub`
+// publishes.  False on a stopped run or a breakdown (no block touches the
+// residual then); rzs[p] was published by an earlier pass.
+template <typename T>
+__device__ __forceinline__ bool cg_alpha_consume(const double* partial,
+                                                 int count, Scalars* sc, int p,
+                                                 bool pub, T& alpha) {
+  if (sc->halt[p] || sc->done) return false;
+  double pAp = 0.0;
+  for (int i = threadIdx.x & 63; i < count; i += 64) pAp += partial[i];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) pAp += __shfl_xor(pAp, o, 64);
+  const double rz = sc->rzs[p];
+  if (pub) cg_alpha_set(pAp, sc, p);
+  if (!(pAp > 0.0) || !isfinite(pAp)) return false;
+  alpha = T(rz / pAp);
+  return true;
 }
 
 }  // namespace rve

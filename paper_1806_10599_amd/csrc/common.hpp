@@ -105,6 +105,16 @@ struct Scalars {
   // follow: the direction kernel of the next iteration returns at once)
   double alphas[2];
   int32_t halt[2];
+  // r.z of the preconditioned residual, by parity like rrs; the start's r.r
+  // and r.z (of the residual rounded to the CG precision, published by the
+  // residual reduction and handed back by init_scalars) and eta^2
+  double rzs[2];
+  double rr0, rz0;
+  double eta2;
+  // what the end of the solve adds: x = xi + xalpha pi, nothing if !xvalid
+  double xalpha;
+  int32_t xvalid;
+  int32_t pad2;
 };
 
 constexpr int kBlock = 256;

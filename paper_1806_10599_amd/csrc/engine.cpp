@@ -91,28 +91,30 @@ Engine::Engine(const rve_config& cfg) : cfg_(cfg) {
   dFt_prev_ = (double*)alloc(f9);
   dFt_pp_ = (double*)alloc(f9);
   K_ = alloc(81 * N_ * tsz);
-  x_ = alloc(9 * N_ * tsz);
-  r_ = alloc(9 * N_ * tsz);
-  p0_ = alloc(9 * N_ * tsz);
-  p1_ = alloc(9 * N_ * tsz);
+  rho_ = alloc(3 * N_ * tsz);
+  pi_ = alloc(3 * N_ * tsz);
+  xi_ = alloc(3 * N_ * tsz);
+  p_ = alloc(9 * N_ * tsz);
   Kp_ = alloc(9 * N_ * tsz);
   spec_ = alloc(9 * N_ / 2 * 2 * tsz);
   spec64_ = fp64_ ? spec_ : alloc(9 * N_ / 2 * 2 * sizeof(double));
-  nslab32_ = slab_blocks(n_, false);
-  nslab64_ = slab_blocks(n_, true);
-  // room for the partials of any schedule (one component per slab block)
+  // room for the partials of any schedule (one component per slab block,
+  // four kz columns per pencil block)
   partial_inv_ = (double*)alloc(9 * n_ * sizeof(double));
-  partial_red_ = (double*)alloc(kRedBlocks * sizeof(double));
-  // the direction kernel's partials, or pass A's when it is folded in
+  partial_res_ = (double*)alloc(3 * residual_blocks(n_) * sizeof(double));
+  partial_cg_ = (double*)alloc(2 * cg_pencil_blocks(n_, 4) * sizeof(double));
+  // the K:p kernel's partials, or pass A's when it is folded in
   partial_kp_ = (double*)alloc(std::max(kp_blocks(N_), 9 * n_) * sizeof(double));
   psum_ = (double*)alloc(9 * n_ * sizeof(double));
   psq_ = (double*)alloc(9 * n_ * sizeof(double));
   sc_ = (Scalars*)alloc(sizeof(Scalars));
   RVE_HIP(hipMemsetAsync(sc_, 0, sizeof(Scalars), st_));
-  // the timed matvecs of the schedule tuner may read these before the
+  // the timed iterations of the schedule tuner may read these before the
   // solver writes them: start from zeros
-  for (void* f : {K_, r_, x_, p0_, p1_})
-    RVE_HIP(hipMemsetAsync(f, 0, (f == K_ ? 81 : 9) * N_ * tsz, st_));
+  RVE_HIP(hipMemsetAsync(K_, 0, 81 * N_ * tsz, st_));
+  for (void* f : {rho_, pi_, xi_})
+    RVE_HIP(hipMemsetAsync(f, 0, 3 * N_ * tsz, st_));
+  for (void* f : {p_, Kp_}) RVE_HIP(hipMemsetAsync(f, 0, 9 * N_ * tsz, st_));
   phase_ = (int32_t*)alloc(N_ * sizeof(int32_t));
   order_ = (int32_t*)alloc(N_ * sizeof(int32_t));
   table_ = nullptr;
@@ -222,6 +224,7 @@ void Engine::set_microstructure(const int32_t* phase, int32_t G,
   }
   if (!(params_[3] > 0 && params_[4] > 0 && params_[5] >= 1 && params_[7] >= 0))
     throw Error(RVE_EINVAL, "bad flow-rule parameters");
+  set_preconditioner(cg_preconditioner(params_));
   std::vector<double> tab = label_table(G, quat, law, params_);
   if (G > labels_) {
     table_ = (double*)alloc(tab.size() * sizeof(double));
@@ -321,6 +324,7 @@ void Engine::set_user_material(rve_umat_fn fn, void* user, int32_t nstatev,
   RVE_HIP(hipGetLastError());
   RVE_HIP(hipStreamSynchronize(st_));
   reset_macro_state();
+  set_preconditioner(0.0);   // nothing is known of the material: plain CG
   umat_fn_ = fn;
   umat_user_ = user;
   nsv_ = nstatev;
@@ -349,23 +353,27 @@ LawParams Engine::law_params(double dt) const {
 }
 
 void Engine::residual_passes(const double* P, Scalars* pub) {
-  SpectralLaunch<double> L;
-  L.src = SRC_FIELD;
-  L.in_field = P;
-  L.spec = (cplx<double>*)spec64_;
-  L.tw = (const cplx<double>*)tw64_;
-  L.vt = (const double*)vt64_;
-  L.psum = psum_;
-  L.psq = psq_;
-  L.dst = DST_NORM;
-  L.out_d = r64_;
-  L.partial_inv = partial_inv_;
-  launch_G<double>(n_, L, st_);
-  launch_reduce(RED_RESID, partial_inv_, nslab64_, psum_, psq_, n_,
-                1.0 / (double)N_, sc_, sc_->pbar, st_, pub);
+  auto run = [&](auto tag) {
+    using T = decltype(tag);
+    ResidualLaunch<T> L;
+    L.P = P;
+    L.spec = (cplx<double>*)spec64_;
+    L.tw = (const cplx<double>*)tw64_;
+    L.vt = (const double*)vt64_;
+    L.rho = (cplx<T>*)rho_;
+    L.prec = prec_;
+    L.psum = psum_;
+    L.psq = psq_;
+    L.part = partial_res_;
+    launch_residual<T>(n_, L, st_);
+  };
+  if (fp64_) run(double{}); else run(float{});
+  launch_reduce_residual(partial_res_, residual_blocks(n_), psum_, psq_, n_,
+                         1.0 / (double)N_, sc_, st_, pub);
 }
 
-// constitutive update at F_ with the committed state, then r64 = G(P)
+// constitutive update at F_ with the committed state, then the residual G(P)
+// (the start of the CG run in Fourier space)
 int Engine::evaluate(const double* dg_start, double dt, double& rel,
                      double& res, double& pn) {
   launch_fill_i32(&sc_->fails, 0, 1, st_);
@@ -409,6 +417,8 @@ int Engine::evaluate(const double* dg_start, double dt, double& rel,
   res = std::sqrt(h.res2);
   pn = std::sqrt(h.P2);
   rel = pn > 0 ? res / pn : 0.0;
+  rr0_ = h.rr0;
+  rz0_ = h.rz0;
   for (int i = 0; i < 9; ++i) Pbar_new_[i] = h.pbar[i];
   return h.fails;
 }
@@ -436,60 +446,52 @@ void Engine::tangent(double dt) {
   timer_.end(5, st_);
 }
 
-// One CG iteration as a sequence of launch steps; run(cls, launch) issues a
-// step (cls: kernel class for live timing, -1 untimed).
-template <typename T, typename Run>
-void Engine::cg_iteration_steps(int parity, Run&& run) {
+template <typename T>
+CgLaunch<T> Engine::cg_launch(int parity, int cpb, int tt, int fused) const {
   const bool dbl = sizeof(T) == sizeof(double);
-  T* p_new = (T*)(parity ? p0_ : p1_);
-  const int nslab = slab_blocks(n_, dbl, sched_cpb_);
-  const T* p_old = (const T*)(parity ? p1_ : p0_);
-  // beta from the last inverse pass's r.r partials, the previous
-  // iteration's x += alpha p_old, p = r + beta p_old and y = K : p with the
-  // p . y partials, in one streaming pass (or folded into pass A)
-  if (!sched_fused_)
-    run(7, [&] {
-      launch_kp<T>((const T*)K_, (const T*)r_, p_old, p_new, (T*)Kp_, sc_, N_,
-                   st_, partial_inv_, nslab, parity, (T*)x_, partial_kp_);
-    });
-  // G(y); pass A (pass B when fused) publishes alpha = r.r / p.y, pass C
-  // applies r -= alpha G(y) and writes the new r.r partials
-  SpectralLaunch<T> L;
-  if (sched_fused_) {
-    L.src = SRC_KP;
-    L.K = (const T*)K_;
-    L.r = (const T*)r_;
-    L.p_old = p_old;
-    L.x = (T*)x_;
-    L.pinv = partial_inv_;
-    L.pinv_count = nslab;
-  } else {
-    L.src = SRC_FIELD;
-    L.in_field = (const T*)Kp_;
-  }
-  L.p_new = p_new;
+  const int npen = cg_pencil_blocks(n_, tt);
+  CgLaunch<T> L;
+  L.K = (const T*)K_;
+  L.p = (T*)p_;
+  L.y = (const T*)Kp_;
+  L.F = F_;
   L.spec = (cplx<T>*)spec_;
   L.tw = (const cplx<T>*)(dbl ? tw64_ : tw32_);
   L.vt = (const T*)(dbl ? vt64_ : vt32_);
-  L.dst = DST_CG;
-  L.r_io = (T*)r_;
+  L.rho = (cplx<T>*)rho_;
+  L.pi = (cplx<T>*)pi_;
+  L.xi = (cplx<T>*)xi_;
+  L.prec = prec_;
   L.pkp = partial_kp_;
-  L.pkp_count = sched_fused_ ? nslab : kp_blocks(N_);
-  L.parity = parity;
-  L.partial_inv = partial_inv_;
+  L.pkp_count = kp_blocks(N_);
+  L.prr = partial_cg_;
+  L.prz = partial_cg_ + npen;
+  L.prr_out = partial_cg_;
+  L.prz_out = partial_cg_ + npen;
   L.sc = sc_;
-  L.cpb = sched_cpb_;
-  L.tt = sched_tt_;
-  if (timer_.mask() & 7u) {
-    for (int pass = 0; pass < 3; ++pass)  // passes A, B, C one by one
-      run(pass, [&, pass] {
-        SpectralLaunch<T> Lp = L;
-        Lp.passes = 1 << pass;
-        launch_G<T>(n_, Lp, st_);
-      });
-  } else {
-    run(-1, [&] { launch_G<T>(n_, L, st_); });
-  }
+  L.parity = parity;
+  L.cpb = cpb;
+  L.tt = tt;
+  L.fused = fused;
+  return L;
+}
+
+// One CG iteration as a sequence of launch steps; run(cls, launch) issues a
+// step (cls: kernel class for live timing).  The direction pass takes beta
+// from the last residual pass's partials and applies the previous
+// iteration's x += alpha p; pass A publishes alpha = r.z / p.(K:p) (the
+// residual pass forms it when K:p is folded into pass A).
+template <typename T, typename Run>
+void Engine::cg_iteration_steps(int parity, Run&& run) {
+  const CgLaunch<T> L = cg_launch<T>(parity, sched_cpb_, sched_tt_, sched_fused_);
+  run(3, [&] { launch_cg<T>(n_, L, kPassDir, st_); });
+  run(2, [&] { launch_cg<T>(n_, L, kPassP, st_); });
+  if (!sched_fused_)
+    run(7, [&] {
+      launch_kp<T>(L.K, L.p, (T*)Kp_, sc_, N_, partial_kp_, st_);
+    });
+  run(0, [&] { launch_cg<T>(n_, L, kPassA, st_); });
+  run(1, [&] { launch_cg<T>(n_, L, kPassRes, st_); });
 }
 
 template <typename T>
@@ -501,7 +503,7 @@ void Engine::cg_iteration(int parity) {
   });
 }
 
-// kernel classes launched inside a CG iteration: passes A-C, update, K:p
+// kernel classes launched inside a CG iteration: passes A-C, direction, K:p
 constexpr uint32_t kCgClasses = 0x8Fu;
 
 // The CG chunk as one graph.  Without live timing the chunk is captured in
@@ -509,11 +511,14 @@ constexpr uint32_t kCgClasses = 0x8Fu;
 // steps are bracketed by event-record nodes, linked in launch order.
 template <typename T>
 void Engine::capture_graph() {
+  auto close = [&](int parity, Scalars* pub) {
+    const int npen = cg_pencil_blocks(n_, sched_tt_);
+    launch_cg_close(partial_cg_, partial_cg_ + npen, npen, sc_, parity, st_, pub);
+  };
   if (!(timer_.mask() & kCgClasses)) {
     RVE_HIP(hipStreamBeginCapture(st_, hipStreamCaptureModeThreadLocal));
     for (int j = 0; j < cfg_.cg_chunk; ++j) cg_iteration<T>(j & 1);
-    launch_cg_close(partial_inv_, slab_blocks(n_, sizeof(T) == 8, sched_cpb_),
-                    sc_, 0, st_);
+    close(0, nullptr);
     RVE_HIP(hipStreamEndCapture(st_, &graph_def_));
   } else {
     RVE_HIP(hipGraphCreate(&graph_def_, 0));
@@ -548,22 +553,18 @@ void Engine::capture_graph() {
       }
     };
     for (int j = 0; j < cfg_.cg_chunk; ++j) cg_iteration_steps<T>(j & 1, step);
-    step(-1, [&] {
-      launch_cg_close(partial_inv_,
-                      slab_blocks(n_, sizeof(T) == 8, sched_cpb_), sc_, 0, st_);
-    });
+    step(-1, [&] { close(0, nullptr); });
   }
   RVE_HIP(hipGraphInstantiate(&graph_, graph_def_, nullptr, nullptr, 0));
 }
 
-// Picks the fastest schedule of the CG matvec G(K : p) for this grid and
-// precision (components per slab block in passes A and C, kz columns per
-// pass-B block, and whether the direction kernel is folded into pass A) by
-// timing one matvec with each valid candidate on the live buffers, with
-// alpha = beta = 0 (p = r + 0 p_old, x += 0 p_old: the memory traffic of
-// an iteration after the first; the CG vectors are re-initialised
-// afterwards): the direction kernel and the three passes, or the three
-// passes with the folded pass A.
+// Picks the fastest schedule of the CG iteration for this grid and precision
+// (components per slab block in passes A and C and whether K:p is folded into
+// pass A; the kz columns per pencil block, which the order of the norms'
+// sums follows, are those of cg_tile) by timing one iteration with each
+// candidate on the live buffers with alpha = beta = 0, which leaves the
+// residual as it is (the direction and the iterate are written anew by the
+// next solve).
 template <typename T>
 void Engine::autotune() {
   const bool dbl = sizeof(T) == sizeof(double);
@@ -576,9 +577,9 @@ void Engine::autotune() {
   std::vector<Cand> cand;
   for (int fused : {0, 1})
     for (int cpb : {1, 3})
-      for (int tt : {4, 8, 16})
-        if (schedule_valid(n_, dbl, cpb, tt)) cand.push_back({cpb, tt, fused});
-  // alpha = 0 in every slot: the timed passes leave r and x unchanged
+      if (schedule_valid(n_, dbl, cpb, cg_tile(n_)))
+        cand.push_back({cpb, cg_tile(n_), fused});
+  // alpha = 0 in every slot: the timed passes leave the residual unchanged
   launch_bench_scalars(sc_, st_);
   // three interleaved rounds, the best of each candidate's timings: robust
   // against clock and cache drift between candidates
@@ -586,33 +587,13 @@ void Engine::autotune() {
   constexpr int reps = 4;
   for (int round = 0; round < 3; ++round)
     for (size_t c = 0; c < cand.size(); ++c) {
-      SpectralLaunch<T> L;
-      if (cand[c].fused) {
-        L.src = SRC_KP;
-        L.K = (const T*)K_;
-        L.r = (const T*)r_;
-        L.p_old = (const T*)p0_;
-        L.x = (T*)x_;
-      } else {
-        L.src = SRC_FIELD;
-        L.in_field = (const T*)Kp_;
-      }
-      L.p_new = (T*)p1_;
-      L.spec = (cplx<T>*)spec_;
-      L.tw = (const cplx<T>*)(dbl ? tw64_ : tw32_);
-      L.vt = (const T*)(dbl ? vt64_ : vt32_);
-      L.dst = DST_CG;
-      L.r_io = (T*)r_;
-      L.partial_inv = partial_inv_;
-      L.sc = sc_;
-      L.cpb = cand[c].cpb;
-      L.tt = cand[c].tt;
+      CgLaunch<T> L = cg_launch<T>(0, cand[c].cpb, cand[c].tt, cand[c].fused);
+      L.prr = nullptr;   // alpha and beta from the scalars
       auto matvec = [&] {
+        launch_cg<T>(n_, L, kPassDir | kPassP, st_);
         if (!cand[c].fused)
-          launch_kp<T>((const T*)K_, (const T*)r_, (const T*)p0_, (T*)p1_,
-                       (T*)Kp_, sc_, N_, st_, nullptr, 0, 0, (T*)x_,
-                       partial_kp_);
-        launch_G<T>(n_, L, st_);
+          launch_kp<T>(L.K, L.p, (T*)Kp_, sc_, N_, partial_kp_, st_);
+        launch_cg<T>(n_, L, kPassA | kPassRes, st_);
       };
       matvec();  // untimed first launch
       RVE_HIP(hipEventRecord(ev[0], st_));
@@ -639,6 +620,26 @@ void Engine::autotune() {
   sched_ms_ = best / reps;
 }
 
+// the captured CG chunk holds its schedule, events and preconditioner
+void Engine::drop_graph() {
+  RVE_HIP(hipStreamSynchronize(st_));
+  if (graph_) {
+    RVE_HIP(hipGraphExecDestroy(graph_));
+    graph_ = nullptr;
+  }
+  if (graph_def_) {
+    RVE_HIP(hipGraphDestroy(graph_def_));
+    graph_def_ = nullptr;
+  }
+  timer_.recycle(graph_pairs_);
+}
+
+void Engine::set_preconditioner(double prec) {
+  if (prec == prec_) return;
+  drop_graph();
+  prec_ = prec;
+}
+
 void Engine::tune() {
   set_schedule(0, 0, 0);  // drops a captured graph
   if (fp64_) autotune<double>(); else autotune<float>();
@@ -651,30 +652,18 @@ void Engine::set_schedule(int cpb, int tt, int fused) {
     if (!schedule_valid(n_, fp64_, cpb, tt))
       throw Error(RVE_EINVAL, "no such FFT schedule for this grid and precision");
   }
-  RVE_HIP(hipStreamSynchronize(st_));
-  if (graph_) {
-    RVE_HIP(hipGraphExecDestroy(graph_));
-    graph_ = nullptr;
-  }
-  if (graph_def_) {
-    RVE_HIP(hipGraphDestroy(graph_def_));
-    graph_def_ = nullptr;
-  }
-  timer_.recycle(graph_pairs_);
+  drop_graph();
   sched_cpb_ = cpb;
   sched_tt_ = tt;
   sched_fused_ = (cpb || tt) ? fused : 0;
   sched_ms_ = 0.0;
 }
 
-// CG on G(K : x) = b with b = -r64 (text after Eq. 16), from x = 0
+// CG on G(K : x) = -G(P) (text after Eq. 16), from x = 0, then F += x
 template <typename T>
 void Engine::cg_solve(int& iters, bool& breakdown, double eta) {
   if (!sched_cpb_) autotune<T>();
-  launch_init_scalars(sc_, cfg_.cg_max_iter, eta, st_);
-  launch_cg_init<T>(r64_, (T*)r_, (T*)x_, partial_red_, kRedBlocks, 9 * N_, st_);
-  launch_reduce(RED_INIT, partial_red_, kRedBlocks, nullptr, nullptr, 0, 0.0,
-                sc_, nullptr, st_);
+  launch_init_scalars(sc_, cfg_.cg_max_iter, eta, rr0_, rz0_, st_);
   RVE_HIP(hipGetLastError());
   // Chunks are queued one ahead of the host's convergence check: chunk k+1
   // is enqueued before the scalars of chunk k are waited for, so the device
@@ -683,8 +672,7 @@ void Engine::cg_solve(int& iters, bool& breakdown, double eta) {
   // each of its launches still costs a dispatch.  With direct launches the
   // length of the chunk queued ahead (at most cg_chunk) follows the r.r
   // decay seen so far: the iterations expected to remain after the chunk in
-  // flight, at least one, since the direction kernel that follows a chunk
-  // whose closing kernel stops the run applies the last x += alpha p.
+  // flight, at least one.
   int parity = 0;
   auto enqueue = [&](int slot, int len) {
     if (cfg_.use_graph) {
@@ -697,9 +685,9 @@ void Engine::cg_solve(int& iters, bool& breakdown, double eta) {
         parity ^= 1;
       }
       // the closing kernel copies the scalars into the slot itself
-      launch_cg_close(partial_inv_,
-                      slab_blocks(n_, sizeof(T) == 8, sched_cpb_), sc_, parity,
-                      st_, sc_pub_ + 1 + slot);
+      const int npen = cg_pencil_blocks(n_, sched_tt_);
+      launch_cg_close(partial_cg_, partial_cg_ + npen, npen, sc_, parity, st_,
+                      sc_pub_ + 1 + slot);
     }
     if (cfg_.use_graph)
       RVE_HIP(hipMemcpyAsync(sc_host_ + 1 + slot, sc_, sizeof(Scalars),
@@ -742,6 +730,9 @@ void Engine::cg_solve(int& iters, bool& breakdown, double eta) {
     eta2bb = h.eta2bb;
     ++k;
   }
+  // F += x, behind the queued chunk (whose passes find the run stopped)
+  launch_cg<T>(n_, cg_launch<T>(0, sched_cpb_, sched_tt_, 0), kPassFinal, st_);
+  RVE_HIP(hipGetLastError());
   // the live timings of this solve are read at the next synchronous scalar
   // read, once the queued chunk has drained
   iters = h.iters;
@@ -818,6 +809,9 @@ int Engine::increment(const double Fbar_new[9], double dt,
     } else {
       swap_trial_sets();
       std::swap(F_, F2_);
+      const size_t rb = 3 * N_ * (fp64_ ? sizeof(double) : sizeof(float));
+      RVE_HIP(hipMemcpyAsync(rho2_, rho_, rb, hipMemcpyDeviceToDevice, st_));
+      const double rrL = rr0_, rzL = rz0_;
       double pbarL[9];
       for (int i = 0; i < 9; ++i) pbarL[i] = Pbar_new_[i];
       pre_fails = evaluate(dg_start, dt, rel, res, pn);
@@ -826,6 +820,9 @@ int Engine::increment(const double Fbar_new[9], double dt,
       if (failsL == 0 && relL < rel) {
         swap_trial_sets();
         std::swap(F_, F2_);
+        RVE_HIP(hipMemcpyAsync(rho_, rho2_, rb, hipMemcpyDeviceToDevice, st_));
+        rr0_ = rrL;
+        rz0_ = rzL;
         rel = relL;
         res = resL;
         pn = pnL;
@@ -887,11 +884,9 @@ int Engine::increment(const double Fbar_new[9], double dt,
     if (fp64_) {
       tangent<double>(dt);
       cg_solve<double>(iters, bd, eta);
-      launch_add_to_F<double>(F_, (const double*)x_, 9 * N_, st_);
     } else {
       tangent<float>(dt);
       cg_solve<float>(iters, bd, eta);
-      launch_add_to_F<float>(F_, (const float*)x_, 9 * N_, st_);
     }
     RVE_HIP(hipGetLastError());
     if (it < RVE_MAX_NEWTON_LOG) loc.cg_iters[it] = iters;
@@ -1189,12 +1184,10 @@ void Engine::set_state(const void* src, size_t bytes) {
 
 void Engine::apply_G_fp64(const double* in, double* out) {
   SpectralLaunch<double> L;
-  L.src = SRC_FIELD;
   L.in_field = in;
   L.spec = (cplx<double>*)spec64_;
   L.tw = (const cplx<double>*)tw64_;
   L.vt = (const double*)vt64_;
-  L.dst = DST_NORM;
   L.out_d = out;
   L.partial_inv = partial_inv_;
   launch_G<double>(n_, L, st_);
@@ -1213,12 +1206,10 @@ void Engine::debug_apply_G(const double* in, double* out, int precision) {
     }
     launch_convert<float>(r64_, (float*)dbg32_, 9 * N_, st_);
     SpectralLaunch<float> L;
-    L.src = SRC_FIELD;
     L.in_field = (const float*)dbg32_;
     L.spec = (cplx<float>*)dbgspec32_;
     L.tw = (const cplx<float>*)tw32_;
     L.vt = (const float*)vt32_;
-    L.dst = DST_NORM;
     L.out_d = P_;
     L.partial_inv = partial_inv_;
     launch_G<float>(n_, L, st_);
@@ -1300,26 +1291,17 @@ void Engine::debug_set_field(int field, const double* src, size_t bytes) {
 }
 
 // Kernel classes of the live timing and of bench_kernels:
-//   0 pass A (z/y FFT of K:p; under a fused schedule also the direction,
-//     the previous x update and K:p)            1 pass B (x FFT, projection)
-//   2 pass C (inverse y/z FFT, r -= alpha G(K:p), r.r)
-//   3 unused (the vector update rides on classes 2 and 7, or 0)
+//   0 pass A (z/y FFT of K:p; under a fused schedule also K:p)
+//   1 residual (x FFT, r -= alpha G(K:p), norms)
+//   2 pass C (inverse y/z FFT of the direction)
+//   3 direction (z = M r, p = z + beta p, x += alpha p, inverse x FFT)
 //   4 return mapping (FP64)                     5 tangent
-//   6 FP64 residual G(P) (three passes + reduction)
-//   7 direction, previous x update and K:p (unfused schedules)
+//   6 FP64 residual G(P) (two passes + reduction)
+//   7 K:p (unfused schedules)
 void Engine::set_timing(uint32_t mask) {
   if (mask == timer_.mask()) return;
   // captured CG graphs hold (or lack) the timing events: capture again
-  RVE_HIP(hipStreamSynchronize(st_));
-  if (graph_) {
-    RVE_HIP(hipGraphExecDestroy(graph_));
-    graph_ = nullptr;
-  }
-  if (graph_def_) {
-    RVE_HIP(hipGraphDestroy(graph_def_));
-    graph_def_ = nullptr;
-  }
-  timer_.recycle(graph_pairs_);
+  drop_graph();
   if ((mask >> 4) & 1u) {
     if (!rm_iters_) {
       rm_iters_ = (int32_t*)alloc(N_ * sizeof(int32_t));
@@ -1408,51 +1390,22 @@ void Engine::bench_kernels(int reps, double* ms, int count) {
     if (fp64_) tangent<double>(dt); else tangent<float>(dt);
   });
   timed(6, [&] { residual_passes(P_); });
-  auto passes = [&](auto tag, int mask) {
-    using T = decltype(tag);
-    const bool dbl = sizeof(T) == sizeof(double);
-    SpectralLaunch<T> L;
-    if (sched_fused_) {
-      L.src = SRC_KP;
-      L.K = (const T*)K_;
-      L.r = (const T*)r_;
-      L.p_old = (const T*)p0_;
-      L.x = (T*)x_;
-    } else {
-      L.src = SRC_FIELD;
-      L.in_field = (const T*)Kp_;
-    }
-    L.p_new = (T*)p1_;
-    L.spec = (cplx<T>*)spec_;
-    L.tw = (const cplx<T>*)(dbl ? tw64_ : tw32_);
-    L.vt = (const T*)(dbl ? vt64_ : vt32_);
-    L.dst = DST_CG;
-    L.r_io = (T*)r_;
-    L.partial_inv = partial_inv_;
-    L.sc = sc_;
-    L.passes = mask;
-    L.cpb = sched_cpb_;
-    L.tt = sched_tt_;
-    launch_G<T>(n_, L, st_);
-  };
   // the CG kernels as a CG run launches them after its first iteration,
-  // with alpha = beta = 0 (p = r + 0 p_old, x += 0 p_old, r -= 0 G(y)): the
-  // vectors keep their values
+  // with alpha = beta = 0 (the residual keeps its value)
   launch_bench_scalars(sc_, st_);
-  if (!sched_fused_) timed(7, [&] {
-    if (fp64_)
-      launch_kp<double>((const double*)K_, (const double*)r_,
-                        (const double*)p0_, (double*)p1_, (double*)Kp_, sc_,
-                        N_, st_, nullptr, 0, 0, (double*)x_, partial_kp_);
-    else
-      launch_kp<float>((const float*)K_, (const float*)r_, (const float*)p0_,
-                       (float*)p1_, (float*)Kp_, sc_, N_, st_, nullptr, 0, 0,
-                       (float*)x_, partial_kp_);
-  });
-  for (int b = 0; b < 3; ++b) {
-    timed(b, [&] {
-      if (fp64_) passes(double{}, 1 << b); else passes(float{}, 1 << b);
-    });
+  auto cg = [&](auto tag) {
+    using T = decltype(tag);
+    CgLaunch<T> L = cg_launch<T>(0, sched_cpb_, sched_tt_, sched_fused_);
+    L.prr = nullptr;
+    timed(3, [&] { launch_cg<T>(n_, L, kPassDir, st_); });
+    timed(2, [&] { launch_cg<T>(n_, L, kPassP, st_); });
+    if (!sched_fused_)
+      timed(7, [&] { launch_kp<T>(L.K, L.p, (T*)Kp_, sc_, N_, partial_kp_, st_); });
+    timed(0, [&] { launch_cg<T>(n_, L, kPassA, st_); });
+    timed(1, [&] { launch_cg<T>(n_, L, kPassRes, st_); });
+  };
+  if (sched_cpb_) {
+    if (fp64_) cg(double{}); else cg(float{});
   }
   RVE_HIP(hipGetLastError());
   RVE_HIP(hipEventDestroy(ev[0]));
@@ -1465,7 +1418,6 @@ void Engine::swap_trial_sets() {
   std::swap(Fpi_t_, Fpi_t2_);
   std::swap(chi_t_, chi_t2_);
   std::swap(dg_t_, dg_t2_);
-  std::swap(r64_, r64b_);
 }
 
 void Engine::attach_net(Net* net) {
@@ -1488,6 +1440,7 @@ void Engine::second_trial_set() {
   chi_t2_ = (double*)alloc(f12);
   dg_t2_ = (double*)alloc(f12);
   r64b_ = (double*)alloc(f9);
+  rho2_ = alloc(3 * N_ * (fp64_ ? sizeof(double) : sizeof(float)));
 }
 
 void Engine::feature_args(const double Fbar_new[9], FeatArgs& a, double& s_k) {

@@ -86,6 +86,8 @@ class Engine {
   template <typename T>
   void cg_solve(int& iters, bool& breakdown, double eta);
   template <typename T>
+  CgLaunch<T> cg_launch(int parity, int cpb, int tt, int fused) const;
+  template <typename T>
   void cg_iteration(int parity);
   template <typename T, typename Run>
   void cg_iteration_steps(int parity, Run&& run);
@@ -107,6 +109,8 @@ class Engine {
   void second_trial_set();
   void swap_trial_sets();
   void reset_macro_state();
+  void drop_graph();
+  void set_preconditioner(double prec);
   // copy of the committed state (device arrays and host macro state) for
   // the rollback of a failed adaptive step
   void take_snapshot();
@@ -126,12 +130,20 @@ class Engine {
   // Newton scratch
   double *F_, *P_, *Fpi_t_, *chi_t_, *dg_t_, *r64_;
   void* K_;      // [81][N] float (mixed) or double (fp64)
-  // CG vectors (T) and spectra
-  void *x_, *r_, *p0_, *p1_;
-  void* Kp_;     // K : p of the current CG direction
+  // CG vectors in Fourier space ([3][n][n][n/2] complex T): residual,
+  // direction, iterate; the direction and K : p in real space
+  void *rho_, *pi_, *xi_;
+  void* p_;
+  void* Kp_;
   void* spec_;        // complex T
   void* spec64_;      // complex double (aliases spec_ in fp64 mode)
-  double *partial_inv_, *partial_red_, *partial_kp_, *psum_, *psq_;
+  double *partial_inv_, *partial_kp_, *psum_, *psq_;
+  double* partial_res_;   // FP64 residual: r.r, r.z, ||G(P)||^2 per block
+  double* partial_cg_;    // CG pencil passes: r.r and r.z per block
+  // r.r and r.z of the CG start, from the last residual; prec_: the
+  // preconditioner's (lambda + mu)/(lambda + 2 mu)
+  double rr0_ = 0.0, rz0_ = 0.0;
+  double prec_ = 0.0;
   Scalars* sc_;
   // coherent pinned: [0] sync reads, [1..2] chunks; sc_pub_: its device
   // address, where the closing and residual kernels write
@@ -143,7 +155,6 @@ class Engine {
   std::vector<int32_t> order_host_;
   double* table_;
   void *tw32_, *tw64_, *vt32_, *vt64_;
-  int nslab32_, nslab64_;
   int sched_cpb_ = 0, sched_tt_ = 0;   // 0: not tuned yet
   int sched_fused_ = 0;
   double sched_ms_ = 0.0;
@@ -205,6 +216,7 @@ class Engine {
   // second trial set for the learned-vs-plain predictor comparison
   double *F2_ = nullptr, *P2_ = nullptr, *Fpi_t2_ = nullptr, *chi_t2_ = nullptr,
          *dg_t2_ = nullptr, *r64b_ = nullptr;
+  void* rho2_ = nullptr;   // the stashed candidate's residual
 };
 
 }  // namespace rve

@@ -5,18 +5,17 @@
 
 namespace rve {
 
-enum { SRC_FIELD = 0, SRC_KP = 1 };
-// pass C outputs: the field (||out||^2 partials), the field and p . out
-// partials (batched CG), r -= alpha out in place (single-RVE CG)
-enum { DST_NORM = 0, DST_DOT = 1, DST_CG = 2 };
+// pass A inputs: a field, or this block's rows of K:p from the direction's
+// field
+enum { SRC_FIELD = 0, SRC_KROW = 1 };
+// pass C outputs: the field (||out||^2 partials), the direction's field,
+// F += the iterate
+enum { DST_NORM = 0, DST_P = 1, DST_ADDF = 2 };
 
 template <typename T>
 struct SlabFwdArgs {
-  const T* field;      // SRC_FIELD: [9][N^3]
-  const T* K;          // SRC_KP: [81][N^3]
-  const T* r;          // SRC_KP: CG residual
-  const T* p_old;      // SRC_KP: previous direction
-  T* p_new;            // SRC_KP: new direction (written)
+  const T* field;      // [9][N^3] (SRC_KROW: the direction)
+  const T* K;          // SRC_KROW: [81][N^3]
   cplx<T>* spec;       // [9][N][N][N/2]
   const cplx<T>* tw;   // exp(-2 pi i m / N)
   double* psum;        // optional [9][N] per-slab sums
@@ -30,24 +29,7 @@ struct SlabFwdArgs {
   int pkp_count = 0;
   int parity = 0;
   Scalars* scw = nullptr;
-  // SRC_KP in a single-RVE CG run (the direction kernel folded into pass A):
-  // the r.r partials of the last inverse pass (beta), the iterate x (the
-  // previous iteration's x += alpha p_old on this block's components) and
-  // the per-block partials of p . (K:p) written for pass B's alpha
-  const double* pinv = nullptr;
-  int pinv_count = 0;
-  T* x = nullptr;
-  double* pkp_out = nullptr;
-};
-
-// The direction step a pass-A block applies with SRC_KP: p = r (first) or
-// r + beta p_old, and with upd the pending x += alpha p_old
-template <typename T>
-struct KpStep {
-  bool first;
-  T beta;
-  bool upd;
-  T alpha;
+  double* pkp_out = nullptr;  // SRC_KROW: [9][N] partials of p.(K:p)
 };
 
 template <typename T>
@@ -57,12 +39,38 @@ struct PencilArgs {
   const T* vt;         // [3][N] wave-vector components per axis
   T invN3;
   const Scalars* sc;   // optional early exit
-  // optional (fused single-RVE CG run): block 0 reduces pass A's p.(K:p)
-  // partials and publishes alpha in slot `parity` of scw
-  const double* pkp = nullptr;
-  int pkp_count = 0;
-  int parity = 0;
-  Scalars* scw = nullptr;
+};
+
+// CG vectors per frequency: see pencil_fwd_body and pencil_inv_body
+template <typename T, typename TR>
+struct PencilFwdArgs {
+  const cplx<T>* spec;
+  const cplx<T>* tw;
+  const T* vt;
+  cplx<TR>* rho;       // [3][N][N][N/2]
+  double invN3, prec;
+  double *prr, *prz;   // per-block r.r and r.z
+  double* pres;        // per-block ||G(P)||^2 (residual)
+  const Scalars* sc;
+  int parity;
+  // K:p folded into pass A: its p.(K:p) partials (alpha is formed here)
+  const double* pkp;
+  int pkp_count;
+  Scalars* scw;
+};
+template <typename T>
+struct PencilInvArgs {
+  cplx<T>* spec;
+  const cplx<T>* tw;
+  const T* vt;
+  const cplx<T>* rho;
+  cplx<T>* pi;
+  cplx<T>* xi;
+  T invN3, prec;
+  const double *prr, *prz;  // partials of the last pass (null: timing)
+  int count;
+  Scalars* scw;
+  int parity;
 };
 
 template <typename T, typename TO>
@@ -70,51 +78,70 @@ struct SlabInvArgs {
   const cplx<T>* spec;
   const cplx<T>* tw;
   TO* out;             // [9][N^3]
-  const T* pdot;       // DST_DOT: direction for p . Ap
   double* partial;     // per block
   const Scalars* sc;   // optional early exit
-  int64_t cs;          // component stride of out / pdot
-  // DST_CG: r -= alpha G(y) in place with alpha = sc->alphas[parity]; the
-  // partials are those of the new r . r (out is not written)
-  T* rio = nullptr;
-  int parity = 0;
+  int64_t cs;          // component stride of out
+  const T* vt = nullptr;    // DST_P, DST_ADDF: wave vectors
 };
 
+// G of a field (default schedule)
 template <typename T>
 struct SpectralLaunch {
-  int src = SRC_FIELD, dst = DST_NORM;
   const T* in_field = nullptr;
-  const T* K = nullptr;
-  const T* r = nullptr;
-  const T* p_old = nullptr;
-  T* p_new = nullptr;
   cplx<T>* spec = nullptr;
   const cplx<T>* tw = nullptr;
   const T* vt = nullptr;
-  double* psum = nullptr;
-  double* psq = nullptr;
-  T* out_T = nullptr;
   double* out_d = nullptr;
   double* partial_inv = nullptr;
-  Scalars* sc = nullptr;
-  // CG run (dst = DST_CG): the p.(K:p) partials for alpha (published by
-  // pass A with src = SRC_FIELD, by pass B with src = SRC_KP, whose pass A
-  // writes them), the residual updated in place by pass C, and the
-  // iteration's parity
-  const double* pkp = nullptr;
-  int pkp_count = 0;
-  T* r_io = nullptr;
-  int parity = 0;
-  // fused CG run (src = SRC_KP): the r.r partials of the last pass C and the
-  // iterate x, as the direction kernel takes them
-  const double* pinv = nullptr;
-  int pinv_count = 0;
-  T* x = nullptr;
-  int passes = 7;   // bit 0: pass A, bit 1: pass B, bit 2: pass C
-  int cpb = 0;      // components per slab block in passes A and C (1 or 3;
-                    // 0: the default of the grid edge and precision)
-  int tt = 0;       // kz columns per pass-B block (4, 8 or 16; 0: default)
 };
+
+// Passes of a single-RVE CG iteration in launch order: the direction (inverse
+// x FFT), p in real space, [K:p,] pass A, the residual (forward x FFT); and
+// the end of the solve, F += x.
+enum { kPassDir = 1, kPassP = 2, kPassA = 4, kPassRes = 8, kPassFinal = 16 };
+template <typename T>
+struct CgLaunch {
+  const T* K = nullptr;
+  T* p = nullptr;              // direction [9][N^3]
+  const T* y = nullptr;        // K : p [9][N^3]
+  double* F = nullptr;         // kPassFinal
+  cplx<T>* spec = nullptr;
+  const cplx<T>* tw = nullptr;
+  const T* vt = nullptr;
+  cplx<T>* rho = nullptr;      // CG vectors [3][N][N][N/2]
+  cplx<T>* pi = nullptr;
+  cplx<T>* xi = nullptr;
+  double prec = 0.0;           // (lambda + mu)/(lambda + 2 mu) of M
+  double* pkp = nullptr;       // p.(K:p) partials
+  int pkp_count = 0;
+  const double *prr = nullptr, *prz = nullptr;  // last pass's (null: timing)
+  double *prr_out = nullptr, *prz_out = nullptr;
+  Scalars* sc = nullptr;
+  int parity = 0;
+  int cpb = 0, tt = 0;         // components per slab block, kz columns per
+  int fused = 0;               // pencil block; K:p folded into pass A
+};
+template <typename T>
+void launch_cg(int n, const CgLaunch<T>& L, int mask, hipStream_t s);
+
+// FP64 residual of P: rho = -(P v) in the CG precision TR, psum/psq of P,
+// and 3 * residual_blocks(n) partials (r.r, r.z, ||G(P)||^2)
+template <typename TR>
+struct ResidualLaunch {
+  const double* P = nullptr;
+  cplx<double>* spec = nullptr;
+  const cplx<double>* tw = nullptr;
+  const double* vt = nullptr;
+  cplx<TR>* rho = nullptr;
+  double prec = 0.0;
+  double *psum = nullptr, *psq = nullptr;
+  double* part = nullptr;
+};
+template <typename TR>
+void launch_residual(int n, const ResidualLaunch<TR>& L, hipStream_t s);
+int residual_blocks(int n);
+int cg_pencil_blocks(int n, int tt);
+int cg_tile(int n);   // the kz columns of a pencil block a handle picks
 
 template <typename T>
 void launch_G(int n, const SpectralLaunch<T>& L, hipStream_t s);
@@ -128,20 +155,22 @@ int pencil_blocks(int n, bool fp64, int tt = 0);
 bool schedule_valid(int n, bool fp64, int cpb, int tt);
 
 // One RVE of a batch: where its voxels, spectrum and scalars live and where
-// its blocks start in the pass-A/C (blk[0]) and pass-B (blk[1]) grids.
+// its blocks start in the grids of the slab passes (blk[0]), the CG pencil
+// passes (blk[1]) and the pencil pass of G (blk[2]).
 template <typename T>
 struct SpecItem {
   int n;
-  int blk[2];
+  int blk[3];
   int cpb;              // components per slab block (1 or 3)
   int tt;               // kz columns per pencil block (4, 8 or 16)
-  int pad;
+  int npen;             // CG pencil blocks of this RVE
   int64_t off;          // voxel offset in the arena
-  int64_t soff;         // complex offset of the spectrum
+  int64_t soff;         // complex offset of the spectrum (CG vectors: / 3)
   const cplx<T>* tw;
   const T* vt;
   Scalars* sc;          // this RVE's scalars
-  double* partial;      // pass-C partials (slab_blocks entries)
+  double* pkp;          // pass A's p.(K:p) partials [9][n]
+  double* prr;          // pencil partials: r.r, r.z, ||G(P)||^2 (3 npen)
   double* psum;         // residual pass sums [9][n]
   double* psq;
 };
@@ -153,20 +182,37 @@ struct BatchSpec {
   int cpbs = 3;         // slab schedules among the items (bit 0: cpb 1,
                         // bit 1: cpb 3)
   int64_t cs;           // voxels in the arena (component stride)
-  const T* field;       // SRC_FIELD input
+  const T* field;       // SRC_FIELD input, or the CG direction p
   const T* K;
-  const T* r;
-  const T* p_old;
-  T* p_new;
+  T* p;
   cplx<T>* spec;
+  cplx<T>* rho;         // CG vectors
+  cplx<T>* pi;
+  cplx<T>* xi;
+  double prec;
+  int parity;
+  int timing;           // alpha and beta from the scalars (schedule tuner)
+};
+// blocks of the slab and CG pencil grids and their dynamic LDS
+struct BatchGrid {
+  int A = 0, B = 0;
+  size_t ldsA = 0, ldsB = 0;
 };
 
-// passes of a batch: src SRC_FIELD (residual: out_d, norms) or SRC_KP (CG:
-// out_T = Ap, p.Ap partials); block counts of the three grids
+// out = G(field)
 template <typename T>
-void launch_G_batch(const BatchSpec<T>& b, int src, T* out_T, double* out_d,
-                    int blocksA, int blocksB, size_t ldsA, size_t ldsB,
+void launch_G_batch(const BatchSpec<T>& b, double* out, const BatchGrid& g,
                     hipStream_t s);
+// FP64 residual of the field: rho, norm partials, psum and psq
+template <typename TR>
+void launch_residual_batch(const BatchSpec<double>& b, cplx<TR>* rho,
+                           const BatchGrid& g, hipStream_t s);
+// one CG iteration; the end of the solve, F += x
+template <typename T>
+void launch_cg_batch(const BatchSpec<T>& b, const BatchGrid& g, hipStream_t s);
+template <typename T>
+void launch_cg_final_batch(const BatchSpec<T>& b, double* F, const BatchGrid& g,
+                           hipStream_t s);
 // dynamic LDS of the batched slab and pencil passes of one grid edge
 // under a schedule (throws for an invalid one)
 template <typename T>
@@ -277,58 +323,40 @@ struct CommitArgs {
 
 void launch_predict(double* F, const double* Fprev, const double dFbar[9],
                     int64_t N, hipStream_t s);
+// y = K : p and the per-block p . y (kp_blocks entries); returns at once on
+// a stopped run
 template <typename T>
-void launch_cg_init(const double* r64, T* r, T* x, double* partial, int nblk,
-                    int64_t n9, hipStream_t s);
-// partial: r.r partials of the last inverse pass (a CG run; the kernel also
-// applies the previous iteration's x += alpha p_old when x != null); null:
-// first, beta and alpha from the scalars.  pkp: per-block p . (K : p), one
-// entry per block of the grid (kp_blocks).
-template <typename T>
-void launch_kp(const T* K, const T* r, const T* p_old, T* p_new, T* y,
-               Scalars* sc, int64_t N, hipStream_t s,
-               const double* partial = nullptr, int count = 0, int parity = 0,
-               T* x = nullptr, double* pkp = nullptr);
+void launch_kp(const T* K, const T* p, T* y, const Scalars* sc, int64_t N,
+               double* pkp, hipStream_t s);
 int kp_blocks(int64_t N);  // one voxel per thread
-// the CG decision after the last update of a chunk; parity: that of the
-// iteration that would follow; pub (coherent pinned host memory, or null):
-// where the kernel also copies the scalars for the host
-void launch_cg_close(const double* partial, int count, Scalars* sc,
-                     int parity, hipStream_t s, Scalars* pub = nullptr);
-template <typename T>
-void launch_add_to_F(double* F, const T* x, int64_t n9, hipStream_t s);
+// the CG decision after the last update of a chunk from the partials of the
+// last pencil pass; parity: that of the iteration that would follow; pub
+// (coherent pinned host memory, or null): where the kernel also copies the
+// scalars for the host
+void launch_cg_close(const double* prr, const double* prz, int count,
+                     Scalars* sc, int parity, hipStream_t s,
+                     Scalars* pub = nullptr);
 template <typename T>
 void launch_convert(const double* in, T* out, int64_t n, hipStream_t s);
 
-enum { RED_INIT = 0, RED_ALPHA = 1, RED_BETA = 2, RED_RESID = 3 };
-// pub: as for launch_cg_close (RED_RESID only)
-void launch_reduce(int op, const double* partial, int count,
-                   const double* psum, const double* psq, int nslab_sums,
-                   double invN3, Scalars* sc, double* pbar, hipStream_t s,
-                   Scalars* pub = nullptr);
+// the scalars of a residual: ||G(P)||^2 and the r.r, r.z of the CG start
+// from 3 x count partials, ||P||^2 and <P>; pub: as for launch_cg_close
+void launch_reduce_residual(const double* part, int count, const double* psum,
+                            const double* psq, int nslab_sums, double invN3,
+                            Scalars* sc, hipStream_t s, Scalars* pub = nullptr);
 void launch_commit(const CommitArgs& a, hipStream_t s);
 void launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 void launch_fill_f64(double* p, double v, int64_t n, hipStream_t s);
 void launch_cauchy(const double* F, const double* P, double* sig, int64_t N,
                    hipStream_t s);
-void launch_init_scalars(Scalars* sc, int max_iters, double eta, hipStream_t s);
+// the start of a CG run: its cap and tolerance, r.r and r.z of its start
+void launch_init_scalars(Scalars* sc, int max_iters, double eta, double rr0,
+                         double rz0, hipStream_t s);
 void launch_bench_scalars(Scalars* sc, hipStream_t s);
 
-constexpr int kRedBlocks = 1024;  // grid of the elementwise reductions
-
 // ---------------------------------------------------------- batch helpers
-// Elementwise batch kernels give each RVE its own run of blocks so that
-// every block's partial sum belongs to one RVE.
-struct SegItem {
-  int64_t off;      // voxel offset in the arena
-  int64_t n9;       // 9 * voxels of this RVE
-  int blk0;         // first block of this RVE
-  int nblk;
-  double* partial;  // per-block partials of this RVE (nblk entries)
-  Scalars* sc;
-};
 struct RedItem {
-  const double* partial;
+  const double* partial;   // 3 x count
   int count;
   const double* psum;
   const double* psq;
@@ -336,22 +364,13 @@ struct RedItem {
   double invN3;
 };
 // CG of a whole batch in one launch of resident blocks (grid barriers between
-// passes); even / odd: the pass arguments of even and odd iterations (p_old
-// and p_new swapped)
+// passes); even / odd: the pass arguments of even and odd iterations
 template <typename T>
 struct BatchCG {
   BatchSpec<T> even, odd;
-  const SegItem* seg;
-  int seg_blocks;
-  const RedItem* red_inv;   // p.Ap partials of the inverse pass
-  const RedItem* red_seg;   // r.r partials of the update
   Scalars* scs;
   int nitems;
   int blocksA, blocksB;
-  int64_t cs;
-  T* x;
-  T* r;
-  T* Ap;
   int max_iters;            // iterations of this launch at most
   unsigned* bar;            // barrier state (kBatchBarWords words, zero at
                             // start but for the generation)
@@ -364,16 +383,9 @@ void launch_cg_batch_persistent(const BatchCG<T>& c, int grid, size_t lds,
 // blocks of the persistent CG kernel that are resident at once
 template <typename T>
 int cg_batch_persistent_grid(size_t lds);
-template <typename T>
-void launch_cg_init_batch(const SegItem* items, int nitems, int blocks,
-                          int64_t cs, const double* r64, T* r, T* x,
-                          hipStream_t s);
-template <typename T>
-void launch_cg_update_batch(const SegItem* items, int nitems, int blocks,
-                            int64_t cs, T* x, T* r, const T* p, const T* Ap,
-                            hipStream_t s);
-void launch_reduce_batch(int op, const RedItem* items, int nitems,
-                         Scalars* scs, hipStream_t s);
+// the scalars of every active RVE's residual (launch_reduce_residual)
+void launch_reduce_batch(const RedItem* items, int nitems, Scalars* scs,
+                         hipStream_t s);
 void launch_predict_batch(double* F, const double* Fprev, const uint8_t* vrve,
                           const double* dF /*[B][9]*/, int64_t N,
                           hipStream_t s);

@@ -33,4 +33,20 @@ __host__ __device__ inline double forcing_eta(int32_t mode, double cg_tol,
   return fmin(0.1, eta);
 }
 
+// (lambda + mu)/(lambda + 2 mu) of the isotropic medium whose Green operator
+// preconditions the CG runs, from the grains' cubic constants (params: C11,
+// C12, C44 first): their Voigt average, with 0.7 of its shear modulus, since
+// the flowing grains are softer in shear but not in bulk.  Only this ratio
+// matters to CG, and the optimum is flat: on 16^3 and 24^3 polycrystals
+// without and with 8 % particles, 0.75 to 0.87 take the same iterations to
+// within one in twenty, 0.5 a quarter more, 0 (plain CG) 1.7 times as many.
+// Constants without a positive medium: plain CG.
+inline double cg_preconditioner(const double* params) {
+  const double mu_el = (params[0] - params[1] + 3.0 * params[2]) / 5.0;
+  const double bulk = (params[0] + 2.0 * params[1]) / 3.0;
+  const double mu = 0.7 * mu_el, lam = bulk - 2.0 / 3.0 * mu;
+  const double c = (lam + mu) / (lam + 2.0 * mu);
+  return mu > 0.0 && bulk > 0.0 && c > 0.0 && c < 0.99 ? c : 0.0;
+}
+
 }  // namespace rve

@@ -102,12 +102,10 @@ void noalloc_apply_G(int n, const double L[3], int projection, const double* in,
   hipLaunchKernelGGL(noalloc_tables_kernel, dim3(1), dim3(256), 0, s, n, L[0],
                      L[1], L[2], projection, tw, vt);
   SpectralLaunch<double> G;
-  G.src = SRC_FIELD;
   G.in_field = in;
   G.spec = (cplx<double>*)(base + kSpecOff);
   G.tw = tw;
   G.vt = vt;
-  G.dst = DST_NORM;
   G.out_d = out;
   G.partial_inv = (double*)(base + kPartOff);
   launch_G<double>(n, G, s);

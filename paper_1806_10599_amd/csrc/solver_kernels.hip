@@ -4,7 +4,6 @@
 //   fixed-order (deterministic) reductions (text after Eq. 16), the Newton
 //   update F += dF, the commit of the increment with the fatigue indicators
 //   of Sec. 3.3, Eqs. 23-24.
-#include "batch_cg.hpp"
 #include "cg_scalars.hpp"
 #include "kernels.hpp"
 #include "newton.hpp"
@@ -37,180 +36,63 @@ void launch_predict(double* F, const double* Fprev, const double dFbar[9],
                      dFbar[5], dFbar[6], dFbar[7], dFbar[8]);
 }
 
-// r = -r64 (rounded to T), x = 0, partial sums of r.r
+// Material product of a CG direction (Sec. 2.1, Eqs. 15-16): per voxel
+// y_c = sum_d K[9c + d] p_d and the block's partial of p . y; one voxel per
+// thread, K streamed once, coalesced per component.  The stop flag of the
+// run is tested once the voxel's loads are issued.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void cg_init_kernel(
-    const double* __restrict__ r64, T* __restrict__ r, T* __restrict__ x,
-    double* __restrict__ partial, int64_t n9) {
-  __shared__ double red[kBlock];
-  double acc = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n9;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const T b = T(-r64[i]);
-    r[i] = b;
-    x[i] = T(0);
-    acc += double(b) * double(b);
-  }
-  const double t = block_reduce(acc, red);
-  if (threadIdx.x == 0) partial[blockIdx.x] = t;
-}
-
-template <typename T>
-void launch_cg_init(const double* r64, T* r, T* x, double* partial, int nblk,
-                    int64_t n9, hipStream_t s) {
-  hipLaunchKernelGGL((cg_init_kernel<T>), dim3(nblk), dim3(kBlock), 0, s, r64,
-                     r, x, partial, n9);
-}
-
-// CG direction and material product (Sec. 2.1, Eqs. 15-16): per voxel
-// p = r (first iteration) or r + beta p_old, then y = K : p
-// (y_c = sum_d K[9c + d] p_d); one voxel per thread, K streamed once,
-// coalesced per component.  With partial != null (a CG run) the kernel
-// takes the CG decision itself from the r.r partials of the last inverse
-// pass and, from the second iteration on, applies the previous iteration's
-// x += alpha p_old (its alpha was published by that iteration's forward
-// pass); it returns at once when the previous iteration halted the run, and
-// applies only the pending x update when this one stops it.  The decision
-// waits for the partials while the voxel's r, p_old and first KP entries of
-// K are already in flight: their loads are issued first, unconditionally
-// (clamped indices), so that the partial sum's latency hides behind them.
-// Without partial it takes first, beta and alpha from the scalars (kernel
-// timing).  With pkp != null each block writes its partial of p . (K : p).
-template <typename T, int PU>
 __global__ __launch_bounds__(kBlock) void kp_kernel(
-    const T* __restrict__ K, const T* __restrict__ r,
-    const T* __restrict__ p_old, T* __restrict__ p_new, T* __restrict__ y,
-    T* __restrict__ x, Scalars* __restrict__ sc, int64_t N,
-    const double* __restrict__ partial, int count,
-    double* __restrict__ pkp, int parity) {
-  // FP32: the voxel's r, p_old and first KP entries of K loaded before the
-  // decision, the rest of K right after it (about 120 VGPRs, four waves per
-  // SIMD); FP64: everything after it, K read inside the product (holding
-  // the data across the decision would halve the occupancy)
-  constexpr bool kEarly = sizeof(T) == 4;
-  constexpr int KP = kEarly ? 36 : 0;
-  __shared__ double red[kBlock];
+    const T* __restrict__ K, const T* __restrict__ p, T* __restrict__ y,
+    const Scalars* __restrict__ sc, int64_t N, double* __restrict__ pkp) {
+  __shared__ double red[kBlock / 64];
   const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t vl = v < N ? v : N - 1;
-  RrPartials<kEarly ? PU : 1> rp;
-  if (partial && kEarly) rp.load(partial, count);
-  T kv[81], rv[9], pv[9];
-  auto load_vectors = [&] {
+  const int32_t stopped = __hip_atomic_load(&sc->done, __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT);
+  T pd[9];
 #pragma unroll
-    for (int d = 0; d < 9; ++d) {
-      rv[d] = r[d * N + vl];
-      pv[d] = p_old[d * N + vl];
-    }
-  };
-  if constexpr (kEarly) load_vectors();
-#pragma unroll
-  for (int i = 0; i < KP; ++i) kv[i] = K[i * N + vl];
-  bool first, upd, stop = false;
-  T beta, alpha_prev;
-  if (partial) {
-    // every flag read here was written by an earlier launch: block 0 of this
-    // launch publishes slot `parity` (and done), which no block reads
-    const int q = parity ^ 1;
-    if (sc->halt[q]) {
-      if (blockIdx.x == 0 && threadIdx.x == 0) sc->halt[parity] = 1;
-      return;
-    }
-    const int prev = sc->its[q];
-    first = prev < 0;
-    BetaStep d{first, false, 0.0};
-    if (!first) {
-      if constexpr (!kEarly) rp.load(partial, count);
-      d = cg_beta_step(sc, parity, prev, rp.sum(partial, count));
-    }
-    if (first && sc->done) return;  // b = 0: nothing to solve
-    upd = !first && x != nullptr;
-    alpha_prev = T(sc->alphas[q]);
-    stop = d.stop;
-    beta = T(d.beta);
-  } else {
-    if (sc->done) return;
-    first = sc->first != 0;
-    beta = T(sc->beta);
-    upd = x != nullptr;
-    alpha_prev = T(sc->alpha);
-  }
-  if constexpr (!kEarly) load_vectors();
+  for (int d = 0; d < 9; ++d) pd[d] = p[d * N + vl];
   double acc = 0.0;
+  // FP32: every entry of K in flight at once (about 100 VGPRs)
+  constexpr bool kAll = sizeof(T) == 4;
+  T kv[kAll ? 81 : 1];
+  if constexpr (kAll) {
+#pragma unroll
+    for (int i = 0; i < 81; ++i) kv[i] = K[i * N + vl];
+  }
+  if (stopped) return;
   if (v < N) {
-    if (stop) {
-#pragma unroll
-      for (int d = 0; d < 9; ++d)
-        if (upd) x[d * N + v] += alpha_prev * pv[d];
-      return;
-    }
-    if constexpr (kEarly) {
-#pragma unroll
-      for (int i = KP; i < 81; ++i) kv[i] = K[i * N + v];
-    }
-    T pd[9];
-#pragma unroll
-    for (int d = 0; d < 9; ++d) {
-      T val = rv[d];
-      if (!first) val += beta * pv[d];
-      if (upd) x[d * N + v] += alpha_prev * pv[d];
-      pd[d] = val;
-      p_new[d * N + v] = val;
-    }
 #pragma unroll
     for (int c = 0; c < 9; ++c) {
-      T acc_c = T(0);
+      T s = T(0);
 #pragma unroll
-      for (int d = 0; d < 9; ++d)
-        acc_c += (kEarly ? kv[9 * c + d] : K[(9 * c + d) * N + v]) * pd[d];
-      y[c * N + v] = acc_c;
-      acc += double(pd[c]) * double(acc_c);
+      for (int d = 0; d < 9; ++d) {
+        if constexpr (kAll)
+          s += kv[9 * c + d] * pd[d];
+        else
+          s += K[(9 * c + d) * N + v] * pd[d];
+      }
+      y[c * N + v] = s;
+      acc += double(pd[c]) * double(s);
     }
   }
-  if (stop) return;
-  if (pkp) {
-    const double t = block_reduce(acc, red);
-    if (threadIdx.x == 0) pkp[blockIdx.x] = t;
-  }
+  const double t = block_reduce(acc, red);
+  if (threadIdx.x == 0) pkp[blockIdx.x] = t;
 }
 
 int kp_blocks(int64_t N) { return (int)((N + kBlock - 1) / kBlock); }
 
 template <typename T>
-void launch_kp(const T* K, const T* r, const T* p_old, T* p_new, T* y,
-               Scalars* sc, int64_t N, hipStream_t s, const double* partial,
-               int count, int parity, T* x, double* pkp) {
-  // early partial loads per lane: all of them up to 576 (64^3 with one
-  // component per slab block) or 1152 partials
-  const dim3 grid((unsigned)kp_blocks(N));
-  if (count <= 9 * 64)
-    launch((kp_kernel<T, 9>), grid, dim3(kBlock), 0, s, K, r, p_old, p_new, y,
-           x, sc, N, partial, count, pkp, parity);
-  else
-    launch((kp_kernel<T, 18>), grid, dim3(kBlock), 0, s, K, r, p_old, p_new,
-           y, x, sc, N, partial, count, pkp, parity);
+void launch_kp(const T* K, const T* p, T* y, const Scalars* sc, int64_t N,
+               double* pkp, hipStream_t s) {
+  launch((kp_kernel<T>), dim3((unsigned)kp_blocks(N)), dim3(kBlock), 0, s, K, p,
+         y, sc, N, pkp);
 }
 
-template void launch_kp<float>(const float*, const float*, const float*,
-                               float*, float*, Scalars*, int64_t, hipStream_t,
-                               const double*, int, int, float*, double*);
-template void launch_kp<double>(const double*, const double*, const double*,
-                                double*, double*, Scalars*, int64_t,
-                                hipStream_t, const double*, int, int, double*,
-                                double*);
-
-template <typename T>
-__global__ void add_to_F_kernel(double* __restrict__ F,
-                                const T* __restrict__ x, int64_t n9) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n9;
-       i += (int64_t)gridDim.x * blockDim.x)
-    F[i] += double(x[i]);
-}
-
-template <typename T>
-void launch_add_to_F(double* F, const T* x, int64_t n9, hipStream_t s) {
-  hipLaunchKernelGGL((add_to_F_kernel<T>), dim3(2048), dim3(kBlock), 0, s, F,
-                     x, n9);
-}
+template void launch_kp<float>(const float*, const float*, float*,
+                               const Scalars*, int64_t, double*, hipStream_t);
+template void launch_kp<double>(const double*, const double*, double*,
+                                const Scalars*, int64_t, double*, hipStream_t);
 
 template <typename T>
 __global__ void convert_kernel(const double* __restrict__ in,
@@ -226,77 +108,84 @@ void launch_convert(const double* in, T* out, int64_t n, hipStream_t s) {
                      out, n);
 }
 
-// Single-block fixed-order reductions that also advance the CG scalars.
-__global__ __launch_bounds__(kBlock) void reduce_kernel(
-    int op, const double* __restrict__ partial, int count,
-    const double* __restrict__ psum, const double* __restrict__ psq, int nss,
-    double invN3, Scalars* __restrict__ sc, double* __restrict__ pbar,
-    Scalars* pub) {
-  __shared__ double red[kBlock];
-  if ((op == RED_ALPHA || op == RED_BETA) && sc->done) return;
-  const double tot = cg_sum_partials(partial, count, red);
-  if (op == RED_RESID) {
-    double a2 = 0.0;
-    for (int i = threadIdx.x; i < 9 * nss; i += blockDim.x) a2 += psq[i];
-    const double P2 = block_reduce(a2, red);
-    for (int c = 0; c < 9; ++c) {
-      double a1 = 0.0;
-      for (int i = threadIdx.x; i < nss; i += blockDim.x) a1 += psum[c * nss + i];
-      const double m = block_reduce(a1, red);
-      if (threadIdx.x == 0) pbar[c] = m * invN3;
-    }
-    if (threadIdx.x == 0) {
-      sc->res2 = tot;
-      sc->P2 = P2;
-    }
-    if (pub) publish_scalars(sc, pub);
-    return;
+// The scalars of an FP64 residual, one block, fixed order: r.r and r.z of the
+// CG start and ||G(P)||^2 from 3 x count partials, ||P||^2 and <P>
+__device__ __forceinline__ void reduce_residual_block(const RedItem& it,
+                                                      Scalars* sc, double* red) {
+  const double rr = cg_sum_partials(it.partial, it.count, red);
+  const double rz = cg_sum_partials(it.partial + it.count, it.count, red);
+  const double res2 = cg_sum_partials(it.partial + 2 * it.count, it.count, red);
+  const double P2 = cg_sum_partials(it.psq, 9 * it.nss, red);
+  for (int c = 0; c < 9; ++c) {
+    const double m = cg_sum_partials(it.psum + c * it.nss, it.nss, red);
+    if (threadIdx.x == 0) sc->pbar[c] = m * it.invN3;
   }
-  if (threadIdx.x != 0) return;
-  cg_scalar_update(op, tot, sc);
+  if (threadIdx.x == 0) {
+    sc->rr0 = rr;
+    sc->rz0 = rz;
+    sc->res2 = res2;
+    sc->P2 = P2;
+  }
 }
 
-// End of a CG chunk: the decision the direction kernel of the next
-// iteration (parity p) would take, published for the host; it writes only
-// slot p, which that kernel rewrites with the same values.  When it stops
-// the run, that direction kernel (always queued after it) still applies the
-// pending x += alpha p.
-__global__ __launch_bounds__(kBlock) void cg_close_kernel(
-    const double* __restrict__ partial, int count, Scalars* __restrict__ sc,
-    int p, Scalars* pub) {
-  if (!sc->done) (void)cg_beta_consume(partial, count, sc, p);
+__global__ __launch_bounds__(kBlock) void reduce_residual_kernel(
+    RedItem it, Scalars* __restrict__ sc, Scalars* pub) {
+  __shared__ double red[kBlock / 64];
+  reduce_residual_block(it, sc, red);
   if (pub) publish_scalars(sc, pub);
 }
 
-void launch_cg_close(const double* partial, int count, Scalars* sc,
-                     int parity, hipStream_t s, Scalars* pub) {
-  hipLaunchKernelGGL(cg_close_kernel, dim3(1), dim3(kBlock), 0, s, partial,
+// one block per RVE
+__global__ __launch_bounds__(kBlock) void reduce_batch_kernel(
+    const RedItem* __restrict__ items, Scalars* __restrict__ scs) {
+  __shared__ double red[kBlock / 64];
+  Scalars* sc = scs + blockIdx.x;
+  if (!sc->inactive) reduce_residual_block(items[blockIdx.x], sc, red);
+}
+
+void launch_reduce_batch(const RedItem* items, int nitems, Scalars* scs,
+                         hipStream_t s) {
+  hipLaunchKernelGGL(reduce_batch_kernel, dim3(nitems), dim3(kBlock), 0, s,
+                     items, scs);
+}
+
+// End of a CG chunk: the decision the direction pass of the next iteration
+// (parity p) would take, published for the host; it writes only slot p,
+// which that pass rewrites with the same values.
+__global__ __launch_bounds__(kBlock) void cg_close_kernel(
+    const double* __restrict__ prr, const double* __restrict__ prz, int count,
+    Scalars* __restrict__ sc, int p, Scalars* pub) {
+  if (!sc->done) (void)cg_beta_consume(prr, prz, count, sc, p);
+  if (pub) publish_scalars(sc, pub);
+}
+
+void launch_cg_close(const double* prr, const double* prz, int count,
+                     Scalars* sc, int parity, hipStream_t s, Scalars* pub) {
+  hipLaunchKernelGGL(cg_close_kernel, dim3(1), dim3(kBlock), 0, s, prr, prz,
                      count, sc, parity, pub);
 }
 
-void launch_reduce(int op, const double* partial, int count,
-                   const double* psum, const double* psq, int nss,
-                   double invN3, Scalars* sc, double* pbar, hipStream_t s,
-                   Scalars* pub) {
-  hipLaunchKernelGGL(reduce_kernel, dim3(1), dim3(kBlock), 0, s, op, partial,
-                     count, psum, psq, nss, invN3, sc, pbar, pub);
+void launch_reduce_residual(const double* part, int count, const double* psum,
+                            const double* psq, int nss, double invN3,
+                            Scalars* sc, hipStream_t s, Scalars* pub) {
+  hipLaunchKernelGGL(reduce_residual_kernel, dim3(1), dim3(kBlock), 0, s,
+                     RedItem{part, count, psum, psq, nss, invN3}, sc, pub);
 }
 
-__global__ void init_scalars_kernel(Scalars* sc, int max_iters, double eta) {
+__global__ void init_scalars_kernel(Scalars* sc, int max_iters, double eta,
+                                    double rr0, double rz0) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
-    sc->max_iters = max_iters;
-    sc->eta2bb = eta * eta;
-    sc->done = 0;
-    sc->fails = 0;
+    sc->rr0 = rr0;
+    sc->rz0 = rz0;
+    cg_start(sc, max_iters, eta);
   }
 }
 
 __global__ void bench_scalars_kernel(Scalars* sc) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
-    // a matvec on p = r + 0 p_old that leaves the vectors unchanged
-    // (alpha = beta = 0) and reads p_old as every iteration after the first
+    // an iteration that leaves the residual unchanged (alpha = beta = 0)
+    // and reads every vector
     sc->done = 0;
-    sc->first = 0;
     sc->alpha = 0.0;
     sc->beta = 0.0;
     sc->alphas[0] = sc->alphas[1] = 0.0;
@@ -307,10 +196,10 @@ void launch_bench_scalars(Scalars* sc, hipStream_t s) {
   hipLaunchKernelGGL(bench_scalars_kernel, dim3(1), dim3(64), 0, s, sc);
 }
 
-void launch_init_scalars(Scalars* sc, int max_iters, double eta,
-                         hipStream_t s) {
+void launch_init_scalars(Scalars* sc, int max_iters, double eta, double rr0,
+                         double rz0, hipStream_t s) {
   hipLaunchKernelGGL(init_scalars_kernel, dim3(1), dim3(64), 0, s, sc,
-                     max_iters, eta);
+                     max_iters, eta, rr0, rz0);
 }
 
 // Commit: accumulate the indicator fields from the converged trial state.
@@ -439,14 +328,6 @@ void launch_cauchy(const double* F, const double* P, double* sig, int64_t N,
                      sig, N);
 }
 
-template void launch_cg_init<float>(const double*, float*, float*, double*,
-                                    int, int64_t, hipStream_t);
-template void launch_cg_init<double>(const double*, double*, double*, double*,
-                                     int, int64_t, hipStream_t);
-template void launch_add_to_F<float>(double*, const float*, int64_t,
-                                     hipStream_t);
-template void launch_add_to_F<double>(double*, const double*, int64_t,
-                                      hipStream_t);
 template void launch_convert<float>(const double*, float*, int64_t,
                                     hipStream_t);
 template void launch_convert<double>(const double*, double*, int64_t,
@@ -454,53 +335,6 @@ template void launch_convert<double>(const double*, double*, int64_t,
 
 
 // ------------------------------------------------------------------ batch
-// (block bodies in batch_cg.hpp)
-template <typename T>
-__global__ __launch_bounds__(kBlock) void cg_init_batch_kernel(
-    const SegItem* __restrict__ items, int nitems, int64_t cs,
-    const double* __restrict__ r64, T* __restrict__ r, T* __restrict__ x) {
-  __shared__ double red[kBlock / 64];
-  cg_init_batch_block<T>(items, nitems, cs, r64, r, x, blockIdx.x, red);
-}
-
-template <typename T>
-void launch_cg_init_batch(const SegItem* items, int nitems, int blocks,
-                          int64_t cs, const double* r64, T* r, T* x,
-                          hipStream_t s) {
-  hipLaunchKernelGGL((cg_init_batch_kernel<T>), dim3(blocks), dim3(kBlock), 0,
-                     s, items, nitems, cs, r64, r, x);
-}
-
-template <typename T>
-__global__ __launch_bounds__(kBlock) void cg_update_batch_kernel(
-    const SegItem* __restrict__ items, int nitems, int64_t cs,
-    T* __restrict__ x, T* __restrict__ r, const T* __restrict__ p,
-    const T* __restrict__ Ap) {
-  __shared__ double red[kBlock / 64];
-  cg_update_batch_block<T>(items, nitems, cs, x, r, p, Ap, blockIdx.x, red);
-}
-
-template <typename T>
-void launch_cg_update_batch(const SegItem* items, int nitems, int blocks,
-                            int64_t cs, T* x, T* r, const T* p, const T* Ap,
-                            hipStream_t s) {
-  hipLaunchKernelGGL((cg_update_batch_kernel<T>), dim3(blocks), dim3(kBlock),
-                     0, s, items, nitems, cs, x, r, p, Ap);
-}
-
-// one block per RVE
-__global__ __launch_bounds__(kBlock) void reduce_batch_kernel(
-    int op, const RedItem* __restrict__ items, Scalars* __restrict__ scs) {
-  __shared__ double red[kBlock / 64];
-  reduce_batch_block(op, items, scs, blockIdx.x, red);
-}
-
-void launch_reduce_batch(int op, const RedItem* items, int nitems,
-                         Scalars* scs, hipStream_t s) {
-  hipLaunchKernelGGL(reduce_batch_kernel, dim3(nitems), dim3(kBlock), 0, s, op,
-                     items, scs);
-}
-
 __global__ void newton_control_batch_kernel(Scalars* __restrict__ scs,
                                             BatchLog* __restrict__ log,
                                             int nitems, int it, NewtonCtl ctl) {
@@ -538,10 +372,7 @@ __global__ void newton_control_batch_kernel(Scalars* __restrict__ scs,
     return;
   }
   const double eta = forcing_eta(ctl.forcing, ctl.cg_tol, ctl.newton_tol, rel);
-  sc.max_iters = ctl.cg_max;
-  sc.eta2bb = eta * eta;
-  sc.done = 0;
-  sc.fails = 0;
+  cg_start(&sc, ctl.cg_max, eta);
 }
 
 void launch_newton_control_batch(Scalars* scs, BatchLog* log, int nitems,
@@ -648,18 +479,5 @@ void launch_commit_batch(const CommitBatchArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(commit_batch_kernel, dim3((unsigned)((a.N + kBlock - 1) / kBlock)),
                      dim3(kBlock), 0, s, a);
 }
-
-template void launch_cg_init_batch<float>(const SegItem*, int, int, int64_t,
-                                          const double*, float*, float*,
-                                          hipStream_t);
-template void launch_cg_init_batch<double>(const SegItem*, int, int, int64_t,
-                                           const double*, double*, double*,
-                                           hipStream_t);
-template void launch_cg_update_batch<float>(const SegItem*, int, int, int64_t,
-                                            float*, float*, const float*,
-                                            const float*, hipStream_t);
-template void launch_cg_update_batch<double>(const SegItem*, int, int, int64_t,
-                                             double*, double*, const double*,
-                                             const double*, hipStream_t);
 
 }  // namespace rve

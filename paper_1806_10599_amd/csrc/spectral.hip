@@ -20,11 +20,12 @@
 //
 // Only the delta_ik structure of the operator is used: row i of the output
 // depends on row i of the input, so pass B never needs all nine components.
-#include "batch_cg.hpp"
 #include "cg_scalars.hpp"
 #include "common.hpp"
 #include "fft.hpp"
 #include "kernels.hpp"
+
+#include <type_traits>
 
 namespace rve {
 
@@ -132,12 +133,11 @@ __device__ __forceinline__ bool stopped_now(int32_t f) {
 // ------------------------------------------------------------------ pass A
 // lb: logical block within this RVE's pass-A grid
 // gate: the run's scalars when the pass must return at once on a stopped
-// run (returns false then); with SRC_KP the check precedes all work
+// run (returns false then); with SRC_KROW the check precedes all work
 template <typename T, int N, int CPB, int SRC>
 __device__ __forceinline__ bool slab_fwd_body(const SlabFwdArgs<T>& a, int lb,
                                               cplx<T>* lds, cplx<T>* tw,
                                               double* red,
-                                              const KpStep<T>& st,
                                               const Scalars* gate = nullptr) {
   constexpr int H = N / 2;
   constexpr int NG = 9 / CPB;
@@ -145,7 +145,7 @@ __device__ __forceinline__ bool slab_fwd_body(const SlabFwdArgs<T>& a, int lb,
   const int x = lb / NG;
   const int grp = lb - x * NG;
   const int32_t stopped = stop_flag(gate);
-  if (SRC == SRC_KP && stopped_now(stopped)) return false;
+  if (SRC != SRC_FIELD && stopped_now(stopped)) return false;
   constexpr int PER0 = (H * N + kBlock - 1) / kBlock;
   TwiddleStage<T, N, SRC == SRC_FIELD && kDeferTw<T, N>(PER0)> tws;
   tws.load(a.tw, tw);
@@ -197,48 +197,32 @@ __device__ __forceinline__ bool slab_fwd_body(const SlabFwdArgs<T>& a, int lb,
   }
   tws.store(tw);
   if (stopped_now(stopped)) return false;
-  double kacc = 0.0;  // p . (K:p) over this block's components
-  for (int t = threadIdx.x; SRC == SRC_KP && t < H * N; t += blockDim.x) {
+  double kacc[CPB];  // p . (K:p) of each component over the slab
+#pragma unroll
+  for (int q = 0; q < CPB; ++q) kacc[q] = 0.0;
+  for (int t = threadIdx.x; SRC == SRC_KROW && t < H * N; t += blockDim.x) {
     const int yp = t / N, z = t - (t / N) * N;
     T out[2][CPB];
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
       const int64_t v = ((int64_t)x * N + yp + hh * H) * N + z;
-      if constexpr (SRC == SRC_FIELD) {
+      T pd[9];
 #pragma unroll
-        for (int q = 0; q < CPB; ++q)
-          out[hh][q] = a.field[(grp * CPB + q) * cs + v];
-      } else {
-        T pd[9];
+      for (int d = 0; d < 9; ++d) pd[d] = a.field[d * cs + v];
 #pragma unroll
-        for (int d = 0; d < 9; ++d) {
-          T val = a.r[d * cs + v];
-          if (!st.first) val += st.beta * a.p_old[d * cs + v];
-          pd[d] = val;
-        }
+      for (int q = 0; q < CPB; ++q) {
+        const int c = grp * CPB + q;
+        T acc = T(0);
 #pragma unroll
-        for (int q = 0; q < CPB; ++q) {
-          const int c = grp * CPB + q;
-          if (st.upd) a.x[c * cs + v] += st.alpha * a.p_old[c * cs + v];
-          a.p_new[c * cs + v] = pd[c];
-          T acc = T(0);
-#pragma unroll
-          for (int d = 0; d < 9; ++d) acc += a.K[(9 * c + d) * cs + v] * pd[d];
-          out[hh][q] = acc;
-          kacc += double(pd[c]) * double(acc);
-        }
+        for (int d = 0; d < 9; ++d) acc += a.K[(9 * c + d) * cs + v] * pd[d];
+        out[hh][q] = acc;
+        kacc[q] += double(pd[c]) * double(acc);
       }
     }
 #pragma unroll
-    for (int q = 0; q < CPB; ++q) {
-#pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        ss[q] += double(out[hh][q]) * double(out[hh][q]);
-        s1[q] += double(out[hh][q]);
-      }
+    for (int q = 0; q < CPB; ++q)
       lds[q * SlabGeom<N>::PLANE + yp * SlabGeom<N>::PITCH + z] =
           cplx<T>{out[0][q], out[1][q]};
-    }
   }
   __syncthreads();
 
@@ -277,9 +261,13 @@ __device__ __forceinline__ bool slab_fwd_body(const SlabFwdArgs<T>& a, int lb,
     const int c = grp * CPB + q;
     a.spec[((size_t)(c * N + x) * N + ky) * H + kz] = lds[cm(q * H + kz, ky)];
   }
-  if (SRC == SRC_KP && a.pkp_out) {
-    const double t1 = block_sum(kacc, red);
-    if (threadIdx.x == 0) a.pkp_out[lb] = t1;
+  if (SRC == SRC_KROW && a.pkp_out) {
+    // per component and slab: the same sums under every schedule
+#pragma unroll
+    for (int q = 0; q < CPB; ++q) {
+      const double t1 = block_sum(kacc[q], red);
+      if (threadIdx.x == 0) a.pkp_out[(grp * CPB + q) * N + x] = t1;
+    }
   }
   if (a.psum) {
     // per-slab, per-component sum and sum of squares: [9][N]
@@ -401,7 +389,318 @@ __device__ __forceinline__ bool pencil_body(const PencilArgs<T>& a, int lb,
   return true;
 }
 
+// ------------------------------------- CG vectors in the x-transformed pencils
+// The vectors of a CG run live in Fourier space.  A compatible field is
+// A_ij = a_i v_j per frequency, so three half spectra hold the residual
+// (rho_i = sum_j R_ij v_j of the unnormalised spectrum R), the direction
+// (pi_i, p_ij = pi_i v_j with the 1/N^3 of the inverse transform) and the
+// iterate (xi_i, the same), layout [i][ky][kx][kz].  G needs no tensor of its
+// own: the projection of K:p is the contraction with v, so
+//   pencil_fwd_body: FFT along x of K:p, rho -= alpha (K:p) v, and the norms
+//     r.r = sum |rho|^2 / |v|^2 / N^3 and r.z (Parseval; every frequency of
+//     one half space counts twice);
+//   pencil_inv_body: z = M r, pi = z + beta pi, xi += alpha_prev pi_prev, and
+//     the inverse FFT along x of the direction.
+// M = I - prec n (x) n, n = v/|v|, is the Green operator of an isotropic
+// medium up to a factor, prec = (lambda + mu)/(lambda + 2 mu): a plain CG for
+// prec = 0.  Of row i only two lines are transformed each way: v_y and v_z
+// are constant along x, so y_i2 and y_i3 are combined before the forward
+// transform, and the inverse needs pi_i and v_x pi_i.
+// In the plane kz = 0 both a frequency and its mirror are stored.  Their
+// transforms round differently, and the part of rho that is not Hermitian
+// would never be reduced (the real field does not contain it): the mirror
+// half (mirrored) is left out of the norms, and the direction takes the
+// other half's rho there.
+// Bound by the latency of one load, six-line transform and store per block.
+template <int N>
+__device__ __forceinline__ bool mirrored(int kx, int ky, int kz) {
+  return kz == 0 && (ky > N / 2 || (ky == 0 && kx > N / 2));
+}
+
+template <typename T, int N, int TT>
+struct PencilGeom {
+  static constexpr int H = N / 2;
+  static constexpr int TP = TT + 1;          // LDS pitch of a kx row
+  static constexpr int LS = N * TP + TT;     // LDS stride of a line group
+  static constexpr int LDS = 6 * LS;
+  static constexpr int NTILE = (H + TT - 1) / TT;
+};
+
+template <int N, int TT>
+struct PencilMap {
+  __device__ __forceinline__ int operator()(int line, int kx) const {
+    const int j = line / TT;
+    return j * PencilGeom<float, N, TT>::LS + kx * (TT + 1) + (line - j * TT);
+  }
+};
+
+// the frequency of a pencil item, its wave vector, and 1/|v|^2 (zero where
+// the operator is: the null frequency and the Nyquist ones)
+template <typename T, int N>
+struct Freq {
+  T v1, v2, v3, inv;
+  double wgt;
+  __device__ __forceinline__ Freq(const T* __restrict__ vt, int kx, int ky,
+                                  int kz, bool in) {
+    constexpr int H = N / 2;
+    const int kzc = kz < H ? kz : 0;
+    v1 = vt[kx];
+    v2 = vt[N + ky];
+    v3 = vt[2 * N + kzc];
+    const bool zero = !in || kx == H || ky == H || (kx == 0 && ky == 0 && kz == 0);
+    const T n2 = v1 * v1 + v2 * v2 + v3 * v3;
+    inv = zero ? T(0) : T(1) / n2;
+    wgt = mirrored<N>(kx, ky, kz) ? 0.0 : 2.0;
+  }
+};
+
+template <int N>
+__device__ __forceinline__ size_t sv_index(int i, int ky, int kx, int kz) {
+  return ((size_t)(i * N + ky) * N + kx) * (N / 2) + kz;
+}
+
+// RES: rho = -(P v) of the FP64 residual, rounded to TR, and ||G(P)||^2 in
+// pres besides the norms of the rounded one; else rho -= alpha (K:p) v
+template <typename T, typename TR, int N, int TT, int NT, bool RES>
+__device__ __forceinline__ bool pencil_fwd_body(const PencilFwdArgs<T, TR>& a,
+                                                int lb, cplx<T>* lds,
+                                                cplx<T>* tw, double* red,
+                                                T alpha,
+                                                const Scalars* gate) {
+  using G = PencilGeom<T, N, TT>;
+  constexpr int H = G::H, TP = G::TP, LS = G::LS;
+  const int tile = lb % G::NTILE, ky = lb / G::NTILE, kz0 = tile * TT;
+  const int ncol = (H - kz0) < TT ? (H - kz0) : TT;
+  const int32_t stopped = stop_flag(gate);
+  for (int t = threadIdx.x; t < N; t += NT) tw[t] = a.tw[t];
+  const T v2 = a.vt[N + ky];
+  constexpr int PER = (3 * N * TT + NT - 1) / NT;
+  constexpr int CH0 = sizeof(T) == 4 ? 4 : 1;
+  constexpr int CH = PER < CH0 ? PER : CH0;
+  // this thread's frequencies; their rho is loaded with the spectrum when it
+  // is at most two items per thread
+  constexpr int PP = (N * TT + NT - 1) / NT;
+  constexpr bool kEarly = !RES && PP <= 2;
+  cplx<TR> rv[kEarly ? PP : 1][3];
+  if constexpr (kEarly) {
+#pragma unroll
+    for (int u = 0; u < PP; ++u) {
+      const int t = threadIdx.x + u * NT;
+      const int kx = t / TT, tt = t - (t / TT) * TT;
+      if (t < N * TT && tt < ncol)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) rv[u][i] = a.rho[sv_index<N>(i, ky, kx, kz0 + tt)];
+    }
+  }
+  for (int c0 = 0; c0 < PER; c0 += CH) {
+    cplx<T> y[CH][3];
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+      const int t = threadIdx.x + (c0 + u) * NT;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) y[u][j] = {T(0), T(0)};
+      if (c0 + u < PER && t < 3 * N * TT) {
+        const int i = t / (N * TT), rem = t - i * N * TT;
+        const int x = rem / TT, tt = rem - (rem / TT) * TT;
+        if (tt < ncol)
+#pragma unroll
+          for (int j = 0; j < 3; ++j)
+            y[u][j] = a.spec[((size_t)((3 * i + j) * N + x) * N + ky) * H + kz0 + tt];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+      const int t = threadIdx.x + (c0 + u) * NT;
+      if (c0 + u < PER && t < 3 * N * TT) {
+        const int i = t / (N * TT), rem = t - i * N * TT;
+        const int x = rem / TT, tt = rem - (rem / TT) * TT;
+        const T v3 = a.vt[2 * N + (tt < ncol ? kz0 + tt : 0)];
+        lds[2 * i * LS + x * TP + tt] = y[u][0];
+        lds[(2 * i + 1) * LS + x * TP + tt] = {v2 * y[u][1].x + v3 * y[u][2].x,
+                                               v2 * y[u][1].y + v3 * y[u][2].y};
+      }
+    }
+  }
+  if (stopped_now(stopped)) return false;
+  __syncthreads();
+  if (ky != H) fft_lines<N, -1>(lds, tw, 6 * TT, PencilMap<N, TT>());
+
+  double srr = 0.0, srz = 0.0, sres = 0.0;
+#pragma unroll
+  for (int u = 0; u < PP; ++u) {
+    const int t = threadIdx.x + u * NT;
+    const int kx = t / TT, tt = t - (t / TT) * TT;
+    if (t >= N * TT || tt >= ncol) continue;
+    const Freq<T, N> f(a.vt, kx, ky, kz0 + tt, true);
+    cplx<TR> r[3];
+    double w2 = 0.0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const cplx<T> y0 = lds[2 * i * LS + kx * TP + tt];
+      const cplx<T> y1 = lds[(2 * i + 1) * LS + kx * TP + tt];
+      const cplx<T> w = {f.v1 * y0.x + y1.x, f.v1 * y0.y + y1.y};
+      const size_t at = sv_index<N>(i, ky, kx, kz0 + tt);
+      if constexpr (RES) {
+        w2 += double(w.x) * double(w.x) + double(w.y) * double(w.y);
+        r[i] = f.inv == T(0) ? cplx<TR>{TR(0), TR(0)} : cplx<TR>{TR(-w.x), TR(-w.y)};
+      } else {
+        if constexpr (kEarly) r[i] = rv[u][i]; else r[i] = a.rho[at];
+        if (f.inv != T(0)) r[i] = {r[i].x - TR(alpha) * TR(w.x), r[i].y - TR(alpha) * TR(w.y)};
+      }
+      a.rho[at] = r[i];
+    }
+    double q = 0.0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      q += double(r[i].x) * double(r[i].x) + double(r[i].y) * double(r[i].y);
+    const T dx = T(r[0].x) * f.v1 + T(r[1].x) * f.v2 + T(r[2].x) * f.v3;
+    const T dy = T(r[0].y) * f.v1 + T(r[1].y) * f.v2 + T(r[2].y) * f.v3;
+    const double in = f.wgt * double(f.inv);
+    const double l = (double(dx) * double(dx) + double(dy) * double(dy)) * double(f.inv);
+    srr += in * q;
+    srz += in * (q - a.prec * l);
+    sres += in * w2;
+  }
+  const double t1 = block_sum_fixed(srr, red);
+  const double t2 = block_sum_fixed(srz, red);
+  if (threadIdx.x == 0) {
+    a.prr[lb] = t1 * a.invN3;
+    a.prz[lb] = t2 * a.invN3;
+  }
+  if constexpr (RES) {
+    const double t3 = block_sum_fixed(sres, red);
+    if (threadIdx.x == 0) a.pres[lb] = t3 * a.invN3;
+  }
+  return true;
+}
+
+// FINAL: the inverse FFT along x of the iterate xi + xalpha pi (nothing is
+// written but the spectrum); else the next direction and its inverse FFT
+template <typename T, int N, int TT, int NT, bool FINAL>
+__device__ __forceinline__ void pencil_inv_body(const PencilInvArgs<T>& a,
+                                                int lb, cplx<T>* lds,
+                                                cplx<T>* tw) {
+  using G = PencilGeom<T, N, TT>;
+  const bool pub = lb == 0 && threadIdx.x == 0;
+  constexpr int H = G::H, TP = G::TP, LS = G::LS;
+  const int tile = lb % G::NTILE, ky = lb / G::NTILE, kz0 = tile * TT;
+  const int ncol = (H - kz0) < TT ? (H - kz0) : TT;
+  // the loads of the vectors and partials are issued before the decision
+  constexpr int PP = (N * TT + NT - 1) / NT;
+  constexpr bool kEarly = PP <= (sizeof(T) == 4 ? 2 : 1);
+  constexpr int PE = kEarly ? PP : 1;
+  cplx<T> rv[PE][3], pv[PE][3], xv[PE][3];
+  auto load = [&](int u, int w) {
+    const int t = threadIdx.x + u * NT;
+    const int kx = t / TT, tt = t - (t / TT) * TT;
+    if (t < N * TT && tt < ncol)
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        const size_t at = sv_index<N>(i, ky, kx, kz0 + tt);
+        if (!FINAL) {
+          const bool m = mirrored<N>(kx, ky, kz0 + tt);
+          const cplx<T> r = a.rho[m ? sv_index<N>(i, (N - ky) % N, (N - kx) % N, 0) : at];
+          rv[w][i] = {m ? -r.x : r.x, r.y};   // v is odd: rho(-k) = -conj
+        }
+        pv[w][i] = a.pi[at];
+        xv[w][i] = a.xi[at];
+      }
+  };
+  if constexpr (kEarly) {
+#pragma unroll
+    for (int u = 0; u < PP; ++u) load(u, u);
+  }
+  bool first = false;
+  T beta = T(0), alpha = T(0);
+  bool valid = true;
+  Scalars* sc = a.scw;
+  if constexpr (FINAL) {
+    valid = sc->xvalid != 0;
+    alpha = T(sc->xalpha);
+  } else if (a.prr) {
+    // every flag read here was written by an earlier pass: block 0 of
+    // the RVE publishes slot `parity` (and done), which no block reads
+    const int q = a.parity ^ 1;
+    WavePartials<8> wr, wz;
+    wr.load(a.prr, a.count);
+    wz.load(a.prz, a.count);
+    if (sc->halt[q]) {
+      if (pub) sc->halt[a.parity] = 1;
+      return;
+    }
+    const int prev = sc->its[q];
+    const double rr = prev < 0 ? sc->rr0 : wr.sum(a.prr, a.count);
+    const double rz = prev < 0 ? sc->rz0 : wz.sum(a.prz, a.count);
+    const BetaStep d = cg_beta_step(sc, a.parity, prev, rr, rz, pub);
+    if (d.stop) return;
+    first = d.first;
+    beta = T(d.beta);
+    alpha = first ? T(0) : T(sc->alphas[q]);
+  } else {  // timing: alpha = beta = 0
+    beta = T(sc->beta);
+    alpha = T(sc->alpha);
+  }
+  for (int t = threadIdx.x; t < N; t += NT) tw[t] = a.tw[t];
+#pragma unroll
+  for (int u = 0; u < PP; ++u) {
+    const int w = kEarly ? u : 0;
+    if constexpr (!kEarly) load(u, 0);
+    const int t = threadIdx.x + u * NT;
+    const int kx = t / TT, tt = t - (t / TT) * TT;
+    if (t >= N * TT) continue;
+    const bool in = tt < ncol;
+    const Freq<T, N> f(a.vt, kx, ky, kz0 + tt, in);
+    cplx<T> p[3];
+    if constexpr (FINAL) {
+#pragma unroll
+      for (int i = 0; i < 3; ++i)
+        p[i] = (in && valid) ? cplx<T>{xv[w][i].x + alpha * pv[w][i].x,
+                                       xv[w][i].y + alpha * pv[w][i].y}
+                             : cplx<T>{T(0), T(0)};
+    } else if (in) {
+      const cplx<T>* r = rv[w];
+      const T g = a.prec * f.inv;
+      const T dx = g * (r[0].x * f.v1 + r[1].x * f.v2 + r[2].x * f.v3);
+      const T dy = g * (r[0].y * f.v1 + r[1].y * f.v2 + r[2].y * f.v3);
+      const T sc3 = a.invN3 * f.inv;
+      const T vv[3] = {f.v1, f.v2, f.v3};
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        p[i] = {sc3 * (r[i].x - vv[i] * dx), sc3 * (r[i].y - vv[i] * dy)};
+        cplx<T> x = {T(0), T(0)};
+        if (!first) {
+          p[i] = {p[i].x + beta * pv[w][i].x, p[i].y + beta * pv[w][i].y};
+          x = {xv[w][i].x + alpha * pv[w][i].x, xv[w][i].y + alpha * pv[w][i].y};
+        }
+        const size_t at = sv_index<N>(i, ky, kx, kz0 + tt);
+        a.pi[at] = p[i];
+        a.xi[at] = x;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 3; ++i) p[i] = {T(0), T(0)};
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      lds[2 * i * LS + kx * TP + tt] = {f.v1 * p[i].x, f.v1 * p[i].y};
+      lds[(2 * i + 1) * LS + kx * TP + tt] = p[i];
+    }
+  }
+  __syncthreads();
+  if (ky != H) fft_lines<N, +1>(lds, tw, 6 * TT, PencilMap<N, TT>());
+  for (int t = threadIdx.x; t < 6 * N * TT; t += NT) {
+    const int l = t / (N * TT), rem = t - l * N * TT;
+    const int x = rem / TT, tt = rem - (rem / TT) * TT;
+    if (tt < ncol)
+      a.spec[((size_t)((3 * (l / 2) + (l & 1)) * N + x) * N + ky) * H + kz0 + tt] =
+          lds[l * LS + x * TP + tt];
+  }
+}
+
 // ------------------------------------------------------------------ pass C
+// DST_P and DST_ADDF read the planes of an expanded direction (pencil_inv_
+// body): component 3 i + j of it is v_j times a spectrum of row i, of which
+// the planes 3 i (j = 0, with v_x applied) and 3 i + 1 are stored.
 template <typename T, typename TO, int N, int CPB, int DST>
 __device__ __forceinline__ bool slab_inv_body(const SlabInvArgs<T, TO>& a,
                                               int lb, cplx<T>* lds,
@@ -409,6 +708,7 @@ __device__ __forceinline__ bool slab_inv_body(const SlabInvArgs<T, TO>& a,
                                               const Scalars* gate = nullptr) {
   constexpr int H = N / 2;
   constexpr int NG = 9 / CPB;
+  constexpr bool kExpand = DST == DST_P || DST == DST_ADDF;
   const int64_t cs = a.cs;
   const int x = lb / NG;
   const int grp = lb - x * NG;
@@ -416,33 +716,6 @@ __device__ __forceinline__ bool slab_inv_body(const SlabInvArgs<T, TO>& a,
   constexpr int PER0 = (CPB * N * H + kBlock - 1) / kBlock;
   TwiddleStage<T, N, kDeferTw<T, N>(PER0)> tws;
   tws.load(a.tw, tw);
-  // the real-space operand of the output step (r of a CG run, or the dot
-  // product's field): when it is one chunk per thread of one component,
-  // its loads are issued now and their latency hides behind the transforms
-  // (three components would hold 48 more registers across them)
-  constexpr int PER2 = (H * N + kBlock - 1) / kBlock;
-  constexpr int CH2 = PER2 < kStage<T, N> ? PER2 : kStage<T, N>;
-  constexpr bool kSrc = DST == DST_DOT || DST == DST_CG;
-  constexpr bool kEarly = kSrc && PER2 <= CH2 && CPB == 1;
-  T pve[kEarly ? CH2 : 1][CPB][2];
-  auto load_src = [&](int c0, auto& pv) {
-    const T* src = (DST == DST_CG) ? a.rio : a.pdot;
-#pragma unroll
-    for (int u = 0; u < CH2; ++u) {
-      const int t = threadIdx.x + (c0 + u) * kBlock;
-      if (c0 + u < PER2 && t < H * N) {
-        const int yp = t / N, z = t - (t / N) * N;
-#pragma unroll
-        for (int q = 0; q < CPB; ++q)
-#pragma unroll
-          for (int hh = 0; hh < 2; ++hh) {
-            const int64_t v = ((int64_t)x * N + yp + hh * H) * N + z;
-            pv[u][q][hh] = src[(grp * CPB + q) * cs + v];
-          }
-      }
-    }
-  };
-  if constexpr (kEarly) load_src(0, pve);
   const ColMap<N> cm;
   {
     constexpr int PER = PER0;
@@ -457,7 +730,8 @@ __device__ __forceinline__ bool slab_inv_body(const SlabInvArgs<T, TO>& a,
           const int rem = t - q * N * H;
           const int ky = rem / H, kz = rem - (rem / H) * H;
           const int c = grp * CPB + q;
-          val[u] = a.spec[((size_t)(c * N + x) * N + ky) * H + kz];
+          const int pl = kExpand && c % 3 == 2 ? c - 1 : c;
+          val[u] = a.spec[((size_t)(pl * N + x) * N + ky) * H + kz];
         }
       }
 #pragma unroll
@@ -467,6 +741,13 @@ __device__ __forceinline__ bool slab_inv_body(const SlabInvArgs<T, TO>& a,
           const int q = t / (N * H);
           const int rem = t - q * N * H;
           const int ky = rem / H, kz = rem - (rem / H) * H;
+          if constexpr (kExpand) {
+            const int j = (grp * CPB + q) % 3;
+            if (j > 0) {
+              const T f = a.vt[j == 1 ? N + ky : 2 * N + kz];
+              val[u] = {f * val[u].x, f * val[u].y};
+            }
+          }
           lds[cm(q * H + kz, ky)] = val[u];
         }
       }
@@ -474,8 +755,6 @@ __device__ __forceinline__ bool slab_inv_body(const SlabInvArgs<T, TO>& a,
   }
   tws.store(tw);
   if (stopped_now(stopped)) return false;
-  T alpha = T(0);
-  if constexpr (DST == DST_CG) alpha = T(a.sc->alphas[a.parity]);
   __syncthreads();
   fft_lines<N, +1>(lds, tw, CPB * H, ColMap<N>());
 
@@ -499,49 +778,25 @@ __device__ __forceinline__ bool slab_inv_body(const SlabInvArgs<T, TO>& a,
   fft_lines<N, +1>(lds, tw, CPB * H, RowMap<N>());
 
   double acc = 0.0;
-  {
-    // the p (or r) loads of a chunk are issued together (same order of the
-    // sum)
-    constexpr int PER = PER2;
-    constexpr int CH = CH2;
-    for (int c0 = 0; c0 < PER; c0 += CH) {
-      T pvl[CH2][CPB][2];
-      if constexpr (kSrc && !kEarly) load_src(c0, pvl);
+  for (int t = threadIdx.x; t < H * N; t += kBlock) {
+    const int yp = t / N, z = t - (t / N) * N;
 #pragma unroll
-      for (int u = 0; u < CH; ++u) {
-        const int t = threadIdx.x + (c0 + u) * kBlock;
-        if (!(c0 + u < PER && t < H * N)) continue;
-        const int yp = t / N, z = t - (t / N) * N;
+    for (int q = 0; q < CPB; ++q) {
+      const int c = grp * CPB + q;
+      const cplx<T> zz = lds[q * SlabGeom<N>::PLANE + yp * SlabGeom<N>::PITCH + z];
 #pragma unroll
-        for (int q = 0; q < CPB; ++q) {
-          const int c = grp * CPB + q;
-          const cplx<T> zz = lds[q * SlabGeom<N>::PLANE + yp * SlabGeom<N>::PITCH + z];
-#pragma unroll
-          for (int hh = 0; hh < 2; ++hh) {
-            const int64_t v = ((int64_t)x * N + yp + hh * H) * N + z;
-            const T val = hh ? zz.y : zz.x;
-            T src_v = T(0);
-            if constexpr (kEarly)
-              src_v = pve[u][q][hh];
-            else if constexpr (kSrc)
-              src_v = pvl[u][q][hh];
-            if constexpr (DST == DST_CG) {
-              const T rn = src_v - alpha * val;
-              a.rio[c * cs + v] = rn;
-              acc += double(rn) * double(rn);
-            } else if constexpr (DST == DST_DOT) {
-              a.out[c * cs + v] = TO(val);
-              acc += double(src_v) * double(val);
-            } else {
-              a.out[c * cs + v] = TO(val);
-              acc += double(val) * double(val);
-            }
-          }
-        }
+      for (int hh = 0; hh < 2; ++hh) {
+        const int64_t v = ((int64_t)x * N + yp + hh * H) * N + z;
+        const T val = hh ? zz.y : zz.x;
+        if constexpr (DST == DST_ADDF)
+          a.out[c * cs + v] += TO(val);
+        else
+          a.out[c * cs + v] = TO(val);
+        if constexpr (DST == DST_NORM) acc += double(val) * double(val);
       }
     }
   }
-  if (a.partial) {
+  if (DST == DST_NORM && a.partial) {
     double tot = block_sum(acc, red);
     if (threadIdx.x == 0) a.partial[lb] = tot;
   }
@@ -561,14 +816,6 @@ struct SpectralTraits {
 };
 
 // ---------------------------------------------------- single-RVE kernels
-// the direction step of an SRC_KP pass A that takes it from the scalars
-// (p = r or r + beta p_old, no x update)
-template <typename T>
-__device__ __forceinline__ KpStep<T> kp_step_of(const Scalars* sc) {
-  if (!sc) return KpStep<T>{true, T(0), false, T(0)};
-  return KpStep<T>{sc->first != 0, T(sc->beta), false, T(0)};
-}
-
 template <typename T, int N, int CPB, int SRC>
 __global__ __launch_bounds__(kBlock) void slab_fwd_kernel(SlabFwdArgs<T> a) {
   __shared__ cplx<T> lds[CPB * SlabGeom<N>::PLANE];
@@ -577,80 +824,59 @@ __global__ __launch_bounds__(kBlock) void slab_fwd_kernel(SlabFwdArgs<T> a) {
   // done comes from an earlier launch, except after a breakdown that block
   // 0 of this launch publishes at its end (cg_alpha_publish): blocks that
   // read done before that write and go on only fill the spectrum, which
-  // the inverse pass of a stopped run never reads (it returns on done).
-  // The body reads it and returns once its loads are issued.
-  KpStep<T> st = kp_step_of<T>(SRC == SRC_KP ? a.sc : nullptr);
-  if (SRC == SRC_KP && a.x) {  // timing of the folded pass: x += alpha p_old
-    st.upd = true;
-    st.alpha = T(a.sc->alpha);
-  }
+  // the passes of a stopped run never read (they return on done).  The body
+  // reads it and returns once its loads are issued.
   if (!slab_fwd_body<T, N, CPB, SRC>(a, xcd_remap(blockIdx.x, gridDim.x), lds,
-                                     tw, red, st, a.sc))
+                                     tw, red, a.sc))
     return;
   if (a.pkp && blockIdx.x == 0)
     cg_alpha_publish(a.pkp, a.pkp_count, a.scw, a.parity, red);
-}
-
-// Pass A of a single-RVE CG iteration with the direction kernel folded in
-// (Sec. 2.1, Eqs. 15-16): every block takes the CG decision of the
-// direction kernel itself from the r.r partials of the last pass C (the
-// same fixed-order sum in every block, cg_beta_consume), applies the
-// previous iteration's x += alpha p_old on its own components, forms
-// p = r + beta p_old at each voxel of its slab (all nine components: the
-// nine blocks of a slab run on one XCD and share r and p_old through its
-// L2), writes its components of p and transforms its rows of K : p, and
-// writes its partial of p . (K:p) for the alpha that pass B publishes.  It
-// returns at once after a halted iteration, and applies only the pending x
-// update when this iteration stops the run.
-template <typename T, int N, int CPB>
-__global__ __launch_bounds__(kBlock) void slab_fwd_cg_kernel(SlabFwdArgs<T> a) {
-  __shared__ cplx<T> lds[CPB * SlabGeom<N>::PLANE];
-  __shared__ cplx<T> tw[N];
-  __shared__ double red[kBlock];
-  Scalars* sc = a.scw;
-  // every flag read here was written by an earlier launch: block 0 of this
-  // launch publishes slot `parity` (and done), which no block reads
-  const int q = a.parity ^ 1;
-  if (sc->halt[q]) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) sc->halt[a.parity] = 1;
-    return;
-  }
-  const BetaStep d = cg_beta_consume(a.pinv, a.pinv_count, sc, a.parity);
-  if (d.first && sc->done) return;  // b = 0: nothing to solve
-  const KpStep<T> st{d.first, T(d.beta), !d.first && a.x != nullptr,
-                     T(sc->alphas[q])};
-  const int lb = xcd_remap(blockIdx.x, gridDim.x);
-  if (d.stop) {
-    if (st.upd) {
-      constexpr int NG = 9 / CPB;
-      const int x0 = lb / NG, grp = lb - (lb / NG) * NG;
-      for (int t = threadIdx.x; t < N * N; t += blockDim.x) {
-        const int64_t v = (int64_t)x0 * N * N + t;
-#pragma unroll
-        for (int qq = 0; qq < CPB; ++qq) {
-          const int c = grp * CPB + qq;
-          a.x[c * a.cs + v] += st.alpha * a.p_old[c * a.cs + v];
-        }
-      }
-    }
-    return;
-  }
-  slab_fwd_body<T, N, CPB, SRC_KP>(a, lb, lds, tw, red, st);
 }
 
 template <typename T, int N, int TT>
 __global__ __launch_bounds__(kBlock) void pencil_proj_kernel(PencilArgs<T> a) {
   __shared__ cplx<T> lds[3 * (N * (TT + 1) + TT)];
   __shared__ cplx<T> tw[N];
-  __shared__ double red[kBlock];
-  if (!pencil_body<T, N, TT>(a, xcd_remap(blockIdx.x, gridDim.x), lds, tw,
-                             a.sc))
-    return;
-  // fused CG run: alpha = r.r / p.(K:p) from pass A's partials (a breakdown
-  // sets done, which the pass-B blocks that already started ignore: their
-  // spectrum is not used, pass C returns)
-  if (a.pkp && blockIdx.x == 0)
-    cg_alpha_publish(a.pkp, a.pkp_count, a.scw, a.parity, red);
+  pencil_body<T, N, TT>(a, xcd_remap(blockIdx.x, gridDim.x), lds, tw, a.sc);
+}
+
+// threads of a CG pencil block: 512 once a block has as many frequencies
+// (64^3: one butterfly per thread and radix pass, nine loads in flight each)
+template <int N, int TT>
+constexpr int kPencilThreads = N * TT >= 512 ? 512 : 256;
+
+template <typename T, typename TR, int N, int TT, bool RES>
+__global__ __launch_bounds__((kPencilThreads<N, TT>)) void pencil_fwd_kernel(
+    PencilFwdArgs<T, TR> a) {
+  constexpr int NT = kPencilThreads<N, TT>;
+  __shared__ cplx<T> lds[PencilGeom<T, N, TT>::LDS];
+  __shared__ cplx<T> tw[N];
+  __shared__ double red[NT / 64];
+  T alpha = T(0);
+  if constexpr (!RES) {
+    if (a.pkp) {
+      // K:p folded into pass A: every block forms alpha from its partials
+      // (the same bits), block 0 publishes it; after a breakdown none of
+      // them touches the residual
+      if (!cg_alpha_consume(a.pkp, a.pkp_count, a.scw, a.parity,
+                            blockIdx.x == 0, alpha))
+        return;
+    } else {
+      alpha = T(a.sc->alphas[a.parity]);
+    }
+  }
+  pencil_fwd_body<T, TR, N, TT, NT, RES>(a, xcd_remap(blockIdx.x, gridDim.x),
+                                         lds, tw, red, alpha,
+                                         RES || a.pkp ? nullptr : a.sc);
+}
+
+template <typename T, int N, int TT, bool FINAL>
+__global__ __launch_bounds__((kPencilThreads<N, TT>)) void pencil_inv_kernel(
+    PencilInvArgs<T> a) {
+  __shared__ cplx<T> lds[PencilGeom<T, N, TT>::LDS];
+  __shared__ cplx<T> tw[N];
+  pencil_inv_body<T, N, TT, kPencilThreads<N, TT>, FINAL>(
+      a, xcd_remap(blockIdx.x, gridDim.x), lds, tw);
 }
 
 template <typename T, typename TO, int N, int CPB, int DST>
@@ -689,15 +915,19 @@ __device__ __forceinline__ int batch_item(const BatchSpec<T>& b, int pass,
   return r;
 }
 
-// one RVE's pass bodies in the dynamic LDS of a batched launch
+// Each pass as a block body (blk: the block it plays, a launch's blockIdx.x
+// or a virtual block of the persistent CG kernel) and a one-launch kernel.
+// CPBS: the slab schedules compiled in (bit 0: one component per block,
+// bit 1: three), so that a launch whose RVEs all use one of them does not
+// carry the registers of the other.  A CG pass leaves an RVE whose run has
+// stopped alone, the others one that is inactive.
 template <typename T, int NN, int CPB, int SRC>
 __device__ __forceinline__ void slab_fwd_item(const SlabFwdArgs<T>& a, int lb,
-                                              unsigned char* smem,
-                                              const KpStep<T>& st) {
+                                              unsigned char* smem) {
   cplx<T>* lds = reinterpret_cast<cplx<T>*>(smem);
   cplx<T>* tw = lds + CPB * SlabGeom<NN>::PLANE;
   double* red = reinterpret_cast<double*>(tw + NN);
-  slab_fwd_body<T, NN, CPB, SRC>(a, lb, lds, tw, red, st);
+  slab_fwd_body<T, NN, CPB, SRC>(a, lb, lds, tw, red);
 }
 template <typename T, typename TO, int NN, int CPB, int DST>
 __device__ __forceinline__ void slab_inv_item(const SlabInvArgs<T, TO>& a,
@@ -707,49 +937,34 @@ __device__ __forceinline__ void slab_inv_item(const SlabInvArgs<T, TO>& a,
   double* red = reinterpret_cast<double*>(tw + NN);
   slab_inv_body<T, TO, NN, CPB, DST>(a, lb, lds, tw, red);
 }
-template <typename T, int NN, int TT>
-__device__ __forceinline__ void pencil_item(const PencilArgs<T>& a, int lb,
-                                            unsigned char* smem) {
-  cplx<T>* lds = reinterpret_cast<cplx<T>*>(smem);
-  pencil_body<T, NN, TT>(a, lb, lds, lds + 3 * (NN * (TT + 1) + TT));
-}
 
-// Each pass as a block body (blk: the block it plays, a launch's blockIdx.x
-// or a virtual block of the persistent CG kernel) and a one-launch kernel.
-// CPBS: the slab schedules compiled in (bit 0: one component per block,
-// bit 1: three), so that a launch whose RVEs all use one of them does not
-// carry the registers of the other
 template <typename T, int SRC, int CPBS = 3>
 __device__ __forceinline__ void slab_fwd_batch_block(const BatchSpec<T>& b,
                                                      int blk,
                                                      unsigned char* smem) {
   const int r = batch_item(b, 0, blk);
   const SpecItem<T>& it = b.items[r];
-  if (SRC == SRC_KP ? it.sc->done : it.sc->inactive) return;
+  if (SRC == SRC_KROW ? it.sc->done : it.sc->inactive) return;
   const int lb = blk - it.blk[0];
   SlabFwdArgs<T> a{};
   a.cs = b.cs;
-  a.field = b.field ? b.field + it.off : nullptr;
+  a.field = b.field + it.off;
   a.K = b.K ? b.K + it.off : nullptr;
-  a.r = b.r ? b.r + it.off : nullptr;
-  a.p_old = b.p_old ? b.p_old + it.off : nullptr;
-  a.p_new = b.p_new ? b.p_new + it.off : nullptr;
   a.spec = b.spec + it.soff;
   a.tw = it.tw;
-  a.psum = it.psum;
+  a.psum = SRC == SRC_FIELD ? it.psum : nullptr;
   a.psq = it.psq;
-  a.sc = it.sc;
-  const KpStep<T> st = kp_step_of<T>(SRC == SRC_KP ? it.sc : nullptr);
+  a.pkp_out = it.pkp;
   switch (it.n) {
 #define RVE_CASE(NN)                                                         \
   case NN:                                                                   \
     if constexpr ((CPBS & 2) && cpb3_fits<T, NN>())                          \
       if (it.cpb == 3) {                                                     \
-        slab_fwd_item<T, NN, 3, SRC>(a, lb, smem, st);                       \
+        slab_fwd_item<T, NN, 3, SRC>(a, lb, smem);                           \
         break;                                                               \
       }                                                                      \
     if constexpr ((CPBS & 1) || !cpb3_fits<T, NN>())                         \
-      slab_fwd_item<T, NN, 1, SRC>(a, lb, smem, st);                         \
+      slab_fwd_item<T, NN, 1, SRC>(a, lb, smem);                             \
     break;
     RVE_BATCH_SIZES(RVE_CASE)
 #undef RVE_CASE
@@ -762,43 +977,141 @@ __global__ __launch_bounds__(kBlock) void slab_fwd_batch_kernel(BatchSpec<T> b) 
   slab_fwd_batch_block<T, SRC, CPBS>(b, blockIdx.x, smem);
 }
 
+// G of a field: projection of the pencils (blk[2])
 template <typename T>
-__device__ __forceinline__ void pencil_batch_block(const BatchSpec<T>& b,
-                                                   int cg, int blk,
-                                                   unsigned char* smem) {
-  const int r = batch_item(b, 1, blk);
+__global__ __launch_bounds__(kBlock) void pencil_batch_kernel(BatchSpec<T> b) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int r = batch_item(b, 2, blockIdx.x);
   const SpecItem<T>& it = b.items[r];
-  if (cg ? it.sc->done : it.sc->inactive) return;
-  const int lb = blk - it.blk[1];
+  if (it.sc->inactive) return;
+  const int lb = blockIdx.x - it.blk[2];
   PencilArgs<T> a{};
   a.spec = b.spec + it.soff;
   a.tw = it.tw;
   a.vt = it.vt;
-  a.sc = nullptr;
+  cplx<T>* lds = reinterpret_cast<cplx<T>*>(smem);
   switch (it.n) {
+#define RVE_PENCIL(NN, TT)                                                   \
+  {                                                                          \
+    a.invN3 = T(1.0 / (double(NN) * NN * NN));                               \
+    pencil_body<T, NN, TT>(a, lb, lds, lds + 3 * (NN * (TT + 1) + TT));      \
+    break;                                                                   \
+  }
 #define RVE_CASE(NN)                                                         \
   case NN:                                                                   \
-    a.invN3 = T(1.0 / (double(NN) * NN * NN));                               \
     if constexpr (pencil_fits<T, NN, 16>())                                  \
-      if (it.tt == 16) {                                                     \
-        pencil_item<T, NN, 16>(a, lb, smem);                                 \
-        break;                                                               \
-      }                                                                      \
-    if (it.tt == 4)                                                          \
-      pencil_item<T, NN, 4>(a, lb, smem);                                    \
-    else                                                                     \
-      pencil_item<T, NN, 8>(a, lb, smem);                                    \
-    break;
+      if (it.tt == 16) RVE_PENCIL(NN, 16)                                    \
+    if (it.tt == 4) RVE_PENCIL(NN, 4)                                        \
+    RVE_PENCIL(NN, 8)
     RVE_BATCH_SIZES(RVE_CASE)
 #undef RVE_CASE
+#undef RVE_PENCIL
   }
 }
 
-template <typename T>
-__global__ __launch_bounds__(kBlock) void pencil_batch_kernel(BatchSpec<T> b,
-                                                              int cg) {
+// the residual pass of a CG iteration, or (RES) of the FP64 residual
+template <typename T, typename TR, bool RES>
+__device__ __forceinline__ void pencil_fwd_batch_block(const BatchSpec<T>& b,
+                                                       cplx<TR>* rho, int blk,
+                                                       unsigned char* smem) {
+  const int r = batch_item(b, 1, blk);
+  const SpecItem<T>& it = b.items[r];
+  const int lb = blk - it.blk[1];
+  PencilFwdArgs<T, TR> a{};
+  T alpha = T(0);
+  if constexpr (RES) {
+    if (it.sc->inactive) return;
+    a.pres = it.prr + 2 * it.npen;
+  } else if (b.timing) {
+    alpha = T(it.sc->alpha);
+  } else {
+    if (!cg_alpha_consume(it.pkp, 9 * it.n, it.sc, b.parity, lb == 0, alpha))
+      return;
+  }
+  a.spec = b.spec + it.soff;
+  a.tw = it.tw;
+  a.vt = it.vt;
+  a.rho = rho + it.soff / 3;
+  a.prec = b.prec;
+  a.prr = it.prr;
+  a.prz = it.prr + it.npen;
+  switch (it.n) {
+#define RVE_PENCIL(NN, TT)                                                   \
+  {                                                                          \
+    a.invN3 = 1.0 / (double(NN) * NN * NN);                                  \
+    cplx<T>* lds = reinterpret_cast<cplx<T>*>(smem);                         \
+    cplx<T>* tw = lds + PencilGeom<T, NN, TT>::LDS;                          \
+    pencil_fwd_body<T, TR, NN, TT, kBlock, RES>(                             \
+        a, lb, lds, tw, reinterpret_cast<double*>(tw + NN), alpha, nullptr); \
+    break;                                                                   \
+  }
+#define RVE_CASE(NN)                                                         \
+  case NN:                                                                   \
+    if constexpr (pencil_fits<T, NN, 16>())                                  \
+      if (it.tt == 16) RVE_PENCIL(NN, 16)                                    \
+    if (it.tt == 4) RVE_PENCIL(NN, 4)                                        \
+    RVE_PENCIL(NN, 8)
+    RVE_BATCH_SIZES(RVE_CASE)
+#undef RVE_CASE
+#undef RVE_PENCIL
+  }
+}
+
+template <typename T, typename TR, bool RES>
+__global__ __launch_bounds__(kBlock) void pencil_fwd_batch_kernel(
+    BatchSpec<T> b, cplx<TR>* rho) {
   extern __shared__ __align__(16) unsigned char smem[];
-  pencil_batch_block<T>(b, cg, blockIdx.x, smem);
+  pencil_fwd_batch_block<T, TR, RES>(b, rho, blockIdx.x, smem);
+}
+
+template <typename T, bool FINAL>
+__device__ __forceinline__ void pencil_inv_batch_block(const BatchSpec<T>& b,
+                                                       int blk,
+                                                       unsigned char* smem) {
+  const int r = batch_item(b, 1, blk);
+  const SpecItem<T>& it = b.items[r];
+  // a run that stopped in an earlier iteration stays stopped (halt); done
+  // itself is written by block 0 of the RVE in this pass
+  if (it.sc->inactive) return;
+  const int lb = blk - it.blk[1];
+  PencilInvArgs<T> a{};
+  a.spec = b.spec + it.soff;
+  a.tw = it.tw;
+  a.vt = it.vt;
+  a.rho = b.rho + it.soff / 3;
+  a.pi = b.pi + it.soff / 3;
+  a.xi = b.xi + it.soff / 3;
+  a.prec = T(b.prec);
+  a.prr = b.timing ? nullptr : it.prr;
+  a.prz = it.prr + it.npen;
+  a.count = it.npen;
+  a.scw = it.sc;
+  a.parity = b.parity;
+  switch (it.n) {
+#define RVE_PENCIL(NN, TT)                                                   \
+  {                                                                          \
+    a.invN3 = T(1.0 / (double(NN) * NN * NN));                               \
+    cplx<T>* lds = reinterpret_cast<cplx<T>*>(smem);                         \
+    pencil_inv_body<T, NN, TT, kBlock, FINAL>(                               \
+        a, lb, lds, lds + PencilGeom<T, NN, TT>::LDS);                       \
+    break;                                                                   \
+  }
+#define RVE_CASE(NN)                                                         \
+  case NN:                                                                   \
+    if constexpr (pencil_fits<T, NN, 16>())                                  \
+      if (it.tt == 16) RVE_PENCIL(NN, 16)                                    \
+    if (it.tt == 4) RVE_PENCIL(NN, 4)                                        \
+    RVE_PENCIL(NN, 8)
+    RVE_BATCH_SIZES(RVE_CASE)
+#undef RVE_CASE
+#undef RVE_PENCIL
+  }
+}
+
+template <typename T, bool FINAL>
+__global__ __launch_bounds__(kBlock) void pencil_inv_batch_kernel(BatchSpec<T> b) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  pencil_inv_batch_block<T, FINAL>(b, blockIdx.x, smem);
 }
 
 template <typename T, typename TO, int DST, int CPBS = 3>
@@ -807,16 +1120,14 @@ __device__ __forceinline__ void slab_inv_batch_block(const BatchSpec<T>& b,
                                                      unsigned char* smem) {
   const int r = batch_item(b, 0, blk);
   const SpecItem<T>& it = b.items[r];
-  if (DST == DST_DOT ? it.sc->done : it.sc->inactive) return;
+  if (DST == DST_P ? it.sc->done : it.sc->inactive) return;
   const int lb = blk - it.blk[0];
   SlabInvArgs<T, TO> a{};
   a.cs = b.cs;
   a.spec = b.spec + it.soff;
   a.tw = it.tw;
+  a.vt = it.vt;
   a.out = out + it.off;
-  a.pdot = b.p_new ? b.p_new + it.off : nullptr;
-  a.partial = it.partial;
-  a.sc = nullptr;
   switch (it.n) {
 #define RVE_CASE(NN)                                                         \
   case NN:                                                                   \
@@ -842,13 +1153,11 @@ __global__ __launch_bounds__(kBlock) void slab_inv_batch_kernel(BatchSpec<T> b,
 
 // ------------------------------------------------- persistent batched CG
 // The CG iterations of every RVE of a batch in one launch of resident
-// blocks: each iteration runs the three FFT/projection passes of G(K:p)
-// (p = r + beta p_old fused into the first), the per-RVE p.Ap reduction,
-// the vector update and the r.r reduction, each over all RVEs' blocks,
-// with a grid-wide barrier between them; it stops when every RVE's CG is
-// done (converged, broken down or at its cap).  A barrier that waits
-// beyond a bound (blocks not all resident) sets an error flag and lets the
-// kernel run out instead of hanging; the host turns the flag into an error.
+// blocks: the passes of the one-launch form with a grid-wide barrier between
+// them; it stops when every RVE's CG is done (converged, broken down or at
+// its cap).  A barrier that waits beyond a bound (blocks not all resident)
+// sets an error flag and lets the kernel run out instead of hanging; the
+// host turns the flag into an error.
 // Barrier state (unsigned words, one 128-byte line each part): [0] the
 // generation, [32 (1 + g)] the arrival count of group g = blockIdx.x % 8
 // (the hardware deals consecutive blocks round-robin over the eight XCDs),
@@ -911,62 +1220,62 @@ __device__ __forceinline__ bool grid_barrier(unsigned* bar, unsigned nblocks,
 // the passes as calls (not inlined into one body, which would hold the
 // registers of all of them at once)
 template <typename T>
-__device__ __noinline__ void pc_slab_fwd(const BatchSpec<T>& b, int blk,
-                                         unsigned char* smem) {
-  slab_fwd_batch_block<T, SRC_KP>(b, blk, smem);
+__device__ __noinline__ void pc_dir(const BatchSpec<T>& b, int blk,
+                                    unsigned char* smem) {
+  pencil_inv_batch_block<T, false>(b, blk, smem);
 }
 template <typename T>
-__device__ __noinline__ void pc_pencil(const BatchSpec<T>& b, int blk,
-                                       unsigned char* smem) {
-  pencil_batch_block<T>(b, 1, blk, smem);
+__device__ __noinline__ void pc_p(const BatchSpec<T>& b, int blk,
+                                  unsigned char* smem) {
+  slab_inv_batch_block<T, T, DST_P>(b, b.p, blk, smem);
 }
 template <typename T>
-__device__ __noinline__ void pc_slab_inv(const BatchSpec<T>& b, T* Ap, int blk,
-                                         unsigned char* smem) {
-  slab_inv_batch_block<T, T, DST_DOT>(b, Ap, blk, smem);
+__device__ __noinline__ void pc_krow(const BatchSpec<T>& b, int blk,
+                                     unsigned char* smem) {
+  slab_fwd_batch_block<T, SRC_KROW>(b, blk, smem);
 }
 template <typename T>
-__device__ __noinline__ void pc_update(const BatchCG<T>& c, const T* p, int blk,
-                                       double* red) {
-  cg_update_batch_block<T>(c.seg, c.nitems, c.cs, c.x, c.r, p, c.Ap, blk, red);
-}
-__device__ __noinline__ void pc_reduce(int op, const RedItem* items,
-                                       Scalars* scs, int b, double* red) {
-  reduce_batch_block(op, items, scs, b, red);
+__device__ __noinline__ void pc_res(const BatchSpec<T>& b, int blk,
+                                    unsigned char* smem) {
+  pencil_fwd_batch_block<T, T, false>(b, b.rho, blk, smem);
 }
 
 template <typename T>
 __global__ __launch_bounds__(kBlock) void cg_batch_persistent_kernel(
     BatchCG<T> c) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ double red[kBlock / 64];
   __shared__ int active;
   for (int j = 0; j < c.max_iters; ++j) {
-    // every block takes the same decision from the same scalars
+    const BatchSpec<T>& b = (j & 1) ? c.odd : c.even;
+    for (int vb = blockIdx.x; vb < c.blocksB; vb += gridDim.x) {
+      pc_dir<T>(b, vb, smem);
+      __syncthreads();
+    }
+    if (!grid_barrier(c.bar, gridDim.x, c.err)) return;
+    // every block takes the same decision: done changes next in the
+    // residual pass, two barriers on
     if (threadIdx.x == 0) active = 0;
     __syncthreads();
-    for (int b = threadIdx.x; b < c.nitems; b += blockDim.x)
-      if (!c.scs[b].done) active = 1;
+    for (int r = threadIdx.x; r < c.nitems; r += blockDim.x)
+      if (!__hip_atomic_load(&c.scs[r].done, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT))
+        active = 1;
     __syncthreads();
     if (!active) break;
-    const BatchSpec<T>& b = (j & 1) ? c.odd : c.even;
-    for (int vb = blockIdx.x; vb < c.blocksA; vb += gridDim.x)
-      pc_slab_fwd<T>(b, vb, smem);
+    for (int vb = blockIdx.x; vb < c.blocksA; vb += gridDim.x) {
+      pc_p<T>(b, vb, smem);
+      __syncthreads();
+    }
     if (!grid_barrier(c.bar, gridDim.x, c.err)) return;
-    for (int vb = blockIdx.x; vb < c.blocksB; vb += gridDim.x)
-      pc_pencil<T>(b, vb, smem);
+    for (int vb = blockIdx.x; vb < c.blocksA; vb += gridDim.x) {
+      pc_krow<T>(b, vb, smem);
+      __syncthreads();
+    }
     if (!grid_barrier(c.bar, gridDim.x, c.err)) return;
-    for (int vb = blockIdx.x; vb < c.blocksA; vb += gridDim.x)
-      pc_slab_inv<T>(b, c.Ap, vb, smem);
-    if (!grid_barrier(c.bar, gridDim.x, c.err)) return;
-    for (int r = blockIdx.x; r < c.nitems; r += gridDim.x)
-      pc_reduce(RED_ALPHA, c.red_inv, c.scs, r, red);
-    if (!grid_barrier(c.bar, gridDim.x, c.err)) return;
-    for (int vb = blockIdx.x; vb < c.seg_blocks; vb += gridDim.x)
-      pc_update<T>(c, b.p_new, vb, red);
-    if (!grid_barrier(c.bar, gridDim.x, c.err)) return;
-    for (int r = blockIdx.x; r < c.nitems; r += gridDim.x)
-      pc_reduce(RED_BETA, c.red_seg, c.scs, r, red);
+    for (int vb = blockIdx.x; vb < c.blocksB; vb += gridDim.x) {
+      pc_res<T>(b, vb, smem);
+      __syncthreads();
+    }
     if (!grid_barrier(c.bar, gridDim.x, c.err)) return;
   }
 }
@@ -1008,140 +1317,213 @@ void launch_G_passes(const SpectralLaunch<T>& L, hipStream_t s) {
   constexpr int H = N / 2;
   constexpr int NTILE = (H + TT - 1) / TT;
   const int nslab = N * (9 / CPB);
-  if (!(L.passes & 1)) {
-  } else if (L.src == SRC_FIELD) {
-    SlabFwdArgs<T> fa{};
-    fa.cs = (int64_t)N * N * N;
-    fa.field = L.in_field;
-    fa.spec = L.spec;
-    fa.tw = L.tw;
-    fa.psum = L.psum;
-    fa.psq = L.psq;
-    fa.sc = L.sc;
-    if (L.pkp) {
-      fa.pkp = L.pkp;
-      fa.pkp_count = L.pkp_count;
-      fa.parity = L.parity;
-      fa.scw = L.sc;
-    }
-    launch((slab_fwd_kernel<T, N, CPB, SRC_FIELD>), dim3(nslab),
-                       dim3(kBlock), 0, s, fa);
-  } else {
-    SlabFwdArgs<T> fa{};
-    fa.cs = (int64_t)N * N * N;
-    fa.K = L.K;
-    fa.r = L.r;
-    fa.p_old = L.p_old;
-    fa.p_new = L.p_new;
-    fa.spec = L.spec;
-    fa.tw = L.tw;
-    fa.psum = nullptr;
-    fa.psq = nullptr;
-    fa.sc = L.sc;
-    if (L.pinv) {
-      // fused CG run: pass A writes the p.(K:p) partials that pass B reduces
-      fa.pinv = L.pinv;
-      fa.pinv_count = L.pinv_count;
-      fa.x = L.x;
-      fa.pkp_out = const_cast<double*>(L.pkp);
-      fa.parity = L.parity;
-      fa.scw = L.sc;
-      launch((slab_fwd_cg_kernel<T, N, CPB>), dim3(nslab), dim3(kBlock), 0, s,
-             fa);
-    } else {
-      // direction and K:p from the scalars (with x: x += alpha p_old too)
-      fa.x = L.x;
-      launch((slab_fwd_kernel<T, N, CPB, SRC_KP>), dim3(nslab),
-                         dim3(kBlock), 0, s, fa);
-    }
-  }
-  if (L.passes & 2) {
+  SlabFwdArgs<T> fa{};
+  fa.cs = (int64_t)N * N * N;
+  fa.field = L.in_field;
+  fa.spec = L.spec;
+  fa.tw = L.tw;
+  launch((slab_fwd_kernel<T, N, CPB, SRC_FIELD>), dim3(nslab), dim3(kBlock), 0,
+         s, fa);
   PencilArgs<T> pa{};
   pa.spec = L.spec;
   pa.tw = L.tw;
   pa.vt = L.vt;
   pa.invN3 = T(1.0 / (double(N) * N * N));
-  pa.sc = L.sc;
-  if (L.src == SRC_KP && L.pinv && L.pkp) {
-    pa.pkp = L.pkp;
-    pa.pkp_count = L.pkp_count;
-    pa.parity = L.parity;
-    pa.scw = L.sc;
+  pa.sc = nullptr;
+  launch((pencil_proj_kernel<T, N, TT>), dim3(N * NTILE * 3), dim3(kBlock), 0,
+         s, pa);
+  SlabInvArgs<T, double> ia{};
+  ia.cs = (int64_t)N * N * N;
+  ia.spec = L.spec;
+  ia.tw = L.tw;
+  ia.out = L.out_d;
+  ia.partial = L.partial_inv;
+  launch((slab_inv_kernel<T, double, N, CPB, DST_NORM>), dim3(nslab),
+         dim3(kBlock), 0, s, ia);
+}
+
+// the passes of a CG iteration (mask: kPassDir .. kPassRes) or the end of
+// the solve (kPassFinal)
+template <typename T, int N, int CPB, int TT>
+void launch_cg_sched(const CgLaunch<T>& L, int mask, hipStream_t s) {
+  using G = PencilGeom<T, N, TT>;
+  const int nslab = N * (9 / CPB), npen = N * G::NTILE;
+  const T invN3 = T(1.0 / (double(N) * N * N));
+  if (mask & (kPassDir | kPassFinal)) {
+    PencilInvArgs<T> a{};
+    a.spec = L.spec;
+    a.tw = L.tw;
+    a.vt = L.vt;
+    a.rho = L.rho;
+    a.pi = L.pi;
+    a.xi = L.xi;
+    a.invN3 = invN3;
+    a.prec = T(L.prec);
+    a.prr = L.prr;
+    a.prz = L.prz;
+    a.count = npen;
+    a.scw = L.sc;
+    a.parity = L.parity;
+    if (mask & kPassDir)
+      launch((pencil_inv_kernel<T, N, TT, false>), dim3(npen),
+             dim3(kPencilThreads<N, TT>), 0, s, a);
+    else
+      launch((pencil_inv_kernel<T, N, TT, true>), dim3(npen),
+             dim3(kPencilThreads<N, TT>), 0, s, a);
   }
-  launch((pencil_proj_kernel<T, N, TT>), dim3(N * NTILE * 3),
-                     dim3(kBlock), 0, s, pa);
+  if (mask & kPassP) {
+    SlabInvArgs<T, T> a{};
+    a.cs = (int64_t)N * N * N;
+    a.spec = L.spec;
+    a.tw = L.tw;
+    a.vt = L.vt;
+    a.out = L.p;
+    a.sc = L.sc;
+    launch((slab_inv_kernel<T, T, N, CPB, DST_P>), dim3(nslab), dim3(kBlock),
+           0, s, a);
   }
-  if (!(L.passes & 4)) {
-  } else if (L.dst == DST_CG) {
-    SlabInvArgs<T, T> ia{};
-    ia.cs = (int64_t)N * N * N;
-    ia.spec = L.spec;
-    ia.tw = L.tw;
-    ia.out = nullptr;
-    ia.pdot = nullptr;
-    ia.partial = L.partial_inv;
-    ia.sc = L.sc;
-    ia.rio = L.r_io;
-    ia.parity = L.parity;
-    launch((slab_inv_kernel<T, T, N, CPB, DST_CG>), dim3(nslab),
-                       dim3(kBlock), 0, s, ia);
-  } else if (L.dst == DST_DOT) {
-    SlabInvArgs<T, T> ia{};
-    ia.cs = (int64_t)N * N * N;
-    ia.spec = L.spec;
-    ia.tw = L.tw;
-    ia.out = L.out_T;
-    ia.pdot = L.p_new;
-    ia.partial = L.partial_inv;
-    ia.sc = L.sc;
-    launch((slab_inv_kernel<T, T, N, CPB, DST_DOT>), dim3(nslab),
-                       dim3(kBlock), 0, s, ia);
-  } else {
-    SlabInvArgs<T, double> ia{};
-    ia.cs = (int64_t)N * N * N;
-    ia.spec = L.spec;
-    ia.tw = L.tw;
-    ia.out = L.out_d;
-    ia.pdot = nullptr;
-    ia.partial = L.partial_inv;
-    ia.sc = nullptr;
-    launch((slab_inv_kernel<T, double, N, CPB, DST_NORM>),
-                       dim3(nslab), dim3(kBlock), 0, s, ia);
+  if (mask & kPassFinal) {
+    SlabInvArgs<T, double> a{};
+    a.cs = (int64_t)N * N * N;
+    a.spec = L.spec;
+    a.tw = L.tw;
+    a.vt = L.vt;
+    a.out = L.F;
+    launch((slab_inv_kernel<T, double, N, CPB, DST_ADDF>), dim3(nslab),
+           dim3(kBlock), 0, s, a);
+  }
+  if (mask & kPassA) {
+    SlabFwdArgs<T> a{};
+    a.cs = (int64_t)N * N * N;
+    a.spec = L.spec;
+    a.tw = L.tw;
+    a.sc = L.sc;
+    if (L.fused) {
+      a.field = L.p;
+      a.K = L.K;
+      a.pkp_out = L.pkp;
+      launch((slab_fwd_kernel<T, N, CPB, SRC_KROW>), dim3(nslab), dim3(kBlock),
+             0, s, a);
+    } else {
+      a.field = L.y;
+      if (L.prr) {
+        a.pkp = L.pkp;
+        a.pkp_count = L.pkp_count;
+        a.parity = L.parity;
+        a.scw = L.sc;
+      }
+      launch((slab_fwd_kernel<T, N, CPB, SRC_FIELD>), dim3(nslab),
+             dim3(kBlock), 0, s, a);
+    }
+  }
+  if (mask & kPassRes) {
+    PencilFwdArgs<T, T> a{};
+    a.spec = L.spec;
+    a.tw = L.tw;
+    a.vt = L.vt;
+    a.rho = L.rho;
+    a.invN3 = 1.0 / (double(N) * N * N);
+    a.prec = L.prec;
+    a.prr = L.prr_out;
+    a.prz = L.prz_out;
+    a.sc = L.sc;
+    a.scw = L.sc;
+    a.parity = L.parity;
+    if (L.fused && L.prr) {
+      a.pkp = L.pkp;
+      a.pkp_count = 9 * N;
+    }
+    launch((pencil_fwd_kernel<T, T, N, TT, false>), dim3(npen),
+           dim3(kPencilThreads<N, TT>), 0, s, a);
   }
 }
 
-// the schedule (cpb, tt) of one launch; 0 picks the default of the traits
+// the FP64 residual of the field P: its norm partials and the start of the
+// CG run (default schedule)
+template <typename TR, int N>
+void launch_residual_n(const ResidualLaunch<TR>& L, hipStream_t s) {
+  constexpr int CPB = SpectralTraits<double, N>::CPB;
+  constexpr int TT = SpectralTraits<double, N>::TT;
+  SlabFwdArgs<double> fa{};
+  fa.cs = (int64_t)N * N * N;
+  fa.field = L.P;
+  fa.spec = L.spec;
+  fa.tw = L.tw;
+  fa.psum = L.psum;
+  fa.psq = L.psq;
+  launch((slab_fwd_kernel<double, N, CPB, SRC_FIELD>), dim3(N * (9 / CPB)),
+         dim3(kBlock), 0, s, fa);
+  PencilFwdArgs<double, TR> a{};
+  a.spec = L.spec;
+  a.tw = L.tw;
+  a.vt = L.vt;
+  a.rho = L.rho;
+  a.invN3 = 1.0 / (double(N) * N * N);
+  a.prec = L.prec;
+  a.prr = L.part;
+  a.prz = L.part + residual_blocks(N);
+  a.pres = L.part + 2 * residual_blocks(N);
+  launch((pencil_fwd_kernel<double, TR, N, TT, true>), dim3(residual_blocks(N)),
+         dim3(kPencilThreads<N, TT>), 0, s, a);
+}
+
+#define RVE_GRID_SIZES(X) X(16) X(24) X(32) X(40) X(48) X(64) X(96) X(128)
+
+template <typename TR>
+void launch_residual(int n, const ResidualLaunch<TR>& L, hipStream_t s) {
+  switch (n) {
+#define RVE_CASE(NN) case NN: return launch_residual_n<TR, NN>(L, s);
+    RVE_GRID_SIZES(RVE_CASE)
+#undef RVE_CASE
+  }
+  throw Error(-1, "unsupported grid size for the FFT passes");
+}
+
 template <typename T, int N>
-void launch_G_sched(const SpectralLaunch<T>& L, hipStream_t s) {
-  const int cpb = L.cpb ? L.cpb : SpectralTraits<T, N>::CPB;
-  const int tt = L.tt ? L.tt : SpectralTraits<T, N>::TT;
+void launch_cg_n(const CgLaunch<T>& L, int mask, hipStream_t s) {
+  const int cpb = L.cpb, tt = L.tt;
   if (cpb == 3) {
     if constexpr (cpb3_fits<T, N>()) {
       if constexpr (pencil_fits<T, N, 16>())
-        if (tt == 16) return launch_G_passes<T, N, 3, 16>(L, s);
-      if (tt == 8) return launch_G_passes<T, N, 3, 8>(L, s);
-      if (tt == 4) return launch_G_passes<T, N, 3, 4>(L, s);
+        if (tt == 16) return launch_cg_sched<T, N, 3, 16>(L, mask, s);
+      if (tt == 8) return launch_cg_sched<T, N, 3, 8>(L, mask, s);
+      if (tt == 4) return launch_cg_sched<T, N, 3, 4>(L, mask, s);
     }
   } else if (cpb == 1) {
     if constexpr (pencil_fits<T, N, 16>())
-      if (tt == 16) return launch_G_passes<T, N, 1, 16>(L, s);
-    if (tt == 8) return launch_G_passes<T, N, 1, 8>(L, s);
-    if (tt == 4) return launch_G_passes<T, N, 1, 4>(L, s);
+      if (tt == 16) return launch_cg_sched<T, N, 1, 16>(L, mask, s);
+    if (tt == 8) return launch_cg_sched<T, N, 1, 8>(L, mask, s);
+    if (tt == 4) return launch_cg_sched<T, N, 1, 4>(L, mask, s);
   }
   throw Error(-1, "unsupported FFT schedule");
 }
 
 template <typename T>
+void launch_cg(int n, const CgLaunch<T>& L, int mask, hipStream_t s) {
+  switch (n) {
+#define RVE_CASE(NN) case NN: return launch_cg_n<T, NN>(L, mask, s);
+    RVE_GRID_SIZES(RVE_CASE)
+#undef RVE_CASE
+  }
+  throw Error(-1, "unsupported grid size for the FFT passes");
+}
+
+template <typename T, int N>
+void launch_G_n(const SpectralLaunch<T>& L, hipStream_t s) {
+  launch_G_passes<T, N, SpectralTraits<T, N>::CPB, SpectralTraits<T, N>::TT>(L, s);
+}
+
+template <typename T>
 void launch_G(int n, const SpectralLaunch<T>& L, hipStream_t s) {
   switch (n) {
-    case 16: launch_G_sched<T, 16>(L, s); break;
-    case 24: launch_G_sched<T, 24>(L, s); break;
-    case 32: launch_G_sched<T, 32>(L, s); break;
-    case 40: launch_G_sched<T, 40>(L, s); break;
-    case 48: launch_G_sched<T, 48>(L, s); break;
-    case 64: launch_G_sched<T, 64>(L, s); break;
-    case 96: launch_G_sched<T, 96>(L, s); break;
-    case 128: launch_G_sched<T, 128>(L, s); break;
+    case 16: launch_G_n<T, 16>(L, s); break;
+    case 24: launch_G_n<T, 24>(L, s); break;
+    case 32: launch_G_n<T, 32>(L, s); break;
+    case 40: launch_G_n<T, 40>(L, s); break;
+    case 48: launch_G_n<T, 48>(L, s); break;
+    case 64: launch_G_n<T, 64>(L, s); break;
+    case 96: launch_G_n<T, 96>(L, s); break;
+    case 128: launch_G_n<T, 128>(L, s); break;
     default: throw Error(-1, "unsupported grid size for the FFT passes");
   }
 }
@@ -1170,6 +1552,20 @@ int pencil_blocks(int n, bool fp64, int tt_sel) {
   const int tt = tt_sel ? tt_sel : (fp64 ? 8 : 16);
   return n * ((n / 2 + tt - 1) / tt) * 3;
 }
+
+int residual_blocks(int n) {
+  constexpr int TT = 8;   // SpectralTraits<double, N>::TT
+  return n * ((n / 2 + TT - 1) / TT);
+}
+
+// kz columns per CG pencil block: four fill the chip better up to 48^3 (48^3
+// FP32: direction and residual pass 5.9 + 6.3 us against 6.8 + 6.7 with
+// eight), from 64^3 on the 64-byte segments of eight are faster (6.1 + 6.5
+// against 6.8 + 7.0 us; 128^3: 31.7 + 29.3 against 36.7 + 31.8); sixteen
+// lose everywhere (8.4 + 8.4; 35.8 + 40.1)
+int cg_tile(int n) { return n < 64 ? 4 : 8; }
+
+int cg_pencil_blocks(int n, int tt) { return n * ((n / 2 + tt - 1) / tt); }
 
 bool schedule_valid(int n, bool fp64, int cpb, int tt) {
   if (tt != 4 && tt != 8 && tt != 16) return false;
@@ -1205,10 +1601,11 @@ void batch_lds(int n, int cpb, int tt, size_t& slab, size_t& pencil) {
   if (!batch_supported(n)) throw Error(-1, "grid edge not supported in a batch");
   if (!schedule_valid(n, sizeof(T) == 8, cpb, tt))
     throw Error(-1, "no such FFT schedule for this grid edge and precision");
-  // the layouts of slab_fwd_item / slab_inv_item and pencil_item
+  // the layouts of slab_fwd_item / slab_inv_item and the CG pencils
   const size_t plane = (size_t)(n / 2) * (n + 1);
   slab = (cpb * plane + n) * sizeof(cplx<T>) + kBlock * sizeof(double);
-  pencil = (3 * ((size_t)n * (tt + 1) + tt) + n) * sizeof(cplx<T>);
+  pencil = (6 * ((size_t)n * (tt + 1) + tt) + n) * sizeof(cplx<T>) +
+           kBlock / 64 * sizeof(double);
 }
 
 // the default schedule of a grid edge and precision
@@ -1230,73 +1627,120 @@ void default_schedule(int n, bool fp64, int& cpb, int& tt) {
   if (fp64) pick(double{}); else pick(float{});
 }
 
-template <typename T, int CPBS>
-void launch_G_batch_cpbs(const BatchSpec<T>& b, int src, T* out_T,
-                         double* out_d, int blocksA, int blocksB, size_t ldsA,
-                         size_t ldsB, hipStream_t s) {
-  if (src == SRC_FIELD) {
-    hipLaunchKernelGGL((slab_fwd_batch_kernel<T, SRC_FIELD, CPBS>),
-                       dim3(blocksA), dim3(kBlock), ldsA, s, b);
-    hipLaunchKernelGGL((pencil_batch_kernel<T>), dim3(blocksB), dim3(kBlock),
-                       ldsB, s, b, 0);
-    hipLaunchKernelGGL((slab_inv_batch_kernel<T, double, DST_NORM, CPBS>),
-                       dim3(blocksA), dim3(kBlock), ldsA, s, b, out_d);
-  } else {
-    hipLaunchKernelGGL((slab_fwd_batch_kernel<T, SRC_KP, CPBS>), dim3(blocksA),
-                       dim3(kBlock), ldsA, s, b);
-    hipLaunchKernelGGL((pencil_batch_kernel<T>), dim3(blocksB), dim3(kBlock),
-                       ldsB, s, b, 1);
-    hipLaunchKernelGGL((slab_inv_batch_kernel<T, T, DST_DOT, CPBS>),
-                       dim3(blocksA), dim3(kBlock), ldsA, s, b, out_T);
-  }
+// f(integral_constant of the slab schedules present)
+template <typename F>
+void with_cpbs(int cpbs, F&& f) {
+  if (cpbs == 1) f(std::integral_constant<int, 1>{});
+  else if (cpbs == 2) f(std::integral_constant<int, 2>{});
+  else f(std::integral_constant<int, 3>{});
 }
 
 template <typename T>
-void launch_G_batch(const BatchSpec<T>& b, int src, T* out_T, double* out_d,
-                    int blocksA, int blocksB, size_t ldsA, size_t ldsB,
+void launch_G_batch(const BatchSpec<T>& b, double* out, const BatchGrid& g,
                     hipStream_t s) {
-  if (b.cpbs == 1)
-    launch_G_batch_cpbs<T, 1>(b, src, out_T, out_d, blocksA, blocksB, ldsA, ldsB, s);
-  else if (b.cpbs == 2)
-    launch_G_batch_cpbs<T, 2>(b, src, out_T, out_d, blocksA, blocksB, ldsA, ldsB, s);
-  else
-    launch_G_batch_cpbs<T, 3>(b, src, out_T, out_d, blocksA, blocksB, ldsA, ldsB, s);
+  with_cpbs(b.cpbs, [&](auto cp) {
+    constexpr int C = decltype(cp)::value;
+    hipLaunchKernelGGL((slab_fwd_batch_kernel<T, SRC_FIELD, C>), dim3(g.A),
+                       dim3(kBlock), g.ldsA, s, b);
+    hipLaunchKernelGGL((pencil_batch_kernel<T>), dim3(3 * g.B), dim3(kBlock),
+                       g.ldsB, s, b);
+    hipLaunchKernelGGL((slab_inv_batch_kernel<T, double, DST_NORM, C>),
+                       dim3(g.A), dim3(kBlock), g.ldsA, s, b, out);
+  });
+}
+
+template <typename TR>
+void launch_residual_batch(const BatchSpec<double>& b, cplx<TR>* rho,
+                           const BatchGrid& g, hipStream_t s) {
+  with_cpbs(b.cpbs, [&](auto cp) {
+    constexpr int C = decltype(cp)::value;
+    hipLaunchKernelGGL((slab_fwd_batch_kernel<double, SRC_FIELD, C>), dim3(g.A),
+                       dim3(kBlock), g.ldsA, s, b);
+  });
+  hipLaunchKernelGGL((pencil_fwd_batch_kernel<double, TR, true>), dim3(g.B),
+                     dim3(kBlock), g.ldsB, s, b, rho);
+}
+
+template <typename T>
+void launch_cg_batch(const BatchSpec<T>& b, const BatchGrid& g, hipStream_t s) {
+  with_cpbs(b.cpbs, [&](auto cp) {
+    constexpr int C = decltype(cp)::value;
+    hipLaunchKernelGGL((pencil_inv_batch_kernel<T, false>), dim3(g.B),
+                       dim3(kBlock), g.ldsB, s, b);
+    hipLaunchKernelGGL((slab_inv_batch_kernel<T, T, DST_P, C>), dim3(g.A),
+                       dim3(kBlock), g.ldsA, s, b, b.p);
+    hipLaunchKernelGGL((slab_fwd_batch_kernel<T, SRC_KROW, C>), dim3(g.A),
+                       dim3(kBlock), g.ldsA, s, b);
+    hipLaunchKernelGGL((pencil_fwd_batch_kernel<T, T, false>), dim3(g.B),
+                       dim3(kBlock), g.ldsB, s, b, b.rho);
+  });
+}
+
+template <typename T>
+void launch_cg_final_batch(const BatchSpec<T>& b, double* F, const BatchGrid& g,
+                           hipStream_t s) {
+  with_cpbs(b.cpbs, [&](auto cp) {
+    constexpr int C = decltype(cp)::value;
+    hipLaunchKernelGGL((pencil_inv_batch_kernel<T, true>), dim3(g.B),
+                       dim3(kBlock), g.ldsB, s, b);
+    hipLaunchKernelGGL((slab_inv_batch_kernel<T, double, DST_ADDF, C>),
+                       dim3(g.A), dim3(kBlock), g.ldsA, s, b, F);
+  });
 }
 
 // Dynamic LDS above the default 64 KiB must be allowed per kernel before
 // the first launch.
-template <typename T, int CPBS>
-void batch_allow_lds_cpbs(size_t slab) {
-  const void* slabs[] = {
-      reinterpret_cast<const void*>(&slab_fwd_batch_kernel<T, SRC_FIELD, CPBS>),
-      reinterpret_cast<const void*>(&slab_fwd_batch_kernel<T, SRC_KP, CPBS>),
-      reinterpret_cast<const void*>(&slab_inv_batch_kernel<T, double, DST_NORM, CPBS>),
-      reinterpret_cast<const void*>(&slab_inv_batch_kernel<T, T, DST_DOT, CPBS>)};
-  for (const void* f : slabs)
-    RVE_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)slab));
-}
-
 template <typename T>
 void batch_allow_lds(size_t slab, size_t pencil) {
-  batch_allow_lds_cpbs<T, 1>(slab);
-  batch_allow_lds_cpbs<T, 2>(slab);
-  batch_allow_lds_cpbs<T, 3>(slab);
-  RVE_HIP(hipFuncSetAttribute(
-      reinterpret_cast<const void*>(&pencil_batch_kernel<T>),
-      hipFuncAttributeMaxDynamicSharedMemorySize, (int)pencil));
+  auto allow = [](const void* f, size_t bytes) {
+    RVE_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)bytes));
+  };
+  for (int cpbs = 1; cpbs <= 3; ++cpbs)
+    with_cpbs(cpbs, [&](auto cp) {
+      constexpr int C = decltype(cp)::value;
+      allow((const void*)&slab_fwd_batch_kernel<T, SRC_FIELD, C>, slab);
+      allow((const void*)&slab_fwd_batch_kernel<T, SRC_KROW, C>, slab);
+      allow((const void*)&slab_inv_batch_kernel<T, double, DST_NORM, C>, slab);
+      allow((const void*)&slab_inv_batch_kernel<T, double, DST_ADDF, C>, slab);
+      allow((const void*)&slab_inv_batch_kernel<T, T, DST_P, C>, slab);
+    });
+  allow((const void*)&pencil_batch_kernel<T>, pencil);
+  allow((const void*)&pencil_fwd_batch_kernel<T, T, false>, pencil);
+  allow((const void*)&pencil_inv_batch_kernel<T, false>, pencil);
+  allow((const void*)&pencil_inv_batch_kernel<T, true>, pencil);
+  if constexpr (sizeof(T) == 8) {
+    allow((const void*)&pencil_fwd_batch_kernel<double, float, true>, pencil);
+    allow((const void*)&pencil_fwd_batch_kernel<double, double, true>, pencil);
+  }
 }
 
 template void batch_allow_lds<float>(size_t, size_t);
 template void batch_allow_lds<double>(size_t, size_t);
-template void launch_G_batch<float>(const BatchSpec<float>&, int, float*,
-                                    double*, int, int, size_t, size_t,
-                                    hipStream_t);
-template void launch_G_batch<double>(const BatchSpec<double>&, int, double*,
-                                     double*, int, int, size_t, size_t,
+template void launch_G_batch<float>(const BatchSpec<float>&, double*,
+                                    const BatchGrid&, hipStream_t);
+template void launch_G_batch<double>(const BatchSpec<double>&, double*,
+                                     const BatchGrid&, hipStream_t);
+template void launch_residual_batch<float>(const BatchSpec<double>&,
+                                           cplx<float>*, const BatchGrid&,
+                                           hipStream_t);
+template void launch_residual_batch<double>(const BatchSpec<double>&,
+                                            cplx<double>*, const BatchGrid&,
+                                            hipStream_t);
+template void launch_cg_batch<float>(const BatchSpec<float>&, const BatchGrid&,
                                      hipStream_t);
+template void launch_cg_batch<double>(const BatchSpec<double>&,
+                                      const BatchGrid&, hipStream_t);
+template void launch_cg_final_batch<float>(const BatchSpec<float>&, double*,
+                                           const BatchGrid&, hipStream_t);
+template void launch_cg_final_batch<double>(const BatchSpec<double>&, double*,
+                                            const BatchGrid&, hipStream_t);
 template void batch_lds<float>(int, int, int, size_t&, size_t&);
 template void batch_lds<double>(int, int, int, size_t&, size_t&);
+template void launch_cg<float>(int, const CgLaunch<float>&, int, hipStream_t);
+template void launch_cg<double>(int, const CgLaunch<double>&, int, hipStream_t);
+template void launch_residual<float>(int, const ResidualLaunch<float>&, hipStream_t);
+template void launch_residual<double>(int, const ResidualLaunch<double>&, hipStream_t);
 template void launch_G<float>(int, const SpectralLaunch<float>&, hipStream_t);
 template void launch_G<double>(int, const SpectralLaunch<double>&, hipStream_t);
 
