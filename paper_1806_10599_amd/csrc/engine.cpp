@@ -349,6 +349,9 @@ LawParams Engine::law_params(double dt) const {
   lp.inv_g = 1.0 / lp.g;
   lp.inv_a = 1.0 / (dt * lp.gdot0);
   lp.nint = flow_exponent_int(lp.nexp);
+  lp.c11m12 = params_[0] - params_[1];
+  lp.c12 = params_[1];
+  lp.c44 = params_[2];
   return lp;
 }
 

@@ -239,6 +239,7 @@ struct LawParams {
   double gdot0, g, nexp, c_af, d_af, dt;
   double inv_g, inv_a;   // 1/g and 1/(dt gdot0), formed once on the host
   int32_t nint;          // nexp when it is an integer in [1, 64], else 0
+  double c11m12, c12, c44;   // cubic constants of the grains: C11 - C12, ...
 };
 
 // the flow-rule exponent as an integer when it is one (powers by products)

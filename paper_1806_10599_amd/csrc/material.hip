@@ -17,10 +17,11 @@
 // formed in FP64 with one logarithm per slip (flow_residual); the Jacobian,
 // which only steers the iteration towards the root of R, in FP32.
 //
-// The 12x12 Jacobian is diag(D) + U W^T with rank-6 factors (the resolved
-// stresses depend on the slips only through the symmetric elastic strain),
-// so each Newton step and each tangent column costs one 6x6 solve
-// (Sherman-Morrison-Woodbury) instead of a 12x12 one.
+// The 12x12 Jacobian is diag(D) + U W^T with low-rank factors (the resolved
+// stresses depend on the slips only through the symmetric elastic strain,
+// and not on its trace), so each Newton step costs one 5x5 solve and each
+// tangent column one 6x6 solve (Sherman-Morrison-Woodbury) instead of a
+// 12x12 one.
 //
 // Work order: crystal voxels first, then the particle voxels (an index list
 // built with the microstructure), so that wavefronts iterating the local
@@ -99,51 +100,6 @@ __device__ __forceinline__ void asinh_pow(double x, double n, int ni,
   const double L = log1p(big ? q : s + s * s / (1.0 + q));
   val = sgn(x) * ((big ? e : 0.0) + L);
   der = (ax > 0.0) ? n * (big ? 1.0 : s) / (ax * q) : 0.0;
-}
-
-// The local residual R = asinh(u) - asinh(|x|^n sign x), u = dg / a, with
-// one logarithm: asinh(u) = su ln A, A = |u| + sqrt(1 + u^2), and
-// asinh(|x|^n sign x) = sx ln B, B = y + sqrt(1 + y^2), y = |x|^n, so
-// R = s ln(A / B) when the signs agree (or one is zero; s the nonzero one)
-// and R = su ln(A B) when they differ -- exact identities.  Near the root
-// A / B is close to one and ln(A / B) carries an absolute error of a few
-// units of 1e-16 (the two-logarithm difference carries that much relative
-// to ln A).  The derivative of asinh(|x|^n sign x) (Jacobian only) is
-// returned in single precision.  Past |x| = 1e7 and for non-integer n the
-// two functions are evaluated apart (asinh_pow, asinh_bf).
-__device__ __forceinline__ double asinh_bf(double u);
-__device__ __forceinline__ void flow_residual(double t, double inv_a, double x,
-                                              double n, int ni, double& R,
-                                              float& der) {
-  const double ax = fabs(x);
-  if (ni > 0 && ax < 1e7) {
-    const double y = ipow_n(ax, ni);
-    const double B = y + sqrt(fma(y, y, 1.0));
-    const double au = fabs(t * inv_a);
-    const double A = au + sqrt(fma(au, au, 1.0));
-    const double su = (t > 0.0) ? 1.0 : ((t < 0.0) ? -1.0 : 0.0);
-    const double sx = (x > 0.0) ? 1.0 : ((x < 0.0) ? -1.0 : 0.0);
-    const bool differ = su * sx < 0.0;
-    const double s = (su != 0.0) ? su : sx;
-    R = s * log(differ ? A * B : A / B);
-    const float yf = (float)y;
-    const float r = (y >= 1e18) ? 1.0f : yf * rsqrtf(fmaf(yf, yf, 1.0f));
-    der = (ax > 1e-30) ? (float)n * r * __builtin_amdgcn_rcpf((float)ax) : 0.0f;
-    return;
-  }
-  double val, d;
-  asinh_pow(x, n, ni, val, d);
-  R = asinh_bf(t * inv_a) - val;
-  der = (float)d;
-}
-
-// asinh(u) in one branch-free form, exact for every u:
-// asinh(|u|) = log1p(|u| + u^2 / (1 + sqrt(1 + u^2))), with the quotient
-// written as |u| (|u| / (1 + q)) so that it cannot overflow.
-__device__ __forceinline__ double asinh_bf(double u) {
-  const double au = fabs(u);
-  const double q = sqrt(1.0 + au * au);
-  return copysign(log1p(au + au * (au / (1.0 + q))), u);
 }
 
 __device__ __forceinline__ void mm3(const double* A, const double* B,
@@ -441,286 +397,442 @@ __device__ __forceinline__ void load9(const double* __restrict__ p, int64_t v,
   for (int c = 0; c < 9; ++c) o[c] = p[c * N + v];
 }
 
-// ---- return mapping with several lanes per voxel ----------------------------
-// LPV consecutive lanes (2 or 4, inside one quad) share a voxel; lane h of
-// the group owns the slips kOwn*h .. kOwn*h + kOwn - 1 (kOwn = 12 / LPV).
-// Sums over slips are formed per lane and completed across the group in a
-// butterfly (x + other at each level: the same value on every lane, since
-// floating-point addition commutes), so all lanes of a voxel take every
-// decision on identical numbers and run the same iterations.  Splitting the
-// per-slip state removes the register spills of the one-lane kernel.
+// E = R^T (Fe^T Fe - 1) R / 2
+__device__ __forceinline__ void lattice_strain(const double* Fe, const double* R,
+                                               double* E) {
+  double C[9], B[9];
+#pragma unroll
+  for (int p = 0; p < 3; ++p)
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      C[3 * p + q] = 0.5 * (Fe[p] * Fe[q] + Fe[3 + p] * Fe[3 + q] +
+                            Fe[6 + p] * Fe[6 + q] - (p == q ? 1.0 : 0.0));
+  mm3(C, R, B);
+#pragma unroll
+  for (int p = 0; p < 3; ++p)
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      E[3 * p + q] = R[p] * B[q] + R[3 + p] * B[3 + q] + R[6 + p] * B[6 + q];
+}
 
-// the value of lane (this ^ X) within the quad, X in {1, 2}
-template <int X>
-__device__ __forceinline__ double quad_xor(double x) {
-  constexpr int ctrl = (X == 1) ? 0xB1 : 0x4E;  // quad_perm 1,0,3,2 / 2,3,0,1
+// ---- return mapping, four lanes per voxel -----------------------------------
+// The local problem is solved in the lattice frame, G = Fe R with R the
+// grain's orientation, where the slip systems and the cubic stiffness are the
+// same constants for every grain: no table is read inside the iteration but
+// R once.  Lane h of a quad owns the three slips of plane h.  The planes are
+// (1 1 1) with the signs sg_h applied to the lattice axes, (+++), (-++),
+// (+-+), (++-), and with them its directions are (1 -1 0), (1 0 -1),
+// (0 1 -1) up to the sign of the whole system (plane_slip), so every lane
+// runs the same constants.  With m = (1 1 1)/sqrt 3 for a plane's three
+// slips, its sum over slips is one vector times m:
+//   G = Gs - sum_h v_h (x) sg_h / sqrt 3,  v_h = Gs (sg_h d_h),
+// d_h = sum_j dg_j s_j, completed over the quad by three butterflies (the
+// same value on every lane, since floating-point addition commutes) and the
+// columns' single sign changes by broadcasts.  All lanes of a voxel take
+// every decision on identical numbers and run the same iterations.
+
+// the value of another lane of the quad (quad_perm control)
+template <int CTRL>
+__device__ __forceinline__ double quad_perm(double x) {
   const unsigned long long u = (unsigned long long)__double_as_longlong(x);
   const int lo = __builtin_amdgcn_mov_dpp((int)(unsigned)(u & 0xffffffffull),
-                                          ctrl, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), ctrl, 0xF,
+                                          CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), CTRL, 0xF,
                                           0xF, false);
   return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) |
                                           (unsigned long long)(unsigned)lo));
 }
-template <int LPV>
-__device__ __forceinline__ double grp_sum(double x) {
-  x = x + quad_xor<1>(x);
-  if constexpr (LPV == 4) x = x + quad_xor<2>(x);
-  return x;
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E;  // quad_perm 1,0,3,2 and 2,3,0,1
+__device__ __forceinline__ double quad_sum(double x) {
+  x = x + quad_perm<kXor1>(x);
+  return x + quad_perm<kXor2>(x);
 }
-template <int LPV>
-__device__ __forceinline__ double grp_max(double x) {
-  x = fmax(x, quad_xor<1>(x));
-  if constexpr (LPV == 4) x = fmax(x, quad_xor<2>(x));
-  return x;
+__device__ __forceinline__ double quad_max(double x) {
+  x = fmax(x, quad_perm<kXor1>(x));
+  return fmax(x, quad_perm<kXor2>(x));
+}
+__device__ __forceinline__ float quad_sumf(float x) {
+  x = x + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(
+              __builtin_bit_cast(int, x), kXor1, 0xF, 0xF, false));
+  return x + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(
+                 __builtin_bit_cast(int, x), kXor2, 0xF, 0xF, false));
+}
+// 1.0 on any lane of the quad -> true on all
+__device__ __forceinline__ bool quad_any(bool b) {
+  int v = b ? 1 : 0;
+  v |= __builtin_amdgcn_mov_dpp(v, kXor1, 0xF, 0xF, false);
+  v |= __builtin_amdgcn_mov_dpp(v, kXor2, 0xF, 0xF, false);
+  return v != 0;
 }
 
-// R, h of the own slips at t = dg + lam*step and Q = Fe^T Fes
-template <int LPV, int kOwn = 12 / LPV>
-__device__ __forceinline__ void pr_eval(const double* Fes,
-                                        const double* __restrict__ chi0p,
-                                        int64_t N, int h, const double* dg,
-                                        const double* step, double lam,
-                                        const double* __restrict__ tb0,
-                                        const LawParams& lp, double a,
-                                        double* R, float* hd, float* Q) {
-  double dFe[9];
+// index of plane h's slip j in the order of the state arrays, and the sign of
+// that system relative to the plane's signs applied to (1 -1 0), (1 0 -1) and
+// (0 1 -1): slips and back stresses change sign with it
+__device__ __forceinline__ int plane_slip(int h, int j) {
+  const unsigned t = j == 0 ? 0x9740u : (j == 1 ? 0xA651u : 0xB832u);
+  return (int)((t >> (4 * h)) & 15u);
+}
+__device__ __forceinline__ double plane_sign(int h, int j) {
+  return (j < 2 ? h == 1 : h == 2) ? -1.0 : 1.0;
+}
+
+// x with its sign changed where bit 31 of mask is set
+__device__ __forceinline__ double flip(double x, unsigned mask) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(x);
+  return __longlong_as_double((long long)(u ^ ((unsigned long long)mask << 32)));
+}
+__device__ __forceinline__ float flip(float x, unsigned mask) {
+  return __builtin_bit_cast(float, __builtin_bit_cast(unsigned, x) ^ mask);
+}
+// the signs of plane h on the lattice axes, as masks
+struct PlaneSigns {
+  unsigned m[3];
+  __device__ __forceinline__ explicit PlaneSigns(int h) {
 #pragma unroll
-  for (int i = 0; i < 9; ++i) dFe[i] = 0.0;
-#pragma unroll
-  for (int j = 0; j < kOwn; ++j) {
-    const double* __restrict__ tb = opaque(tb0) + 3 * (kOwn * h + j);
-    const double t = dg[j] + lam * step[j];
-    const double s0 = tb[kTabS], s1 = tb[kTabS + 1], s2 = tb[kTabS + 2];
-    const double m0 = tb[kTabM], m1 = tb[kTabM + 1], m2 = tb[kTabM + 2];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const double u = t * (Fes[3 * i] * s0 + Fes[3 * i + 1] * s1 +
-                            Fes[3 * i + 2] * s2);
-      dFe[3 * i] += u * m0;
-      dFe[3 * i + 1] += u * m1;
-      dFe[3 * i + 2] += u * m2;
+    for (int i = 0; i < 3; ++i) m[i] = h == i + 1 ? 0x80000000u : 0u;
+  }
+  __device__ __forceinline__ unsigned both(int i, int j) const { return m[i] ^ m[j]; }
+};
+
+// x > 0 of normal range: Goldschmidt's iteration for the square root and
+// Newton's for the quotient from the hardware's reciprocal estimates, a last
+// correction with the fused residual (results within one unit in the last
+// place; the special cases of the library functions do not occur here)
+__device__ __forceinline__ double sqrt_pos(double x) {
+  const double r = __builtin_amdgcn_rsq(x);
+  double g = x * r, h = 0.5 * r;
+  const double e = fma(-h, g, 0.5);
+  g = fma(g, e, g);
+  h = fma(h, e, h);
+  return fma(fma(-g, g, x), h, g);
+}
+__device__ __forceinline__ double div_pos(double a, double b) {
+  double r = __builtin_amdgcn_rcp(b);
+  r = fma(fma(-b, r, 1.0), r, r);
+  r = fma(fma(-b, r, 1.0), r, r);
+  const double q = a * r;
+  return fma(fma(-b, q, a), r, q);
+}
+
+// log2 of a positive number of any size in single precision
+__device__ __forceinline__ float log2_single(double x) {
+  return (float)__builtin_amdgcn_frexp_exp(x) +
+         __builtin_amdgcn_logf((float)__builtin_amdgcn_frexp_mant(x));
+}
+
+// The local residual R = asinh(u) - asinh(|x|^n sign x), u = dg / a, through
+// A = |u| + sqrt(1 + u^2) and B = y + sqrt(1 + y^2), y = |x|^n:
+// R = s ln(A / B) when the signs agree (or one is zero; s the nonzero one)
+// and R = su ln(A B) when they differ -- exact identities.  Near the root the
+// logarithm is 2 atanh(q), q = (A - B)/(A + B) or (A B - 1)/(A B + 1), in
+// FP64 (|q| <= 0.05: the first term left out is below 1e-17), so R there
+// carries an absolute error of a few units of 1e-16, which is what the
+// converged slips depend on.  Further away, where R only steers the
+// iteration, single precision serves.  The derivative of
+// asinh(|x|^n sign x) (Jacobian only) is in single precision.  Past
+// |x| = 1e7, where y^2 would leave the FP64 range, ln B = n ln|x| + ln 2.
+// Non-integer n (INTN false): the two functions are evaluated apart.
+__device__ __forceinline__ double asinh_bf(double u);
+template <bool INTN>
+__device__ __forceinline__ void flow_residual(double t, double inv_a, double x,
+                                              double n, int ni, double& R,
+                                              float& der) {
+  const double ax = fabs(x);
+  if constexpr (INTN) {
+    const bool huge = ax >= 1e7;
+    const double y = ipow_n(huge ? 1e7 : ax, ni);
+    const double B = y + sqrt_pos(fma(y, y, 1.0));
+    const double au = fabs(t * inv_a);
+    const double A = au + sqrt_pos(fma(au, au, 1.0));
+    const bool differ = (t > 0.0 && x < 0.0) || (t < 0.0 && x > 0.0);
+    const double num = differ ? fma(A, B, -1.0) : A - B;
+    const double den = differ ? fma(A, B, 1.0) : A + B;
+    const double q = div_pos(num, den);
+    double r;
+    if (fabs(q) <= 0.05 && !huge) {
+      const double q2 = q * q;
+      r = 2.0 * q * fma(q2, fma(q2, fma(q2, fma(q2, fma(q2, 1.0 / 11.0, 1.0 / 9.0),
+                                                1.0 / 7.0), 0.2), 1.0 / 3.0), 1.0);
+    } else {
+      const float la = log2_single(A);
+      const float lb = huge ? (float)n * log2_single(ax) + 1.0f : log2_single(B);
+      r = (double)(0.69314718055994531f * (differ ? la + lb : la - lb));
     }
+    const double s = (t != 0.0) ? t : x;
+    R = s < 0.0 ? -r : r;
+    const float yf = (float)y;
+    const float rs = (y >= 1e18) ? 1.0f : yf * rsqrtf(fmaf(yf, yf, 1.0f));
+    der = (ax > 1e-30) ? (float)n * rs * __builtin_amdgcn_rcpf((float)ax) : 0.0f;
+  } else {
+    double val, d;
+    asinh_pow(x, n, ni, val, d);
+    R = asinh_bf(t * inv_a) - val;
+    der = (float)d;
   }
-  double Fe[9];
+}
+
+// asinh(u) in one branch-free form, exact for every u:
+// asinh(|u|) = log1p(|u| + u^2 / (1 + sqrt(1 + u^2))), with the quotient
+// written as |u| (|u| / (1 + q)) so that it cannot overflow.
+__device__ __forceinline__ double asinh_bf(double u) {
+  const double au = fabs(u);
+  const double q = sqrt(1.0 + au * au);
+  return copysign(log1p(au + au * (au / (1.0 + q))), u);
+}
+
+constexpr double kInvSqrt6 = 0.40824829046386301637;
+constexpr float kInvSqrt6f = 0.40824829046386302f;
+
+// dG = sum over the slips of dg_a (B s_a) (x) m_a for the lane's slips t and
+// a matrix B in the lattice frame, completed over the quad
+__device__ __forceinline__ void slip_sum(const double* B, const double* t,
+                                         const PlaneSigns& sg, double* dG) {
+  const double d0 = flip(kInvSqrt6 * (t[0] + t[1]), sg.m[0]);
+  const double d1 = flip(kInvSqrt6 * (t[2] - t[0]), sg.m[1]);
+  const double d2 = flip(-kInvSqrt6 * (t[1] + t[2]), sg.m[2]);
 #pragma unroll
-  for (int i = 0; i < 9; ++i) Fe[i] = Fes[i] - grp_sum<LPV>(dFe[i]);
-  double S[6];
-  {
-    double C[9];
-#pragma unroll
-    for (int p = 0; p < 3; ++p)
-#pragma unroll
-      for (int q = 0; q < 3; ++q)
-        C[3 * p + q] = Fe[p] * Fe[q] + Fe[3 + p] * Fe[3 + q] + Fe[6 + p] * Fe[6 + q];
-    const double E[6] = {0.5 * (C[0] - 1.0), 0.5 * (C[4] - 1.0),
-                         0.5 * (C[8] - 1.0), 0.5 * C[5],
-                         0.5 * C[2],         0.5 * C[1]};
-    cmul6(opaque(tb0) + kTabC, E, S);
+  for (int i = 0; i < 3; ++i) {
+    const double v = B[3 * i] * d0 + B[3 * i + 1] * d1 + B[3 * i + 2] * d2;
+    const double T = quad_sum(v);
+    dG[3 * i] = fma(-2.0, quad_perm<0x55>(v), T);
+    dG[3 * i + 1] = fma(-2.0, quad_perm<0xAA>(v), T);
+    dG[3 * i + 2] = fma(-2.0, quad_perm<0xFF>(v), T);
   }
+}
+
+// The elastic strain in the lattice frame at G = Gs - dG: with that of Gs,
+//   E = Es - sym((Gs - dG/2)^T dG),
+// which subtracts no unit matrix (Es = R^T (Fes^T Fes - 1) R / 2 is exactly
+// zero in an undeformed voxel, and so are then its stress and P).
+__device__ __forceinline__ double strain_term(const double* Gs, const double* dG,
+                                              int p, int q) {
+  double e = 0.0;
 #pragma unroll
-  for (int j = 0; j < kOwn; ++j) {
-    const double* __restrict__ tb = opaque(tb0) + 3 * (kOwn * h + j);
-    const double t = dg[j] + lam * step[j];
-    const double s0 = tb[kTabS], s1 = tb[kTabS + 1], s2 = tb[kTabS + 2];
-    const double m0 = tb[kTabM], m1 = tb[kTabM + 1], m2 = tb[kTabM + 2];
-    const double Sm0 = S[0] * m0 + S[5] * m1 + S[4] * m2;
-    const double Sm1 = S[5] * m0 + S[1] * m1 + S[3] * m2;
-    const double Sm2 = S[4] * m0 + S[3] * m1 + S[2] * m2;
-    const double tau = s0 * Sm0 + s1 * Sm1 + s2 * Sm2;
-    const double chi0 = opaque(chi0p)[(kOwn * h + j) * N];
-    const double chi = (chi0 + lp.c_af * t) / (1.0 + lp.d_af * fabs(t));
-    const double x = (tau - chi) * lp.inv_g;
-    float der;
-    flow_residual(t, lp.inv_a, x, lp.nexp, lp.nint, R[j], der);
-    hd[j] = der;
+  for (int i = 0; i < 9; i += 3) {
+    e += fma(-0.5, dG[i + p], Gs[i + p]) * dG[i + q];
+    if (p != q) e += fma(-0.5, dG[i + q], Gs[i + q]) * dG[i + p];
   }
-  // Q = Fe^T Fes for the Jacobian, which only steers the Newton iteration
-  // (its root is that of R, formed in FP64): single precision
+  return p == q ? e : 0.5 * e;
+}
+
+// R and slopes of the lane's slips at t = dg + lam * step, and Q = G^T Gs
+// there, with the plane's signs on both indices, for the Jacobian; es: the
+// strain Es as e11 - e22, e11 - e33, e12, e13, e23 (m and s of a slip are
+// orthogonal: only these enter its resolved shear)
+template <bool INTN>
+__device__ __forceinline__ void pr_eval(const double* Gs, const double* es,
+                                        const double* chi0,
+                                        const double* dg, const double* step,
+                                        double lam, const PlaneSigns& sg,
+                                        const LawParams& lp, double* R,
+                                        float* hd, float* Q) {
+  double t[3], G[9];
+#pragma unroll
+  for (int j = 0; j < 3; ++j) t[j] = dg[j] + lam * step[j];
+  slip_sum(Gs, t, sg, G);   // dG
+  const double x0 = strain_term(Gs, G, 0, 0);
+  const double kd = kInvSqrt6 * lp.c11m12, k44 = 2.0 * kInvSqrt6 * lp.c44;
+  const double d01 = kd * (es[0] - (x0 - strain_term(Gs, G, 1, 1)));
+  const double d02 = kd * (es[1] - (x0 - strain_term(Gs, G, 2, 2)));
+  const double c01 = flip(k44 * (es[2] - strain_term(Gs, G, 0, 1)), sg.both(0, 1));
+  const double c02 = flip(k44 * (es[3] - strain_term(Gs, G, 0, 2)), sg.both(0, 2));
+  const double c12 = flip(k44 * (es[4] - strain_term(Gs, G, 1, 2)), sg.both(1, 2));
+#pragma unroll
+  for (int i = 0; i < 9; ++i) G[i] = Gs[i] - G[i];
 #pragma unroll
   for (int i = 0; i < 3; ++i)
 #pragma unroll
-    for (int j = 0; j < 3; ++j)
-      Q[3 * i + j] = (float)(Fe[i] * Fes[j] + Fe[3 + i] * Fes[3 + j] +
-                             Fe[6 + i] * Fes[6 + j]);
-}
-
-// V_a = sym((Q s_a) (x) m_a) in Voigt order, single precision
-__device__ __forceinline__ void make_Vf(const float* Q,
-                                        const double* __restrict__ tb, int al,
-                                        float* V) {
-  const float s0 = (float)tb[kTabS + 3 * al], s1 = (float)tb[kTabS + 3 * al + 1],
-              s2 = (float)tb[kTabS + 3 * al + 2];
-  const float m0 = (float)tb[kTabM + 3 * al], m1 = (float)tb[kTabM + 3 * al + 1],
-              m2 = (float)tb[kTabM + 3 * al + 2];
-  float qs[3];
+    for (int j = 0; j < 3; ++j) {
+      const float q = (float)G[i] * (float)Gs[j] + (float)G[3 + i] * (float)Gs[3 + j] +
+                      (float)G[6 + i] * (float)Gs[6 + j];
+      Q[3 * i + j] = flip(q, sg.both(i, j));
+    }
+  const double tau[3] = {d01 + (c02 - c12), d02 + (c01 - c12),
+                         (d02 - d01) + (c01 - c02)};
 #pragma unroll
-  for (int i = 0; i < 3; ++i) qs[i] = Q[3 * i] * s0 + Q[3 * i + 1] * s1 + Q[3 * i + 2] * s2;
-  V[0] = qs[0] * m0;
-  V[1] = qs[1] * m1;
-  V[2] = qs[2] * m2;
-  V[3] = 0.5f * (qs[1] * m2 + qs[2] * m1);
-  V[4] = 0.5f * (qs[0] * m2 + qs[2] * m0);
-  V[5] = 0.5f * (qs[0] * m1 + qs[1] * m0);
+  for (int j = 0; j < 3; ++j) {
+    const double chi = div_pos(chi0[j] + lp.c_af * t[j], 1.0 + lp.d_af * fabs(t[j]));
+    flow_residual<INTN>(t[j], lp.inv_a, (tau[j] - chi) * lp.inv_g, lp.nexp, lp.nint,
+                  R[j], hd[j]);
+  }
 }
 
-template <int LPV>
-__device__ __forceinline__ float grp_sumf(float x) {
-  x = x + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(
-              __builtin_bit_cast(int, x), 0xB1, 0xF, 0xF, false));
-  if constexpr (LPV == 4)
-    x = x + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(
-                __builtin_bit_cast(int, x), 0x4E, 0xF, 0xF, false));
-  return x;
-}
+// The slips' symmetric Schmid tensors have no trace: in the orthonormal basis
+// (e11 - e22)/sqrt 2, (e11 + e22 - 2 e33)/sqrt 6, sqrt 2 e23, sqrt 2 e13,
+// sqrt 2 e12 of the trace-free tensors they are five-vectors.  Those of the
+// plane (1 1 1), in units of 1/sqrt 12:
+__device__ constexpr float kSchmid5[3][5] = {{2.0f, 0.0f, -1.0f, 1.0f, 0.0f},
+                                             {1.0f, 1.7320508075688773f, -1.0f, 0.0f, 1.0f},
+                                             {-1.0f, 1.7320508075688773f, 0.0f, -1.0f, 1.0f}};
 
-// Newton step of the own slips: step = -J^-1 R, J = diag(D) + U W^T.  The
-// Jacobian only steers the iteration (the root is that of the FP64
-// residual R), so it is formed and solved in single precision: the step
-// is then exact to single-precision rounding, which leaves the local
-// Newton iteration converging as before to the FP64 root.
-template <int LPV, int kOwn = 12 / LPV>
+// Newton step of the lane's slips: step = -J^-1 R.  J = diag(1/D) + h N V^T
+// with V_a = sym((Q s_a) (x) m_a), Q = G^T Gs, and N_a = C : sym(S0_a); in
+// the basis above, with C's square root on both factors, Woodbury's
+// capacitance matrix is the 5x5  1 + sum_a D_a h_a v_a (x) n_a.  v_a differs
+// from n_a by the elastic strain only, so the matrix is close to symmetric
+// and positive definite and is eliminated without pivoting.  The Jacobian
+// only steers the iteration (the root is that of the FP64 residual R): single
+// precision.
 __device__ __forceinline__ void pr_step(const double* dg, const double* R,
                                         const float* hd, const float* Q,
-                                        const double* __restrict__ chi0p,
-                                        int64_t N, int h,
-                                        const double* __restrict__ tb0,
-                                        const LawParams& lp, double a,
-                                        double* step) {
-  LU6T<float> L;
+                                        const double* chi0, const PlaneSigns& sg,
+                                        const LawParams& lp, float a2, double* step) {
+  // basis components' signs and roots of the moduli
+  const float kd = sqrtf((float)lp.c11m12), ks = sqrtf(2.0f * (float)lp.c44);
+  const float k5[5] = {kd, kd, flip(ks, sg.both(1, 2)), flip(ks, sg.both(0, 2)),
+                       flip(ks, sg.both(0, 1))};
+  const float inv_g = (float)lp.inv_g, c_af = (float)lp.c_af, d_af = (float)lp.d_af;
+  float M[25], V[3][5], D[3], z[5];
 #pragma unroll
-  for (int i = 0; i < 36; ++i) L.M[i] = 0.0f;
-  float D[kOwn];
-  const float inv_g = (float)lp.inv_g, c_af = (float)lp.c_af,
-              d_af = (float)lp.d_af, a2 = (float)(a * a);
+  for (int i = 0; i < 25; ++i) M[i] = 0.0f;
 #pragma unroll
-  for (int j = 0; j < kOwn; ++j) {
-    const int al = kOwn * h + j;
-    const double* __restrict__ tb = opaque(tb0);
-    const float chi0 = (float)opaque(chi0p)[al * N];
+  for (int i = 0; i < 5; ++i) z[i] = 0.0f;
+  float f[3];
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
     const float dgf = (float)dg[j];
-    const float den = 1.0f / (1.0f + d_af * fabsf(dgf));
-    const float chi = (chi0 + c_af * dgf) * den;
-    const float sg = (dgf > 0.0f) ? 1.0f : ((dgf < 0.0f) ? -1.0f : 0.0f);
-    const float dchi = (c_af - d_af * sg * chi) * den;
-    // D holds the reciprocal of the diagonal of the local Jacobian
-    D[j] = 1.0f / (rsqrtf(a2 + dgf * dgf) + hd[j] * inv_g * dchi);
-    float V[6];
-    make_Vf(Q, tb, al, V);
-    const float f = hd[j] * inv_g * D[j];
-    // row factor of the rank-one term, formed once per slip
-    float w[6];
-#pragma unroll
-    for (int J = 0; J < 6; ++J) w[J] = f * (float)(VW[J] * tb[kTabN + 6 * al + J]);
-#pragma unroll
-    for (int I = 0; I < 6; ++I)
-#pragma unroll
-      for (int J = 0; J < 6; ++J) L.M[6 * I + J] += V[I] * w[J];
+    const float den = __builtin_amdgcn_rcpf(1.0f + d_af * fabsf(dgf));
+    const float chi = ((float)chi0[j] + c_af * dgf) * den;
+    const float s = (dgf > 0.0f) ? 1.0f : ((dgf < 0.0f) ? -1.0f : 0.0f);
+    const float dchi = (c_af - d_af * s * chi) * den;
+    D[j] = __builtin_amdgcn_rcpf(rsqrtf(a2 + dgf * dgf) + hd[j] * inv_g * dchi);
+    f[j] = hd[j] * inv_g * D[j];
+    // Q s_j of (1 -1 0), (1 0 -1), (0 1 -1), in units of 1/sqrt 2
+    constexpr int ps[3] = {0, 0, 1}, ms[3] = {1, 2, 2};
+    const float q0 = Q[ps[j]] - Q[ms[j]], q1 = Q[3 + ps[j]] - Q[3 + ms[j]],
+                q2 = Q[6 + ps[j]] - Q[6 + ms[j]];
+    // sym(q (x) (1 1 1)) in the basis, in units of 1/sqrt 6
+    constexpr float r2 = 0.70710678118654752f, r6 = 0.40824829046386302f;
+    V[j][0] = kInvSqrt6f * k5[0] * r2 * (q0 - q1);
+    V[j][1] = kInvSqrt6f * k5[1] * r6 * (q0 + q1 - 2.0f * q2);
+    V[j][2] = kInvSqrt6f * k5[2] * r2 * (q1 + q2);
+    V[j][3] = kInvSqrt6f * k5[3] * r2 * (q0 + q2);
+    V[j][4] = kInvSqrt6f * k5[4] * r2 * (q0 + q1);
+    const float sj = -(float)R[j] * D[j];
     step[j] = -R[j] * (double)D[j];
+#pragma unroll
+    for (int I = 0; I < 5; ++I) {
+      z[I] += V[j][I] * sj;
+      const float fv = f[j] * V[j][I];
+#pragma unroll
+      for (int J = 0; J < 5; ++J)
+        if (kSchmid5[j][J] != 0.0f) M[5 * I + J] += fv * kSchmid5[j][J];
+    }
+  }
+  constexpr float r12 = 0.28867513459481288f;   // 1/sqrt 12
+#pragma unroll
+  for (int I = 0; I < 5; ++I) {
+    z[I] = quad_sumf(z[I]);
+#pragma unroll
+    for (int J = 0; J < 5; ++J)
+      M[5 * I + J] = (I == J ? 1.0f : 0.0f) + quad_sumf(M[5 * I + J] * (r12 * k5[J]));
+  }
+  // z <- M^-1 z
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    const float ip = __builtin_amdgcn_rcpf(M[6 * k]);
+    M[6 * k] = ip;
+#pragma unroll
+    for (int r = k + 1; r < 5; ++r) {
+      const float m = M[5 * r + k] * ip;
+#pragma unroll
+      for (int J = k + 1; J < 5; ++J) M[5 * r + J] -= m * M[5 * k + J];
+      z[r] -= m * z[k];
+    }
   }
 #pragma unroll
-  for (int i = 0; i < 36; ++i) L.M[i] = ((i % 7 == 0) ? 1.0f : 0.0f) + grp_sumf<LPV>(L.M[i]);
-  lu6_factor(L);
-  float z[6] = {0, 0, 0, 0, 0, 0};
+  for (int k = 4; k >= 0; --k) {
 #pragma unroll
-  for (int j = 0; j < kOwn; ++j) {
-    float V[6];
-    make_Vf(Q, opaque(tb0), kOwn * h + j, V);
-    const float sj = (float)step[j];
-#pragma unroll
-    for (int I = 0; I < 6; ++I) z[I] += V[I] * sj;
+    for (int J = k + 1; J < 5; ++J) z[k] -= M[5 * k + J] * z[J];
+    z[k] *= M[6 * k];
   }
 #pragma unroll
-  for (int I = 0; I < 6; ++I) z[I] = grp_sumf<LPV>(z[I]);
-  lu6_solve(L, z);
+  for (int I = 0; I < 5; ++I) z[I] *= r12 * k5[I];
 #pragma unroll
-  for (int j = 0; j < kOwn; ++j) {
-    const double* __restrict__ tb = opaque(tb0) + kTabN + 6 * (kOwn * h + j);
+  for (int j = 0; j < 3; ++j) {
     float u = 0.0f;
 #pragma unroll
-    for (int J = 0; J < 6; ++J) u += (float)(VW[J] * tb[J]) * z[J];
-    step[j] -= (double)(hd[j] * inv_g * u * D[j]);
+    for (int J = 0; J < 5; ++J)
+      if (kSchmid5[j][J] != 0.0f) u += kSchmid5[j][J] * z[J];
+    step[j] -= (double)(f[j] * u);
   }
 }
 
-template <int kOwn>
-__device__ __forceinline__ double own_half_sq(const double* R) {
-  double m = 0.0;
-#pragma unroll
-  for (int j = 0; j < kOwn; ++j) m += R[j] * R[j];
-  return 0.5 * m;
+__device__ __forceinline__ double half_sq(const double* R) {
+  return 0.5 * (R[0] * R[0] + R[1] * R[1] + R[2] * R[2]);
 }
 
-// damped Newton with Armijo backtracking on |R|^2/2 over the group (the
-// iteration of the one-lane formulation); dg holds the own slips
-template <int LPV, int kOwn = 12 / LPV>
-__device__ __forceinline__ bool pr_local_solve(const double* Fes,
-                                               const double* __restrict__ chi0p,
-                                               int64_t N, int h, double* dg,
-                                               const double* __restrict__ tb,
+// damped Newton with Armijo backtracking on |R|^2/2 over the quad; dg holds
+// the lane's slips
+template <bool INTN>
+__device__ __forceinline__ bool pr_local_solve(const double* Gs,
+                                               const double* es,
+                                               const double* chi0, double* dg,
+                                               const PlaneSigns& sg,
                                                const LawParams& lp, double a,
                                                int& iters, int& evals) {
-  double R[kOwn], step[kOwn];
-  float hd[kOwn], Q[9];
-#pragma unroll
-  for (int j = 0; j < kOwn; ++j) step[j] = 0.0;
-  pr_eval<LPV>(Fes, chi0p, N, h, dg, step, 0.0, tb, lp, a, R, hd, Q);
+  double R[3], step[3] = {0.0, 0.0, 0.0};
+  float hd[3], Q[9];
+  const float a2 = (float)(a * a);
+  pr_eval<INTN>(Gs, es, chi0, dg, step, 0.0, sg, lp, R, hd, Q);
   ++evals;
   for (int it = 0; it < LOCAL_MAXIT; ++it) {
     ++iters;
-    pr_step<LPV>(dg, R, hd, Q, chi0p, N, h, tb, lp, a, step);
-    double smax = 0.0, dmax = 0.0, rmax = 0.0, bad = 0.0;
+    pr_step(dg, R, hd, Q, chi0, sg, lp, a2, step);
+    double smax = 0.0, dmax = 0.0, rmax = 0.0;
+    bool bad = false;
 #pragma unroll
-    for (int j = 0; j < kOwn; ++j) {
+    for (int j = 0; j < 3; ++j) {
       smax = fmax(smax, fabs(step[j]));
       dmax = fmax(dmax, fabs(dg[j] + step[j]));
       rmax = fmax(rmax, fabs(R[j]));
-      bad = isfinite(step[j]) ? bad : 1.0;
+      bad = bad || !isfinite(step[j]);
     }
-    smax = grp_max<LPV>(smax);
-    dmax = grp_max<LPV>(dmax);
-    rmax = grp_max<LPV>(rmax);
-    bad = grp_max<LPV>(bad);
-    if (bad == 0.0 && smax <= LOCAL_ATOL + LOCAL_RTOL * dmax) {
+    smax = quad_max(smax);
+    dmax = quad_max(dmax);
+    if (!quad_any(bad) && smax <= LOCAL_ATOL + LOCAL_RTOL * dmax) {
 #pragma unroll
-      for (int j = 0; j < kOwn; ++j) dg[j] += step[j];
+      for (int j = 0; j < 3; ++j) dg[j] += step[j];
       return true;
     }
-    const double merit0 = grp_sum<LPV>(own_half_sq<kOwn>(R));
+    const double merit0 = quad_sum(half_sq(R));
     double lam = 1.0, lam_used = 1.0;
     bool accepted = false;
     for (int ls = 0; ls < 40; ++ls) {
-      pr_eval<LPV>(Fes, chi0p, N, h, dg, step, lam, tb, lp, a, R, hd, Q);
+      pr_eval<INTN>(Gs, es, chi0, dg, step, lam, sg, lp, R, hd, Q);
       ++evals;
       lam_used = lam;
-      const double mt = grp_sum<LPV>(own_half_sq<kOwn>(R));
+      const double mt = quad_sum(half_sq(R));
       if (isfinite(mt) && mt <= (1.0 - 1e-4 * lam) * merit0) {
         accepted = true;
         break;
       }
       lam *= 0.5;
     }
-    double nf = 0.0;
+    bool nf = false;
 #pragma unroll
-    for (int j = 0; j < kOwn; ++j) {
+    for (int j = 0; j < 3; ++j) {
       dg[j] = dg[j] + lam_used * step[j];
-      nf = isfinite(dg[j]) ? nf : 1.0;
+      nf = nf || !isfinite(dg[j]);
     }
-    if (grp_max<LPV>(nf) != 0.0) return false;
-    if (!accepted && rmax <= LOCAL_RFLOOR) return true;
+    if (quad_any(nf)) return false;
+    if (!accepted && quad_max(rmax) <= LOCAL_RFLOOR) return true;
   }
   return false;
 }
 
 }  // namespace
 
-// LPV lanes per voxel (see pr_eval); 256 threads per block
-template <int LPV, int MINB>
-__global__ __launch_bounds__(256, MINB) void return_map_group_kernel(ConstArgs A) {
-  constexpr int kOwn = 12 / LPV;
+// Bound by the issue of the local iteration (about 1000 vector instructions
+// per Newton step and residual, a third of them FP64, for the sixteen voxels
+// of a wavefront): 64^3, 5.6 evaluations per voxel, 665 us in the sample frame
+// with tables -> 246 us; 32^3 122 -> 57, 16^3 82 -> 34 us.  The 178 MB of a
+// 64^3 launch would take 35 us.
+template <bool INTN, int BLK, int WAVES>
+__global__ __launch_bounds__(BLK, WAVES) void return_map_kernel(ConstArgs A) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t g = t / LPV;
-  const int h = (int)(t % LPV);
+  const int64_t g = t / 4;
+  const int h = (int)(t % 4);
   if (g >= A.N) return;  // all lanes of a voxel leave together
   const int64_t v = A.order ? (int64_t)A.order[g] : g;
   if (A.vrve && A.scs[A.vrve[v]].inactive) return;
@@ -747,13 +859,13 @@ __global__ __launch_bounds__(256, MINB) void return_map_group_kernel(ConstArgs A
     mm3(F, S, P);
 #pragma unroll
     for (int c = 0; c < 9; ++c)
-      if (c % LPV == h) {
+      if (c % 4 == h) {
         A.P[c * N + v] = P[c];
         A.Fpi[c * N + v] = A.Fpi0[c * N + v];
       }
 #pragma unroll
-    for (int j = 0; j < kOwn; ++j) {
-      const int al = kOwn * h + j;
+    for (int j = 0; j < 3; ++j) {
+      const int al = 3 * h + j;
       A.chi[al * N + v] = A.chi0[al * N + v];
       A.dg[al * N + v] = 0.0;
     }
@@ -763,96 +875,89 @@ __global__ __launch_bounds__(256, MINB) void return_map_group_kernel(ConstArgs A
     }
     return;
   }
-  double dg[kOwn];
-  double warm = 0.0;
+  const PlaneSigns sg(h);
+  double dg[3], chi0[3];
+  bool warm = false;
 #pragma unroll
-  for (int j = 0; j < kOwn; ++j) {
-    dg[j] = A.dg0 ? A.dg0[(kOwn * h + j) * N + v] : 0.0;
-    warm = (dg[j] != 0.0) ? 1.0 : warm;
+  for (int j = 0; j < 3; ++j) {
+    const int64_t at = plane_slip(h, j) * N + v;
+    chi0[j] = plane_sign(h, j) * A.chi0[at];
+    dg[j] = A.dg0 ? plane_sign(h, j) * A.dg0[at] : 0.0;
+    warm = warm || dg[j] != 0.0;
   }
-  warm = grp_max<LPV>(warm);
-  double Fes[9];
+  warm = quad_any(warm);
+  // Gs = F Fp^-1_0 R and its strain in the lattice frame
+  double Gs[9], es[5], e0;
   {
-    double Fpi0[9];
-    load9(A.Fpi0, v, N, Fpi0);
-    mm3(F, Fpi0, Fes);
+    double Fp0[9], Rm[9], Fes[9];
+    load9(A.Fpi0, v, N, Fp0);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) Rm[i] = tb[kTabR + i];
+    mm3(F, Fp0, Fes);
+    mm3(Fes, Rm, Gs);
+    double E[9];
+    lattice_strain(Fes, Rm, E);
+    e0 = E[0];
+    es[0] = E[0] - E[4];
+    es[1] = E[0] - E[8];
+    es[2] = E[1];
+    es[3] = E[2];
+    es[4] = E[5];
   }
   const double a = A.lp.dt * A.lp.gdot0;
-  const double* chi0p = A.chi0 + v;
   int iters = 0, evals = 0;
   bool ok = false;
   for (int attempt = 0; attempt < 2 && !ok; ++attempt) {
     if (attempt == 1) {
-      if (warm == 0.0) break;
+      if (!warm) break;
 #pragma unroll
-      for (int j = 0; j < kOwn; ++j) dg[j] = 0.0;  // retry from zero slips
+      for (int j = 0; j < 3; ++j) dg[j] = 0.0;  // retry from zero slips
     }
-    ok = pr_local_solve<LPV>(Fes, chi0p, N, h, dg, tb, A.lp, a, iters, evals);
+    ok = pr_local_solve<INTN>(Gs, es, chi0, dg, sg, A.lp, a, iters, evals);
   }
   if (!ok && h == 0) atomicAdd(A.vrve ? &A.scs[A.vrve[v]].fails : A.fails, 1);
-  // final state: Fp^-1 = Fp^-1_0 (I - sum dg s (x) m), Fe = F Fp^-1,
-  // S = C : Ee, P = Fe S Fp^-T
-  double Fpi0[9];
-  load9(opaque(A.Fpi0), v, N, Fpi0);
-  double dFpi[9], dFe[9];
-#pragma unroll
-  for (int i = 0; i < 9; ++i) dFpi[i] = dFe[i] = 0.0;
-#pragma unroll
-  for (int j = 0; j < kOwn; ++j) {
-    const double* __restrict__ tj = opaque(tb) + 3 * (kOwn * h + j);
-    const double s0 = tj[kTabS], s1 = tj[kTabS + 1], s2 = tj[kTabS + 2];
-    const double m0 = tj[kTabM], m1 = tj[kTabM + 1], m2 = tj[kTabM + 2];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const double u = dg[j] * (Fpi0[3 * i] * s0 + Fpi0[3 * i + 1] * s1 +
-                                Fpi0[3 * i + 2] * s2);
-      dFpi[3 * i] += u * m0;
-      dFpi[3 * i + 1] += u * m1;
-      dFpi[3 * i + 2] += u * m2;
-      const double w = dg[j] * (Fes[3 * i] * s0 + Fes[3 * i + 1] * s1 +
-                                Fes[3 * i + 2] * s2);
-      dFe[3 * i] += w * m0;
-      dFe[3 * i + 1] += w * m1;
-      dFe[3 * i + 2] += w * m2;
-    }
-  }
-  double Fpi[9], Fe[9];
-#pragma unroll
-  for (int i = 0; i < 9; ++i) {
-    Fpi[i] = Fpi0[i] - grp_sum<LPV>(dFpi[i]);
-    Fe[i] = Fes[i] - grp_sum<LPV>(dFe[i]);
-  }
-  double S[6];
+  // final state: Fp^-1 = Fp^-1_0 - dFp R^T, G = Fe R, S = C : Ee, and
+  // P = Fe S Fp^-T = G S (Fp^-1 R)^T, S in the lattice frame
+  double G[9], GS[9];
+  slip_sum(Gs, dg, sg, G);
   {
-    double C[9];
+    const double x0 = e0 - strain_term(Gs, G, 0, 0);
+    const double x1 = (e0 - es[0]) - strain_term(Gs, G, 1, 1);
+    const double x2 = (e0 - es[1]) - strain_term(Gs, G, 2, 2);
+    const double tr = A.lp.c12 * (x0 + x1 + x2), k44 = 2.0 * A.lp.c44;
+    const double s01 = k44 * (es[2] - strain_term(Gs, G, 0, 1));
+    const double s02 = k44 * (es[3] - strain_term(Gs, G, 0, 2));
+    const double s12 = k44 * (es[4] - strain_term(Gs, G, 1, 2));
+    const double S[9] = {A.lp.c11m12 * x0 + tr, s01, s02, s01,
+                         A.lp.c11m12 * x1 + tr, s12, s02, s12,
+                         A.lp.c11m12 * x2 + tr};
 #pragma unroll
-    for (int p = 0; p < 3; ++p)
-#pragma unroll
-      for (int q = 0; q < 3; ++q)
-        C[3 * p + q] = Fe[p] * Fe[q] + Fe[3 + p] * Fe[3 + q] + Fe[6 + p] * Fe[6 + q];
-    const double E[6] = {0.5 * (C[0] - 1.0), 0.5 * (C[4] - 1.0),
-                         0.5 * (C[8] - 1.0), 0.5 * C[5],
-                         0.5 * C[2],         0.5 * C[1]};
-    cmul6(opaque(tb) + kTabC, E, S);
+    for (int i = 0; i < 9; ++i) G[i] = Gs[i] - G[i];
+    mm3(G, S, GS);
   }
-  const double Sf[9] = {S[0], S[5], S[4], S[5], S[1], S[3], S[4], S[3], S[2]};
-  double FeS[9];
-  mm3(Fe, Sf, FeS);
+  double Fp0[9], Rm[9], B[9], dFp[9];
+  load9(opaque(A.Fpi0), v, N, Fp0);
+#pragma unroll
+  for (int i = 0; i < 9; ++i) Rm[i] = opaque(tb)[kTabR + i];
+  mm3(Fp0, Rm, B);
+  slip_sum(B, dg, sg, dFp);
+#pragma unroll
+  for (int i = 0; i < 9; ++i) B[i] -= dFp[i];
 #pragma unroll
   for (int c = 0; c < 9; ++c) {
-    if (c % LPV != h) continue;
+    if (c % 4 != h) continue;
     const int i = c / 3, j = c - 3 * (c / 3);
-    const double P = FeS[3 * i] * Fpi[3 * j] + FeS[3 * i + 1] * Fpi[3 * j + 1] +
-                     FeS[3 * i + 2] * Fpi[3 * j + 2];
-    A.P[c * N + v] = P;
-    A.Fpi[c * N + v] = Fpi[c];
+    A.P[c * N + v] = GS[3 * i] * B[3 * j] + GS[3 * i + 1] * B[3 * j + 1] +
+                     GS[3 * i + 2] * B[3 * j + 2];
+    A.Fpi[c * N + v] = Fp0[c] - (dFp[3 * i] * Rm[3 * j] + dFp[3 * i + 1] * Rm[3 * j + 1] +
+                                 dFp[3 * i + 2] * Rm[3 * j + 2]);
   }
 #pragma unroll
-  for (int j = 0; j < kOwn; ++j) {
-    const int al = kOwn * h + j;
-    const double chi0 = A.chi0[al * N + v];
-    A.chi[al * N + v] = (chi0 + A.lp.c_af * dg[j]) / (1.0 + A.lp.d_af * fabs(dg[j]));
-    A.dg[al * N + v] = dg[j];
+  for (int j = 0; j < 3; ++j) {
+    const int64_t at = plane_slip(h, j) * N + v;
+    const double sj = plane_sign(h, j);
+    A.chi[at] = sj * (chi0[j] + A.lp.c_af * dg[j]) / (1.0 + A.lp.d_af * fabs(dg[j]));
+    A.dg[at] = sj * dg[j];
   }
   if (A.iters && h == 0) {
     A.iters[v] = iters;
@@ -1072,13 +1177,26 @@ tangent_kernel(TangentArgs<TK> A) {
   }
 }
 
-// four lanes per voxel at two waves per SIMD: the fastest of the measured
-// shapes (2 or 4 lanes, 1 or 2 waves per SIMD) at 64^3
+// Three wavefronts per SIMD at 72 bytes of scratch beat two without once the
+// grid fills them (64^3 242 against 255 us, four with 208 bytes 318 us); up
+// to 32^3, whose wavefronts are two per SIMD in all, two without scratch are
+// faster (32^3 55 against 57.5 us, 16^3 34 against 39 us), in blocks of one
+// wavefront so that the smallest grids reach every CU.
+template <bool INTN>
+static void return_map_sized(const ConstArgs& a, hipStream_t s) {
+  if (a.N <= 32768)
+    launch(return_map_kernel<INTN, 64, 2>, dim3((unsigned)((4 * a.N + 63) / 64)),
+           dim3(64), 0, s, a);
+  else
+    launch(return_map_kernel<INTN, 256, 3>,
+           dim3((unsigned)((4 * a.N + 255) / 256)), dim3(256), 0, s, a);
+}
+
 void launch_return_map(const ConstArgs& a, hipStream_t s) {
-  constexpr int kLanes = 4, kBlk = 256;
-  const int64_t grid = (kLanes * a.N + kBlk - 1) / kBlk;
-  launch(return_map_group_kernel<kLanes, 2>, dim3((unsigned)grid), dim3(kBlk),
-         0, s, a);
+  if (a.lp.nint > 0)
+    return_map_sized<true>(a, s);
+  else
+    return_map_sized<false>(a, s);
 }
 
 void launch_rm_count(const int32_t* iters, const int32_t* evals, int64_t N,
