@@ -49,7 +49,7 @@ FP64_PEAK_TFLOPS = 78.6
 # path (each datum read or written once; the packed half spectrum of nine
 # components is 9 x n^3/2 complex = 36 B per voxel)
 PASS_BYTES_F32 = {
-    "matvec_kp": 4 * (81 + 9 + 9),                  # K, p in; K:p out
+    "matvec_kp": 4 * (51 + 9 + 9),                  # tangent, p in; K:p out
     "matvec_pass_a": 4 * 9 + 36,                    # K:p in, half spectrum out
     "matvec_pass_b": 36 + 2 * 12,                   # spectrum in, rho in and out
     "matvec_pass_c": 24 + 4 * 9,                    # six planes in, p out
@@ -59,7 +59,7 @@ PASS_BYTES_F32 = {
 # the same with K:p folded into pass A (fused schedule): no K:p round trip
 PASS_BYTES_F32_FUSED = dict(
     {k: v for k, v in PASS_BYTES_F32.items() if k != "matvec_kp"},
-    matvec_pass_a=4 * (81 + 9) + 36)
+    matvec_pass_a=4 * (51 + 9) + 36)
 
 
 def pass_bytes(fused):

@@ -5,6 +5,7 @@
 // leaves the work of the following iterations.
 #include "batch.hpp"
 #include "cg_scalars.hpp"
+#include "kp_apply.hpp"
 #include "newton.hpp"
 
 #include <algorithm>
@@ -82,11 +83,12 @@ BatchEngine::BatchEngine(const rve_config& cfg, int count, const int32_t* n)
   dg_t_ = (double*)alloc(f12);
   r64_ = (double*)alloc(f9);
   dFt_ = (double*)alloc(f9);
-  K_ = alloc(81 * Nt_ * tsz);
+  K_ = alloc(kKComp * Nt_ * tsz);
   rho_ = alloc(3 * Nt_ * tsz);
   pi_ = alloc(3 * Nt_ * tsz);
   xi_ = alloc(3 * Nt_ * tsz);
   p_ = alloc(9 * Nt_ * tsz);
+  y_ = alloc(9 * Nt_ * tsz);
   spec_ = alloc(St_ * 2 * tsz);
   spec64_ = fp64_ ? spec_ : alloc(St_ * 2 * sizeof(double));
   phase_ = (int32_t*)alloc(Nt_ * sizeof(int32_t));
@@ -122,12 +124,11 @@ BatchEngine::BatchEngine(const rve_config& cfg, int count, const int32_t* n)
   for (int b = 0; b < B_; ++b) psn += 9 * n_[b];
   psum_ = (double*)alloc(psn * sizeof(double));
   psq_ = (double*)alloc(psn * sizeof(double));
-  // partials per RVE, room for any schedule: pass A's p.(K:p) (one component
-  // per slab block), the CG pencils' (four kz columns per block), those of
-  // the FP64 residual
+  // partials per RVE, room for any schedule: p.(K:p), the CG pencils' (four
+  // kz columns per block), those of the FP64 residual
   int64_t pp = 0;
   for (int b = 0; b < B_; ++b)
-    pp += 9 * n_[b] + 3 * cg_pencil_blocks(n_[b], 4) + 3 * residual_blocks(n_[b]);
+    pp += n_[b] * n_[b] * n_[b] / kBlock + 3 * cg_pencil_blocks(n_[b], 4) + 3 * residual_blocks(n_[b]);
   partials_ = (double*)alloc(pp * sizeof(double));
   items32_ = alloc(B_ * sizeof(SpecItem<float>));
   items64_ = alloc(B_ * sizeof(SpecItem<double>));
@@ -139,10 +140,10 @@ BatchEngine::BatchEngine(const rve_config& cfg, int count, const int32_t* n)
   RVE_HIP(hipMemcpyAsync(vrve_, vr.data(), Nt_, hipMemcpyHostToDevice, st_));
   // the timed iterations of the schedule tuner read these before the solver
   // writes them: start from zeros
-  RVE_HIP(hipMemsetAsync(K_, 0, 81 * Nt_ * tsz, st_));
+  RVE_HIP(hipMemsetAsync(K_, 0, kKComp * Nt_ * tsz, st_));
   for (void* f : {rho_, pi_, xi_})
     RVE_HIP(hipMemsetAsync(f, 0, 3 * Nt_ * tsz, st_));
-  RVE_HIP(hipMemsetAsync(p_, 0, 9 * Nt_ * tsz, st_));
+  for (void* f : {p_, y_}) RVE_HIP(hipMemsetAsync(f, 0, 9 * Nt_ * tsz, st_));
   RVE_HIP(hipStreamSynchronize(st_));
 
   if (cfg_.use_graph) {
@@ -185,7 +186,7 @@ void BatchEngine::build_tables() {
   grid32_ = grid64_ = BatchGrid{};
   cpbs32_ = cpbs64_ = 0;
   for (int b = 0; b < B_; ++b) {
-    const int nb = n_[b];
+    const int nb = n_[b], nvb = nb * nb * nb / kBlock;
     auto fill = [&](auto& it, BatchGrid& g, bool dbl, int& cpbs) {
       using T = std::remove_reference_t<decltype(it.tw[0].x)>;
       int cpb = 0, tt = 0;
@@ -214,8 +215,9 @@ void BatchEngine::build_tables() {
       it.tw = (const cplx<T>*)(dbl ? tw64_ : tw32_) + twoff_[b];
       it.vt = (const T*)(dbl ? vt64_ : vt32_) + vtoff_[b];
       it.pkp = partials_ + pp;
-      it.prr = it.pkp + 9 * nb;
+      it.prr = it.pkp + nvb;
       g.A += slab_blocks(nb, dbl, cpb);
+      g.V = (int)(Nt_ / kBlock);
       g.B += it.npen;
       size_t s1, s2;
       batch_lds<T>(nb, cpb, tt, s1, s2);
@@ -228,10 +230,10 @@ void BatchEngine::build_tables() {
     // from them before the CG passes write theirs, in FP64 mode in the same
     // place
     if (!fp64_)
-      it64[b].prr = partials_ + pp + 9 * nb + 3 * cg_pencil_blocks(nb, 4);
+      it64[b].prr = partials_ + pp + nvb + 3 * cg_pencil_blocks(nb, 4);
     red[b] = RedItem{it64[b].prr, it64[b].npen, it64[b].psum, it64[b].psq, nb,
                      1.0 / ((double)nb * nb * nb)};
-    pp += 9 * nb + 3 * cg_pencil_blocks(nb, 4) + 3 * residual_blocks(nb);
+    pp += nvb + 3 * cg_pencil_blocks(nb, 4) + 3 * residual_blocks(nb);
     pso += 9 * nb;
   }
   if (grid32_.ldsA > 65536 || grid32_.ldsB > 65536)
@@ -566,8 +568,9 @@ BatchSpec<T> BatchEngine::spec(bool cg, int parity) const {
   b.prec = prec_;
   if (cg) {
     b.K = (const T*)K_;
-    b.field = (const T*)p_;
     b.p = (T*)p_;
+    b.y = (T*)y_;
+    b.vrve = vrve_;
     b.spec = (cplx<T>*)spec_;
     b.rho = (cplx<T>*)rho_;
     b.pi = (cplx<T>*)pi_;
@@ -808,6 +811,7 @@ void BatchEngine::newton_solve_device(int it, const LawParams& lp) {
   c.nitems = B_;
   c.blocksA = g.A;
   c.blocksB = g.B;
+  c.blocksV = g.V;
   c.max_iters = cfg_.cg_max_iter + 1;
   c.bar = bar_;
   c.err = (int*)(bar_ + kBatchBarWords);

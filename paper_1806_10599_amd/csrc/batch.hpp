@@ -78,7 +78,7 @@ class BatchEngine {
   // arena fields
   double *Fprev_, *Pc_, *Fpi_c_, *chi_c_, *dg_c_, *pcyc_, *pcyc_lit_, *wcyc_;
   double *F_, *P_, *Fpi_t_, *chi_t_, *dg_t_, *r64_, *dFt_;
-  void *K_, *p_, *spec_, *spec64_;
+  void *K_, *p_, *y_, *spec_, *spec64_;
   void *rho_, *pi_, *xi_;   // CG vectors in Fourier space (pencil passes)
   double prec_ = 0.0;       // the preconditioner's (lambda + mu)/(lambda + 2 mu)
   int32_t* phase_;

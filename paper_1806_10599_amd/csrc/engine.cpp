@@ -1,5 +1,6 @@
 // RVE engine: buffers and the increment algorithm (see engine.hpp).
 #include "engine.hpp"
+#include "kp_apply.hpp"
 #include "newton.hpp"
 
 #include <algorithm>
@@ -90,7 +91,7 @@ Engine::Engine(const rve_config& cfg) : cfg_(cfg) {
   r64_ = (double*)alloc(f9);
   dFt_prev_ = (double*)alloc(f9);
   dFt_pp_ = (double*)alloc(f9);
-  K_ = alloc(81 * N_ * tsz);
+  K_ = alloc(kKComp * N_ * tsz);
   rho_ = alloc(3 * N_ * tsz);
   pi_ = alloc(3 * N_ * tsz);
   xi_ = alloc(3 * N_ * tsz);
@@ -111,7 +112,7 @@ Engine::Engine(const rve_config& cfg) : cfg_(cfg) {
   RVE_HIP(hipMemsetAsync(sc_, 0, sizeof(Scalars), st_));
   // the timed iterations of the schedule tuner may read these before the
   // solver writes them: start from zeros
-  RVE_HIP(hipMemsetAsync(K_, 0, 81 * N_ * tsz, st_));
+  RVE_HIP(hipMemsetAsync(K_, 0, kKComp * N_ * tsz, st_));
   for (void* f : {rho_, pi_, xi_})
     RVE_HIP(hipMemsetAsync(f, 0, 3 * N_ * tsz, st_));
   for (void* f : {p_, Kp_}) RVE_HIP(hipMemsetAsync(f, 0, 9 * N_ * tsz, st_));
@@ -300,6 +301,7 @@ void Engine::set_user_material(rve_umat_fn fn, void* user, int32_t nstatev,
   if (!fn) throw Error(RVE_EINVAL, "null user material");
   if (nstatev < 0 || nstatev > 1024) throw Error(RVE_EINVAL, "nstatev out of [0, 1024]");
   if (nstatev > 0 && !statev0) throw Error(RVE_EINVAL, "null initial state variables");
+  full_tangent();
   if (!usig_) {
     usig_ = (double*)alloc(6 * N_ * sizeof(double));
     udds_ = (double*)alloc(36 * N_ * sizeof(double));
@@ -441,7 +443,7 @@ void Engine::tangent(double dt) {
   a.N = N_;
   if (umat_fn_) {
     // user material: K from the last evaluation's sigma and tangent (Eq. A.16)
-    launch_umat_tangent<T>(F_, usig_, udds_, N_, (T*)K_, st_);
+    launch_umat_tangent<T>(F_, usig_, udds_, N_, (T*)Kfull_, st_);
     return;
   }
   timer_.begin(5, st_);
@@ -454,7 +456,8 @@ CgLaunch<T> Engine::cg_launch(int parity, int cpb, int tt, int fused) const {
   const bool dbl = sizeof(T) == sizeof(double);
   const int npen = cg_pencil_blocks(n_, tt);
   CgLaunch<T> L;
-  L.K = (const T*)K_;
+  L.kfull = umat_fn_ != nullptr;
+  L.K = (const T*)(L.kfull ? Kfull_ : K_);
   L.p = (T*)p_;
   L.y = (const T*)Kp_;
   L.F = F_;
@@ -491,7 +494,7 @@ void Engine::cg_iteration_steps(int parity, Run&& run) {
   run(2, [&] { launch_cg<T>(n_, L, kPassP, st_); });
   if (!sched_fused_)
     run(7, [&] {
-      launch_kp<T>(L.K, L.p, (T*)Kp_, sc_, N_, partial_kp_, st_);
+      launch_kp<T>(L.K, L.kfull, L.p, (T*)Kp_, sc_, N_, partial_kp_, st_);
     });
   run(0, [&] { launch_cg<T>(n_, L, kPassA, st_); });
   run(1, [&] { launch_cg<T>(n_, L, kPassRes, st_); });
@@ -595,7 +598,7 @@ void Engine::autotune() {
       auto matvec = [&] {
         launch_cg<T>(n_, L, kPassDir | kPassP, st_);
         if (!cand[c].fused)
-          launch_kp<T>(L.K, L.p, (T*)Kp_, sc_, N_, partial_kp_, st_);
+          launch_kp<T>(L.K, L.kfull, L.p, (T*)Kp_, sc_, N_, partial_kp_, st_);
         launch_cg<T>(n_, L, kPassA | kPassRes, st_);
       };
       matvec();  // untimed first launch
@@ -637,9 +640,16 @@ void Engine::drop_graph() {
   timer_.recycle(graph_pairs_);
 }
 
+// room for dP/dF (a user material's tangent, the test hook's)
+void Engine::full_tangent() {
+  if (Kfull_) return;
+  const size_t bytes = kKFull * N_ * (fp64_ ? sizeof(double) : sizeof(float));
+  Kfull_ = alloc(bytes);
+  RVE_HIP(hipMemsetAsync(Kfull_, 0, bytes, st_));   // the tuner may read it
+}
+
 void Engine::set_preconditioner(double prec) {
-  if (prec == prec_) return;
-  drop_graph();
+  drop_graph();   // it also holds the tangent's form
   prec_ = prec;
 }
 
@@ -1249,9 +1259,16 @@ void Engine::debug_constitutive(const double* F, double dt, double* P, double* K
   a.order = order_;
   a.N = N_;
   launch_return_map(a, st_);
-  // the tangent the solver itself forms (FP32 in mixed mode)
+  // the tangent the solver itself forms (FP32 in mixed mode), as dP/dF
   if (K) {
-    if (fp64_) tangent<double>(dt); else tangent<float>(dt);
+    full_tangent();
+    if (fp64_) {
+      tangent<double>(dt);
+      launch_expand_tangent((const double*)K_, (double*)Kfull_, N_, st_);
+    } else {
+      tangent<float>(dt);
+      launch_expand_tangent((const float*)K_, (float*)Kfull_, N_, st_);
+    }
   }
   RVE_HIP(hipGetLastError());
   Scalars h;
@@ -1261,11 +1278,11 @@ void Engine::debug_constitutive(const double* F, double dt, double* P, double* K
     RVE_HIP(hipMemcpyAsync(P, P_, 9 * N_ * sizeof(double), hipMemcpyDeviceToHost, st_));
   std::vector<float> K32;
   if (K && fp64_)
-    RVE_HIP(hipMemcpyAsync(K, K_, 81 * N_ * sizeof(double),
+    RVE_HIP(hipMemcpyAsync(K, Kfull_, 81 * N_ * sizeof(double),
                            hipMemcpyDeviceToHost, st_));
   if (K && !fp64_) {
     K32.resize(81 * N_);
-    RVE_HIP(hipMemcpyAsync(K32.data(), K_, 81 * N_ * sizeof(float),
+    RVE_HIP(hipMemcpyAsync(K32.data(), Kfull_, 81 * N_ * sizeof(float),
                            hipMemcpyDeviceToHost, st_));
   }
   if (dg)
@@ -1403,7 +1420,7 @@ void Engine::bench_kernels(int reps, double* ms, int count) {
     timed(3, [&] { launch_cg<T>(n_, L, kPassDir, st_); });
     timed(2, [&] { launch_cg<T>(n_, L, kPassP, st_); });
     if (!sched_fused_)
-      timed(7, [&] { launch_kp<T>(L.K, L.p, (T*)Kp_, sc_, N_, partial_kp_, st_); });
+      timed(7, [&] { launch_kp<T>(L.K, L.kfull, L.p, (T*)Kp_, sc_, N_, partial_kp_, st_); });
     timed(0, [&] { launch_cg<T>(n_, L, kPassA, st_); });
     timed(1, [&] { launch_cg<T>(n_, L, kPassRes, st_); });
   };

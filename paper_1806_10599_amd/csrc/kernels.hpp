@@ -15,7 +15,8 @@ enum { DST_NORM = 0, DST_P = 1, DST_ADDF = 2 };
 template <typename T>
 struct SlabFwdArgs {
   const T* field;      // [9][N^3] (SRC_KROW: the direction)
-  const T* K;          // SRC_KROW: [81][N^3]
+  const T* K;          // SRC_KROW: the tangent, 81 components with kfull,
+  bool kfull;          // else its stored form
   cplx<T>* spec;       // [9][N][N][N/2]
   const cplx<T>* tw;   // exp(-2 pi i m / N)
   double* psum;        // optional [9][N] per-slab sums
@@ -102,6 +103,7 @@ enum { kPassDir = 1, kPassP = 2, kPassA = 4, kPassRes = 8, kPassFinal = 16 };
 template <typename T>
 struct CgLaunch {
   const T* K = nullptr;
+  bool kfull = false;          // K is dP/dF, 81 components (user materials)
   T* p = nullptr;              // direction [9][N^3]
   const T* y = nullptr;        // K : p [9][N^3]
   double* F = nullptr;         // kPassFinal
@@ -169,7 +171,7 @@ struct SpecItem {
   const cplx<T>* tw;
   const T* vt;
   Scalars* sc;          // this RVE's scalars
-  double* pkp;          // pass A's p.(K:p) partials [9][n]
+  double* pkp;          // p.(K:p) partials (kp_blocks)
   double* prr;          // pencil partials: r.r, r.z, ||G(P)||^2 (3 npen)
   double* psum;         // residual pass sums [9][n]
   double* psq;
@@ -182,9 +184,11 @@ struct BatchSpec {
   int cpbs = 3;         // slab schedules among the items (bit 0: cpb 1,
                         // bit 1: cpb 3)
   int64_t cs;           // voxels in the arena (component stride)
-  const T* field;       // SRC_FIELD input, or the CG direction p
-  const T* K;
-  T* p;
+  const T* field;       // input of the forward slab pass (CG: K:p)
+  const T* K;           // stored tangent
+  T* p;                 // CG direction and K:p
+  T* y;
+  const uint8_t* vrve;  // RVE of each voxel
   cplx<T>* spec;
   cplx<T>* rho;         // CG vectors
   cplx<T>* pi;
@@ -196,6 +200,7 @@ struct BatchSpec {
 // blocks of the slab and CG pencil grids and their dynamic LDS
 struct BatchGrid {
   int A = 0, B = 0;
+  int V = 0;            // voxels / kBlock
   size_t ldsA = 0, ldsB = 0;
 };
 
@@ -279,7 +284,7 @@ struct TangentArgs {
   const double* dg;      // converged trial slips
   const int32_t* phase;
   const double* table;
-  TK* K;                 // [81][N]
+  TK* K;                 // [51][N]: D, S2, F (kp_apply.hpp)
   LawParams lp;
   int64_t N;
   const uint8_t* vrve;
@@ -307,6 +312,9 @@ void launch_rm_count(const int32_t* iters, const int32_t* evals, int64_t N,
                      unsigned long long* stats, hipStream_t s);
 template <typename TK>
 void launch_tangent(const TangentArgs<TK>& a, hipStream_t s);
+// dP/dF, 81 components, from the stored tangent
+template <typename TK>
+void launch_expand_tangent(const TK* K, TK* out, int64_t N, hipStream_t s);
 
 // ------------------------------------------------------------- solver ops
 struct CommitArgs {
@@ -325,10 +333,10 @@ struct CommitArgs {
 void launch_predict(double* F, const double* Fprev, const double dFbar[9],
                     int64_t N, hipStream_t s);
 // y = K : p and the per-block p . y (kp_blocks entries); returns at once on
-// a stopped run
+// a stopped run.  full: K is dP/dF, 81 components, else the stored tangent
 template <typename T>
-void launch_kp(const T* K, const T* p, T* y, const Scalars* sc, int64_t N,
-               double* pkp, hipStream_t s);
+void launch_kp(const T* K, bool full, const T* p, T* y, const Scalars* sc,
+               int64_t N, double* pkp, hipStream_t s);
 int kp_blocks(int64_t N);  // one voxel per thread
 // the CG decision after the last update of a chunk from the partials of the
 // last pencil pass; parity: that of the iteration that would follow; pub
@@ -371,7 +379,7 @@ struct BatchCG {
   BatchSpec<T> even, odd;
   Scalars* scs;
   int nitems;
-  int blocksA, blocksB;
+  int blocksA, blocksB, blocksV;
   int max_iters;            // iterations of this launch at most
   unsigned* bar;            // barrier state (kBatchBarWords words, zero at
                             // start but for the generation)

@@ -29,10 +29,7 @@
 //
 // Particles: isotropic St-Venant-Kirchhoff, P = F S, S = lam tr(E) I + 2 mu E.
 #include "kernels.hpp"
-
-#ifndef RVE_TAN_MINB32
-#define RVE_TAN_MINB32 2
-#endif
+#include "kp_apply.hpp"
 
 namespace rve {
 
@@ -112,28 +109,6 @@ __device__ __forceinline__ void mm3(const double* A, const double* B,
                      A[3 * i + 2] * B[6 + j];
 }
 
-// S (Voigt) = C : E (Voigt), C_IJ from the table
-__device__ __forceinline__ void cmul6(const double* __restrict__ Cv,
-                                      const double* E, double* S) {
-  double We[6];
-#pragma unroll
-  for (int J = 0; J < 6; ++J) We[J] = VW[J] * E[J];
-#pragma unroll
-  for (int I = 0; I < 6; ++I) {
-    double acc = 0.0;
-#pragma unroll
-    for (int J = 0; J < 6; ++J) acc += Cv[6 * I + J] * We[J];
-    S[I] = acc;
-  }
-}
-
-struct CpEval {
-  double Fe[9];
-  double S[6];
-  double chi[12];
-  double h[12];   // d asinh(|x|^n sign x) / dx, x = (tau - chi)/g
-};
-
 // d/dx asinh(|x|^n sign x) = n y / (|x| sqrt(1 + y^2)), y = |x|^n (FP64;
 // the same branches as asinh_pow, without the function value)
 __device__ __forceinline__ double flow_slope(double x, double n, int ni) {
@@ -145,250 +120,6 @@ __device__ __forceinline__ double flow_slope(double x, double n, int ni) {
   double val, der;
   asinh_pow(x, n, ni, val, der);
   return der;
-}
-
-// State at the converged slips dg for the tangent (elastic deformation,
-// stress, back stresses, flow slopes).  Fes = F Fp^-1_0.
-__device__ __forceinline__ void cp_eval(const double* Fes,
-                                        const double* chi0, const double* dg,
-                                        const double* __restrict__ tb,
-                                        const LawParams& lp, double a,
-                                        CpEval& e) {
-  tb = opaque(tb);
-#pragma unroll
-  for (int i = 0; i < 9; ++i) e.Fe[i] = Fes[i];
-#pragma unroll
-  for (int al = 0; al < 12; ++al) {
-    const double s0 = tb[kTabS + 3 * al], s1 = tb[kTabS + 3 * al + 1],
-                 s2 = tb[kTabS + 3 * al + 2];
-    const double m0 = tb[kTabM + 3 * al], m1 = tb[kTabM + 3 * al + 1],
-                 m2 = tb[kTabM + 3 * al + 2];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const double u = dg[al] * (Fes[3 * i] * s0 + Fes[3 * i + 1] * s1 +
-                                 Fes[3 * i + 2] * s2);
-      e.Fe[3 * i] -= u * m0;
-      e.Fe[3 * i + 1] -= u * m1;
-      e.Fe[3 * i + 2] -= u * m2;
-    }
-  }
-  double C[9];
-#pragma unroll
-  for (int p = 0; p < 3; ++p)
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-      C[3 * p + q] = e.Fe[p] * e.Fe[q] + e.Fe[3 + p] * e.Fe[3 + q] +
-                     e.Fe[6 + p] * e.Fe[6 + q];
-  const double E[6] = {0.5 * (C[0] - 1.0), 0.5 * (C[4] - 1.0),
-                       0.5 * (C[8] - 1.0), 0.5 * C[5],
-                       0.5 * C[2],         0.5 * C[1]};
-  cmul6(tb + kTabC, E, e.S);
-  const double* S = e.S;
-#pragma unroll
-  for (int al = 0; al < 12; ++al) {
-    const double s0 = tb[kTabS + 3 * al], s1 = tb[kTabS + 3 * al + 1],
-                 s2 = tb[kTabS + 3 * al + 2];
-    const double m0 = tb[kTabM + 3 * al], m1 = tb[kTabM + 3 * al + 1],
-                 m2 = tb[kTabM + 3 * al + 2];
-    const double Sm0 = S[0] * m0 + S[5] * m1 + S[4] * m2;
-    const double Sm1 = S[5] * m0 + S[1] * m1 + S[3] * m2;
-    const double Sm2 = S[4] * m0 + S[3] * m1 + S[2] * m2;
-    const double tau = s0 * Sm0 + s1 * Sm1 + s2 * Sm2;
-    const double chi = (chi0[al] + lp.c_af * dg[al]) / (1.0 + lp.d_af * fabs(dg[al]));
-    const double x = (tau - chi) * lp.inv_g;
-    e.chi[al] = chi;
-    e.h[al] = flow_slope(x, lp.nexp, lp.nint);
-  }
-}
-
-// Q = Fe^T Fes
-__device__ __forceinline__ void make_Q(const double* Fe, const double* Fes,
-                                       double* Q) {
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-      Q[3 * i + j] = Fe[i] * Fes[j] + Fe[3 + i] * Fes[3 + j] +
-                     Fe[6 + i] * Fes[6 + j];
-}
-
-// V_a = sym((Q s_a) (x) m_a) in Voigt order, in the precision T of Q
-template <typename T>
-__device__ __forceinline__ void make_V(const T* Q, const double* __restrict__ tb,
-                                       int al, T* V) {
-  const T s0 = (T)tb[kTabS + 3 * al], s1 = (T)tb[kTabS + 3 * al + 1],
-          s2 = (T)tb[kTabS + 3 * al + 2];
-  const T m[3] = {(T)tb[kTabM + 3 * al], (T)tb[kTabM + 3 * al + 1],
-                  (T)tb[kTabM + 3 * al + 2]};
-  T qs[3];
-#pragma unroll
-  for (int i = 0; i < 3; ++i) qs[i] = Q[3 * i] * s0 + Q[3 * i + 1] * s1 + Q[3 * i + 2] * s2;
-  V[0] = qs[0] * m[0];
-  V[1] = qs[1] * m[1];
-  V[2] = qs[2] * m[2];
-  V[3] = T(0.5) * (qs[1] * m[2] + qs[2] * m[1]);
-  V[4] = T(0.5) * (qs[0] * m[2] + qs[2] * m[0]);
-  V[5] = T(0.5) * (qs[0] * m[1] + qs[1] * m[0]);
-}
-
-// Gaussian elimination of the 6x6 capacitance matrix with partial pivoting
-// by compare-and-swap; the swap decisions are kept for later right-hand sides.
-template <typename T>
-struct LU6T {
-  T M[36];
-  T ip[6];   // reciprocals of the pivots
-  uint32_t swaps;
-};
-using LU6 = LU6T<double>;
-
-template <typename T>
-__device__ __forceinline__ void lu6_factor(LU6T<T>& L) {
-  uint32_t sw = 0;
-  int bit = 0;
-#pragma unroll
-  for (int k = 0; k < 6; ++k) {
-#pragma unroll
-    for (int r = k + 1; r < 6; ++r) {
-      const bool s = fabs(L.M[6 * r + k]) > fabs(L.M[6 * k + k]);
-      if (s) {
-        // columns < k hold the multipliers of earlier steps; they stay with
-        // the step that made them (the solve applies swap k, then step k)
-#pragma unroll
-        for (int j = k; j < 6; ++j) {
-          const T t = L.M[6 * k + j];
-          L.M[6 * k + j] = L.M[6 * r + j];
-          L.M[6 * r + j] = t;
-        }
-      }
-      sw |= (s ? 1u : 0u) << bit;
-      ++bit;
-    }
-    const T inv = T(1) / L.M[6 * k + k];
-    L.ip[k] = inv;
-#pragma unroll
-    for (int r = k + 1; r < 6; ++r) {
-      const T f = L.M[6 * r + k] * inv;
-      L.M[6 * r + k] = f;
-#pragma unroll
-      for (int j = k + 1; j < 6; ++j) L.M[6 * r + j] -= f * L.M[6 * k + j];
-    }
-  }
-  L.swaps = sw;
-}
-
-template <typename T>
-__device__ __forceinline__ void lu6_solve(const LU6T<T>& L, T* z) {
-  int bit = 0;
-#pragma unroll
-  for (int k = 0; k < 6; ++k) {
-#pragma unroll
-    for (int r = k + 1; r < 6; ++r) {
-      if ((L.swaps >> bit) & 1u) {
-        const T t = z[k];
-        z[k] = z[r];
-        z[r] = t;
-      }
-      ++bit;
-    }
-#pragma unroll
-    for (int r = k + 1; r < 6; ++r) z[r] -= L.M[6 * r + k] * z[k];
-  }
-#pragma unroll
-  for (int k = 5; k >= 0; --k) {
-    T acc = z[k];
-#pragma unroll
-    for (int j = k + 1; j < 6; ++j) acc -= L.M[6 * k + j] * z[j];
-    z[k] = acc * L.ip[k];
-  }
-}
-
-// Diagonal D, factor h and the factored capacitance matrix at the slips dg,
-// in the precision T (the state e comes from an FP64 evaluation).
-template <typename T>
-__device__ __forceinline__ void cp_jacobian(const CpEval& e, const double* Fes,
-                                            const double* dg,
-                                            const double* __restrict__ tb,
-                                            const LawParams& lp, double a,
-                                            T* D, T* hg, T* Q, LU6T<T>& L) {
-  tb = opaque(tb);
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-      Q[3 * i + j] = (T)(e.Fe[i] * Fes[j] + e.Fe[3 + i] * Fes[3 + j] +
-                         e.Fe[6 + i] * Fes[6 + j]);
-#pragma unroll
-  for (int i = 0; i < 36; ++i) L.M[i] = (i % 7 == 0) ? T(1) : T(0);
-#pragma unroll
-  for (int al = 0; al < 12; ++al) {
-    const double ad = fabs(dg[al]);
-    const double dchi = (lp.c_af - lp.d_af * sgn(dg[al]) * e.chi[al]) / (1.0 + lp.d_af * ad);
-    const double hgd = e.h[al] * lp.inv_g;
-    hg[al] = (T)hgd;
-    // D holds the reciprocal of the diagonal of the local Jacobian
-    D[al] = (T)(1.0 / (1.0 / sqrt(a * a + dg[al] * dg[al]) + hgd * dchi));
-    T V[6];
-    make_V(Q, tb, al, V);
-    const T f = hg[al] * D[al];
-    // row factor of the rank-one term, formed once per slip
-    T w[6];
-#pragma unroll
-    for (int J = 0; J < 6; ++J) w[J] = f * (T)(VW[J] * tb[kTabN + 6 * al + J]);
-#pragma unroll
-    for (int I = 0; I < 6; ++I)
-#pragma unroll
-      for (int J = 0; J < 6; ++J) L.M[6 * I + J] += V[I] * w[J];
-  }
-  lu6_factor(L);
-}
-
-// out = J^-1 rhs with J = diag(D) + U W^T, U_a = hg_a w N_a, W_a = V_a
-// (iD = 1/D from cp_jacobian)
-template <typename T>
-__device__ __forceinline__ void cp_jsolve(const T* rhs, const T* iD,
-                                          const T* hg, const T* Q,
-                                          const double* __restrict__ tb,
-                                          const LU6T<T>& L, T* out) {
-  tb = opaque(tb);
-  T z[6] = {0, 0, 0, 0, 0, 0};
-#pragma unroll
-  for (int al = 0; al < 12; ++al) {
-    out[al] = rhs[al] * iD[al];
-    T V[6];
-    make_V(Q, tb, al, V);
-#pragma unroll
-    for (int I = 0; I < 6; ++I) z[I] += V[I] * out[al];
-  }
-  lu6_solve(L, z);
-#pragma unroll
-  for (int al = 0; al < 12; ++al) {
-    T u = 0;
-#pragma unroll
-    for (int J = 0; J < 6; ++J) u += (T)(VW[J] * tb[kTabN + 6 * al + J]) * z[J];
-    out[al] -= hg[al] * u * iD[al];
-  }
-}
-
-// C = A B (3x3, row-major) and S = C : E (Voigt, C_IJ from the table) in T
-template <typename T>
-__device__ __forceinline__ void mm3t(const T* A, const T* B, T* C) {
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-      C[3 * i + j] = A[3 * i] * B[j] + A[3 * i + 1] * B[3 + j] +
-                     A[3 * i + 2] * B[6 + j];
-}
-template <typename T>
-__device__ __forceinline__ void cmul6t(const double* __restrict__ Cv,
-                                       const T* E, T* S) {
-#pragma unroll
-  for (int I = 0; I < 6; ++I) {
-    T acc = 0;
-#pragma unroll
-    for (int J = 0; J < 6; ++J) acc += (T)(Cv[6 * I + J] * VW[J]) * E[J];
-    S[I] = acc;
-  }
 }
 
 __device__ __forceinline__ void load9(const double* __restrict__ p, int64_t v,
@@ -664,6 +395,11 @@ __device__ __forceinline__ void pr_eval(const double* Gs, const double* es,
 __device__ constexpr float kSchmid5[3][5] = {{2.0f, 0.0f, -1.0f, 1.0f, 0.0f},
                                              {1.0f, 1.7320508075688773f, -1.0f, 0.0f, 1.0f},
                                              {-1.0f, 1.7320508075688773f, 0.0f, -1.0f, 1.0f}};
+
+__device__ constexpr double kSchmid5d[3][5] = {
+    {2.0, 0.0, -1.0, 1.0, 0.0},
+    {1.0, 1.73205080756887729353, -1.0, 0.0, 1.0},
+    {-1.0, 1.73205080756887729353, 0.0, -1.0, 1.0}};
 
 // Newton step of the lane's slips: step = -J^-1 R.  J = diag(1/D) + h N V^T
 // with V_a = sym((Q s_a) (x) m_a), Q = G^T Gs, and N_a = C : sym(S0_a); in
@@ -993,187 +729,285 @@ __global__ __launch_bounds__(256) void rm_count_kernel(
   if (threadIdx.x < 4) atomicAdd(&stats[threadIdx.x], red[threadIdx.x][0]);
 }
 
-// FP32 linear algebra (mixed mode): two waves per SIMD with 448 B of scratch
-// per lane beat one wave without (0.336 against 0.382 ms at 64^3)
+// ---- consistent tangent ----------------------------------------------------
+// P = F S2(C), C = F^T F, with the second Piola stress S2 = Fp^-1 S Fp^-T, so
+//   K_ijkl = d_ik (S2)_lj + F_im D_mj,nl F_kn,   D = 2 dS2/dC,
+// and K is stored as D, S2 and F (kKComp entries per voxel): six strain
+// directions instead of nine gradients here, and 51 instead of 81 numbers
+// for every K:p (kp_apply).  In the lattice frame, A = Fp^-1 R:
+//   dS = Y^-1 (A^T dE A),   Y = C^-1 + sum_a f_a V_a (x) S0_a,
+//   dg_a = f_a S0_a : dS,   dS2 = A dS A^T - sum_a dg_a 2 sym(y_a (x) u_a),
+// y_a = Fp^-1_0 R s_a, u_a = A S m_a, f_a = (h_a/g) / (1/sqrt(a^2 + dg^2) +
+// (h_a/g) dchi/ddg), V_a = sym((G^T Gs s_a) (x) m_a).  In the orthonormal
+// basis of kSchmid5 completed by the trace, C^-1 is diagonal and S0_a has no
+// trace: Y is a 5x5 block, close to symmetric positive definite (eliminated
+// without pivoting), and one row for the trace, solved by substitution.
+// FP64 up to the stress and the flow slopes, the rest in the precision of K.
+//
+// Bound by its instructions (about 2500 per voxel) and 540 B per voxel in
+// FP32.  64^3: 330 us with nine Woodbury solves per voxel on table entries
+// (448 B of scratch per lane) -> 52 us, 128^3 2430 -> 435 us; three wavefronts
+// per SIMD need 464 B of scratch per lane and take 115 us at 64^3.
+constexpr int kPlaneSign[4][3] = {{1, 1, 1}, {-1, 1, 1}, {1, -1, 1}, {1, 1, -1}};
+constexpr int kPlaneSlip[4][3] = {{0, 1, 2}, {4, 5, 3}, {7, 6, 8}, {9, 10, 11}};
+constexpr int kPlaneFlip[4][3] = {{1, 1, 1}, {-1, -1, 1}, {1, 1, -1}, {1, 1, 1}};
+
 template <typename TK>
-__global__ __launch_bounds__(128, sizeof(TK) == 4 ? RVE_TAN_MINB32 : 1) void
+__device__ __forceinline__ void tangent_voxel(const TangentArgs<TK>& A, int64_t v) {
+  const int64_t N = A.N;
+  const double* __restrict__ tb = A.table + (int64_t)A.phase[v] * kTableStride;
+  double F[9];
+  load9(A.F, v, N, F);
+#pragma unroll
+  for (int c = 0; c < 9; ++c) A.K[(42 + c) * N + v] = TK(F[c]);
+  if (tb[0] != 0.0) {   // isotropic SVK: S2 = lam tr E + 2 mu E
+    const double lam = tb[kTabLam], mu = tb[kTabMu];
+    double C[9];
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+        C[3 * p + q] = F[p] * F[q] + F[3 + p] * F[3 + q] + F[6 + p] * F[6 + q];
+    const double tr = 0.5 * (C[0] + C[4] + C[8] - 3.0);
+    A.K[36 * N + v] = TK(mu * (C[0] - 1.0) + lam * tr);
+    A.K[37 * N + v] = TK(mu * (C[4] - 1.0) + lam * tr);
+    A.K[38 * N + v] = TK(mu * (C[8] - 1.0) + lam * tr);
+    A.K[39 * N + v] = TK(mu * C[5]);
+    A.K[40 * N + v] = TK(mu * C[2]);
+    A.K[41 * N + v] = TK(mu * C[1]);
+#pragma unroll
+    for (int I = 0; I < 6; ++I)
+#pragma unroll
+      for (int J = 0; J < 6; ++J) {
+        double d = (I < 3 && J < 3) ? lam : 0.0;
+        if (I == J) d += I < 3 ? 2.0 * mu : mu;
+        A.K[(6 * I + J) * N + v] = TK(d);
+      }
+    return;
+  }
+  const LawParams& lp = A.lp;
+  const double a = lp.dt * lp.gdot0;
+  // slips in the planes' frames, and the plastic increment 1 - sum dg s (x) m
+  double dg[4][3], Ap[9];
+#pragma unroll
+  for (int i = 0; i < 9; ++i) Ap[i] = (i % 4 == 0) ? 1.0 : 0.0;
+#pragma unroll
+  for (int h = 0; h < 4; ++h) {
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+      dg[h][j] = kPlaneFlip[h][j] * A.dg[kPlaneSlip[h][j] * N + v];
+    const double d[3] = {kInvSqrt6 * (dg[h][0] + dg[h][1]),
+                         kInvSqrt6 * (dg[h][2] - dg[h][0]),
+                         -kInvSqrt6 * (dg[h][1] + dg[h][2])};
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+        Ap[3 * i + j] -= (kPlaneSign[h][i] * kPlaneSign[h][j]) * d[i];
+  }
+  TK Y0[9], Ac[9], Q[9], Fs[9];   // Fp^-1_0 R, Fp^-1 R, G^T Gs, Fp^-1 R S
+  TK S[6];
+  double S64[6];
+  {
+    double Fp0[9], Rm[9], B[9], Gs[9], G[9], A64[9];
+    load9(A.Fpi0, v, N, Fp0);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) Rm[i] = tb[kTabR + i];
+    mm3(Fp0, Rm, B);
+    mm3(F, B, Gs);
+    mm3(B, Ap, A64);
+    mm3(Gs, Ap, G);
+    double E[6];
+    constexpr int vi[6] = {0, 1, 2, 1, 0, 0}, vj[6] = {0, 1, 2, 2, 2, 1};
+#pragma unroll
+    for (int I = 0; I < 6; ++I)
+      E[I] = 0.5 * (G[vi[I]] * G[vj[I]] + G[3 + vi[I]] * G[3 + vj[I]] +
+                    G[6 + vi[I]] * G[6 + vj[I]] - (I < 3 ? 1.0 : 0.0));
+    const double tr = lp.c12 * (E[0] + E[1] + E[2]);
+#pragma unroll
+    for (int I = 0; I < 6; ++I) {
+      S64[I] = I < 3 ? lp.c11m12 * E[I] + tr : 2.0 * lp.c44 * E[I];
+      S[I] = TK(S64[I]);
+    }
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+      Y0[i] = TK(B[i]);
+      Ac[i] = TK(A64[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+        Q[3 * i + j] = TK(G[i]) * TK(Gs[j]) + TK(G[3 + i]) * TK(Gs[3 + j]) +
+                       TK(G[6 + i]) * TK(Gs[6 + j]);
+  }
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    Fs[3 * i] = Ac[3 * i] * S[0] + Ac[3 * i + 1] * S[5] + Ac[3 * i + 2] * S[4];
+    Fs[3 * i + 1] = Ac[3 * i] * S[5] + Ac[3 * i + 1] * S[1] + Ac[3 * i + 2] * S[3];
+    Fs[3 * i + 2] = Ac[3 * i] * S[4] + Ac[3 * i + 1] * S[3] + Ac[3 * i + 2] * S[2];
+  }
+  {
+    auto s2 = [&](int i, int j) {
+      return Fs[3 * i] * Ac[3 * j] + Fs[3 * i + 1] * Ac[3 * j + 1] +
+             Fs[3 * i + 2] * Ac[3 * j + 2];
+    };
+    A.K[36 * N + v] = s2(0, 0);
+    A.K[37 * N + v] = s2(1, 1);
+    A.K[38 * N + v] = s2(2, 2);
+    A.K[39 * N + v] = s2(1, 2);
+    A.K[40 * N + v] = s2(0, 2);
+    A.K[41 * N + v] = s2(0, 1);
+  }
+  // Phi: the basis tensors pushed forward by A (columns), in the order 11,
+  // 22, 33, 23, 13, 12; L starts as Phi and takes the plastic part
+  TK Phi[6][6], L[6][5], Y[25], yt[5];
+  {
+    constexpr int vi[6] = {0, 1, 2, 1, 0, 0}, vj[6] = {0, 1, 2, 2, 2, 1};
+    const TK r2 = TK(0.70710678118654752440), r3 = TK(0.57735026918962576451),
+             r6 = TK(0.40824829046386301637);
+#pragma unroll
+    for (int I = 0; I < 6; ++I) {
+      const TK* p = Ac + 3 * vi[I];
+      const TK* q = Ac + 3 * vj[I];
+      const TK w0 = p[0] * q[0], w1 = p[1] * q[1], w2 = p[2] * q[2];
+      Phi[I][0] = r2 * (w0 - w1);
+      Phi[I][1] = r6 * (w0 + w1 - TK(2) * w2);
+      Phi[I][2] = r2 * (p[1] * q[2] + p[2] * q[1]);
+      Phi[I][3] = r2 * (p[0] * q[2] + p[2] * q[0]);
+      Phi[I][4] = r2 * (p[0] * q[1] + p[1] * q[0]);
+      Phi[I][5] = r3 * (w0 + w1 + w2);
+#pragma unroll
+      for (int k = 0; k < 5; ++k) L[I][k] = Phi[I][k];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 25; ++i) Y[i] = TK(0);
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    Y[6 * i] = TK(i < 2 ? 1.0 / lp.c11m12 : 0.5 / lp.c44);
+    yt[i] = TK(0);
+  }
+#pragma unroll
+  for (int h = 0; h < 4; ++h) {
+    constexpr double k6 = kInvSqrt6;
+    const int g0 = kPlaneSign[h][0], g1 = kPlaneSign[h][1], g2 = kPlaneSign[h][2];
+    const double t0 = S64[0] + (g0 * g1) * S64[5] + (g0 * g2) * S64[4];
+    const double t1 = (g0 * g1) * S64[5] + S64[1] + (g1 * g2) * S64[3];
+    const double t2 = (g0 * g2) * S64[4] + (g1 * g2) * S64[3] + S64[2];
+    const double tau[3] = {k6 * (t0 - t1), k6 * (t0 - t2), k6 * (t1 - t2)};
+    const TK u0 = g0 * Fs[0] + g1 * Fs[1] + g2 * Fs[2];
+    const TK u1 = g0 * Fs[3] + g1 * Fs[4] + g2 * Fs[5];
+    const TK u2 = g0 * Fs[6] + g1 * Fs[7] + g2 * Fs[8];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const double d = dg[h][j], ad = fabs(d);
+      const double chi0 = kPlaneFlip[h][j] * A.chi0[kPlaneSlip[h][j] * N + v];
+      const double iden = 1.0 / (1.0 + lp.d_af * ad);
+      const double chi = (chi0 + lp.c_af * d) * iden;
+      const TK hg = TK(flow_slope((tau[j] - chi) * lp.inv_g, lp.nexp, lp.nint) * lp.inv_g);
+      const TK dchi = TK((lp.c_af - lp.d_af * sgn(d) * chi) * iden);
+      const TK f = hg / (TK(1.0 / sqrt(a * a + d * d)) + hg * dchi);
+      // the system s = (sg_p e_p - sg_m e_m)/sqrt 2
+      constexpr int ps[3] = {0, 0, 1}, ms[3] = {1, 2, 2};
+      const int gp = kPlaneSign[h][ps[j]], gm = kPlaneSign[h][ms[j]];
+      const TK q0 = gp * Q[ps[j]] - gm * Q[ms[j]];
+      const TK q1 = gp * Q[3 + ps[j]] - gm * Q[3 + ms[j]];
+      const TK q2 = gp * Q[6 + ps[j]] - gm * Q[6 + ms[j]];
+      const TK y0 = gp * Y0[ps[j]] - gm * Y0[ms[j]];
+      const TK y1 = gp * Y0[3 + ps[j]] - gm * Y0[3 + ms[j]];
+      const TK y2 = gp * Y0[6 + ps[j]] - gm * Y0[6 + ms[j]];
+      const TK fk = f * TK(k6), f12 = fk * TK(0.28867513459481288225);
+      const TK w0 = g0 * q0, w1 = g1 * q1, w2 = g2 * q2;
+      const TK V[5] = {TK(0.70710678118654752440) * (w0 - w1),
+                       TK(k6) * (w0 + w1 - TK(2) * w2),
+                       TK(0.70710678118654752440) * (g2 * q1 + g1 * q2),
+                       TK(0.70710678118654752440) * (g2 * q0 + g0 * q2),
+                       TK(0.70710678118654752440) * (g1 * q0 + g0 * q1)};
+      const TK Vt = TK(0.57735026918962576451) * (w0 + w1 + w2);
+      const TK Z[6] = {TK(2) * y0 * u0, TK(2) * y1 * u1, TK(2) * y2 * u2,
+                       y1 * u2 + y2 * u1, y0 * u2 + y2 * u0, y0 * u1 + y1 * u0};
+#pragma unroll
+      for (int k = 0; k < 5; ++k) {
+        const double c5 = kSchmid5d[j][k] *
+                          (k == 2 ? g1 * g2 : (k == 3 ? g0 * g2 : (k == 4 ? g0 * g1 : 1)));
+        if (c5 == 0.0) continue;
+        const TK fc = f12 * TK(c5);
+#pragma unroll
+        for (int I = 0; I < 5; ++I) Y[5 * I + k] += V[I] * fc;
+        yt[k] += Vt * fc;
+#pragma unroll
+        for (int I = 0; I < 6; ++I) L[I][k] -= Z[I] * fc;
+      }
+    }
+  }
+  // eliminate Y (pivots' reciprocals on the diagonal)
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    const TK ip = TK(1) / Y[6 * k];
+    Y[6 * k] = ip;
+#pragma unroll
+    for (int r = k + 1; r < 5; ++r) {
+      const TK m = Y[5 * r + k] * ip;
+      Y[5 * r + k] = m;
+#pragma unroll
+      for (int J = k + 1; J < 5; ++J) Y[5 * r + J] -= m * Y[5 * k + J];
+    }
+  }
+  const TK k3 = TK(lp.c11m12 + 3.0 * lp.c12);   // C11 + 2 C12
+#pragma unroll
+  for (int J = 0; J < 6; ++J) {   // strain direction J (engineering shears)
+    TK z[5], zt = Phi[J][5];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+      z[k] = Phi[J][k];
+#pragma unroll
+      for (int r = 0; r < k; ++r) z[k] -= Y[5 * k + r] * z[r];
+    }
+#pragma unroll
+    for (int k = 4; k >= 0; --k) {
+#pragma unroll
+      for (int r = k + 1; r < 5; ++r) z[k] -= Y[5 * k + r] * z[r];
+      z[k] *= Y[6 * k];
+      zt -= yt[k] * z[k];
+    }
+    zt *= k3;
+#pragma unroll
+    for (int I = 0; I < 6; ++I) {
+      TK d = Phi[I][5] * zt;
+#pragma unroll
+      for (int k = 0; k < 5; ++k) d += L[I][k] * z[k];
+      A.K[(6 * I + J) * N + v] = d;
+    }
+  }
+}
+
+template <typename TK>
+__global__ __launch_bounds__(128, sizeof(TK) == 4 ? 2 : 1) void
 tangent_kernel(TangentArgs<TK> A) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= A.N) return;
   const int64_t v = A.order ? (int64_t)A.order[i] : i;
   if (A.vrve && A.scs[A.vrve[v]].inactive) return;
-  const int64_t N = A.N;
-  const double* __restrict__ tb = A.table + (int64_t)A.phase[v] * kTableStride;
-  double F[9];
-  load9(A.F, v, N, F);
-  if (tb[0] != 0.0) {
-    // K_ijkl = d_ik S_lj + lam F_ij F_kl + mu F_il F_kj + mu (F F^T)_ik d_jl
-    const double lam = tb[kTabLam], mu = tb[kTabMu];
-    double C[9], B[9];
+  tangent_voxel(A, v);
+}
+
+// K of the test hook: all 81 components from the stored form
+template <typename TK>
+__global__ __launch_bounds__(256) void expand_tangent_kernel(
+    const TK* __restrict__ K, TK* __restrict__ out, int64_t N) {
+  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (v >= N) return;
+  TK Kv[kKComp];
 #pragma unroll
-    for (int p = 0; p < 3; ++p)
-#pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        C[3 * p + q] = F[p] * F[q] + F[3 + p] * F[3 + q] + F[6 + p] * F[6 + q];
-        B[3 * p + q] = F[3 * p] * F[3 * q] + F[3 * p + 1] * F[3 * q + 1] +
-                       F[3 * p + 2] * F[3 * q + 2];
-      }
-    const double tr = 0.5 * (C[0] + C[4] + C[8] - 3.0);
-    double S[9];
-#pragma unroll
-    for (int i = 0; i < 9; ++i) S[i] = mu * (C[i] - ((i % 4 == 0) ? 1.0 : 0.0));
-    S[0] += lam * tr;
-    S[4] += lam * tr;
-    S[8] += lam * tr;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-      for (int j = 0; j < 3; ++j)
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-#pragma unroll
-          for (int l = 0; l < 3; ++l) {
-            double K = lam * F[3 * i + j] * F[3 * k + l] + mu * F[3 * i + l] * F[3 * k + j];
-            if (i == k) K += S[3 * l + j];
-            if (j == l) K += mu * B[3 * i + k];
-            A.K[(int64_t)(9 * (3 * i + j) + 3 * k + l) * N + v] = TK(K);
-          }
-    return;
-  }
-  // the state at the converged slips in FP64; the linear algebra of the
-  // tangent (6x6 factorisation, nine Woodbury solves) and its assembly in
-  // the precision of K (FP32 for the single-precision CG of mixed mode)
-  using TC = TK;
-  double Fpi0[9], chi0[12], dg[12];
-  load9(A.Fpi0, v, N, Fpi0);
-#pragma unroll
-  for (int al = 0; al < 12; ++al) {
-    chi0[al] = A.chi0[al * N + v];
-    dg[al] = A.dg[al * N + v];
-  }
-  double Fes[9];
-  mm3(F, Fpi0, Fes);
-  const double a = A.lp.dt * A.lp.gdot0;
-  CpEval e;
-  cp_eval(Fes, chi0, dg, tb, A.lp, a, e);
-  TC D[12], hg[12], Q[9];
-  LU6T<TC> L;
-  cp_jacobian(e, Fes, dg, tb, A.lp, a, D, hg, Q, L);
-  TC Fpi[9], Fe[9], Fpi0c[9], Fesc[9];
-  {
-    double Fpid[9];
-#pragma unroll
-    for (int i = 0; i < 9; ++i) Fpid[i] = Fpi0[i];
-#pragma unroll
-    for (int al = 0; al < 12; ++al) {
-      const double s0 = tb[kTabS + 3 * al], s1 = tb[kTabS + 3 * al + 1],
-                   s2 = tb[kTabS + 3 * al + 2];
-      const double m0 = tb[kTabM + 3 * al], m1 = tb[kTabM + 3 * al + 1],
-                   m2 = tb[kTabM + 3 * al + 2];
-#pragma unroll
-      for (int i = 0; i < 3; ++i) {
-        const double u = dg[al] * (Fpi0[3 * i] * s0 + Fpi0[3 * i + 1] * s1 +
-                                   Fpi0[3 * i + 2] * s2);
-        Fpid[3 * i] -= u * m0;
-        Fpid[3 * i + 1] -= u * m1;
-        Fpid[3 * i + 2] -= u * m2;
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < 9; ++i) {
-      Fpi[i] = (TC)Fpid[i];
-      Fe[i] = (TC)e.Fe[i];
-      Fpi0c[i] = (TC)Fpi0[i];
-      Fesc[i] = (TC)Fes[i];
-    }
-  }
-  const TC Sf[9] = {(TC)e.S[0], (TC)e.S[5], (TC)e.S[4], (TC)e.S[5], (TC)e.S[1],
-                    (TC)e.S[3], (TC)e.S[4], (TC)e.S[3], (TC)e.S[2]};
-  TC PS[9], FeS[9], B[9];
-  mm3t(Fpi, Sf, PS);   // Fp^-1 S
-  mm3t(Fe, Sf, FeS);   // Fe S
-#pragma unroll
-  for (int l = 0; l < 3; ++l)
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-      B[3 * l + j] = PS[3 * l] * Fpi[3 * j] + PS[3 * l + 1] * Fpi[3 * j + 1] +
-                     PS[3 * l + 2] * Fpi[3 * j + 2];  // Fp^-1 S Fp^-T
-  const double* Cv = tb + kTabC;
-#pragma unroll 1
+  for (int i = 0; i < kKComp; ++i) Kv[i] = K[i * N + v];
   for (int kl = 0; kl < 9; ++kl) {
-    const int k = kl / 3, l = kl - 3 * (kl / 3);
-    // rows k of Fe and l of Fp^-1, B row l: selects keep them in registers
-    TC fk[3], pl[3], Bl[3];
+    TK p[9], y[9];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      fk[c] = (k == 0) ? Fe[c] : ((k == 1) ? Fe[3 + c] : Fe[6 + c]);
-      pl[c] = (l == 0) ? Fpi[c] : ((l == 1) ? Fpi[3 + c] : Fpi[6 + c]);
-      Bl[c] = (l == 0) ? B[c] : ((l == 1) ? B[3 + c] : B[6 + c]);
-    }
-    // dR/dF_kl: b_a = (h_a/g) fk . N_a pl  (dtau_a/dF = Fe N_a Fp^-T)
-    TC b[12], gcol[12];
+    for (int i = 0; i < 9; ++i) p[i] = (i == kl) ? TK(1) : TK(0);
+    kp_apply(Kv, p, y);
 #pragma unroll
-    for (int al = 0; al < 12; ++al) {
-      const double* Na = tb + kTabN + 6 * al;
-      const TC N0 = (TC)Na[0], N1 = (TC)Na[1], N2 = (TC)Na[2], N3 = (TC)Na[3],
-               N4 = (TC)Na[4], N5 = (TC)Na[5];
-      const TC Np0 = N0 * pl[0] + N5 * pl[1] + N4 * pl[2];
-      const TC Np1 = N5 * pl[0] + N1 * pl[1] + N3 * pl[2];
-      const TC Np2 = N4 * pl[0] + N3 * pl[1] + N2 * pl[2];
-      b[al] = hg[al] * (fk[0] * Np0 + fk[1] * Np1 + fk[2] * Np2);
-    }
-    cp_jsolve(b, D, hg, Q, tb, L, gcol);  // d dg / d F_kl
-    // sigma = C : sym(fk (x) pl) - C : sum_a g_a V_a
-    TC E[6], acc6[6] = {0, 0, 0, 0, 0, 0}, acc9[9];
-    E[0] = fk[0] * pl[0];
-    E[1] = fk[1] * pl[1];
-    E[2] = fk[2] * pl[2];
-    E[3] = TC(0.5) * (fk[1] * pl[2] + fk[2] * pl[1]);
-    E[4] = TC(0.5) * (fk[0] * pl[2] + fk[2] * pl[0]);
-    E[5] = TC(0.5) * (fk[0] * pl[1] + fk[1] * pl[0]);
-#pragma unroll
-    for (int i = 0; i < 9; ++i) acc9[i] = 0;
-#pragma unroll
-    for (int al = 0; al < 12; ++al) {
-      TC V[6];
-      make_V(Q, tb, al, V);
-#pragma unroll
-      for (int I = 0; I < 6; ++I) acc6[I] += gcol[al] * V[I];
-      const TC s[3] = {(TC)tb[kTabS + 3 * al], (TC)tb[kTabS + 3 * al + 1],
-                       (TC)tb[kTabS + 3 * al + 2]};
-      const TC m[3] = {(TC)tb[kTabM + 3 * al], (TC)tb[kTabM + 3 * al + 1],
-                       (TC)tb[kTabM + 3 * al + 2]};
-      TC u[3], vv[3], w[3], y[3];
-#pragma unroll
-      for (int i = 0; i < 3; ++i) {
-        u[i] = Fesc[3 * i] * s[0] + Fesc[3 * i + 1] * s[1] + Fesc[3 * i + 2] * s[2];
-        vv[i] = PS[3 * i] * m[0] + PS[3 * i + 1] * m[1] + PS[3 * i + 2] * m[2];
-        w[i] = FeS[3 * i] * m[0] + FeS[3 * i + 1] * m[1] + FeS[3 * i + 2] * m[2];
-        y[i] = Fpi0c[3 * i] * s[0] + Fpi0c[3 * i + 1] * s[1] + Fpi0c[3 * i + 2] * s[2];
-      }
-#pragma unroll
-      for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-          acc9[3 * i + j] += gcol[al] * (u[i] * vv[j] + w[i] * y[j]);
-    }
-#pragma unroll
-    for (int I = 0; I < 6; ++I) E[I] -= acc6[I];
-    TC sg[6];
-    cmul6t(Cv, E, sg);
-    const TC sf[9] = {sg[0], sg[5], sg[4], sg[5], sg[1],
-                      sg[3], sg[4], sg[3], sg[2]};
-    TC Fs[9];
-    mm3t(Fe, sf, Fs);
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        TC K = Fs[3 * i] * Fpi[3 * j] + Fs[3 * i + 1] * Fpi[3 * j + 1] +
-               Fs[3 * i + 2] * Fpi[3 * j + 2] - acc9[3 * i + j];
-        if (i == k) K += Bl[j];
-        A.K[(int64_t)(9 * (3 * i + j) + kl) * N + v] = TK(K);
-      }
+    for (int i = 0; i < 9; ++i) out[(9 * i + kl) * N + v] = y[i];
   }
 }
 
@@ -1213,6 +1047,14 @@ void launch_tangent(const TangentArgs<TK>& a, hipStream_t s) {
                      s, a);
 }
 
+template <typename TK>
+void launch_expand_tangent(const TK* K, TK* out, int64_t N, hipStream_t s) {
+  hipLaunchKernelGGL((expand_tangent_kernel<TK>), dim3((unsigned)((N + 255) / 256)),
+                     dim3(256), 0, s, K, out, N);
+}
+
+template void launch_expand_tangent<float>(const float*, float*, int64_t, hipStream_t);
+template void launch_expand_tangent<double>(const double*, double*, int64_t, hipStream_t);
 template void launch_tangent<float>(const TangentArgs<float>&, hipStream_t);
 template void launch_tangent<double>(const TangentArgs<double>&, hipStream_t);
 

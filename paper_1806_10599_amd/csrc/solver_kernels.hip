@@ -6,6 +6,7 @@
 //   of Sec. 3.3, Eqs. 23-24.
 #include "cg_scalars.hpp"
 #include "kernels.hpp"
+#include "kp_apply.hpp"
 #include "newton.hpp"
 
 namespace rve {
@@ -36,46 +37,14 @@ void launch_predict(double* F, const double* Fprev, const double dFbar[9],
                      dFbar[5], dFbar[6], dFbar[7], dFbar[8]);
 }
 
-// Material product of a CG direction (Sec. 2.1, Eqs. 15-16): per voxel
-// y_c = sum_d K[9c + d] p_d and the block's partial of p . y; one voxel per
-// thread, K streamed once, coalesced per component.  The stop flag of the
-// run is tested once the voxel's loads are issued.
-template <typename T>
+template <typename T, bool FULL>
 __global__ __launch_bounds__(kBlock) void kp_kernel(
     const T* __restrict__ K, const T* __restrict__ p, T* __restrict__ y,
     const Scalars* __restrict__ sc, int64_t N, double* __restrict__ pkp) {
   __shared__ double red[kBlock / 64];
   const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t vl = v < N ? v : N - 1;
-  const int32_t stopped = __hip_atomic_load(&sc->done, __ATOMIC_RELAXED,
-                                            __HIP_MEMORY_SCOPE_AGENT);
-  T pd[9];
-#pragma unroll
-  for (int d = 0; d < 9; ++d) pd[d] = p[d * N + vl];
-  double acc = 0.0;
-  // FP32: every entry of K in flight at once (about 100 VGPRs)
-  constexpr bool kAll = sizeof(T) == 4;
-  T kv[kAll ? 81 : 1];
-  if constexpr (kAll) {
-#pragma unroll
-    for (int i = 0; i < 81; ++i) kv[i] = K[i * N + vl];
-  }
-  if (stopped) return;
-  if (v < N) {
-#pragma unroll
-    for (int c = 0; c < 9; ++c) {
-      T s = T(0);
-#pragma unroll
-      for (int d = 0; d < 9; ++d) {
-        if constexpr (kAll)
-          s += kv[9 * c + d] * pd[d];
-        else
-          s += K[(9 * c + d) * N + v] * pd[d];
-      }
-      y[c * N + v] = s;
-      acc += double(pd[c]) * double(s);
-    }
-  }
+  const double acc = kp_voxel<T, FULL>(K, p, y, v < N ? v : N - 1, N, v < N,
+                                       &sc->done);
   const double t = block_reduce(acc, red);
   if (threadIdx.x == 0) pkp[blockIdx.x] = t;
 }
@@ -83,15 +52,18 @@ __global__ __launch_bounds__(kBlock) void kp_kernel(
 int kp_blocks(int64_t N) { return (int)((N + kBlock - 1) / kBlock); }
 
 template <typename T>
-void launch_kp(const T* K, const T* p, T* y, const Scalars* sc, int64_t N,
-               double* pkp, hipStream_t s) {
-  launch((kp_kernel<T>), dim3((unsigned)kp_blocks(N)), dim3(kBlock), 0, s, K, p,
-         y, sc, N, pkp);
+void launch_kp(const T* K, bool full, const T* p, T* y, const Scalars* sc,
+               int64_t N, double* pkp, hipStream_t s) {
+  const dim3 grid((unsigned)kp_blocks(N));
+  if (full)
+    launch((kp_kernel<T, true>), grid, dim3(kBlock), 0, s, K, p, y, sc, N, pkp);
+  else
+    launch((kp_kernel<T, false>), grid, dim3(kBlock), 0, s, K, p, y, sc, N, pkp);
 }
 
-template void launch_kp<float>(const float*, const float*, float*,
+template void launch_kp<float>(const float*, bool, const float*, float*,
                                const Scalars*, int64_t, double*, hipStream_t);
-template void launch_kp<double>(const double*, const double*, double*,
+template void launch_kp<double>(const double*, bool, const double*, double*,
                                 const Scalars*, int64_t, double*, hipStream_t);
 
 template <typename T>

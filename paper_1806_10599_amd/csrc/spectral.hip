@@ -24,6 +24,7 @@
 #include "common.hpp"
 #include "fft.hpp"
 #include "kernels.hpp"
+#include "kp_apply.hpp"
 
 #include <type_traits>
 
@@ -209,14 +210,50 @@ __device__ __forceinline__ bool slab_fwd_body(const SlabFwdArgs<T>& a, int lb,
       T pd[9];
 #pragma unroll
       for (int d = 0; d < 9; ++d) pd[d] = a.field[d * cs + v];
+      if (a.kfull) {
+#pragma unroll
+        for (int q = 0; q < CPB; ++q) {
+          const int c = grp * CPB + q;
+          T acc = T(0);
+#pragma unroll
+          for (int d = 0; d < 9; ++d) acc += a.K[(9 * c + d) * cs + v] * pd[d];
+          out[hh][q] = acc;
+        }
+      } else {
+        // components of one tensor row i = grp (CPB 3) or c = 3 i + j
+        T F[9], e[6];
+#pragma unroll
+        for (int d = 0; d < 9; ++d) F[d] = a.K[(42 + d) * cs + v];
+        kp_strain(F, pd, e);
+        auto row = [&](int i, int j) {
+          T acc = T(0);
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            const int I = voigt(k, j);
+            T s = T(0);
+#pragma unroll
+            for (int J = 0; J < 6; ++J) s += a.K[(6 * I + J) * cs + v] * e[J];
+            const T pk = i == 0 ? pd[k] : (i == 1 ? pd[3 + k] : pd[6 + k]);
+            const T fk = i == 0 ? F[k] : (i == 1 ? F[3 + k] : F[6 + k]);
+            acc += pk * a.K[(36 + I) * cs + v] + fk * s;
+          }
+          return acc;
+        };
+        if constexpr (CPB == 3) {
+#pragma unroll
+          for (int q = 0; q < CPB; ++q) out[hh][q] = row(grp, q);
+        } else {
+          out[hh][0] = row(grp / 3, grp % 3);
+        }
+      }
 #pragma unroll
       for (int q = 0; q < CPB; ++q) {
         const int c = grp * CPB + q;
-        T acc = T(0);
+        // the direction's component c, without an indexed register
+        T pc = pd[0];
 #pragma unroll
-        for (int d = 0; d < 9; ++d) acc += a.K[(9 * c + d) * cs + v] * pd[d];
-        out[hh][q] = acc;
-        kacc[q] += double(pd[c]) * double(acc);
+        for (int d = 1; d < 9; ++d) pc = (c == d) ? pd[d] : pc;
+        kacc[q] += double(pc) * double(out[hh][q]);
       }
     }
 #pragma unroll
@@ -921,13 +958,13 @@ __device__ __forceinline__ int batch_item(const BatchSpec<T>& b, int pass,
 // bit 1: three), so that a launch whose RVEs all use one of them does not
 // carry the registers of the other.  A CG pass leaves an RVE whose run has
 // stopped alone, the others one that is inactive.
-template <typename T, int NN, int CPB, int SRC>
+template <typename T, int NN, int CPB>
 __device__ __forceinline__ void slab_fwd_item(const SlabFwdArgs<T>& a, int lb,
                                               unsigned char* smem) {
   cplx<T>* lds = reinterpret_cast<cplx<T>*>(smem);
   cplx<T>* tw = lds + CPB * SlabGeom<NN>::PLANE;
   double* red = reinterpret_cast<double*>(tw + NN);
-  slab_fwd_body<T, NN, CPB, SRC>(a, lb, lds, tw, red);
+  slab_fwd_body<T, NN, CPB, SRC_FIELD>(a, lb, lds, tw, red);
 }
 template <typename T, typename TO, int NN, int CPB, int DST>
 __device__ __forceinline__ void slab_inv_item(const SlabInvArgs<T, TO>& a,
@@ -938,43 +975,47 @@ __device__ __forceinline__ void slab_inv_item(const SlabInvArgs<T, TO>& a,
   slab_inv_body<T, TO, NN, CPB, DST>(a, lb, lds, tw, red);
 }
 
-template <typename T, int SRC, int CPBS = 3>
+template <typename T, bool CG, int CPBS = 3>
 __device__ __forceinline__ void slab_fwd_batch_block(const BatchSpec<T>& b,
                                                      int blk,
                                                      unsigned char* smem) {
   const int r = batch_item(b, 0, blk);
   const SpecItem<T>& it = b.items[r];
-  if (SRC == SRC_KROW ? it.sc->done : it.sc->inactive) return;
+  if (CG ? it.sc->done : it.sc->inactive) return;
   const int lb = blk - it.blk[0];
   SlabFwdArgs<T> a{};
   a.cs = b.cs;
-  a.field = b.field + it.off;
-  a.K = b.K ? b.K + it.off : nullptr;
+  a.field = (CG ? b.y : b.field) + it.off;
   a.spec = b.spec + it.soff;
   a.tw = it.tw;
-  a.psum = SRC == SRC_FIELD ? it.psum : nullptr;
+  a.psum = CG ? nullptr : it.psum;
   a.psq = it.psq;
-  a.pkp_out = it.pkp;
   switch (it.n) {
 #define RVE_CASE(NN)                                                         \
   case NN:                                                                   \
     if constexpr ((CPBS & 2) && cpb3_fits<T, NN>())                          \
       if (it.cpb == 3) {                                                     \
-        slab_fwd_item<T, NN, 3, SRC>(a, lb, smem);                           \
+        slab_fwd_item<T, NN, 3>(a, lb, smem);                                \
         break;                                                               \
       }                                                                      \
     if constexpr ((CPBS & 1) || !cpb3_fits<T, NN>())                         \
-      slab_fwd_item<T, NN, 1, SRC>(a, lb, smem);                             \
+      slab_fwd_item<T, NN, 1>(a, lb, smem);                                  \
     break;
     RVE_BATCH_SIZES(RVE_CASE)
 #undef RVE_CASE
   }
 }
 
-template <typename T, int SRC, int CPBS>
+template <typename T, bool CG, int CPBS>
 __global__ __launch_bounds__(kBlock) void slab_fwd_batch_kernel(BatchSpec<T> b) {
   extern __shared__ __align__(16) unsigned char smem[];
-  slab_fwd_batch_block<T, SRC, CPBS>(b, blockIdx.x, smem);
+  slab_fwd_batch_block<T, CG, CPBS>(b, blockIdx.x, smem);
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBlock) void kp_batch_kernel(BatchSpec<T> b) {
+  __shared__ double red[kBlock / 64];
+  kp_batch_block<T>(b, blockIdx.x, red);
 }
 
 // G of a field: projection of the pencils (blk[2])
@@ -1025,7 +1066,7 @@ __device__ __forceinline__ void pencil_fwd_batch_block(const BatchSpec<T>& b,
   } else if (b.timing) {
     alpha = T(it.sc->alpha);
   } else {
-    if (!cg_alpha_consume(it.pkp, 9 * it.n, it.sc, b.parity, lb == 0, alpha))
+    if (!cg_alpha_consume(it.pkp, it.n * it.n * it.n / kBlock, it.sc, b.parity, lb == 0, alpha))
       return;
   }
   a.spec = b.spec + it.soff;
@@ -1230,9 +1271,14 @@ __device__ __noinline__ void pc_p(const BatchSpec<T>& b, int blk,
   slab_inv_batch_block<T, T, DST_P>(b, b.p, blk, smem);
 }
 template <typename T>
-__device__ __noinline__ void pc_krow(const BatchSpec<T>& b, int blk,
-                                     unsigned char* smem) {
-  slab_fwd_batch_block<T, SRC_KROW>(b, blk, smem);
+__device__ __noinline__ void pc_kp(const BatchSpec<T>& b, int blk,
+                                   unsigned char* smem) {
+  kp_batch_block<T>(b, blk, reinterpret_cast<double*>(smem));
+}
+template <typename T>
+__device__ __noinline__ void pc_fwd(const BatchSpec<T>& b, int blk,
+                                    unsigned char* smem) {
+  slab_fwd_batch_block<T, true>(b, blk, smem);
 }
 template <typename T>
 __device__ __noinline__ void pc_res(const BatchSpec<T>& b, int blk,
@@ -1267,8 +1313,13 @@ __global__ __launch_bounds__(kBlock) void cg_batch_persistent_kernel(
       __syncthreads();
     }
     if (!grid_barrier(c.bar, gridDim.x, c.err)) return;
+    for (int vb = blockIdx.x; vb < c.blocksV; vb += gridDim.x) {
+      pc_kp<T>(b, vb, smem);
+      __syncthreads();
+    }
+    if (!grid_barrier(c.bar, gridDim.x, c.err)) return;
     for (int vb = blockIdx.x; vb < c.blocksA; vb += gridDim.x) {
-      pc_krow<T>(b, vb, smem);
+      pc_fwd<T>(b, vb, smem);
       __syncthreads();
     }
     if (!grid_barrier(c.bar, gridDim.x, c.err)) return;
@@ -1401,6 +1452,7 @@ void launch_cg_sched(const CgLaunch<T>& L, int mask, hipStream_t s) {
     if (L.fused) {
       a.field = L.p;
       a.K = L.K;
+      a.kfull = L.kfull;
       a.pkp_out = L.pkp;
       launch((slab_fwd_kernel<T, N, CPB, SRC_KROW>), dim3(nslab), dim3(kBlock),
              0, s, a);
@@ -1640,7 +1692,7 @@ void launch_G_batch(const BatchSpec<T>& b, double* out, const BatchGrid& g,
                     hipStream_t s) {
   with_cpbs(b.cpbs, [&](auto cp) {
     constexpr int C = decltype(cp)::value;
-    hipLaunchKernelGGL((slab_fwd_batch_kernel<T, SRC_FIELD, C>), dim3(g.A),
+    hipLaunchKernelGGL((slab_fwd_batch_kernel<T, false, C>), dim3(g.A),
                        dim3(kBlock), g.ldsA, s, b);
     hipLaunchKernelGGL((pencil_batch_kernel<T>), dim3(3 * g.B), dim3(kBlock),
                        g.ldsB, s, b);
@@ -1654,7 +1706,7 @@ void launch_residual_batch(const BatchSpec<double>& b, cplx<TR>* rho,
                            const BatchGrid& g, hipStream_t s) {
   with_cpbs(b.cpbs, [&](auto cp) {
     constexpr int C = decltype(cp)::value;
-    hipLaunchKernelGGL((slab_fwd_batch_kernel<double, SRC_FIELD, C>), dim3(g.A),
+    hipLaunchKernelGGL((slab_fwd_batch_kernel<double, false, C>), dim3(g.A),
                        dim3(kBlock), g.ldsA, s, b);
   });
   hipLaunchKernelGGL((pencil_fwd_batch_kernel<double, TR, true>), dim3(g.B),
@@ -1669,7 +1721,9 @@ void launch_cg_batch(const BatchSpec<T>& b, const BatchGrid& g, hipStream_t s) {
                        dim3(kBlock), g.ldsB, s, b);
     hipLaunchKernelGGL((slab_inv_batch_kernel<T, T, DST_P, C>), dim3(g.A),
                        dim3(kBlock), g.ldsA, s, b, b.p);
-    hipLaunchKernelGGL((slab_fwd_batch_kernel<T, SRC_KROW, C>), dim3(g.A),
+    if (g.V)   // the tuner's timings leave out what no schedule changes
+      hipLaunchKernelGGL((kp_batch_kernel<T>), dim3(g.V), dim3(kBlock), 0, s, b);
+    hipLaunchKernelGGL((slab_fwd_batch_kernel<T, true, C>), dim3(g.A),
                        dim3(kBlock), g.ldsA, s, b);
     hipLaunchKernelGGL((pencil_fwd_batch_kernel<T, T, false>), dim3(g.B),
                        dim3(kBlock), g.ldsB, s, b, b.rho);
@@ -1699,8 +1753,8 @@ void batch_allow_lds(size_t slab, size_t pencil) {
   for (int cpbs = 1; cpbs <= 3; ++cpbs)
     with_cpbs(cpbs, [&](auto cp) {
       constexpr int C = decltype(cp)::value;
-      allow((const void*)&slab_fwd_batch_kernel<T, SRC_FIELD, C>, slab);
-      allow((const void*)&slab_fwd_batch_kernel<T, SRC_KROW, C>, slab);
+      allow((const void*)&slab_fwd_batch_kernel<T, false, C>, slab);
+      allow((const void*)&slab_fwd_batch_kernel<T, true, C>, slab);
       allow((const void*)&slab_inv_batch_kernel<T, double, DST_NORM, C>, slab);
       allow((const void*)&slab_inv_batch_kernel<T, double, DST_ADDF, C>, slab);
       allow((const void*)&slab_inv_batch_kernel<T, T, DST_P, C>, slab);
