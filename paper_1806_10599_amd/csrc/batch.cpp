@@ -269,7 +269,7 @@ void BatchEngine::build_tables() {
 // columns per pencil block follow cg_tile): every candidate times one
 // iteration of
 // this edge's RVEs alone, through the batched passes, with every RVE
-// active and alpha = beta = 0; three interleaved rounds, the best of each.
+// active and alpha = beta = 0, replayed as a graph.
 // The scalars are restored afterwards; the passes keep the residual and
 // overwrite only the direction, the iterate, the spectrum and the partials,
 // all rewritten by the next solve.
@@ -288,9 +288,6 @@ void BatchEngine::autotune() {
   const std::vector<SpecItem<T>>& full =
       *reinterpret_cast<const std::vector<SpecItem<T>>*>(dbl ? (const void*)&host_it64_
                                                              : (const void*)&host_it32_);
-  hipEvent_t ev[2];
-  RVE_HIP(hipEventCreate(&ev[0]));
-  RVE_HIP(hipEventCreate(&ev[1]));
   std::vector<int> edges(n_);
   std::sort(edges.begin(), edges.end());
   edges.erase(std::unique(edges.begin(), edges.end()), edges.end());
@@ -324,27 +321,20 @@ void BatchEngine::autotune() {
         cand.push_back(std::move(c));
       }
     std::vector<float> best(cand.size(), 0.f);
-    constexpr int reps = 4;
-    for (int round = 0; round < 3; ++round)
-      for (size_t c = 0; c < cand.size(); ++c) {
-        RVE_HIP(hipMemcpyAsync(tune_items_, cand[c].items.data(),
-                               cand[c].items.size() * sizeof(SpecItem<T>),
-                               hipMemcpyHostToDevice, st_));
-        BatchSpec<T> bs = spec<T>(true, 0);
-        bs.items = (const SpecItem<T>*)tune_items_;
-        bs.nitems = (int)cand[c].items.size();
-        bs.cpbs = cand[c].cpb == 3 ? 2 : 1;
-        bs.timing = 1;
-        auto matvec = [&] { launch_cg_batch<T>(bs, cand[c].g, st_); };
-        matvec();  // untimed first launch
-        RVE_HIP(hipEventRecord(ev[0], st_));
-        for (int i = 0; i < reps; ++i) matvec();
-        RVE_HIP(hipEventRecord(ev[1], st_));
-        RVE_HIP(hipEventSynchronize(ev[1]));
-        float t = 0.f;
-        RVE_HIP(hipEventElapsedTime(&t, ev[0], ev[1]));
-        if (round == 0 || t < best[c]) best[c] = t;
-      }
+    constexpr int reps = 8;
+    for (size_t c = 0; c < cand.size(); ++c) {
+      RVE_HIP(hipMemcpyAsync(tune_items_, cand[c].items.data(),
+                             cand[c].items.size() * sizeof(SpecItem<T>),
+                             hipMemcpyHostToDevice, st_));
+      BatchSpec<T> bs = spec<T>(true, 0);
+      bs.items = (const SpecItem<T>*)tune_items_;
+      bs.nitems = (int)cand[c].items.size();
+      bs.cpbs = cand[c].cpb == 3 ? 2 : 1;
+      bs.timing = 1;
+      best[c] = time_as_graph(st_, reps, [&](hipStream_t cs) {
+        launch_cg_batch<T>(bs, cand[c].g, cs);
+      });
+    }
     size_t bi = 0;
     for (size_t c = 1; c < cand.size(); ++c)
       if (best[c] < best[bi]) bi = c;
@@ -353,8 +343,6 @@ void BatchEngine::autotune() {
     sched_ms_[e] = best[bi] / reps;
   }
   RVE_HIP(hipGetLastError());
-  hipEventDestroy(ev[0]);
-  hipEventDestroy(ev[1]);
   std::copy(saved.begin(), saved.end(), sc_host_);
   upload_scalars();
   build_tables();

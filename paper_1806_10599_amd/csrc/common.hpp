@@ -136,4 +136,41 @@ __device__ __forceinline__ double block_sum_fixed(double v, double* red) {
   return r;
 }
 
+// Milliseconds that `reps` runs of the launches of f(stream) take on stream s
+// when they are replayed as one graph, the best of three: between kernels of
+// a few microseconds the host would otherwise set the pace, and the fewest
+// launches would look the fastest.  They are captured on a stream of their
+// own, since s may be the default stream.
+template <typename F>
+float time_as_graph(hipStream_t s, int reps, F&& f) {
+  hipGraph_t def = nullptr;
+  hipGraphExec_t ex = nullptr;
+  hipEvent_t ev[2];
+  RVE_HIP(hipEventCreate(&ev[0]));
+  RVE_HIP(hipEventCreate(&ev[1]));
+  hipStream_t cs;
+  RVE_HIP(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
+  RVE_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
+  for (int i = 0; i < reps; ++i) f(cs);
+  RVE_HIP(hipStreamEndCapture(cs, &def));
+  hipStreamDestroy(cs);
+  RVE_HIP(hipGraphInstantiate(&ex, def, nullptr, nullptr, 0));
+  RVE_HIP(hipGraphLaunch(ex, s));
+  float best = 0.f;
+  for (int round = 0; round < 3; ++round) {
+    RVE_HIP(hipEventRecord(ev[0], s));
+    RVE_HIP(hipGraphLaunch(ex, s));
+    RVE_HIP(hipEventRecord(ev[1], s));
+    RVE_HIP(hipEventSynchronize(ev[1]));
+    float t = 0.f;
+    RVE_HIP(hipEventElapsedTime(&t, ev[0], ev[1]));
+    if (round == 0 || t < best) best = t;
+  }
+  hipGraphExecDestroy(ex);
+  hipGraphDestroy(def);
+  hipEventDestroy(ev[0]);
+  hipEventDestroy(ev[1]);
+  return best;
+}
+
 }  // namespace rve

@@ -574,42 +574,35 @@ void Engine::capture_graph() {
 template <typename T>
 void Engine::autotune() {
   const bool dbl = sizeof(T) == sizeof(double);
-  hipEvent_t ev[2];
-  RVE_HIP(hipEventCreate(&ev[0]));
-  RVE_HIP(hipEventCreate(&ev[1]));
   struct Cand {
     int cpb, tt, fused;
   };
   std::vector<Cand> cand;
+  // One component per slab block is the fastest at every edge (measured per
+  // iteration, three against one: 23.2 / 20.5 us at 32^3 and 52 / 42 us at
+  // 64^3 in single, 21.2 / 20.9 us at 16^3 in double precision), so three
+  // are timed only up to 16^3.  K:p folded into pass A reads the tangent once
+  // per component: 38 / 20.5 us at 32^3 and 72 / 42 us at 64^3; only at
+  // 16^3 in double precision does the launch it saves pay (19.9 / 20.9 us).
   for (int fused : {0, 1})
     for (int cpb : {1, 3})
-      if (schedule_valid(n_, dbl, cpb, cg_tile(n_)))
+      if (schedule_valid(n_, dbl, cpb, cg_tile(n_)) &&
+          (n_ <= 16 || (cpb == 1 && !fused)))
         cand.push_back({cpb, cg_tile(n_), fused});
   // alpha = 0 in every slot: the timed passes leave the residual unchanged
   launch_bench_scalars(sc_, st_);
-  // three interleaved rounds, the best of each candidate's timings: robust
-  // against clock and cache drift between candidates
   std::vector<float> tbest(cand.size(), 0.f);
-  constexpr int reps = 4;
-  for (int round = 0; round < 3; ++round)
-    for (size_t c = 0; c < cand.size(); ++c) {
-      CgLaunch<T> L = cg_launch<T>(0, cand[c].cpb, cand[c].tt, cand[c].fused);
-      L.prr = nullptr;   // alpha and beta from the scalars
-      auto matvec = [&] {
-        launch_cg<T>(n_, L, kPassDir | kPassP, st_);
-        if (!cand[c].fused)
-          launch_kp<T>(L.K, L.kfull, L.p, (T*)Kp_, sc_, N_, partial_kp_, st_);
-        launch_cg<T>(n_, L, kPassA | kPassRes, st_);
-      };
-      matvec();  // untimed first launch
-      RVE_HIP(hipEventRecord(ev[0], st_));
-      for (int i = 0; i < reps; ++i) matvec();
-      RVE_HIP(hipEventRecord(ev[1], st_));
-      RVE_HIP(hipEventSynchronize(ev[1]));
-      float t = 0.f;
-      RVE_HIP(hipEventElapsedTime(&t, ev[0], ev[1]));
-      if (round == 0 || t < tbest[c]) tbest[c] = t;
-    }
+  constexpr int reps = 8;
+  for (size_t c = 0; c < cand.size(); ++c) {
+    CgLaunch<T> L = cg_launch<T>(0, cand[c].cpb, cand[c].tt, cand[c].fused);
+    L.prr = nullptr;   // alpha and beta from the scalars
+    tbest[c] = time_as_graph(st_, reps, [&](hipStream_t cs) {
+      launch_cg<T>(n_, L, kPassDir | kPassP, cs);
+      if (!cand[c].fused)
+        launch_kp<T>(L.K, L.kfull, L.p, (T*)Kp_, sc_, N_, partial_kp_, cs);
+      launch_cg<T>(n_, L, kPassA | kPassRes, cs);
+    });
+  }
   float best = 0.f;
   int bi = -1;
   for (size_t c = 0; c < cand.size(); ++c)
@@ -617,8 +610,6 @@ void Engine::autotune() {
       best = tbest[c];
       bi = (int)c;
     }
-  hipEventDestroy(ev[0]);
-  hipEventDestroy(ev[1]);
   if (bi < 0) throw Error(RVE_EINVAL, "no FFT schedule for this grid");
   sched_cpb_ = cand[bi].cpb;
   sched_tt_ = cand[bi].tt;
