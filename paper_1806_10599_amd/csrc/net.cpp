@@ -1,6 +1,7 @@
 // Warm-start network object: FP32 master parameters with Adam state, bf16
 // MFMA fragments, activation scratch sized for the largest grid seen.
-#include <cstring>
+#include <algorithm>
+#include <cmath>
 
 #include "nn.hpp"
 
@@ -18,8 +19,6 @@ int64_t layer_off(int k) {
   for (int i = 0; i < k; ++i) o += (int64_t)27 * kCin[i] * kCout[i] + kCout[i];
   return o;
 }
-constexpr int kChunk = 4096;   // voxels per weight-gradient block
-constexpr int kBiasBlocks = 64;
 constexpr int kLossBlocks = 256;
 }  // namespace
 
@@ -37,7 +36,6 @@ Net::Net(hipStream_t s, AllocFn a, FreeFn f, void* ctx)
     wf_[k] = (uint16_t*)alloc(fr);
     wb_[k] = (uint16_t*)alloc(fr);
   }
-  wpad_ = (float*)alloc((size_t)27 * kFeat * kWidth * sizeof(float));
   lpart_ = (double*)alloc(kLossBlocks * sizeof(double));
   RVE_HIP(hipHostMalloc((void**)&lhost_, kLossBlocks * sizeof(double),
                         hipHostMallocDefault));
@@ -80,14 +78,36 @@ void Net::ensure(int64_t N) {
   a1_ = (uint16_t*)alloc(N * kWidth * sizeof(uint16_t));
   a2_ = (uint16_t*)alloc(N * kWidth * sizeof(uint16_t));
   a3_ = (uint16_t*)alloc(N * kWidth * sizeof(uint16_t));
+  cap_ = N;
+}
+
+void Net::ensure_train(int64_t N) {
+  ensure(N);
+  if (N <= train_cap_) return;
   d1_ = (uint16_t*)alloc(N * kWidth * sizeof(uint16_t));
   d2_ = (uint16_t*)alloc(N * kWidth * sizeof(uint16_t));
   dy_ = (uint16_t*)alloc(N * kOut * sizeof(uint16_t));
   yf_ = (float*)alloc(N * kOut * sizeof(float));
-  dyf_ = (float*)alloc(N * kOut * sizeof(float));
-  const int64_t nch = (N + kChunk - 1) / kChunk;
-  part_ = (float*)alloc((size_t)nch * 27 * kFeat * kWidth * sizeof(float));
-  cap_ = N;
+  // the chunks grow with N up to kMaxChunks, not always steadily
+  const size_t nch = std::min<int64_t>(kMaxChunks, N / 256);
+  for (int k = 0; k < 4; ++k) {
+    part_[k] = (float*)alloc(nch * 27 * kCIN[k] * kCOUT[k] * sizeof(float));
+    bpart_[k] = (float*)alloc((k == 3 ? (size_t)kLossBlocks : nch) * kCOUT[k] *
+                              sizeof(float));
+  }
+  train_cap_ = N;
+}
+
+// the input where the staging loads can read it, 16 bytes at a time
+const uint16_t* Net::aligned(const uint16_t* X, int64_t N, hipStream_t s) {
+  if (reinterpret_cast<uintptr_t>(X) % 16 == 0) return X;
+  if (N > xcap_) {
+    xcopy_ = (uint16_t*)alloc(N * kFeat * sizeof(uint16_t));
+    xcap_ = N;
+  }
+  RVE_HIP(hipMemcpyAsync(xcopy_, X, N * kFeat * sizeof(uint16_t),
+                         hipMemcpyDeviceToDevice, s));
+  return xcopy_;
 }
 
 void Net::repack() {
@@ -121,6 +141,7 @@ void Net::forward(const uint16_t* X, int n, float* Y, hipStream_t s) {
   if (n % 16) throw Error(-1, "the network needs a grid edge divisible by 16");
   const int64_t N = (int64_t)n * n * n;
   ensure(N);
+  X = aligned(X, N, s ? s : st_);
   // inference inside an increment runs on the RVE's stream; the scratch
   // activations are only touched by work ordered on one stream at a time
   hipStream_t st = s ? s : st_;
@@ -136,9 +157,9 @@ void Net::forward(const uint16_t* X, int n, float* Y, hipStream_t s) {
 double Net::loss(const uint16_t* X, const float* T, int n) {
   if (n % 16) throw Error(-1, "the network needs a grid edge divisible by 16");
   const int64_t N = (int64_t)n * n * n;
-  ensure(N);
+  ensure_train(N);
   forward(X, n, yf_);
-  nn_mse(yf_, T, kOut, kOutReal, N, dy_, dyf_, lpart_, kLossBlocks, st_);
+  nn_mse(yf_, T, kOutReal, N, dy_, bpart_[3], lpart_, kLossBlocks, st_);
   RVE_HIP(hipGetLastError());
   RVE_HIP(hipMemcpyAsync(lhost_, lpart_, kLossBlocks * sizeof(double),
                          hipMemcpyDeviceToHost, st_));
@@ -152,25 +173,22 @@ double Net::train_step(const uint16_t* X, const float* T, int n, float lr,
                        float* grad_host) {
   if (n % 16) throw Error(-1, "the network needs a grid edge divisible by 16");
   const int64_t N = (int64_t)n * n * n;
-  ensure(N);
+  ensure_train(N);
+  X = aligned(X, N, st_);
   forward(X, n, yf_);
-  nn_mse(yf_, T, kOut, kOutReal, N, dy_, dyf_, lpart_, kLossBlocks, st_);
-  const int nch = (int)((N + kChunk - 1) / kChunk);
+  nn_mse(yf_, T, kOutReal, N, dy_, bpart_[3], lpart_, kLossBlocks, st_);
+  const int nch = nn_wgrad_chunks(N);
   const uint16_t* acts[4] = {X, a1_, a2_, a3_};
   const uint16_t* dz = dy_;          // gradient at the output of layer k
   uint16_t* dbuf[2] = {d1_, d2_};
-  float* bpart = part_;              // reused after each layer's dW sum
+  UpdateArgs u{};
   for (int k = 3; k >= 0; --k) {
     const int CIN = kCIN[k], COUT = kCOUT[k];
-    nn_wgrad(CIN, COUT, acts[k], dz, part_, nch, kChunk, n, N, st_);
-    nn_sum_parts(part_, nch, (int64_t)27 * CIN * COUT, wpad_, st_);
-    nn_unpad(wpad_, CIN, COUT, kCin[k], kCout[k], g_ + layer_off(k), st_);
-    nn_bias_grad(COUT, k == 3 ? nullptr : dz, k == 3 ? dyf_ : nullptr, N, bpart,
-                 kBiasBlocks, st_);
-    nn_sum_parts(bpart, kBiasBlocks, COUT, wpad_, st_);
-    RVE_HIP(hipMemcpyAsync(g_ + layer_off(k) + (int64_t)27 * kCin[k] * kCout[k],
-                           wpad_, kCout[k] * sizeof(float),
-                           hipMemcpyDeviceToDevice, st_));
+    // the last layer's bias gradient comes from the unrounded dY (nn_mse)
+    nn_wgrad(CIN, COUT, acts[k], dz, part_[k], k == 3 ? nullptr : bpart_[k], n, N, st_);
+    u.layer[k] = UpdateLayer{layer_off(k), part_[k], bpart_[k], wf_[k], wb_[k],
+                             nch, k == 3 ? kLossBlocks : nch,
+                             kCin[k], kCout[k], CIN, COUT};
     if (k > 0) {
       // gradient at the output of layer k-1, through its ReLU
       uint16_t* out = dbuf[k % 2];
@@ -180,8 +198,18 @@ double Net::train_step(const uint16_t* X, const float* T, int n, float lr,
     }
   }
   ++step_;
-  nn_adam(w_, g_, m_, v_, param_count(), lr, 0.9f, 0.999f, 1e-8f, step_, st_);
-  repack();
+  u.w = w_;
+  u.g = g_;
+  u.m = m_;
+  u.v = v_;
+  u.size = param_count();
+  u.lr = lr;
+  u.b1 = 0.9f;
+  u.b2 = 0.999f;
+  u.eps = 1e-8f;
+  u.c1 = 1.f - powf(u.b1, (float)step_);
+  u.c2 = 1.f - powf(u.b2, (float)step_);
+  nn_update(u, st_);
   RVE_HIP(hipGetLastError());
   if (grad_host)
     RVE_HIP(hipMemcpyAsync(grad_host, g_, param_count() * sizeof(float),

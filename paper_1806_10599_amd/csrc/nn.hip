@@ -8,9 +8,10 @@
 //   master weights FP32 per layer: W[27][cin][cout] then b[cout];
 //   MFMA B fragments bf16 [27][CIN/16][COUT/16][64 lanes][4]: lane l of
 //   fragment (t, kc, nt) holds W[t][16 kc + 4 (l/16) + i][16 nt + l%16].
-// One wave computes 16 consecutive voxels along z times all output
-// channels; lane l feeds voxel row l%16 (A operand: 4 consecutive input
-// channels) and receives outputs for voxels 4 (l/16) + i, channel l%16.
+// The convolutions take the weight fragment as the A operand: one wave
+// computes 16 consecutive voxels along z times all output channels, lane l
+// feeding voxel l%16 (4 consecutive input channels) and receiving four
+// consecutive output channels 4 (l/16) + i of that voxel.
 #include "nn.hpp"
 #include "kernels.hpp"
 
@@ -32,273 +33,383 @@ __device__ __forceinline__ float bf2f(uint16_t h) {
 __device__ __forceinline__ int wrap(int i, int n) {
   return i < 0 ? i + n : (i >= n ? i - n : i);
 }
+// place of W[t][ci][co] in the fragments of a CIN -> COUT convolution
+__device__ __forceinline__ int frag_index(int t, int ci, int co, int CIN, int COUT) {
+  const int f = (t * (CIN / 16) + ci / 16) * (COUT / 16) + co / 16;
+  return f * 256 + ((ci % 16) / 4 * 16 + co % 16) * 4 + ci % 4;
+}
+
+// ---------------------------------------------------------------- staging
+// The lines yb - 1 .. yb + nl - 2 (periodic, all z) of one x plane go from
+// global memory straight to LDS (no registers in between, so all of a
+// wave's loads are in flight at once), 16 bytes = 8 channels per lane.  A
+// load writes the LDS of a wave contiguously, so instead of padded rows the
+// 16-byte pieces of a voxel are permuted by swz<C>(z), on the global side of
+// the load: with it neither the 16 voxels x 16 bytes that half a wave reads
+// for a convolution nor the 8 voxels x 32 bytes of a transposed read share
+// a bank.
+template <int C>
+__device__ __forceinline__ int swz(int z) {
+  return C == 32 ? (((z >> 1) & 2) | ((z >> 3) & 1)) : ((z >> 3) & 1);
+}
+
+typedef __attribute__((address_space(1))) const void gvoid;
+typedef __attribute__((address_space(3))) void lvoid;
+
+// 16 bytes per active lane from src (per lane) to dst + 16 lane (dst the
+// same in all lanes)
+__device__ __forceinline__ void load_lds16(const void* src, void* dst) {
+  __builtin_amdgcn_global_load_lds((gvoid*)src, (lvoid*)dst, 16, 0, 0);
+}
+// the block's loads into LDS have landed
+__device__ __forceinline__ void lds_arrived() {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+}
+
+// `count` 16-byte pieces of src, in order (wv: the wave's index, uniform)
+template <int THREADS>
+__device__ __forceinline__ void stage_flat(const uint16_t* src, uint16_t* dst,
+                                           int count, int wv, int lane) {
+  for (int i0 = 64 * wv; i0 < count; i0 += THREADS)
+    if (i0 + lane < count) load_lds16(src + 8 * (i0 + lane), dst + 8 * i0);
+}
+
+// nl lines from yb - 1 of plane xp, permuted; inv_n = ceil(2^22 / n) (exact
+// quotients: a staged voxel's index is below 2^12 and n at most 2^9)
+template <int C, int THREADS>
+__device__ __forceinline__ void stage_lines(const uint16_t* __restrict__ X,
+                                            uint16_t* dst, int xp, int yb,
+                                            int nl, int n, unsigned inv_n,
+                                            int wv, int lane) {
+  constexpr int CH = C / 8;
+  const int count = nl * n * CH;
+  for (int i0 = 64 * wv; i0 < count; i0 += THREADS) {
+    const int i = i0 + lane;
+    if (i >= count) continue;
+    const int vz = i / CH, pos = i % CH;
+    const int j = (int)(((unsigned)vz * inv_n) >> 22), z = vz - j * n;
+    const int yg = wrap(yb - 1 + j, n);
+    load_lds16(X + (((int64_t)xp * n + yg) * n + z) * C + 8 * (pos ^ swz<C>(z)),
+               dst + 8 * i0);
+  }
+}
+static unsigned inv_edge(int n) { return ((1u << 22) + n - 1) / n; }
+
+// lines a block of vox consecutive voxels stages: those it touches (it
+// starts at a multiple of gcd(vox, n)) and one on either side
+static int conv_lines(int n, int vox) {
+  int g = vox, r = n;
+  while (r) {
+    const int t = g % r;
+    g = r;
+    r = t;
+  }
+  return (n - g + vox + n - 1) / n + 2;
+}
+
+// blocks of neighbouring voxels run on one XCD, whose L2 then holds the
+// lines and planes that they share
+__device__ __forceinline__ int xcd_block() {
+  const int g = (int)gridDim.x, b = (int)blockIdx.x;
+  return g % 8 ? b : (b % 8) * (g / 8) + b / 8;
+}
 
 // ------------------------------------------------------------- convolution
 // EPI: 0 bias + ReLU -> bf16; 1 bias, linear -> f32; 2 no bias, multiply by
 // the mask (mask_act > 0) -> bf16 (backward through the previous ReLU)
 //
-// A block of four waves computes 256 consecutive voxels (kConvTPW = 4
-// 16-voxel tiles per wave; with n % 16 == 0 a block never leaves its x
-// plane: for an edge-64 grid one wave is one z line and the block four
-// neighbouring y lines).  For each dx slice of the stencil the block stages
-// in LDS the B fragments of its nine taps and the input lines it reads
-// (its own y lines and one on either side, all z, of plane x + dx, at a
-// padded voxel stride), and the waves read both operands of every MFMA
-// from LDS: each input datum is fetched from global memory about 4.5 times
-// per layer instead of 27.
-constexpr int kConvTPW = 4;
-constexpr int kConvVox = 4 * kConvTPW * 16;   // voxels per block
-
-// lines of one plane a block stages: its own (at most 256/n + 1 partial
-// lines) and one on either side
-__host__ __device__ constexpr int conv_lines(int n) {
-  return (kConvVox + n - 1) / n + 3;
-}
-// LDS voxel stride in bf16: CIN + 8 keeps the 16 voxel rows of a fragment
-// read on distinct banks and 16-byte staging stores aligned
-template <int CIN>
-constexpr int conv_cs() { return CIN + 8; }
+// A block of four waves computes 64 TPW consecutive voxels (TPW 16-voxel
+// tiles per wave; with n % 16 == 0 a block never leaves its x plane).  For
+// each dx slice of the stencil it stages the fragments of the nine taps and
+// the input lines that it reads, and the waves read both operands of every
+// MFMA from LDS.  Staging through registers, one dependent load at a time,
+// bound the kernel before (32 -> 32 channels at 64^3: 51 us, now 28 us = 515
+// TFLOP/s; at 32^3 23, now 8 us); now the MFMAs (11.5 us at the rate of a
+// 16x16x16 product), the waits at the slices' ends and a last round of
+// blocks that fills a third of the chip do.
 template <int CIN, int COUT>
 constexpr int conv_slice() { return 9 * (CIN / 16) * (COUT / 16) * 64 * 4; }
 template <int CIN, int COUT>
-size_t conv_lds_bytes(int n) {
+size_t conv_lds_bytes(int n, int vox) {
   return ((size_t)conv_slice<CIN, COUT>() +
-          (size_t)conv_lines(n) * n * conv_cs<CIN>()) * sizeof(uint16_t);
+          (size_t)conv_lines(n, vox) * n * CIN) * sizeof(uint16_t);
 }
 
-template <int CIN, int COUT, int EPI>
+template <int CIN, int COUT, int EPI, int TPW>
 __global__ __launch_bounds__(256) void conv_mfma_kernel(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ Wf,
     const float* __restrict__ bias, uint16_t* __restrict__ Yb,
     float* __restrict__ Yf, const uint16_t* __restrict__ mask_act, int n,
-    int64_t N, int cout_real) {
+    unsigned inv_n, int nl, int cout_real) {
   constexpr int KC = CIN / 16, NT = COUT / 16;
   constexpr int SLICE = conv_slice<CIN, COUT>();  // bf16 of one dx slice
-  constexpr int CS = conv_cs<CIN>();
   extern __shared__ __align__(16) uint16_t smem_conv[];
   uint16_t* wl = smem_conv;
   uint16_t* al = smem_conv + SLICE;
   const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int row = lane & 15, grp = lane >> 4;
-  const int64_t n2 = (int64_t)n * n;
-  const int64_t vb = (int64_t)blockIdx.x * kConvVox;   // first voxel
-  const int xb = (int)(vb / n2);
-  const int yb = (int)((vb / n) % n);                  // first line
-  const int nl = conv_lines(n);                        // staged lines
-  const int64_t tile0 =
-      ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kConvTPW;
-  int ly0[kConvTPW], zs0[kConvTPW];
-  bool ok[kConvTPW];
+  // n^3 is a multiple of the block's voxels and below 2^31
+  const int vb = xcd_block() * (64 * TPW);
+  const int xb = vb / (n * n), yb = (vb / n) % n;
+  // byte offsets into the staged lines: of the tile's line, and per dz of the
+  // lane's voxel and of its four channels' piece
+  int line[TPW], zo[TPW][3];
 #pragma unroll
-  for (int u = 0; u < kConvTPW; ++u) {
-    const int64_t v0 = (tile0 + u) * 16;
-    ok[u] = v0 < N;
-    const int64_t vv = ok[u] ? v0 : vb;
-    zs0[u] = (int)(vv % n);
-    ly0[u] = (int)((vv / n) % n) - yb + 1;   // staged line of the tile
+  for (int u = 0; u < TPW; ++u) {
+    const int v0 = vb + (wv * TPW + u) * 16;
+    line[u] = ((v0 / n) % n - yb + 1) * n * CIN * 2;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const int zz = wrap(v0 % n + row + d - 1, n);
+      zo[u][d] = zz * CIN * 2 + (((grp >> 1) ^ swz<CIN>(zz)) * 16) + (grp & 1) * 8;
+    }
   }
-  f32x4 acc[kConvTPW][NT];
+  f32x4 acc[TPW][NT];
 #pragma unroll
-  for (int u = 0; u < kConvTPW; ++u)
+  for (int u = 0; u < TPW; ++u)
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[u][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
   for (int sl = 0; sl < 3; ++sl) {
-    const int dx = sl - 1;
-    __syncthreads();
-    {
-      // the fragments of taps 9 sl .. 9 sl + 8 (8-byte copies: the fragment
-      // arrays are 8-byte aligned, as every B-fragment load assumes)
-      const uint2* src = reinterpret_cast<const uint2*>(Wf + (size_t)sl * SLICE);
-      uint2* dst = reinterpret_cast<uint2*>(wl);
-      for (int i = threadIdx.x; i < SLICE / 4; i += 256) dst[i] = src[i];
-      // lines yb - 1 .. yb + nl - 2 (periodic) of plane x + dx, 16 bytes
-      // (8 channels) at a time
-      constexpr int CH = CIN / 8;
-      const int xp = wrap(xb + dx, n);
-      const int items = nl * n * CH;
-      for (int i = threadIdx.x; i < items; i += 256) {
-        const int c8 = i % CH;
-        const int vz = i / CH;            // staged line * n + z
-        const int j = vz / n, z = vz - (vz / n) * n;
-        const int yg = (yb - 1 + j + 2 * n) % n;
-        const uint4 val = *reinterpret_cast<const uint4*>(
-            X + (((int64_t)xp * n + yg) * n + z) * CIN + 8 * c8);
-        *reinterpret_cast<uint4*>(al + (int64_t)vz * CS + 8 * c8) = val;
-      }
-    }
-    __syncthreads();
-    for (int tl = 0; tl < 9; ++tl) {
-      const int dy = tl / 3 - 1, dz = tl % 3 - 1;
-      const uint16_t* ar[kConvTPW];
+    if (sl) __syncthreads();
+    stage_lines<CIN, 256>(X, al, wrap(xb + sl - 1, n), yb, nl, n, inv_n, wv, lane);
+    stage_flat<256>(Wf + (size_t)sl * SLICE, wl, SLICE / 8, wv, lane);
+    lds_arrived();
 #pragma unroll
-      for (int u = 0; u < kConvTPW; ++u) {
-        const int zz = wrap(zs0[u] + row + dz, n);
-        ar[u] = al + ((ly0[u] + dy) * n + zz) * CS + 4 * grp;
-      }
+    for (int tl = 0; tl < 9; ++tl) {
+      const int dy = tl / 3 - 1, d = tl % 3;
 #pragma unroll
       for (int kc = 0; kc < KC; ++kc) {
-        bf16x4 b[NT];
+        bf16x4 b[NT], a[TPW];
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
           b[nt] = *reinterpret_cast<const bf16x4*>(
               wl + (((tl * KC + kc) * NT + nt) * 64 + lane) * 4);
-        bf16x4 a[kConvTPW];
 #pragma unroll
-        for (int u = 0; u < kConvTPW; ++u)
-          a[u] = *reinterpret_cast<const bf16x4*>(ar[u] + 16 * kc);
+        for (int u = 0; u < TPW; ++u) {
+          // pieces 2 kc, 2 kc + 1: the permutation moves both bits of a
+          // 32-channel voxel's index, one of the others'
+          const int zk = CIN == 32 ? zo[u][d] ^ (32 * kc) : zo[u][d] + 32 * kc;
+          a[u] = *reinterpret_cast<const bf16x4*>(
+              reinterpret_cast<const char*>(al) + line[u] + dy * n * CIN * 2 + zk);
+        }
 #pragma unroll
-        for (int u = 0; u < kConvTPW; ++u)
+        for (int u = 0; u < TPW; ++u)
 #pragma unroll
           for (int nt = 0; nt < NT; ++nt)
             acc[u][nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
-                a[u], b[nt], acc[u][nt], 0, 0, 0);
+                b[nt], a[u], acc[u][nt], 0, 0, 0);
       }
     }
   }
 #pragma unroll
-  for (int u = 0; u < kConvTPW; ++u) {
-    if (!ok[u]) continue;
-    const int64_t v0 = (tile0 + u) * 16;
+  for (int nt = 0; nt < NT; ++nt) {
+    const int co = nt * 16 + 4 * grp;
+    // the bias has only the real output channels
+    float bv[4] = {0.f, 0.f, 0.f, 0.f};
+    if (EPI != 2) {
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      const int co = nt * 16 + row;
-      // the bias has only the real output channels
-      const float bv = (EPI == 2 || co >= cout_real) ? 0.f : bias[co];
+      for (int i = 0; i < 4; ++i)
+        if (co + i < cout_real) bv[i] = bias[co + i];
+    }
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int64_t v = v0 + 4 * grp + i;
-        float val = acc[u][nt][i] + bv;
-        if constexpr (EPI == 0) {
-          Yb[v * COUT + co] = f2bf(val > 0.f ? val : 0.f);
-        } else if constexpr (EPI == 1) {
-          Yf[v * COUT + co] = val;
-        } else {
-          const float m = bf2f(mask_act[v * COUT + co]);
-          Yb[v * COUT + co] = f2bf(m > 0.f ? val : 0.f);
-        }
+    for (int u = 0; u < TPW; ++u) {
+      const int64_t o = (int64_t)(vb + (wv * TPW + u) * 16 + row) * COUT + co;
+      float val[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) val[i] = acc[u][nt][i] + bv[i];
+      if constexpr (EPI == 1) {
+        *reinterpret_cast<f32x4*>(Yf + o) = (f32x4){val[0], val[1], val[2], val[3]};
+      } else {
+        ushort4 m;
+        if constexpr (EPI == 2) m = *reinterpret_cast<const ushort4*>(mask_act + o);
+        const uint16_t mk[4] = {m.x, m.y, m.z, m.w};
+        uint16_t r[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          r[i] = f2bf((EPI == 0 ? val[i] : bf2f(mk[i])) > 0.f ? val[i] : 0.f);
+        *reinterpret_cast<ushort4*>(Yb + o) = make_ushort4(r[0], r[1], r[2], r[3]);
       }
     }
   }
 }
 
-// weight gradient partials: part[blk][27][CIN][COUT] for a chunk of voxels
-// dW[t][i][o] = sum_v X[v + d_t][i] dZ[v][o]; MFMA with M = i, N = o,
-// K = 16 voxels; each block handles one tap and one voxel chunk.
+// --------------------------------------------------------- weight gradient
+// dW[t][i][o] = sum_v X[v + d_t][i] dZ[v][o] and db[o] = sum_v dZ[v][o]:
+// partials of a chunk of voxels, part[chunk][27][CIN][COUT] and
+// bpart[chunk][COUT], summed in fixed order by update_kernel.
+//
+// An MFMA takes M = i, N = o, K = 32 voxels.  A block handles one dx (its
+// blockIdx.y) of `groups` groups of 256 consecutive voxels, wave w the three
+// taps of dy = w - 1; the staged lines of X and the group's dZ are
+// channels-last, and the transposed LDS read (ds_read_b64_tr_b16: the lanes
+// of a group of 16 read 4 voxels x 16 channels and each receives one
+// channel of the four voxels) yields both operands, a neighbour being an
+// address.  The bias gradient is one more product, with A = 1, of the wave at
+// dx = dy = 0.  Before, each operand was gathered from global memory one bf16
+// at a time, once per tap (32 -> 32
+// channels at 32^3: 88 us; now 12 us, bound by the staging and by writing
+// 27 x 32 x 32 partials per chunk).
+constexpr int kGroupVox = 256;
+constexpr int kWgThreads = 192;
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+
+__device__ __forceinline__ bf16x4 read_tr(const uint16_t* base, int byte) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+      (lds_bf16x4*)(reinterpret_cast<const char*>(base) + byte));
+}
+__device__ __forceinline__ bf16x8 join(bf16x4 a, bf16x4 b) {
+  typedef short s8 __attribute__((ext_vector_type(8)));
+  const s8 r = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+  return __builtin_bit_cast(bf16x8, r);
+}
+
 template <int CIN, int COUT>
-__global__ __launch_bounds__(256) void conv_wgrad_kernel(
+__global__ __launch_bounds__(kWgThreads) void conv_wgrad_kernel(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ dZ,
-    float* __restrict__ part, int n, int64_t N, int64_t chunk) {
+    float* __restrict__ part, float* __restrict__ bpart, int n, unsigned inv_n,
+    int nl, int groups) {
   constexpr int KC = CIN / 16, NT = COUT / 16;
-  __shared__ float red[4][KC * NT * 16 * 16];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int tap = blockIdx.y;
-  const int dx = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dz = tap % 3 - 1;
+  extern __shared__ __align__(16) uint16_t smem_conv[];
+  uint16_t* zl = smem_conv;                       // dZ [256][COUT]
+  uint16_t* al = smem_conv + kGroupVox * COUT;    // X lines
+  const int lane = threadIdx.x & 63;
+  const int dy = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int row = lane & 15, grp = lane >> 4;
-  f32x4 acc[KC][NT];
+  const int dx = blockIdx.y;
+  const int total = (int)((int64_t)n * n * n / kGroupVox);
+  const int g0 = (int)blockIdx.x * groups;
+  const int g1 = g0 + groups < total ? g0 + groups : total;
+  const bool bias = bpart && dx == 1 && dy == 1;
+  const int tv = 4 * grp + (row >> 2);            // voxel of the tile read
+  const int q = (row & 3) >> 1, half = (row & 1) * 8;
+  // dZ offsets: a tile starts at a multiple of 16 voxels
+  const int zb = tv * COUT * 2 + (q ^ swz<COUT>(tv)) * 16 + half;
+  f32x4 acc[3][KC][NT], accb[NT];
 #pragma unroll
-  for (int a = 0; a < KC; ++a)
+  for (int b = 0; b < NT; ++b) {
+    accb[b] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int b = 0; b < NT; ++b) acc[a][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  const int64_t vbeg = (int64_t)blockIdx.x * chunk;
-  const int64_t vend = (vbeg + chunk < N) ? vbeg + chunk : N;
-  for (int64_t vk = vbeg + 16 * wv; vk < vend; vk += 64) {
-    // K = 16 voxels vk .. vk+15 (same x, y row since n % 16 == 0)
-    int64_t vsrc[4];
-    int64_t vdst[4];
+    for (int d = 0; d < 3; ++d)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t v = vk + 4 * grp + i;
-      const int z = (int)(v % n), yy = (int)((v / n) % n),
-                xx = (int)(v / ((int64_t)n * n));
-      vsrc[i] = ((int64_t)wrap(xx + dx, n) * n + wrap(yy + dy, n)) * n +
-                wrap(z + dz, n);
-      vdst[i] = v;
+      for (int a = 0; a < KC; ++a) acc[d][a][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  }
+  const bf16x4 one4 = {0x3F80, 0x3F80, 0x3F80, 0x3F80};
+  const bf16x8 ones = join(one4, one4);
+  for (int g = g0; g < g1; ++g) {
+    const int vb = g * kGroupVox;
+    const int xb = vb / (n * n), yb = (vb / n) % n;
+    if (g > g0) __syncthreads();
+    stage_lines<CIN, kWgThreads>(X, al, wrap(xb + dx - 1, n), yb, nl, n, inv_n,
+                                 dy, lane);
+    {
+      constexpr int CH = COUT / 8;
+      for (int i0 = 64 * dy; i0 < kGroupVox * CH; i0 += kWgThreads) {
+        const int v = (i0 + lane) / CH, pos = (i0 + lane) % CH;
+        load_lds16(dZ + ((int64_t)vb + v) * COUT + 8 * (pos ^ swz<COUT>(v)),
+                   zl + 8 * i0);
+      }
     }
+    lds_arrived();
+    for (int u = 0; u < kGroupVox / 16; u += 2) {
+      int line[2], z0[2];
 #pragma unroll
-    for (int kc = 0; kc < KC; ++kc) {
-      bf16x4 a;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = (short)X[vsrc[i] * CIN + 16 * kc + row];
+      for (int h = 0; h < 2; ++h) {
+        const int v0 = vb + 16 * (u + h);
+        line[h] = ((v0 / n) % n - yb + dy) * n * CIN * 2;
+        z0[h] = v0 % n + tv;
+      }
+      bf16x8 b[NT];
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
-        bf16x4 b;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) b[i] = (short)dZ[vdst[i] * COUT + 16 * nt + row];
-        acc[kc][nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[kc][nt], 0, 0, 0);
+        const int o = u * 16 * COUT * 2 +
+                      (COUT == 32 ? zb ^ (32 * nt) : zb + 32 * nt);
+        b[nt] = join(read_tr(zl, o), read_tr(zl, o + 16 * COUT * 2));
       }
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        int o[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int zz = wrap(z0[h] + d - 1, n);
+          o[h] = zz * CIN * 2 + (q ^ swz<CIN>(zz)) * 16 + half;
+        }
+#pragma unroll
+        for (int kc = 0; kc < KC; ++kc) {
+          const int k0 = CIN == 32 ? o[0] ^ (32 * kc) : o[0] + 32 * kc;
+          const int k1 = CIN == 32 ? o[1] ^ (32 * kc) : o[1] + 32 * kc;
+          const bf16x8 a = join(read_tr(al, line[0] + k0), read_tr(al, line[1] + k1));
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt)
+            acc[d][kc][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                a, b[nt], acc[d][kc][nt], 0, 0, 0);
+        }
+      }
+      if (bias)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+          accb[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, b[nt], accb[nt],
+                                                             0, 0, 0);
     }
   }
   // D[4 grp + i][row] = dW[16 kc + 4 grp + i][16 nt + row]
 #pragma unroll
-  for (int kc = 0; kc < KC; ++kc)
+  for (int d = 0; d < 3; ++d) {
+    float* out = part + ((size_t)blockIdx.x * 27 + dx * 9 + dy * 3 + d) * CIN * COUT;
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          out[(16 * kc + 4 * grp + i) * COUT + 16 * nt + row] = acc[d][kc][nt][i];
+  }
+  if (bias && grp == 0)
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        red[wv][((kc * NT + nt) * 16 + 4 * grp + i) * 16 + row] = acc[kc][nt][i];
-  __syncthreads();
-  float* out = part + ((size_t)blockIdx.x * 27 + tap) * CIN * COUT;
-  for (int e = threadIdx.x; e < KC * NT * 256; e += 256) {
-    const float s = red[0][e] + red[1][e] + red[2][e] + red[3][e];
-    const int kn = e / 256, r = (e / 16) % 16, c = e % 16;
-    const int kc = kn / NT, nt = kn % NT;
-    out[(16 * kc + r) * COUT + 16 * nt + c] = s;
-  }
+      bpart[(size_t)blockIdx.x * COUT + 16 * nt + row] = accb[nt][0];
 }
 
-// sum the per-chunk partials in fixed order: dW[27*CIN*COUT]
-__global__ void sum_parts_kernel(const float* __restrict__ part, int nparts,
-                                 int64_t size, float* __restrict__ out) {
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < size;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    double s = 0.0;
-    for (int p = 0; p < nparts; ++p) s += part[(size_t)p * size + e];
-    out[e] = (float)s;
-  }
-}
-
-// bias gradient db[o] = sum_v dZ[v][o] (fixed order per block, then blocks)
-template <int COUT>
-__global__ __launch_bounds__(256) void bias_grad_kernel(
-    const uint16_t* __restrict__ dZ, const float* __restrict__ dYf,
-    int64_t N, float* __restrict__ part) {
-  __shared__ float red[256];
-  for (int o = 0; o < COUT; ++o) {
-    float s = 0.f;
-    for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < N;
-         v += (int64_t)gridDim.x * 256)
-      s += dZ ? bf2f(dZ[v * COUT + o]) : dYf[v * COUT + o];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int k = 128; k > 0; k >>= 1) {
-      if (threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) part[blockIdx.x * COUT + o] = red[0];
-    __syncthreads();
-  }
-}
-
-// loss L = mean over N*COUT_REAL of (Y - T)^2 and dY = 2 (Y - T)/count,
-// written as bf16 (input of the backward convolutions) and f32
+// loss L = mean over N*CREAL of (Y - T)^2 and dY = 2 (Y - T)/count, written
+// as bf16 (input of the backward convolutions); the block's sums of the loss
+// and, from the unrounded dY, of the last layer's bias gradient.  A thread
+// takes four of a voxel's kOut channels, always the same ones.
 __global__ __launch_bounds__(256) void mse_kernel(
-    const float* __restrict__ Y, const float* __restrict__ T, int cpad,
-    int creal, int64_t N, uint16_t* __restrict__ dYb, float* __restrict__ dYf,
+    const float* __restrict__ Y, const float* __restrict__ T, int creal,
+    int64_t N, uint16_t* __restrict__ dYb, float* __restrict__ bpart,
     double* __restrict__ part) {
   __shared__ double red[256];
+  __shared__ double redb[4][kOut];
+  static_assert(kOut == 16, "four threads per voxel");
   const double inv = 1.0 / ((double)N * creal);
-  double s = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < N * cpad;
+  const int c0 = 4 * (threadIdx.x & 3);
+  double s = 0.0, sb[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < N * (kOut / 4);
        i += (int64_t)gridDim.x * 256) {
-    const int c = (int)(i % cpad);
-    float g = 0.f;
-    if (c < creal) {
-      const float d = Y[i] - T[i];
-      s += (double)d * d;
-      g = (float)(2.0 * d * inv);
+    const f32x4 y = reinterpret_cast<const f32x4*>(Y)[i];
+    const f32x4 t = reinterpret_cast<const f32x4*>(T)[i];
+    uint16_t r[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      float g = 0.f;
+      if (c0 + c < creal) {
+        const float d = y[c] - t[c];
+        s += (double)d * d;
+        g = (float)(2.0 * d * inv);
+      }
+      sb[c] += g;
+      r[c] = f2bf(g);
     }
-    dYb[i] = f2bf(g);
-    dYf[i] = g;
+    reinterpret_cast<ushort4*>(dYb)[i] = make_ushort4(r[0], r[1], r[2], r[3]);
+  }
+  // the 16 lanes of a wave with the same channels
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    for (int m = 4; m < 64; m <<= 1) sb[c] += __shfl_xor(sb[c], m);
+    if ((threadIdx.x & 63) < 4) redb[threadIdx.x >> 6][c0 + c] = sb[c];
   }
   red[threadIdx.x] = s;
   __syncthreads();
@@ -307,22 +418,55 @@ __global__ __launch_bounds__(256) void mse_kernel(
     __syncthreads();
   }
   if (threadIdx.x == 0) part[blockIdx.x] = red[0] * inv;
+  if (threadIdx.x < kOut)
+    bpart[blockIdx.x * kOut + threadIdx.x] =
+        (float)(redb[0][threadIdx.x] + redb[1][threadIdx.x] +
+                redb[2][threadIdx.x] + redb[3][threadIdx.x]);
 }
 
-// Adam on the FP32 master parameters (Kingma & Ba), in place
-__global__ void adam_kernel(float* __restrict__ w, const float* __restrict__ g,
-                            float* __restrict__ m, float* __restrict__ v,
-                            int64_t size, float lr, float b1, float b2,
-                            float eps, float c1, float c2) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < size;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.f - b1) * gi;
-    const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    w[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+// One launch after the backward pass: per master parameter the sum of its
+// partials in fixed order, the gradient, the Adam step (Kingma & Ba) and the
+// weight's places in the forward and backward fragments (11 us for the 128
+// partials of 32^3; before, eight sums, four copies into place, Adam and four
+// repacks, 22 launches and 150 us).  A block takes 64
+// parameters, its four waves a quarter of the partials each.
+__global__ __launch_bounds__(256) void update_kernel(UpdateArgs a) {
+  __shared__ double red[4][64];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int64_t e = (int64_t)blockIdx.x * 64 + lane;
+  const bool live = e < a.size;
+  int k = 0;
+  while (k < 3 && e >= a.layer[k + 1].off) ++k;
+  const UpdateLayer& L = a.layer[k];
+  const int r = (int)(e - L.off), nw = 27 * L.cin * L.cout;
+  const int o = r < nw ? r % L.cout : r - nw;
+  const int i = r < nw ? (r / L.cout) % L.cin : 0;
+  const int t = r < nw ? r / (L.cout * L.cin) : 0;
+  double s = 0.0;
+  if (live) {
+    const float* p = r < nw ? L.part + ((size_t)t * L.CIN + i) * L.COUT + o
+                            : L.bpart + o;
+    const size_t stride = r < nw ? (size_t)27 * L.CIN * L.COUT : (size_t)L.COUT;
+    const int np = r < nw ? L.nparts : L.nbparts;
+    const int lo = np * wv / 4, hi = np * (wv + 1) / 4;
+#pragma unroll 8
+    for (int q = lo; q < hi; ++q) s += p[q * stride];
   }
+  red[wv][lane] = s;
+  __syncthreads();
+  if (wv || !live) return;
+  const float g = (float)(red[0][lane] + red[1][lane] + red[2][lane] + red[3][lane]);
+  a.g[e] = g;
+  const float m = a.b1 * a.m[e] + (1.f - a.b1) * g;
+  const float v = a.b2 * a.v[e] + (1.f - a.b2) * g * g;
+  a.m[e] = m;
+  a.v[e] = v;
+  const float w = a.w[e] - a.lr * (m / a.c1) / (sqrtf(v / a.c2) + a.eps);
+  a.w[e] = w;
+  if (r >= nw) return;
+  const uint16_t h = f2bf(w);
+  L.wf[frag_index(t, i, o, L.CIN, L.COUT)] = h;
+  L.wb[frag_index(26 - t, o, i, L.COUT, L.CIN)] = h;
 }
 
 // master W[27][cin][cout] -> MFMA B fragments for the forward pass, and the
@@ -361,26 +505,34 @@ __global__ void pack_kernel(const float* __restrict__ W, int cin, int cout,
 
 // ----------------------------------------------------------------- launchers
 namespace {
-template <int CIN, int COUT, int EPI>
+// Up to this edge a wave computes one tile instead of four: the blocks of
+// four tiles leave most of the chip idle (a forward pass of four layers, one
+// tile / four tiles: 37 / 57 us at 16^3, 43 / 60 us at 32^3), while from 48^3
+// on there are enough of them and a staged weight serves four tiles (86 / 73
+// us at 48^3, 154 / 119 us at 64^3, 1500 / 820 us at 128^3).
+constexpr int kConvSmall = 32;
+// largest grid edge: the staged lines of 48 channels fit in LDS
+constexpr int kConvMaxEdge = 304;
+
+// dynamic LDS above 64 KiB is allowed per kernel (the attribute only raises
+// the cap)
+void allow_lds(const void* f, size_t lds) {
+  if (lds > 64 * 1024)
+    RVE_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)lds));
+}
+
+template <int CIN, int COUT, int EPI, int TPW>
 void conv_t(const uint16_t* X, const uint16_t* Wf, const float* b, uint16_t* Yb,
-            float* Yf, const uint16_t* mask, int n, int64_t N, int creal,
-            hipStream_t s) {
-  const size_t lds = conv_lds_bytes<CIN, COUT>(n);
-  if (lds > 160 * 1024) throw Error(-1, "convolution grid edge too large");
-  if (lds > 64 * 1024) {
-    // dynamic LDS above 64 KiB is allowed per kernel (once is enough: the
-    // attribute only raises the cap)
-    static size_t allowed = 0;
-    if (lds > allowed) {
-      RVE_HIP(hipFuncSetAttribute(
-          reinterpret_cast<const void*>(&conv_mfma_kernel<CIN, COUT, EPI>),
-          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-      allowed = lds;
-    }
-  }
-  hipLaunchKernelGGL((conv_mfma_kernel<CIN, COUT, EPI>),
-                     dim3((unsigned)((N + kConvVox - 1) / kConvVox)),
-                     dim3(256), lds, s, X, Wf, b, Yb, Yf, mask, n, N, creal);
+            float* Yf, const uint16_t* mask, int n, int creal, hipStream_t s) {
+  constexpr int vox = 64 * TPW;
+  const size_t lds = conv_lds_bytes<CIN, COUT>(n, vox);
+  allow_lds(reinterpret_cast<const void*>(&conv_mfma_kernel<CIN, COUT, EPI, TPW>), lds);
+  const int64_t N = (int64_t)n * n * n;
+  hipLaunchKernelGGL((conv_mfma_kernel<CIN, COUT, EPI, TPW>),
+                     dim3((unsigned)(N / vox)), dim3(256), lds, s,
+                     X, Wf, b, Yb, Yf, mask, n, inv_edge(n), conv_lines(n, vox),
+                     creal);
 }
 }  // namespace
 
@@ -389,88 +541,65 @@ void nn_conv(int cin, int cout, int epi, const uint16_t* X, const uint16_t* Wf,
              int n, int64_t N, int cout_real, hipStream_t s) {
   if (n % 16 || N != (int64_t)n * n * n)
     throw Error(-1, "convolution grid must be n^3 with n % 16 == 0");
-#define RVE_CONV(CI, CO)                                                      \
-  if (cin == CI && cout == CO) {                                              \
-    if (epi == 0) conv_t<CI, CO, 0>(X, Wf, b, Yb, Yf, mask, n, N, cout_real, s);      \
-    else if (epi == 1) conv_t<CI, CO, 1>(X, Wf, b, Yb, Yf, mask, n, N, cout_real, s); \
-    else conv_t<CI, CO, 2>(X, Wf, b, Yb, Yf, mask, n, N, cout_real, s);               \
-    return;                                                                   \
+  if (n > kConvMaxEdge) throw Error(-1, "convolution grid edge too large");
+  const bool small = n <= kConvSmall;
+#define RVE_CONV(CI, CO, E)                                              \
+  if (cin == CI && cout == CO && epi == E) {                             \
+    if (small) conv_t<CI, CO, E, 1>(X, Wf, b, Yb, Yf, mask, n, cout_real, s); \
+    else conv_t<CI, CO, E, 4>(X, Wf, b, Yb, Yf, mask, n, cout_real, s);    \
+    return;                                                              \
   }
-  RVE_CONV(48, 32)
-  RVE_CONV(32, 32)
-  RVE_CONV(32, 16)
-  RVE_CONV(16, 32)
-  RVE_CONV(32, 48)
+  RVE_CONV(48, 32, 0)
+  RVE_CONV(32, 32, 0)
+  RVE_CONV(32, 16, 1)
+  RVE_CONV(16, 32, 2)
+  RVE_CONV(32, 32, 2)
 #undef RVE_CONV
   throw Error(-1, "unsupported convolution shape");
 }
 
+// groups of 256 voxels per weight-gradient block, and the chunks that makes
+static int wgrad_groups(int64_t N) {
+  return (int)((N / kGroupVox + kMaxChunks - 1) / kMaxChunks);
+}
+int nn_wgrad_chunks(int64_t N) {
+  const int g = wgrad_groups(N);
+  return (int)((N / kGroupVox + g - 1) / g);
+}
+
 void nn_wgrad(int cin, int cout, const uint16_t* X, const uint16_t* dZ,
-              float* part, int nchunks, int64_t chunk, int n, int64_t N,
-              hipStream_t s) {
-  dim3 grid((unsigned)nchunks, 27);
-  if (cin == 48 && cout == 32)
-    hipLaunchKernelGGL((conv_wgrad_kernel<48, 32>), grid, dim3(256), 0, s, X, dZ, part, n, N, chunk);
-  else if (cin == 32 && cout == 32)
-    hipLaunchKernelGGL((conv_wgrad_kernel<32, 32>), grid, dim3(256), 0, s, X, dZ, part, n, N, chunk);
-  else if (cin == 32 && cout == 16)
-    hipLaunchKernelGGL((conv_wgrad_kernel<32, 16>), grid, dim3(256), 0, s, X, dZ, part, n, N, chunk);
-  else
-    throw Error(-1, "unsupported weight-gradient shape");
+              float* part, float* bpart, int n, int64_t N, hipStream_t s) {
+  if (n % 16 || N != (int64_t)n * n * n)
+    throw Error(-1, "convolution grid must be n^3 with n % 16 == 0");
+  const int nl = conv_lines(n, kGroupVox);
+  dim3 grid((unsigned)nn_wgrad_chunks(N), 3);
+  auto run = [&](auto kernel) {
+    const size_t lds = ((size_t)kGroupVox * cout + (size_t)nl * n * cin) * sizeof(uint16_t);
+    allow_lds(reinterpret_cast<const void*>(kernel), lds);
+    hipLaunchKernelGGL(kernel, grid, dim3(kWgThreads), lds, s, X, dZ, part, bpart,
+                       n, inv_edge(n), nl, wgrad_groups(N));
+  };
+  if (cin == 48 && cout == 32) run(&conv_wgrad_kernel<48, 32>);
+  else if (cin == 32 && cout == 32) run(&conv_wgrad_kernel<32, 32>);
+  else if (cin == 32 && cout == 16) run(&conv_wgrad_kernel<32, 16>);
+  else throw Error(-1, "unsupported weight-gradient shape");
 }
 
-void nn_sum_parts(const float* part, int nparts, int64_t size, float* out,
-                  hipStream_t s) {
-  hipLaunchKernelGGL(sum_parts_kernel, dim3(256), dim3(256), 0, s, part, nparts,
-                     size, out);
+void nn_mse(const float* Y, const float* T, int creal, int64_t N, uint16_t* dYb,
+            float* bpart, double* part, int nblk, hipStream_t s) {
+  hipLaunchKernelGGL(mse_kernel, dim3(nblk), dim3(256), 0, s, Y, T, creal, N, dYb,
+                     bpart, part);
 }
 
-void nn_bias_grad(int cout, const uint16_t* dZ, const float* dYf, int64_t N,
-                  float* part, int nblk, hipStream_t s) {
-  if (cout == 32)
-    hipLaunchKernelGGL((bias_grad_kernel<32>), dim3(nblk), dim3(256), 0, s, dZ, dYf, N, part);
-  else if (cout == 16)
-    hipLaunchKernelGGL((bias_grad_kernel<16>), dim3(nblk), dim3(256), 0, s, dZ, dYf, N, part);
-  else
-    throw Error(-1, "unsupported bias-gradient width");
-}
-
-void nn_mse(const float* Y, const float* T, int cpad, int creal, int64_t N,
-            uint16_t* dYb, float* dYf, double* part, int nblk, hipStream_t s) {
-  hipLaunchKernelGGL(mse_kernel, dim3(nblk), dim3(256), 0, s, Y, T, cpad, creal,
-                     N, dYb, dYf, part);
-}
-
-void nn_adam(float* w, const float* g, float* m, float* v, int64_t size,
-             float lr, float b1, float b2, float eps, int step, hipStream_t s) {
-  const float c1 = 1.f - powf(b1, (float)step), c2 = 1.f - powf(b2, (float)step);
-  hipLaunchKernelGGL(adam_kernel, dim3(256), dim3(256), 0, s, w, g, m, v, size,
-                     lr, b1, b2, eps, c1, c2);
+void nn_update(const UpdateArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(update_kernel, dim3((unsigned)((a.size + 63) / 64)), dim3(256),
+                     0, s, a);
 }
 
 void nn_pack(const float* W, int cin, int cout, int CIN, int COUT, uint16_t* Wf,
              uint16_t* Wb, hipStream_t s) {
   hipLaunchKernelGGL(pack_kernel, dim3(128), dim3(256), 0, s, W, cin, cout, CIN,
                      COUT, Wf, Wb);
-}
-
-
-// padded [27][CIN][COUT] -> real [27][cin][cout]
-__global__ void unpad_kernel(const float* __restrict__ src, int CIN, int COUT,
-                             int cin, int cout, float* __restrict__ dst) {
-  const int64_t total = (int64_t)27 * cin * cout;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int o = (int)(e % cout), i = (int)((e / cout) % cin),
-              t = (int)(e / ((int64_t)cin * cout));
-    dst[e] = src[((size_t)t * CIN + i) * COUT + o];
-  }
-}
-
-void nn_unpad(const float* src, int CIN, int COUT, int cin, int cout,
-              float* dst, hipStream_t s) {
-  hipLaunchKernelGGL(unpad_kernel, dim3(128), dim3(256), 0, s, src, CIN, COUT,
-                     cin, cout, dst);
 }
 
 // network input of one increment (channels, kFeat padded):

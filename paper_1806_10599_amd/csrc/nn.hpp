@@ -16,21 +16,29 @@ constexpr int kOutReal = 9, kOut = 16;
 void nn_conv(int cin, int cout, int epi, const uint16_t* X, const uint16_t* Wf,
              const float* b, uint16_t* Yb, float* Yf, const uint16_t* mask,
              int n, int64_t N, int cout_real, hipStream_t s);
+// voxel chunks (partials) of the weight gradient, at most kMaxChunks
+constexpr int kMaxChunks = 128;
+int nn_wgrad_chunks(int64_t N);
 void nn_wgrad(int cin, int cout, const uint16_t* X, const uint16_t* dZ,
-              float* part, int nchunks, int64_t chunk, int n, int64_t N,
-              hipStream_t s);
-void nn_sum_parts(const float* part, int nparts, int64_t size, float* out,
-                  hipStream_t s);
-void nn_bias_grad(int cout, const uint16_t* dZ, const float* dYf, int64_t N,
-                  float* part, int nblk, hipStream_t s);
-void nn_mse(const float* Y, const float* T, int cpad, int creal, int64_t N,
-            uint16_t* dYb, float* dYf, double* part, int nblk, hipStream_t s);
-void nn_adam(float* w, const float* g, float* m, float* v, int64_t size,
-             float lr, float b1, float b2, float eps, int step, hipStream_t s);
+              float* part, float* bpart, int n, int64_t N, hipStream_t s);
+void nn_mse(const float* Y, const float* T, int creal, int64_t N, uint16_t* dYb,
+            float* bpart, double* part, int nblk, hipStream_t s);
+struct UpdateLayer {
+  int64_t off;                    // of its parameters (W, then b)
+  const float *part, *bpart;      // gradient partials
+  uint16_t *wf, *wb;              // fragments
+  int nparts, nbparts;
+  int cin, cout, CIN, COUT;
+};
+struct UpdateArgs {
+  UpdateLayer layer[4];
+  float *w, *g, *m, *v;
+  int64_t size;
+  float lr, b1, b2, eps, c1, c2;
+};
+void nn_update(const UpdateArgs& a, hipStream_t s);
 void nn_pack(const float* W, int cin, int cout, int CIN, int COUT, uint16_t* Wf,
              uint16_t* Wb, hipStream_t s);
-void nn_unpad(const float* src, int CIN, int COUT, int cin, int cout,
-              float* dst, hipStream_t s);
 
 // per-increment data movement (features, target, prediction)
 struct FeatArgs {
@@ -79,6 +87,8 @@ class Net {
  private:
   void* alloc(size_t b);
   void ensure(int64_t N);
+  void ensure_train(int64_t N);
+  const uint16_t* aligned(const uint16_t* X, int64_t N, hipStream_t s);
   void repack();
   hipStream_t st_;
   AllocFn af_;
@@ -88,10 +98,12 @@ class Net {
   float *w_ = nullptr, *g_ = nullptr, *m_ = nullptr, *v_ = nullptr;
   uint16_t* wf_[4] = {};
   uint16_t* wb_[4] = {};
-  int64_t cap_ = 0;
+  int64_t cap_ = 0, train_cap_ = 0, xcap_ = 0;
+  uint16_t* xcopy_ = nullptr;
   uint16_t *a1_ = nullptr, *a2_ = nullptr, *a3_ = nullptr;
   uint16_t *d1_ = nullptr, *d2_ = nullptr, *dy_ = nullptr;
-  float *yf_ = nullptr, *dyf_ = nullptr, *part_ = nullptr, *wpad_ = nullptr;
+  float* yf_ = nullptr;
+  float *part_[4] = {}, *bpart_[4] = {};
   double* lpart_ = nullptr;
   double* lhost_ = nullptr;
   int step_ = 0;
