@@ -189,10 +189,8 @@ void BatchEngine::build_tables() {
     const int nb = n_[b], nvb = nb * nb * nb / kBlock;
     auto fill = [&](auto& it, BatchGrid& g, bool dbl, int& cpbs) {
       using T = std::remove_reference_t<decltype(it.tw[0].x)>;
-      int cpb = 0, tt = 0;
-      default_schedule(nb, dbl, cpb, tt);
+      int cpb = 1, tt = cg_tile(nb);
       if (dbl == fp64_) {
-        tt = cg_tile(nb);
         auto f = sched_.find(nb);
         if (f != sched_.end() && f->second[0]) {
           cpb = f->second[0];
@@ -216,7 +214,7 @@ void BatchEngine::build_tables() {
       it.vt = (const T*)(dbl ? vt64_ : vt32_) + vtoff_[b];
       it.pkp = partials_ + pp;
       it.prr = it.pkp + nvb;
-      g.A += slab_blocks(nb, dbl, cpb);
+      g.A += slab_blocks(nb, cpb);
       g.V = (int)(Nt_ / kBlock);
       g.B += it.npen;
       size_t s1, s2;
@@ -311,7 +309,7 @@ void BatchEngine::autotune() {
           it.npen = cg_pencil_blocks(e, tt);
           it.blk[0] = c.g.A;
           it.blk[1] = c.g.B;
-          c.g.A += slab_blocks(e, dbl, cpb);
+          c.g.A += slab_blocks(e, cpb);
           c.g.B += it.npen;
           c.items.push_back(it);
         }

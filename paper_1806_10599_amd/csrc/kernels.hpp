@@ -39,7 +39,14 @@ struct PencilArgs {
   const cplx<T>* tw;
   const T* vt;         // [3][N] wave-vector components per axis
   T invN3;
-  const Scalars* sc;   // optional early exit
+};
+
+// Tables that pass A of a projection computes and writes (tw null: none)
+struct ProjTables {
+  cplx<double>* tw = nullptr;
+  double* vt = nullptr;
+  double L0 = 1.0, L1 = 1.0, L2 = 1.0;
+  bool continuous = false;
 };
 
 // CG vectors per frequency: see pencil_fwd_body and pencil_inv_body
@@ -85,7 +92,7 @@ struct SlabInvArgs {
   const T* vt = nullptr;    // DST_P, DST_ADDF: wave vectors
 };
 
-// G of a field (default schedule)
+// G of a field
 template <typename T>
 struct SpectralLaunch {
   const T* in_field = nullptr;
@@ -94,6 +101,7 @@ struct SpectralLaunch {
   const T* vt = nullptr;
   double* out_d = nullptr;
   double* partial_inv = nullptr;
+  ProjTables tables;
 };
 
 // Passes of a single-RVE CG iteration in launch order: the direction (inverse
@@ -150,9 +158,8 @@ void launch_G(int n, const SpectralLaunch<T>& L, hipStream_t s);
 // G in FP64 with the static scratch array of noalloc.hip (no allocation)
 void noalloc_apply_G(int n, const double L[3], int projection, const double* in,
                      double* out, hipStream_t s);
-// block counts of the slab (A, C) and pencil (B) grids; 0 = default schedule
-int slab_blocks(int n, bool fp64, int cpb = 0);
-int pencil_blocks(int n, bool fp64, int tt = 0);
+// blocks of the slab grids
+int slab_blocks(int n, int cpb);
 // whether a (cpb, tt) schedule exists for the grid edge and precision
 bool schedule_valid(int n, bool fp64, int cpb, int tt);
 
@@ -222,7 +229,6 @@ void launch_cg_final_batch(const BatchSpec<T>& b, double* F, const BatchGrid& g,
 // under a schedule (throws for an invalid one)
 template <typename T>
 void batch_lds(int n, int cpb, int tt, size_t& slab, size_t& pencil);
-void default_schedule(int n, bool fp64, int& cpb, int& tt);
 
 
 bool batch_supported(int n);

@@ -51,34 +51,6 @@ unsigned char* scratch_ptr() {
   return g_ptr[dev];
 }
 
-// FFT twiddles exp(-2 pi i m / n) and the per-axis wave vectors of the
-// operator (Sec. 2.2, Eq. 18; continuous Eq. 19: v = q n / L, discrete
-// Eqs. 20-21: v = tan(q / 2) n / L; the Nyquist entry is never used and is
-// set to 0), the tables the FP64 passes read.
-__global__ void noalloc_tables_kernel(int n, double L0, double L1, double L2,
-                                      int projection, cplx<double>* tw,
-                                      double* vt) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) {
-    double s, c;
-    sincospi(-2.0 * (double)i / (double)n, &s, &c);
-    tw[i] = {c, s};
-  }
-  if (i < 3 * n) {
-    const int d = i / n, idx = i - d * n;
-    const int k = (idx < (n + 1) / 2) ? idx : idx - n;
-    const double Ld = d == 0 ? L0 : (d == 1 ? L1 : L2);
-    double v = 0.0;
-    if (!(n % 2 == 0 && k == -n / 2)) {
-      const double scale = (double)n / Ld;
-      v = projection == RVE_PROJ_CONTINUOUS
-              ? 2.0 * M_PI * (double)k / (double)n * scale
-              : tan(M_PI * (double)k / (double)n) * scale;
-    }
-    vt[i] = v;
-  }
-}
-
 }  // namespace
 
 void noalloc_apply_G(int n, const double L[3], int projection, const double* in,
@@ -99,11 +71,10 @@ void noalloc_apply_G(int n, const double L[3], int projection, const double* in,
   unsigned char* base = scratch_ptr();
   cplx<double>* tw = (cplx<double>*)(base + kTwOff);
   double* vt = (double*)(base + kVtOff);
-  hipLaunchKernelGGL(noalloc_tables_kernel, dim3(1), dim3(256), 0, s, n, L[0],
-                     L[1], L[2], projection, tw, vt);
   SpectralLaunch<double> G;
   G.in_field = in;
   G.spec = (cplx<double>*)(base + kSpecOff);
+  G.tables = ProjTables{tw, vt, L[0], L[1], L[2], projection == RVE_PROJ_CONTINUOUS};
   G.tw = tw;
   G.vt = vt;
   G.out_d = out;
