@@ -137,7 +137,7 @@ __device__ __forceinline__ bool stopped_now(int32_t f) {
 // lb: logical block within this RVE's pass-A grid
 // gate: the run's scalars when the pass must return at once on a stopped
 // run (returns false then); with SRC_KROW the check precedes all work
-template <typename T, int N, int CPB, int SRC>
+template <typename T, int N, int CPB, int SRC, int NT = kBlock>
 __device__ __forceinline__ bool slab_fwd_body(const SlabFwdArgs<T>& a, int lb,
                                               cplx<T>* lds, cplx<T>* tw,
                                               double* red,
@@ -149,7 +149,7 @@ __device__ __forceinline__ bool slab_fwd_body(const SlabFwdArgs<T>& a, int lb,
   const int grp = lb - x * NG;
   const int32_t stopped = stop_flag(gate);
   if (SRC != SRC_FIELD && stopped_now(stopped)) return false;
-  constexpr int PER0 = (H * N + kBlock - 1) / kBlock;
+  constexpr int PER0 = (H * N + NT - 1) / NT;
   TwiddleStage<T, N, SRC == SRC_FIELD && kDeferTw<T, N>(PER0)> tws;
   if (a.tw) tws.load(a.tw, tw);   // else the kernel has filled tw
   double ss[CPB], s1[CPB];
@@ -161,13 +161,13 @@ __device__ __forceinline__ bool slab_fwd_body(const SlabFwdArgs<T>& a, int lb,
   if constexpr (SRC == SRC_FIELD) {
     // the loads of a chunk of items are issued together, then the chunk is
     // written to LDS (same per-thread order of the sums as item by item)
-    constexpr int PER = (H * N + kBlock - 1) / kBlock;
+    constexpr int PER = (H * N + NT - 1) / NT;
     constexpr int CH = PER < kStage<T, N> ? PER : kStage<T, N>;
     for (int c0 = 0; c0 < PER; c0 += CH) {
       T val[CH][2][CPB];
 #pragma unroll
       for (int u = 0; u < CH; ++u) {
-        const int t = threadIdx.x + (c0 + u) * kBlock;
+        const int t = threadIdx.x + (c0 + u) * NT;
         if (c0 + u < PER && t < H * N) {
           const int yp = t / N, z = t - (t / N) * N;
 #pragma unroll
@@ -181,7 +181,7 @@ __device__ __forceinline__ bool slab_fwd_body(const SlabFwdArgs<T>& a, int lb,
       }
 #pragma unroll
       for (int u = 0; u < CH; ++u) {
-        const int t = threadIdx.x + (c0 + u) * kBlock;
+        const int t = threadIdx.x + (c0 + u) * NT;
         if (c0 + u < PER && t < H * N) {
           const int yp = t / N, z = t - (t / N) * N;
 #pragma unroll
@@ -203,7 +203,7 @@ __device__ __forceinline__ bool slab_fwd_body(const SlabFwdArgs<T>& a, int lb,
   double kacc[CPB];  // p . (K:p) of each component over the slab
 #pragma unroll
   for (int q = 0; q < CPB; ++q) kacc[q] = 0.0;
-  for (int t = threadIdx.x; SRC == SRC_KROW && t < H * N; t += blockDim.x) {
+  for (int t = threadIdx.x; SRC == SRC_KROW && t < H * N; t += NT) {
     const int yp = t / N, z = t - (t / N) * N;
     T out[2][CPB];
 #pragma unroll
@@ -269,7 +269,7 @@ __device__ __forceinline__ bool slab_fwd_body(const SlabFwdArgs<T>& a, int lb,
   fft_lines<N, -1>(lds, tw, CPB * H, RowMap<N>());
 
   // unpack the two real-row spectra in place
-  for (int t = threadIdx.x; t < CPB * H * H; t += blockDim.x) {
+  for (int t = threadIdx.x; t < CPB * H * H; t += NT) {
     const int q = t / (H * H);
     const int rem = t - q * H * H;
     const int yp = rem / H, k = rem - (rem / H) * H;
@@ -293,7 +293,7 @@ __device__ __forceinline__ bool slab_fwd_body(const SlabFwdArgs<T>& a, int lb,
 
   // store the spectrum [c][x][ky][kz]
   const ColMap<N> cm;
-  for (int t = threadIdx.x; t < CPB * N * H; t += blockDim.x) {
+  for (int t = threadIdx.x; t < CPB * N * H; t += NT) {
     const int q = t / (N * H);
     const int rem = t - q * N * H;
     const int ky = rem / H, kz = rem - (rem / H) * H;
@@ -726,7 +726,7 @@ __device__ __forceinline__ void pencil_inv_body(const PencilInvArgs<T>& a,
 // It reads the planes that pencil_body and pencil_inv_body write: component
 // 3 i + j is v_j times a spectrum of row i, of which the planes 3 i (j = 0,
 // with v_x applied) and 3 i + 1 are stored.
-template <typename T, typename TO, int N, int CPB, int DST>
+template <typename T, typename TO, int N, int CPB, int DST, int NT = kBlock>
 __device__ __forceinline__ bool slab_inv_body(const SlabInvArgs<T, TO>& a,
                                               int lb, cplx<T>* lds,
                                               cplx<T>* tw, double* red,
@@ -737,7 +737,7 @@ __device__ __forceinline__ bool slab_inv_body(const SlabInvArgs<T, TO>& a,
   const int x = lb / NG;
   const int grp = lb - x * NG;
   const int32_t stopped = stop_flag(gate);
-  constexpr int PER0 = (CPB * N * H + kBlock - 1) / kBlock;
+  constexpr int PER0 = (CPB * N * H + NT - 1) / NT;
   TwiddleStage<T, N, kDeferTw<T, N>(PER0)> tws;
   tws.load(a.tw, tw);
   const ColMap<N> cm;
@@ -748,7 +748,7 @@ __device__ __forceinline__ bool slab_inv_body(const SlabInvArgs<T, TO>& a,
       cplx<T> val[CH];
 #pragma unroll
       for (int u = 0; u < CH; ++u) {
-        const int t = threadIdx.x + (c0 + u) * kBlock;
+        const int t = threadIdx.x + (c0 + u) * NT;
         if (c0 + u < PER && t < CPB * N * H) {
           const int q = t / (N * H);
           const int rem = t - q * N * H;
@@ -760,7 +760,7 @@ __device__ __forceinline__ bool slab_inv_body(const SlabInvArgs<T, TO>& a,
       }
 #pragma unroll
       for (int u = 0; u < CH; ++u) {
-        const int t = threadIdx.x + (c0 + u) * kBlock;
+        const int t = threadIdx.x + (c0 + u) * NT;
         if (c0 + u < PER && t < CPB * N * H) {
           const int q = t / (N * H);
           const int rem = t - q * N * H;
@@ -781,7 +781,7 @@ __device__ __forceinline__ bool slab_inv_body(const SlabInvArgs<T, TO>& a,
   fft_lines<N, +1>(lds, tw, CPB * H, ColMap<N>());
 
   // pack the two half spectra of rows y' and y'+H into one complex line
-  for (int t = threadIdx.x; t < CPB * H * H; t += blockDim.x) {
+  for (int t = threadIdx.x; t < CPB * H * H; t += NT) {
     const int q = t / (H * H);
     const int rem = t - q * H * H;
     const int yp = rem / H, k = rem - (rem / H) * H;
@@ -800,7 +800,7 @@ __device__ __forceinline__ bool slab_inv_body(const SlabInvArgs<T, TO>& a,
   fft_lines<N, +1>(lds, tw, CPB * H, RowMap<N>());
 
   double acc = 0.0;
-  for (int t = threadIdx.x; t < H * N; t += kBlock) {
+  for (int t = threadIdx.x; t < H * N; t += NT) {
     const int yp = t / N, z = t - (t / N) * N;
 #pragma unroll
     for (int q = 0; q < CPB; ++q) {
@@ -833,18 +833,30 @@ template <int N>
 constexpr int kTile = N < 64 ? 4 : 8;
 
 // ---------------------------------------------------- single-RVE kernels
+// Threads of a slab block: 512 where a radix pass of the plane has more than
+// 256 butterflies (48^3: 384, 96^3: 1536, 128^3: 1024), so that 256 threads
+// go through it in several barrier-separated chunks.  Passes A + C, 256 / 512
+// threads: FP32 48^3 15.8 / 14.6 us, 96^3 59.4 / 54.9, 128^3 106.8 / 76.8;
+// FP64 19.2 / 18.1, 101.7 / 90.1, 216.5 / 179.7.  At 64^3 (256 butterflies)
+// half of 512 threads would idle: FP32 16.1 / 19.5, FP64 23.6 / 29.3; 1024
+// threads lose at 96^3 and 128^3 (58.3, 109.9).
+template <typename T, int N>
+constexpr int kSlabThreads = N == 48 || N >= 96 ? 512 : kBlock;
+
 template <typename T, int N, int CPB, int SRC>
-__global__ __launch_bounds__(kBlock) void slab_fwd_kernel(SlabFwdArgs<T> a) {
+__global__ __launch_bounds__((kSlabThreads<T, N>)) void slab_fwd_kernel(
+    SlabFwdArgs<T> a) {
+  constexpr int NT = kSlabThreads<T, N>;
   __shared__ cplx<T> lds[CPB * SlabGeom<N>::PLANE];
   __shared__ cplx<T> tw[N];
-  __shared__ double red[kBlock];
+  __shared__ double red[NT / 64];
   // done comes from an earlier launch, except after a breakdown that block
   // 0 of this launch publishes at its end (cg_alpha_publish): blocks that
   // read done before that write and go on only fill the spectrum, which
   // the passes of a stopped run never read (they return on done).  The body
   // reads it and returns once its loads are issued.
-  if (!slab_fwd_body<T, N, CPB, SRC>(a, xcd_remap(blockIdx.x, gridDim.x), lds,
-                                     tw, red, a.sc))
+  if (!slab_fwd_body<T, N, CPB, SRC, NT>(a, xcd_remap(blockIdx.x, gridDim.x),
+                                         lds, tw, red, a.sc))
     return;
   if (a.pkp && blockIdx.x == 0)
     cg_alpha_publish(a.pkp, a.pkp_count, a.scw, a.parity, red);
@@ -864,11 +876,12 @@ __global__ __launch_bounds__(kBlock) void pencil_proj_kernel(PencilArgs<T> a) {
 // the passes that follow.  A launch of its own for them cost 4 us of the 18
 // of a 16^3 projection.
 template <int N>
-__global__ __launch_bounds__(kBlock) void slab_fwd_tables_kernel(
+__global__ __launch_bounds__((kSlabThreads<double, N>)) void slab_fwd_tables_kernel(
     SlabFwdArgs<double> a, ProjTables p) {
+  constexpr int NT = kSlabThreads<double, N>;
   __shared__ cplx<double> lds[SlabGeom<N>::PLANE];
   __shared__ cplx<double> tw[N];
-  __shared__ double red[kBlock];
+  __shared__ double red[NT / 64];
   const int i = threadIdx.x;
   if (i < N) {
     double sn, cs;
@@ -877,7 +890,7 @@ __global__ __launch_bounds__(kBlock) void slab_fwd_tables_kernel(
     if (blockIdx.x == 0) p.tw[i] = {cs, sn};
   }
   if (blockIdx.x == 0)
-    for (int t = i; t < 3 * N; t += kBlock) {
+    for (int t = i; t < 3 * N; t += NT) {
       const int d = t / N, idx = t - d * N;
       const int k = idx < N / 2 ? idx : idx - N;
       const double scale = (double)N / (d == 0 ? p.L0 : (d == 1 ? p.L1 : p.L2));
@@ -885,8 +898,8 @@ __global__ __launch_bounds__(kBlock) void slab_fwd_tables_kernel(
                 : p.continuous ? 2.0 * M_PI * (double)k / (double)N * scale
                                : tan(M_PI * (double)k / (double)N) * scale;
     }
-  slab_fwd_body<double, N, 1, SRC_FIELD>(a, xcd_remap(blockIdx.x, gridDim.x), lds,
-                                         tw, red);
+  slab_fwd_body<double, N, 1, SRC_FIELD, NT>(a, xcd_remap(blockIdx.x, gridDim.x),
+                                             lds, tw, red);
 }
 
 // threads of a CG pencil block: 512 once a block has as many frequencies
@@ -929,12 +942,14 @@ __global__ __launch_bounds__((kPencilThreads<N, TT>)) void pencil_inv_kernel(
 }
 
 template <typename T, typename TO, int N, int CPB, int DST>
-__global__ __launch_bounds__(kBlock) void slab_inv_kernel(SlabInvArgs<T, TO> a) {
+__global__ __launch_bounds__((kSlabThreads<T, N>)) void slab_inv_kernel(
+    SlabInvArgs<T, TO> a) {
+  constexpr int NT = kSlabThreads<T, N>;
   __shared__ cplx<T> lds[CPB * SlabGeom<N>::PLANE];
   __shared__ cplx<T> tw[N];
-  __shared__ double red[kBlock];
-  slab_inv_body<T, TO, N, CPB, DST>(a, xcd_remap(blockIdx.x, gridDim.x), lds,
-                                    tw, red, a.sc);
+  __shared__ double red[NT / 64];
+  slab_inv_body<T, TO, N, CPB, DST, NT>(a, xcd_remap(blockIdx.x, gridDim.x), lds,
+                                        tw, red, a.sc);
 }
 
 // three component planes per slab block fit the LDS budget of one block
@@ -1394,13 +1409,13 @@ void launch_G_n(const SpectralLaunch<T>& L, hipStream_t s) {
   fa.spec = L.spec;
   if constexpr (sizeof(T) == 8 && N <= RVE_NOALLOC_MAX_N) {
     if (L.tables.tw)
-      launch((slab_fwd_tables_kernel<N>), dim3(9 * N), dim3(kBlock), 0, s, fa,
-             L.tables);
+      launch((slab_fwd_tables_kernel<N>), dim3(9 * N), dim3(kSlabThreads<T, N>), 0,
+             s, fa, L.tables);
   }
   if (!L.tables.tw) {
     fa.tw = L.tw;
-    launch((slab_fwd_kernel<T, N, 1, SRC_FIELD>), dim3(9 * N), dim3(kBlock), 0, s,
-           fa);
+    launch((slab_fwd_kernel<T, N, 1, SRC_FIELD>), dim3(9 * N),
+           dim3(kSlabThreads<T, N>), 0, s, fa);
   }
   PencilArgs<T> pa{};
   pa.spec = L.spec;
@@ -1416,8 +1431,8 @@ void launch_G_n(const SpectralLaunch<T>& L, hipStream_t s) {
   ia.vt = L.vt;
   ia.out = L.out_d;
   ia.partial = L.partial_inv;
-  launch((slab_inv_kernel<T, double, N, 1, DST_NORM>), dim3(9 * N), dim3(kBlock), 0,
-         s, ia);
+  launch((slab_inv_kernel<T, double, N, 1, DST_NORM>), dim3(9 * N),
+         dim3(kSlabThreads<T, N>), 0, s, ia);
 }
 
 // the passes of a CG iteration (mask: kPassDir .. kPassRes) or the end of
@@ -1457,8 +1472,8 @@ void launch_cg_sched(const CgLaunch<T>& L, int mask, hipStream_t s) {
     a.vt = L.vt;
     a.out = L.p;
     a.sc = L.sc;
-    launch((slab_inv_kernel<T, T, N, CPB, DST_P>), dim3(nslab), dim3(kBlock),
-           0, s, a);
+    launch((slab_inv_kernel<T, T, N, CPB, DST_P>), dim3(nslab),
+           dim3(kSlabThreads<T, N>), 0, s, a);
   }
   if (mask & kPassFinal) {
     SlabInvArgs<T, double> a{};
@@ -1468,7 +1483,7 @@ void launch_cg_sched(const CgLaunch<T>& L, int mask, hipStream_t s) {
     a.vt = L.vt;
     a.out = L.F;
     launch((slab_inv_kernel<T, double, N, CPB, DST_ADDF>), dim3(nslab),
-           dim3(kBlock), 0, s, a);
+           dim3(kSlabThreads<T, N>), 0, s, a);
   }
   if (mask & kPassA) {
     SlabFwdArgs<T> a{};
@@ -1481,8 +1496,8 @@ void launch_cg_sched(const CgLaunch<T>& L, int mask, hipStream_t s) {
       a.K = L.K;
       a.kfull = L.kfull;
       a.pkp_out = L.pkp;
-      launch((slab_fwd_kernel<T, N, CPB, SRC_KROW>), dim3(nslab), dim3(kBlock),
-             0, s, a);
+      launch((slab_fwd_kernel<T, N, CPB, SRC_KROW>), dim3(nslab),
+             dim3(kSlabThreads<T, N>), 0, s, a);
     } else {
       a.field = L.y;
       if (L.prr) {
@@ -1492,7 +1507,7 @@ void launch_cg_sched(const CgLaunch<T>& L, int mask, hipStream_t s) {
         a.scw = L.sc;
       }
       launch((slab_fwd_kernel<T, N, CPB, SRC_FIELD>), dim3(nslab),
-             dim3(kBlock), 0, s, a);
+             dim3(kSlabThreads<T, N>), 0, s, a);
     }
   }
   if (mask & kPassRes) {
@@ -1530,7 +1545,7 @@ void launch_residual_n(const ResidualLaunch<TR>& L, hipStream_t s) {
   fa.psum = L.psum;
   fa.psq = L.psq;
   launch((slab_fwd_kernel<double, N, 1, SRC_FIELD>), dim3(9 * N),
-         dim3(kBlock), 0, s, fa);
+         dim3(kSlabThreads<double, N>), 0, s, fa);
   PencilFwdArgs<double, TR> a{};
   a.spec = L.spec;
   a.tw = L.tw;
