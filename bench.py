@@ -73,13 +73,13 @@ def live_classes(fused):
 # algorithmic flops of the return mapping (add, mul, div, sqrt and each
 # elementary function count 1, a fused multiply-add 2; counted once per voxel
 # from the algorithm, not from the instruction stream), FP64 and FP32 apart:
-# per residual evaluation (plastic and elastic deformation, stress, 12
-# resolved shears, back stresses, the one-logarithm residuals; FP32 flow
-# slopes), per local Newton step (FP32 Jacobian: 12 rank-one updates of the
-# 6x6 capacitance matrix, its LU factorisation, the Woodbury solve; FP64
-# step and convergence tests), per crystal voxel (set-up, final Fp^-1 and
-# P) and per particle voxel
-RM_FLOPS = {"eval64": 1206, "eval32": 72, "step64": 60, "step32": 2350,
+# per residual evaluation in the lattice frame (slip sum, elastic strain, 12
+# resolved shears, back stresses, residuals near their root; FP32 flow slopes
+# and Q), per local Newton step (FP32 Jacobian: 12 updates of the 5x5
+# capacitance matrix, its elimination, the Woodbury solve; FP64 step and
+# convergence tests), per crystal voxel (set-up, final Fp^-1 and P) and per
+# particle voxel
+RM_FLOPS = {"eval64": 770, "eval32": 130, "step64": 60, "step32": 1380,
             "crystal64": 825, "particle64": 90}
 # kernel classes timed live in the timed region: the K:p kernel
 # (the dominant kernel, on a sample of its launches) and the return mapping

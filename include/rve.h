@@ -445,9 +445,10 @@ rve_status rve_get_return_map_counts(rve_t h, int64_t out[4], int32_t reset);
    or 16), and fused (0 or 1): whether K : p runs in its own streaming
    kernel (0) or inside the forward z/y transform (1), each block of which
    then forms its own rows of K : p.  All give the same CG up to the order
-   of the FP64 sums.  By default (0, 0, -) the handle times the schedules of
-   its grid edge (both cpb, both fused) once on its own buffers at the first
-   CG solve and keeps the fastest.
+   of the FP64 sums.  By default (0, 0, -) the handle times the schedules
+   that can win at its grid edge (both cpb and both fused up to 16; above,
+   one component and K : p in its own kernel) once on its own buffers at the
+   first CG solve and keeps the fastest.
    rve_set_fft_schedule forces one (or (0, 0, -) to tune again);
    RVE_EINVAL when the schedule does not exist for the grid and precision or
    fused is not 0 or 1.  rve_get_fft_schedule writes (cpb, tt, fused) in use
