@@ -80,44 +80,47 @@ void launch_convert(const double* in, T* out, int64_t n, hipStream_t s) {
                      out, n);
 }
 
-// The scalars of an FP64 residual, one block, fixed order: r.r and r.z of the
-// CG start and ||G(P)||^2 from 3 x count partials, ||P||^2 and <P>
+// The scalars of an FP64 residual, fixed order: r.r and r.z of the CG start
+// and ||G(P)||^2 from 3 x count partials, ||P||^2 and <P>.  One block, a
+// wavefront per sum and no barrier between them (thirteen block sums one
+// after the other took 10.9 us at 32^3, now 3.7).
+constexpr int kRedThreads = 13 * 64;
 __device__ __forceinline__ void reduce_residual_block(const RedItem& it,
-                                                      Scalars* sc, double* red) {
-  const double rr = cg_sum_partials(it.partial, it.count, red);
-  const double rz = cg_sum_partials(it.partial + it.count, it.count, red);
-  const double res2 = cg_sum_partials(it.partial + 2 * it.count, it.count, red);
-  const double P2 = cg_sum_partials(it.psq, 9 * it.nss, red);
-  for (int c = 0; c < 9; ++c) {
-    const double m = cg_sum_partials(it.psum + c * it.nss, it.nss, red);
-    if (threadIdx.x == 0) sc->pbar[c] = m * it.invN3;
-  }
-  if (threadIdx.x == 0) {
-    sc->rr0 = rr;
-    sc->rz0 = rz;
-    sc->res2 = res2;
-    sc->P2 = P2;
-  }
+                                                      Scalars* sc) {
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const double* src = w < 3    ? it.partial + w * it.count
+                      : w == 3 ? it.psq
+                               : it.psum + (w - 4) * it.nss;
+  const int n = w < 3 ? it.count : w == 3 ? 9 * it.nss : it.nss;
+  double v = 0.0;
+#pragma unroll 4
+  for (int i = l; i < n; i += 64) v += src[i];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  if (l) return;
+  if (w == 0) sc->rr0 = v;
+  else if (w == 1) sc->rz0 = v;
+  else if (w == 2) sc->res2 = v;
+  else if (w == 3) sc->P2 = v;
+  else sc->pbar[w - 4] = v * it.invN3;
 }
 
-__global__ __launch_bounds__(kBlock) void reduce_residual_kernel(
+__global__ __launch_bounds__(kRedThreads) void reduce_residual_kernel(
     RedItem it, Scalars* __restrict__ sc, Scalars* pub) {
-  __shared__ double red[kBlock / 64];
-  reduce_residual_block(it, sc, red);
+  reduce_residual_block(it, sc);
   if (pub) publish_scalars(sc, pub);
 }
 
 // one block per RVE
-__global__ __launch_bounds__(kBlock) void reduce_batch_kernel(
+__global__ __launch_bounds__(kRedThreads) void reduce_batch_kernel(
     const RedItem* __restrict__ items, Scalars* __restrict__ scs) {
-  __shared__ double red[kBlock / 64];
   Scalars* sc = scs + blockIdx.x;
-  if (!sc->inactive) reduce_residual_block(items[blockIdx.x], sc, red);
+  if (!sc->inactive) reduce_residual_block(items[blockIdx.x], sc);
 }
 
 void launch_reduce_batch(const RedItem* items, int nitems, Scalars* scs,
                          hipStream_t s) {
-  hipLaunchKernelGGL(reduce_batch_kernel, dim3(nitems), dim3(kBlock), 0, s,
+  hipLaunchKernelGGL(reduce_batch_kernel, dim3(nitems), dim3(kRedThreads), 0, s,
                      items, scs);
 }
 
@@ -140,7 +143,7 @@ void launch_cg_close(const double* prr, const double* prz, int count,
 void launch_reduce_residual(const double* part, int count, const double* psum,
                             const double* psq, int nss, double invN3,
                             Scalars* sc, hipStream_t s, Scalars* pub) {
-  hipLaunchKernelGGL(reduce_residual_kernel, dim3(1), dim3(kBlock), 0, s,
+  hipLaunchKernelGGL(reduce_residual_kernel, dim3(1), dim3(kRedThreads), 0, s,
                      RedItem{part, count, psum, psq, nss, invN3}, sc, pub);
 }
 
