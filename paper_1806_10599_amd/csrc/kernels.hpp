@@ -89,7 +89,7 @@ struct SlabInvArgs {
   double* partial;     // per block
   const Scalars* sc;   // optional early exit
   int64_t cs;          // component stride of out
-  const T* vt = nullptr;    // DST_P, DST_ADDF: wave vectors
+  const T* vt = nullptr;    // wave vectors of the expansion
 };
 
 // G of a field
