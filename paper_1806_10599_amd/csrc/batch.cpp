@@ -283,6 +283,8 @@ void BatchEngine::autotune() {
     sc_host_[b].beta = 0.0;
   }
   upload_scalars();
+  // not what a solve that broke down may have left (0 times infinity)
+  for (void* f : {pi_, xi_}) RVE_HIP(hipMemsetAsync(f, 0, 3 * Nt_ * sizeof(T), st_));
   const std::vector<SpecItem<T>>& full =
       *reinterpret_cast<const std::vector<SpecItem<T>>*>(dbl ? (const void*)&host_it64_
                                                              : (const void*)&host_it32_);

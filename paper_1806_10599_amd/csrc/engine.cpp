@@ -589,8 +589,11 @@ void Engine::autotune() {
       if (schedule_valid(n_, dbl, cpb, cg_tile(n_)) &&
           (n_ <= 16 || (cpb == 1 && !fused)))
         cand.push_back({cpb, cg_tile(n_), fused});
-  // alpha = 0 in every slot: the timed passes leave the residual unchanged
+  // alpha = 0 in every slot: the timed passes leave the residual unchanged;
+  // a solve that broke down may have left an infinite direction, and 0 times
+  // that would reach the residual
   launch_bench_scalars(sc_, st_);
+  for (void* f : {pi_, xi_}) RVE_HIP(hipMemsetAsync(f, 0, 3 * N_ * sizeof(T), st_));
   std::vector<float> tbest(cand.size(), 0.f);
   constexpr int reps = 8;
   for (size_t c = 0; c < cand.size(); ++c) {

@@ -678,10 +678,12 @@ __device__ __forceinline__ void pencil_inv_body(const PencilInvArgs<T>& a,
     cplx<T> p[3];
     if constexpr (FINAL) {
 #pragma unroll
-      for (int i = 0; i < 3; ++i)
-        p[i] = (in && valid) ? cplx<T>{xv[w][i].x + alpha * pv[w][i].x,
-                                       xv[w][i].y + alpha * pv[w][i].y}
-                             : cplx<T>{T(0), T(0)};
+      for (int i = 0; i < 3; ++i) {
+        p[i] = (in && valid) ? xv[w][i] : cplx<T>{T(0), T(0)};
+        // after a breakdown (alpha = 0) pi may be infinite or NaN
+        if (in && valid && alpha != T(0))
+          p[i] = {p[i].x + alpha * pv[w][i].x, p[i].y + alpha * pv[w][i].y};
+      }
     } else if (in) {
       const cplx<T>* r = rv[w];
       const T g = a.prec * f.inv;
