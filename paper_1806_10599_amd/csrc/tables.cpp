@@ -3,6 +3,7 @@
 // (sample-frame slip systems and rotated cubic stiffness).
 #include "tables.hpp"
 
+#include <algorithm>
 #include <cmath>
 #include <stdexcept>
 
@@ -24,13 +25,19 @@ std::vector<double> wave_vectors(int n, const double L[3], int projection) {
   // index k mod n, q = 2 pi k / n.  Continuous operator (Eq. 19): v = q n/L;
   // discrete operator (Eqs. 20-21): v = tan(q/2) n/L.  The Nyquist entry is
   // never used (the operator is zero there) and is set to 0.
+  // The operator does not depend on a common factor of v: lengths are taken in
+  // units of the power of two below the shortest one, which changes no digit
+  // of a result and keeps products with v in the single-precision range
+  // whatever the unit of L is.
+  int unit;
+  std::frexp(std::min(L[0], std::min(L[1], L[2])), &unit);
   std::vector<double> v(3 * n, 0.0);
   for (int d = 0; d < 3; ++d) {
     for (int idx = 0; idx < n; ++idx) {
       const int k = (idx < (n + 1) / 2) ? idx : idx - n;
       if (n % 2 == 0 && k == -n / 2) continue;
       const double q = 2.0 * M_PI * (double)k / (double)n;
-      const double scale = (double)n / L[d];
+      const double scale = (double)n / std::ldexp(L[d], 1 - unit);
       v[d * n + idx] = (projection == 0) ? q * scale : std::tan(0.5 * q) * scale;
     }
   }
