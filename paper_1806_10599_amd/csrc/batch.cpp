@@ -658,12 +658,7 @@ int BatchEngine::increment(const double* Fbar_all, double dt,
     sc_host_[b].inactive = 0;
     sc_host_[b].commit = 0;
   }
-  LawParams lp{params_[3], params_[4], params_[5], params_[6], params_[7], dt,
-               1.0 / params_[4], 1.0 / (dt * params_[3])};
-  lp.nint = flow_exponent_int(lp.nexp);
-  lp.c11m12 = params_[0] - params_[1];
-  lp.c12 = params_[1];
-  lp.c44 = params_[2];
+  const LawParams lp = law_params(params_, dt);
   const double* dg_start = dg_c_;
   std::vector<int> iters(B_, 0);
   for (int it = 0; it <= cfg_.newton_max_iter; ++it) {
@@ -841,12 +836,7 @@ int BatchEngine::increment_device(const double* Fbar_all, double dt,
   upload_scalars();
   RVE_HIP(hipMemcpyAsync(log_, log_host_.data(), B_ * sizeof(BatchLog),
                          hipMemcpyHostToDevice, st_));
-  LawParams lp{params_[3], params_[4], params_[5], params_[6], params_[7], dt,
-               1.0 / params_[4], 1.0 / (dt * params_[3])};
-  lp.nint = flow_exponent_int(lp.nexp);
-  lp.c11m12 = params_[0] - params_[1];
-  lp.c12 = params_[1];
-  lp.c44 = params_[2];
+  const LawParams lp = law_params(params_, dt);
   const int ncap = std::min(kGraphNewton, cfg_.newton_max_iter);
   auto solve = [&](int it) {
     if (fp64_) newton_solve_device<double>(it, lp);

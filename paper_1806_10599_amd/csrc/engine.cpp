@@ -341,20 +341,7 @@ void Engine::read_scalars(Scalars& h) {
 }
 
 LawParams Engine::law_params(double dt) const {
-  LawParams lp;
-  lp.gdot0 = params_[3];
-  lp.g = params_[4];
-  lp.nexp = params_[5];
-  lp.c_af = params_[6];
-  lp.d_af = params_[7];
-  lp.dt = dt;
-  lp.inv_g = 1.0 / lp.g;
-  lp.inv_a = 1.0 / (dt * lp.gdot0);
-  lp.nint = flow_exponent_int(lp.nexp);
-  lp.c11m12 = params_[0] - params_[1];
-  lp.c12 = params_[1];
-  lp.c44 = params_[2];
-  return lp;
+  return rve::law_params(params_, dt);
 }
 
 void Engine::residual_passes(const double* P, Scalars* pub) {

@@ -1,6 +1,8 @@
 // Launch interfaces of the HIP kernels (host side sees only these).
 #pragma once
 
+#include <cmath>
+
 #include "common.hpp"
 
 namespace rve {
@@ -250,13 +252,29 @@ struct LawParams {
   double gdot0, g, nexp, c_af, d_af, dt;
   double inv_g, inv_a;   // 1/g and 1/(dt gdot0), formed once on the host
   int32_t nint;          // nexp when it is an integer in [1, 64], else 0
+  double xmax;           // |x|^(2 nexp) stays below 1e300 up to this |x|
   double c11m12, c12, c44;   // cubic constants of the grains: C11 - C12, ...
 };
 
-// the flow-rule exponent as an integer when it is one (powers by products)
-inline int32_t flow_exponent_int(double n) {
-  const int32_t ni = (int32_t)n;
-  return ((double)ni == n && ni >= 1 && ni <= 64) ? ni : 0;
+// from the constants of a microstructure (rve.h) and the time step
+inline LawParams law_params(const double* p, double dt) {
+  LawParams lp{};
+  lp.gdot0 = p[3];
+  lp.g = p[4];
+  lp.nexp = p[5];
+  lp.c_af = p[6];
+  lp.d_af = p[7];
+  lp.dt = dt;
+  lp.inv_g = 1.0 / lp.g;
+  lp.inv_a = 1.0 / (dt * lp.gdot0);
+  // the exponent as an integer when it is one (powers by products)
+  const int32_t ni = lp.nexp <= 64.0 ? (int32_t)lp.nexp : 0;
+  lp.nint = (double)ni == lp.nexp && ni >= 1 ? ni : 0;
+  lp.xmax = std::pow(10.0, std::fmin(7.0, 150.0 / lp.nexp));
+  lp.c11m12 = p[0] - p[1];
+  lp.c12 = p[1];
+  lp.c44 = p[2];
+  return lp;
 }
 
 struct ConstArgs {

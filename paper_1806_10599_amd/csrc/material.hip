@@ -59,14 +59,7 @@ __device__ __forceinline__ double sgn(double x) {
   return (x > 0.0) ? 1.0 : ((x < 0.0) ? -1.0 : 0.0);
 }
 
-// asinh(|x|^n sign x) and its derivative d/dx = n y / (|x| sqrt(1 + y^2)),
-// y = |x|^n.  For the integer exponents of the flow rule y is formed by
-// repeated squaring and asinh(y) = log1p(y + y (y / (1 + sqrt(1 + y^2))))
-// (an exact identity that needs no logarithm of |x| and no exponential);
-// past |x| = 1e7 (y^2 would leave the FP64 range) and for other exponents
-// the form through s = min(y, 1/y) = exp(-|n ln|x||) is used:
-//   y >= 1: asinh(y) = n ln|x| + log1p(q),                q = sqrt(1 + s^2)
-//   y <  1: asinh(y) = log1p(s + s^2 / (1 + q)).
+// b^ni by repeated squaring
 __device__ __forceinline__ double ipow_n(double b, int ni) {
   if (ni == 20) {   // the workloads' exponent: five products
     const double b2 = b * b, b4 = b2 * b2, b8 = b4 * b4, b16 = b8 * b8;
@@ -80,16 +73,14 @@ __device__ __forceinline__ double ipow_n(double b, int ni) {
   return y;
 }
 
-__device__ __forceinline__ void asinh_pow(double x, double n, int ni,
-                                          double& val, double& der) {
+// asinh(|x|^n sign x) and its derivative d/dx = n y / (|x| sqrt(1 + y^2)),
+// y = |x|^n, through s = min(y, 1/y) = exp(-|n ln|x||), for any exponent and
+// any |x|:
+//   y >= 1: asinh(y) = n ln|x| + log1p(q),                q = sqrt(1 + s^2)
+//   y <  1: asinh(y) = log1p(s + s^2 / (1 + q)).
+__device__ __forceinline__ void asinh_pow(double x, double n, double& val,
+                                          double& der) {
   const double ax = fabs(x);
-  if (ni > 0 && ax < 1e7) {
-    const double y = ipow_n(ax, ni);
-    const double q = sqrt(fma(y, y, 1.0));
-    val = copysign(log1p(y + y * (y / (1.0 + q))), x);
-    der = (ax > 0.0) ? n * (y / (ax * q)) : 0.0;
-    return;
-  }
   const double e = n * log(ax);          // ln y (-inf at x = 0)
   const bool big = e > 0.0;
   const double s = exp(-fabs(e));        // 0 at x = 0
@@ -109,16 +100,16 @@ __device__ __forceinline__ void mm3(const double* A, const double* B,
                      A[3 * i + 2] * B[6 + j];
 }
 
-// d/dx asinh(|x|^n sign x) = n y / (|x| sqrt(1 + y^2)), y = |x|^n (FP64;
-// the same branches as asinh_pow, without the function value)
-__device__ __forceinline__ double flow_slope(double x, double n, int ni) {
+// d/dx asinh(|x|^n sign x) = n y / (|x| sqrt(1 + y^2)), y = |x|^n (FP64; y by
+// products for an integer exponent while y^2 stays in range)
+__device__ __forceinline__ double flow_slope(double x, const LawParams& lp) {
   const double ax = fabs(x);
-  if (ni > 0 && ax < 1e7) {
-    const double y = ipow_n(ax, ni);
-    return (ax > 0.0) ? n * (y / (ax * sqrt(fma(y, y, 1.0)))) : 0.0;
+  if (lp.nint > 0 && ax < lp.xmax) {
+    const double y = ipow_n(ax, lp.nint);
+    return (ax > 0.0) ? lp.nexp * (y / (ax * sqrt(fma(y, y, 1.0)))) : 0.0;
   }
   double val, der;
-  asinh_pow(x, n, ni, val, der);
+  asinh_pow(x, lp.nexp, val, der);
   return der;
 }
 
@@ -261,17 +252,18 @@ __device__ __forceinline__ float log2_single(double x) {
 // converged slips depend on.  Further away, where R only steers the
 // iteration, single precision serves.  The derivative of
 // asinh(|x|^n sign x) (Jacobian only) is in single precision.  Past
-// |x| = 1e7, where y^2 would leave the FP64 range, ln B = n ln|x| + ln 2.
+// LawParams::xmax, where y^2 would leave the FP64 range (|x| of 1e7 up to
+// n = 21, 1e3 for n = 50, 220 for n = 64), ln B = n ln|x| + ln 2.
 // Non-integer n (INTN false): the two functions are evaluated apart.
 __device__ __forceinline__ double asinh_bf(double u);
 template <bool INTN>
-__device__ __forceinline__ void flow_residual(double t, double inv_a, double x,
-                                              double n, int ni, double& R,
+__device__ __forceinline__ void flow_residual(double t, double x,
+                                              const LawParams& lp, double& R,
                                               float& der) {
-  const double ax = fabs(x);
+  const double ax = fabs(x), n = lp.nexp, inv_a = lp.inv_a;
   if constexpr (INTN) {
-    const bool huge = ax >= 1e7;
-    const double y = ipow_n(huge ? 1e7 : ax, ni);
+    const bool huge = ax >= lp.xmax;
+    const double y = ipow_n(huge ? lp.xmax : ax, lp.nint);
     const double B = y + sqrt_pos(fma(y, y, 1.0));
     const double au = fabs(t * inv_a);
     const double A = au + sqrt_pos(fma(au, au, 1.0));
@@ -296,7 +288,7 @@ __device__ __forceinline__ void flow_residual(double t, double inv_a, double x,
     der = (ax > 1e-30) ? (float)n * rs * __builtin_amdgcn_rcpf((float)ax) : 0.0f;
   } else {
     double val, d;
-    asinh_pow(x, n, ni, val, d);
+    asinh_pow(x, n, val, d);
     R = asinh_bf(t * inv_a) - val;
     der = (float)d;
   }
@@ -383,8 +375,7 @@ __device__ __forceinline__ void pr_eval(const double* Gs, const double* es,
 #pragma unroll
   for (int j = 0; j < 3; ++j) {
     const double chi = div_pos(chi0[j] + lp.c_af * t[j], 1.0 + lp.d_af * fabs(t[j]));
-    flow_residual<INTN>(t[j], lp.inv_a, (tau[j] - chi) * lp.inv_g, lp.nexp, lp.nint,
-                  R[j], hd[j]);
+    flow_residual<INTN>(t[j], (tau[j] - chi) * lp.inv_g, lp, R[j], hd[j]);
   }
 }
 
@@ -905,7 +896,7 @@ __device__ __forceinline__ void tangent_voxel(const TangentArgs<TK>& A, int64_t 
       const double chi0 = kPlaneFlip[h][j] * A.chi0[kPlaneSlip[h][j] * N + v];
       const double iden = 1.0 / (1.0 + lp.d_af * ad);
       const double chi = (chi0 + lp.c_af * d) * iden;
-      const TK hg = TK(flow_slope((tau[j] - chi) * lp.inv_g, lp.nexp, lp.nint) * lp.inv_g);
+      const TK hg = TK(flow_slope((tau[j] - chi) * lp.inv_g, lp) * lp.inv_g);
       const TK dchi = TK((lp.c_af - lp.d_af * sgn(d) * chi) * iden);
       const TK f = hg / (TK(1.0 / sqrt(a * a + d * d)) + hg * dchi);
       // the system s = (sg_p e_p - sg_m e_m)/sqrt 2
