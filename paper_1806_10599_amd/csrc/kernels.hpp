@@ -253,6 +253,7 @@ struct LawParams {
   double inv_g, inv_a;   // 1/g and 1/(dt gdot0), formed once on the host
   int32_t nint;          // nexp when it is an integer in [1, 64], else 0
   double xmax;           // |x|^(2 nexp) stays below 1e300 up to this |x|
+  int32_t xexp;          // 2^xexp is the largest power of two up to xmax
   double c11m12, c12, c44;   // cubic constants of the grains: C11 - C12, ...
 };
 
@@ -271,6 +272,7 @@ inline LawParams law_params(const double* p, double dt) {
   const int32_t ni = lp.nexp <= 64.0 ? (int32_t)lp.nexp : 0;
   lp.nint = (double)ni == lp.nexp && ni >= 1 ? ni : 0;
   lp.xmax = std::pow(10.0, std::fmin(7.0, 150.0 / lp.nexp));
+  lp.xexp = std::ilogb(lp.xmax);
   lp.c11m12 = p[0] - p[1];
   lp.c12 = p[1];
   lp.c44 = p[2];

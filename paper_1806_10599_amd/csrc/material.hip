@@ -236,24 +236,35 @@ __device__ __forceinline__ double div_pos(double a, double b) {
   return fma(fma(-b, q, a), r, q);
 }
 
-// log2 of a positive number of any size in single precision
-__device__ __forceinline__ float log2_single(double x) {
-  return (float)__builtin_amdgcn_frexp_exp(x) +
-         __builtin_amdgcn_logf((float)__builtin_amdgcn_frexp_mant(x));
+// 2 atanh(q), |q| <= 0.2005: the first term left out is below 2e-17 of the sum
+__device__ __forceinline__ double atanh2(double q) {
+  const double q2 = q * q;
+  double p = 1.0 / 21.0;
+#pragma unroll
+  for (int m = 9; m >= 0; --m) p = fma(q2, p, 1.0 / (2 * m + 1));
+  return 2.0 * q * p;
+}
+constexpr double kLn2 = 0.69314718055994530942;
+
+// k = log2(p / d) rounded (p and d positive): the exponent and the leading
+// bits of the mantissa are log2 to within 0.086, so |log2(p / d) - k| < 0.587,
+// and k = 0 where p and d are close
+__device__ __forceinline__ int octaves(double p, double d) {
+  return (__double2hiint(p) - __double2hiint(d) + (1 << 19)) >> 20;
 }
 
 // The local residual R = asinh(u) - asinh(|x|^n sign x), u = dg / a, through
 // A = |u| + sqrt(1 + u^2) and B = y + sqrt(1 + y^2), y = |x|^n:
 // R = s ln(A / B) when the signs agree (or one is zero; s the nonzero one)
-// and R = su ln(A B) when they differ -- exact identities.  Near the root the
-// logarithm is 2 atanh(q), q = (A - B)/(A + B) or (A B - 1)/(A B + 1), in
-// FP64 (|q| <= 0.05: the first term left out is below 1e-17), so R there
-// carries an absolute error of a few units of 1e-16, which is what the
-// converged slips depend on.  Further away, where R only steers the
-// iteration, single precision serves.  The derivative of
+// and R = su ln(A B) when they differ -- exact identities.  The logarithm of
+// p / d is k ln 2 + 2 atanh(q), q = (p 2^-k - d)/(p 2^-k + d), with the k
+// that keeps q small: near the root k = 0, and R there carries an absolute
+// error of a few units of 1e-16, which is what the converged slips depend on.
+// FP64 throughout and free of branches.  The derivative of
 // asinh(|x|^n sign x) (Jacobian only) is in single precision.  Past
 // LawParams::xmax, where y^2 would leave the FP64 range (|x| of 1e7 up to
-// n = 21, 1e3 for n = 50, 220 for n = 64), ln B = n ln|x| + ln 2.
+// n = 21, 1e3 for n = 50, 220 for n = 64), y is the power of |x| 2^-j, still
+// so large that B = 2 y, and n j octaves are added to the logarithm.
 // Non-integer n (INTN false): the two functions are evaluated apart.
 __device__ __forceinline__ double asinh_bf(double u);
 template <bool INTN>
@@ -262,25 +273,18 @@ __device__ __forceinline__ void flow_residual(double t, double x,
                                               float& der) {
   const double ax = fabs(x), n = lp.nexp, inv_a = lp.inv_a;
   if constexpr (INTN) {
-    const bool huge = ax >= lp.xmax;
-    const double y = ipow_n(huge ? lp.xmax : ax, lp.nint);
+    const int j = ax >= lp.xmax ? __builtin_amdgcn_frexp_exp(ax) - lp.xexp : 0;
+    const double y = ipow_n(__builtin_amdgcn_ldexp(ax, -j), lp.nint);
     const double B = y + sqrt_pos(fma(y, y, 1.0));
     const double au = fabs(t * inv_a);
     const double A = au + sqrt_pos(fma(au, au, 1.0));
     const bool differ = (t > 0.0 && x < 0.0) || (t < 0.0 && x > 0.0);
-    const double num = differ ? fma(A, B, -1.0) : A - B;
-    const double den = differ ? fma(A, B, 1.0) : A + B;
-    const double q = div_pos(num, den);
-    double r;
-    if (fabs(q) <= 0.05 && !huge) {
-      const double q2 = q * q;
-      r = 2.0 * q * fma(q2, fma(q2, fma(q2, fma(q2, fma(q2, 1.0 / 11.0, 1.0 / 9.0),
-                                                1.0 / 7.0), 0.2), 1.0 / 3.0), 1.0);
-    } else {
-      const float la = log2_single(A);
-      const float lb = huge ? (float)n * log2_single(ax) + 1.0f : log2_single(B);
-      r = (double)(0.69314718055994531f * (differ ? la + lb : la - lb));
-    }
+    const double m = differ ? B : 1.0, d = differ ? 1.0 : B;
+    const int k = octaves(A * m, d);
+    const double As = __builtin_amdgcn_ldexp(A, -k);
+    const double q = div_pos(fma(As, m, -d), fma(As, m, d));
+    const int oct = k + (differ ? lp.nint * j : -lp.nint * j);
+    const double r = fma((double)oct, kLn2, atanh2(q));
     const double s = (t != 0.0) ? t : x;
     R = s < 0.0 ? -r : r;
     const float yf = (float)y;
