@@ -370,8 +370,7 @@ __device__ __forceinline__ void pr_eval(const double* Gs, const double* es,
   for (int i = 0; i < 3; ++i)
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
-      const float q = (float)G[i] * (float)Gs[j] + (float)G[3 + i] * (float)Gs[3 + j] +
-                      (float)G[6 + i] * (float)Gs[6 + j];
+      const float q = (float)(G[i] * Gs[j] + G[3 + i] * Gs[3 + j] + G[6 + i] * Gs[6 + j]);
       Q[3 * i + j] = flip(q, sg.both(i, j));
     }
   const double tau[3] = {d01 + (c02 - c12), d02 + (c01 - c12),
@@ -833,8 +832,7 @@ __device__ __forceinline__ void tangent_voxel(const TangentArgs<TK>& A, int64_t 
     for (int i = 0; i < 3; ++i)
 #pragma unroll
       for (int j = 0; j < 3; ++j)
-        Q[3 * i + j] = TK(G[i]) * TK(Gs[j]) + TK(G[3 + i]) * TK(Gs[3 + j]) +
-                       TK(G[6 + i]) * TK(Gs[6 + j]);
+        Q[3 * i + j] = TK(G[i] * Gs[j] + G[3 + i] * Gs[3 + j] + G[6 + i] * Gs[6 + j]);
   }
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
@@ -900,9 +898,11 @@ __device__ __forceinline__ void tangent_voxel(const TangentArgs<TK>& A, int64_t 
       const double chi0 = kPlaneFlip[h][j] * A.chi0[kPlaneSlip[h][j] * N + v];
       const double iden = 1.0 / (1.0 + lp.d_af * ad);
       const double chi = (chi0 + lp.c_af * d) * iden;
-      const TK hg = TK(flow_slope((tau[j] - chi) * lp.inv_g, lp) * lp.inv_g);
-      const TK dchi = TK((lp.c_af - lp.d_af * sgn(d) * chi) * iden);
-      const TK f = hg / (TK(1.0 / sqrt(a * a + d * d)) + hg * dchi);
+      // f = hg / (1/w + hg dchi), w^2 = a^2 + dg^2, in FP64 like its terms
+      const double hg = flow_slope((tau[j] - chi) * lp.inv_g, lp) * lp.inv_g;
+      const double w = sqrt(a * a + d * d);
+      const double dchi = (lp.c_af - lp.d_af * sgn(d) * chi) * iden;
+      const TK f = TK(hg * w / fma(hg * w, dchi, 1.0));
       // the system s = (sg_p e_p - sg_m e_m)/sqrt 2
       constexpr int ps[3] = {0, 0, 1}, ms[3] = {1, 2, 2};
       const int gp = kPlaneSign[h][ps[j]], gm = kPlaneSign[h][ms[j]];
