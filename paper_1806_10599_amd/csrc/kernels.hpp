@@ -310,7 +310,7 @@ struct TangentArgs {
   const double* dg;      // converged trial slips
   const int32_t* phase;
   const double* table;
-  TK* K;                 // [51][N]: D, S2, F (kp_apply.hpp)
+  TK* K;                 // [51][N]: D, S2, F - 1 (kp_apply.hpp)
   LawParams lp;
   int64_t N;
   const uint8_t* vrve;

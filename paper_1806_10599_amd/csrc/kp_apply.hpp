@@ -1,6 +1,9 @@
 // y = K : p of one voxel from the stored form of the tangent (material.hip):
 // D (6x6, dS2_I = D_IJ e_J with engineering shears e, order 11, 22, 33, 23,
-// 13, 12), S2 and F:  y = p S2 + F (D : sym(F^T p)).
+// 13, 12), S2 and H = F - 1:  y = p S2 + F (D : sym(F^T p)).  H and not F: at
+// the strains of a metal its rounding is hundreds of times smaller, and the
+// products with the unit matrix are exact (a particle's K : p in single
+// precision 8.4e-8 from FP64 with F, 5.1e-8 with H; 81 rounded entries 6.1e-8).
 #pragma once
 
 #include "kernels.hpp"
@@ -17,25 +20,26 @@ __host__ __device__ constexpr int voigt(int i, int j) {
 
 // engineering strains of sym(F^T p)
 template <typename T>
-__device__ __forceinline__ void kp_strain(const T* F, const T* p, T* e) {
+__device__ __forceinline__ void kp_strain(const T* H, const T* p, T* e) {
 #pragma unroll
   for (int i = 0; i < 3; ++i)
-    e[i] = F[i] * p[i] + F[3 + i] * p[3 + i] + F[6 + i] * p[6 + i];
+    e[i] = p[4 * i] + (H[i] * p[i] + H[3 + i] * p[3 + i] + H[6 + i] * p[6 + i]);
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = i + 1; j < 3; ++j)
-      e[voigt(i, j)] = F[i] * p[j] + F[3 + i] * p[3 + j] + F[6 + i] * p[6 + j] +
-                       F[j] * p[i] + F[3 + j] * p[3 + i] + F[6 + j] * p[6 + i];
+      e[voigt(i, j)] = (p[3 * i + j] + p[3 * j + i]) +
+                       (H[i] * p[j] + H[3 + i] * p[3 + j] + H[6 + i] * p[6 + j] +
+                        H[j] * p[i] + H[3 + j] * p[3 + i] + H[6 + j] * p[6 + i]);
 }
 
 // y of all nine components, K[kKComp] in registers
 template <typename T>
 __device__ __forceinline__ void kp_apply(const T* K, const T* p, T* y) {
   const T* S = K + 36;
-  const T* F = K + 42;
+  const T* H = K + 42;
   T e[6], s[6];
-  kp_strain(F, p, e);
+  kp_strain(H, p, e);
 #pragma unroll
   for (int I = 0; I < 6; ++I) {
     T acc = T(0);
@@ -50,8 +54,8 @@ __device__ __forceinline__ void kp_apply(const T* K, const T* p, T* y) {
       T acc = T(0);
 #pragma unroll
       for (int k = 0; k < 3; ++k)
-        acc += p[3 * i + k] * S[voigt(k, j)] + F[3 * i + k] * s[voigt(k, j)];
-      y[3 * i + j] = acc;
+        acc += p[3 * i + k] * S[voigt(k, j)] + H[3 * i + k] * s[voigt(k, j)];
+      y[3 * i + j] = s[voigt(i, j)] + acc;
     }
 }
 

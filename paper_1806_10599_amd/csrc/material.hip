@@ -726,7 +726,7 @@ __global__ __launch_bounds__(256) void rm_count_kernel(
 // ---- consistent tangent ----------------------------------------------------
 // P = F S2(C), C = F^T F, with the second Piola stress S2 = Fp^-1 S Fp^-T, so
 //   K_ijkl = d_ik (S2)_lj + F_im D_mj,nl F_kn,   D = 2 dS2/dC,
-// and K is stored as D, S2 and F (kKComp entries per voxel): six strain
+// and K is stored as D, S2 and F - 1 (kKComp entries per voxel): six strain
 // directions instead of nine gradients here, and 51 instead of 81 numbers
 // for every K:p (kp_apply).  In the lattice frame, A = Fp^-1 R:
 //   dS = Y^-1 (A^T dE A),   Y = C^-1 + sum_a f_a V_a (x) S0_a,
@@ -753,7 +753,8 @@ __device__ __forceinline__ void tangent_voxel(const TangentArgs<TK>& A, int64_t 
   double F[9];
   load9(A.F, v, N, F);
 #pragma unroll
-  for (int c = 0; c < 9; ++c) A.K[(42 + c) * N + v] = TK(F[c]);
+  for (int c = 0; c < 9; ++c)
+    A.K[(42 + c) * N + v] = TK(F[c] - (c % 4 == 0 ? 1.0 : 0.0));
   if (tb[0] != 0.0) {   // isotropic SVK: S2 = lam tr E + 2 mu E
     const double lam = tb[kTabLam], mu = tb[kTabMu];
     double C[9];

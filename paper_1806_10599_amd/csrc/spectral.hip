@@ -223,23 +223,24 @@ __device__ __forceinline__ bool slab_fwd_body(const SlabFwdArgs<T>& a, int lb,
         }
       } else {
         // components of one tensor row i = grp (CPB 3) or c = 3 i + j
-        T F[9], e[6];
+        T H[9], e[6];
 #pragma unroll
-        for (int d = 0; d < 9; ++d) F[d] = a.K[(42 + d) * cs + v];
-        kp_strain(F, pd, e);
+        for (int d = 0; d < 9; ++d) H[d] = a.K[(42 + d) * cs + v];
+        kp_strain(H, pd, e);
         auto row = [&](int i, int j) {
-          T acc = T(0);
+          T acc = T(0), sij = T(0);
 #pragma unroll
           for (int k = 0; k < 3; ++k) {
             const int I = voigt(k, j);
             T s = T(0);
 #pragma unroll
             for (int J = 0; J < 6; ++J) s += a.K[(6 * I + J) * cs + v] * e[J];
+            if (k == i) sij = s;
             const T pk = i == 0 ? pd[k] : (i == 1 ? pd[3 + k] : pd[6 + k]);
-            const T fk = i == 0 ? F[k] : (i == 1 ? F[3 + k] : F[6 + k]);
-            acc += pk * a.K[(36 + I) * cs + v] + fk * s;
+            const T hk = i == 0 ? H[k] : (i == 1 ? H[3 + k] : H[6 + k]);
+            acc += pk * a.K[(36 + I) * cs + v] + hk * s;
           }
-          return acc;
+          return sij + acc;
         };
         if constexpr (CPB == 3) {
 #pragma unroll
