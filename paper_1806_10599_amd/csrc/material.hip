@@ -800,17 +800,16 @@ __device__ __forceinline__ void tangent_voxel(const TangentArgs<TK>& A, int64_t 
       for (int j = 0; j < 3; ++j)
         Ap[3 * i + j] -= (kPlaneSign[h][i] * kPlaneSign[h][j]) * d[i];
   }
-  TK Y0[9], Ac[9], Q[9], Fs[9];   // Fp^-1_0 R, Fp^-1 R, G^T Gs, Fp^-1 R S
-  TK S[6];
-  double S64[6];
+  TK Y0[9], Q[9], Fs[9];   // Fp^-1_0 R, G^T Gs, Fp^-1 R S
+  double Ac[9], S64[6];    // Fp^-1 R, S
   {
-    double Fp0[9], Rm[9], B[9], Gs[9], G[9], A64[9];
+    double Fp0[9], Rm[9], B[9], Gs[9], G[9];
     load9(A.Fpi0, v, N, Fp0);
 #pragma unroll
     for (int i = 0; i < 9; ++i) Rm[i] = tb[kTabR + i];
     mm3(Fp0, Rm, B);
     mm3(F, B, Gs);
-    mm3(B, Ap, A64);
+    mm3(B, Ap, Ac);
     mm3(Gs, Ap, G);
     double E[6];
     constexpr int vi[6] = {0, 1, 2, 1, 0, 0}, vj[6] = {0, 1, 2, 2, 2, 1};
@@ -820,31 +819,27 @@ __device__ __forceinline__ void tangent_voxel(const TangentArgs<TK>& A, int64_t 
                     G[6 + vi[I]] * G[6 + vj[I]] - (I < 3 ? 1.0 : 0.0));
     const double tr = lp.c12 * (E[0] + E[1] + E[2]);
 #pragma unroll
-    for (int I = 0; I < 6; ++I) {
+    for (int I = 0; I < 6; ++I)
       S64[I] = I < 3 ? lp.c11m12 * E[I] + tr : 2.0 * lp.c44 * E[I];
-      S[I] = TK(S64[I]);
-    }
 #pragma unroll
-    for (int i = 0; i < 9; ++i) {
-      Y0[i] = TK(B[i]);
-      Ac[i] = TK(A64[i]);
-    }
+    for (int i = 0; i < 9; ++i) Y0[i] = TK(B[i]);
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
       for (int j = 0; j < 3; ++j)
         Q[3 * i + j] = TK(G[i] * Gs[j] + G[3 + i] * Gs[3 + j] + G[6 + i] * Gs[6 + j]);
   }
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    Fs[3 * i] = Ac[3 * i] * S[0] + Ac[3 * i + 1] * S[5] + Ac[3 * i + 2] * S[4];
-    Fs[3 * i + 1] = Ac[3 * i] * S[5] + Ac[3 * i + 1] * S[1] + Ac[3 * i + 2] * S[3];
-    Fs[3 * i + 2] = Ac[3 * i] * S[4] + Ac[3 * i + 1] * S[3] + Ac[3 * i + 2] * S[2];
-  }
   {
+    double fs[9];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      fs[3 * i] = Ac[3 * i] * S64[0] + Ac[3 * i + 1] * S64[5] + Ac[3 * i + 2] * S64[4];
+      fs[3 * i + 1] = Ac[3 * i] * S64[5] + Ac[3 * i + 1] * S64[1] + Ac[3 * i + 2] * S64[3];
+      fs[3 * i + 2] = Ac[3 * i] * S64[4] + Ac[3 * i + 1] * S64[3] + Ac[3 * i + 2] * S64[2];
+    }
     auto s2 = [&](int i, int j) {
-      return Fs[3 * i] * Ac[3 * j] + Fs[3 * i + 1] * Ac[3 * j + 1] +
-             Fs[3 * i + 2] * Ac[3 * j + 2];
+      return TK(fs[3 * i] * Ac[3 * j] + fs[3 * i + 1] * Ac[3 * j + 1] +
+                fs[3 * i + 2] * Ac[3 * j + 2]);
     };
     A.K[36 * N + v] = s2(0, 0);
     A.K[37 * N + v] = s2(1, 1);
@@ -852,25 +847,27 @@ __device__ __forceinline__ void tangent_voxel(const TangentArgs<TK>& A, int64_t 
     A.K[39 * N + v] = s2(1, 2);
     A.K[40 * N + v] = s2(0, 2);
     A.K[41 * N + v] = s2(0, 1);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) Fs[i] = TK(fs[i]);
   }
   // Phi: the basis tensors pushed forward by A (columns), in the order 11,
   // 22, 33, 23, 13, 12; L starts as Phi and takes the plastic part
   TK Phi[6][6], L[6][5], Y[25], yt[5];
   {
     constexpr int vi[6] = {0, 1, 2, 1, 0, 0}, vj[6] = {0, 1, 2, 2, 2, 1};
-    const TK r2 = TK(0.70710678118654752440), r3 = TK(0.57735026918962576451),
-             r6 = TK(0.40824829046386301637);
+    constexpr double r2 = 0.70710678118654752440, r3 = 0.57735026918962576451,
+                     r6 = 0.40824829046386301637;
 #pragma unroll
     for (int I = 0; I < 6; ++I) {
-      const TK* p = Ac + 3 * vi[I];
-      const TK* q = Ac + 3 * vj[I];
-      const TK w0 = p[0] * q[0], w1 = p[1] * q[1], w2 = p[2] * q[2];
-      Phi[I][0] = r2 * (w0 - w1);
-      Phi[I][1] = r6 * (w0 + w1 - TK(2) * w2);
-      Phi[I][2] = r2 * (p[1] * q[2] + p[2] * q[1]);
-      Phi[I][3] = r2 * (p[0] * q[2] + p[2] * q[0]);
-      Phi[I][4] = r2 * (p[0] * q[1] + p[1] * q[0]);
-      Phi[I][5] = r3 * (w0 + w1 + w2);
+      const double* p = Ac + 3 * vi[I];
+      const double* q = Ac + 3 * vj[I];
+      const double w0 = p[0] * q[0], w1 = p[1] * q[1], w2 = p[2] * q[2];
+      Phi[I][0] = TK(r2 * (w0 - w1));
+      Phi[I][1] = TK(r6 * (w0 + w1 - 2.0 * w2));
+      Phi[I][2] = TK(r2 * (p[1] * q[2] + p[2] * q[1]));
+      Phi[I][3] = TK(r2 * (p[0] * q[2] + p[2] * q[0]));
+      Phi[I][4] = TK(r2 * (p[0] * q[1] + p[1] * q[0]));
+      Phi[I][5] = TK(r3 * (w0 + w1 + w2));
 #pragma unroll
       for (int k = 0; k < 5; ++k) L[I][k] = Phi[I][k];
     }

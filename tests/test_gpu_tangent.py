@@ -36,3 +36,17 @@ def test_particle_tangent_rounding(size):
     K, K32, particle = _tangents(size, 5)
     err = np.abs(K32 - K)[:, particle].max(axis=0)
     assert np.max(err / np.abs(K[:, particle]).max(axis=0)) <= 3 * UNIT
+
+
+def test_elastic_crystal_tangent_rounding():
+    """Grains that do not flow: the stored numbers are FP64 ones rounded once
+    or sums of a few of those, and so is K : p: two roundoffs in the mean."""
+    K, K32, particle = _tangents(1e-4, 6)
+    p = np.random.default_rng(7).standard_normal((9, K.shape[1]))
+    grain = ~particle
+
+    def apply(A):
+        return np.einsum("ijv,jv->iv", A.reshape(9, 9, -1), p)[:, grain]
+
+    err = np.linalg.norm(apply(K32 - K)) / np.linalg.norm(apply(K))
+    assert err <= 2 * UNIT
