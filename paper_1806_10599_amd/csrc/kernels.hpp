@@ -255,6 +255,7 @@ struct LawParams {
   double xmax;           // |x|^(2 nexp) stays below 1e300 up to this |x|
   int32_t xexp;          // 2^xexp is the largest power of two up to xmax
   double c11m12, c12, c44;   // cubic constants of the grains: C11 - C12, ...
+  int32_t definite;      // C11 - C12 and C44 are not negative
 };
 
 // from the constants of a microstructure (rve.h) and the time step
@@ -276,6 +277,7 @@ inline LawParams law_params(const double* p, double dt) {
   lp.c11m12 = p[0] - p[1];
   lp.c12 = p[1];
   lp.c44 = p[2];
+  lp.definite = lp.c11m12 >= 0.0 && lp.c44 >= 0.0;
   return lp;
 }
 

@@ -395,22 +395,63 @@ __device__ constexpr double kSchmid5d[3][5] = {
     {1.0, 1.73205080756887729353, -1.0, 0.0, 1.0},
     {-1.0, 1.73205080756887729353, 0.0, -1.0, 1.0}};
 
+// z <- M^-1 z by elimination, with row interchanges or without
+template <bool PIVOT>
+__device__ __forceinline__ void solve5(float* M, float* z) {
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    if constexpr (PIVOT) {
+#pragma unroll
+      for (int r = k + 1; r < 5; ++r) {
+        const bool s = fabsf(M[5 * r + k]) > fabsf(M[6 * k]);
+#pragma unroll
+        for (int J = k; J < 5; ++J) {
+          const float a = M[5 * k + J], b = M[5 * r + J];
+          M[5 * k + J] = s ? b : a;
+          M[5 * r + J] = s ? a : b;
+        }
+        const float a = z[k], b = z[r];
+        z[k] = s ? b : a;
+        z[r] = s ? a : b;
+      }
+    }
+    const float ip = __builtin_amdgcn_rcpf(M[6 * k]);
+    M[6 * k] = ip;
+#pragma unroll
+    for (int r = k + 1; r < 5; ++r) {
+      const float m = M[5 * r + k] * ip;
+#pragma unroll
+      for (int J = k + 1; J < 5; ++J) M[5 * r + J] -= m * M[5 * k + J];
+      z[r] -= m * z[k];
+    }
+  }
+#pragma unroll
+  for (int k = 4; k >= 0; --k) {
+#pragma unroll
+    for (int J = k + 1; J < 5; ++J) z[k] -= M[5 * k + J] * z[J];
+    z[k] *= M[6 * k];
+  }
+}
+
 // Newton step of the lane's slips: step = -J^-1 R.  J = diag(1/D) + h N V^T
 // with V_a = sym((Q s_a) (x) m_a), Q = G^T Gs, and N_a = C : sym(S0_a); in
-// the basis above, with C's square root on both factors, Woodbury's
-// capacitance matrix is the 5x5  1 + sum_a D_a h_a v_a (x) n_a.  v_a differs
-// from n_a by the elastic strain only, so the matrix is close to symmetric
-// and positive definite and is eliminated without pivoting.  The Jacobian
-// only steers the iteration (the root is that of the FP64 residual R): single
-// precision.
+// the basis above Woodbury's capacitance matrix is the 5x5
+// 1 + sum_a D_a h_a v_a (x) C n_a.  v_a differs from n_a by the elastic strain
+// only, so with D_a h_a >= 0 and moduli that are not negative the matrix is,
+// up to a diagonal similarity, which changes no pivot, close to symmetric
+// positive definite, and it is eliminated without pivoting.  Softening
+// back stresses (D_a h_a < 0) and other constants take row interchanges.
+// The Jacobian only steers the iteration (the root is that of the FP64
+// residual R): single precision.
 __device__ __forceinline__ void pr_step(const double* dg, const double* R,
                                         const float* hd, const float* Q,
                                         const double* chi0, const PlaneSigns& sg,
                                         const LawParams& lp, float a2, double* step) {
-  // basis components' signs and roots of the moduli
-  const float kd = sqrtf((float)lp.c11m12), ks = sqrtf(2.0f * (float)lp.c44);
+  // basis components' moduli, with their signs in the plane's frame
+  const float kd = (float)lp.c11m12, ks = 2.0f * (float)lp.c44;
   const float k5[5] = {kd, kd, flip(ks, sg.both(1, 2)), flip(ks, sg.both(0, 2)),
                        flip(ks, sg.both(0, 1))};
+  bool indefinite = !lp.definite;
   const float inv_g = (float)lp.inv_g, c_af = (float)lp.c_af, d_af = (float)lp.d_af;
   float M[25], V[3][5], D[3], z[5];
 #pragma unroll
@@ -427,17 +468,18 @@ __device__ __forceinline__ void pr_step(const double* dg, const double* R,
     const float dchi = (c_af - d_af * s * chi) * den;
     D[j] = __builtin_amdgcn_rcpf(rsqrtf(a2 + dgf * dgf) + hd[j] * inv_g * dchi);
     f[j] = hd[j] * inv_g * D[j];
+    indefinite = indefinite || f[j] < 0.0f;
     // Q s_j of (1 -1 0), (1 0 -1), (0 1 -1), in units of 1/sqrt 2
     constexpr int ps[3] = {0, 0, 1}, ms[3] = {1, 2, 2};
     const float q0 = Q[ps[j]] - Q[ms[j]], q1 = Q[3 + ps[j]] - Q[3 + ms[j]],
                 q2 = Q[6 + ps[j]] - Q[6 + ms[j]];
     // sym(q (x) (1 1 1)) in the basis, in units of 1/sqrt 6
     constexpr float r2 = 0.70710678118654752f, r6 = 0.40824829046386302f;
-    V[j][0] = kInvSqrt6f * k5[0] * r2 * (q0 - q1);
-    V[j][1] = kInvSqrt6f * k5[1] * r6 * (q0 + q1 - 2.0f * q2);
-    V[j][2] = kInvSqrt6f * k5[2] * r2 * (q1 + q2);
-    V[j][3] = kInvSqrt6f * k5[3] * r2 * (q0 + q2);
-    V[j][4] = kInvSqrt6f * k5[4] * r2 * (q0 + q1);
+    V[j][0] = kInvSqrt6f * r2 * (q0 - q1);
+    V[j][1] = kInvSqrt6f * r6 * (q0 + q1 - 2.0f * q2);
+    V[j][2] = flip(kInvSqrt6f * r2 * (q1 + q2), sg.both(1, 2));
+    V[j][3] = flip(kInvSqrt6f * r2 * (q0 + q2), sg.both(0, 2));
+    V[j][4] = flip(kInvSqrt6f * r2 * (q0 + q1), sg.both(0, 1));
     const float sj = -(float)R[j] * D[j];
     step[j] = -R[j] * (double)D[j];
 #pragma unroll
@@ -457,25 +499,10 @@ __device__ __forceinline__ void pr_step(const double* dg, const double* R,
     for (int J = 0; J < 5; ++J)
       M[5 * I + J] = (I == J ? 1.0f : 0.0f) + quad_sumf(M[5 * I + J] * (r12 * k5[J]));
   }
-  // z <- M^-1 z
-#pragma unroll
-  for (int k = 0; k < 5; ++k) {
-    const float ip = __builtin_amdgcn_rcpf(M[6 * k]);
-    M[6 * k] = ip;
-#pragma unroll
-    for (int r = k + 1; r < 5; ++r) {
-      const float m = M[5 * r + k] * ip;
-#pragma unroll
-      for (int J = k + 1; J < 5; ++J) M[5 * r + J] -= m * M[5 * k + J];
-      z[r] -= m * z[k];
-    }
-  }
-#pragma unroll
-  for (int k = 4; k >= 0; --k) {
-#pragma unroll
-    for (int J = k + 1; J < 5; ++J) z[k] -= M[5 * k + J] * z[J];
-    z[k] *= M[6 * k];
-  }
+  if (quad_any(indefinite))
+    solve5<true>(M, z);
+  else
+    solve5<false>(M, z);
 #pragma unroll
   for (int I = 0; I < 5; ++I) z[I] *= r12 * k5[I];
 #pragma unroll
@@ -729,13 +756,14 @@ __global__ __launch_bounds__(256) void rm_count_kernel(
 // and K is stored as D, S2 and F - 1 (kKComp entries per voxel): six strain
 // directions instead of nine gradients here, and 51 instead of 81 numbers
 // for every K:p (kp_apply).  In the lattice frame, A = Fp^-1 R:
-//   dS = Y^-1 (A^T dE A),   Y = C^-1 + sum_a f_a V_a (x) S0_a,
+//   dS = C Y^-1 (A^T dE A),   Y = 1 + sum_a f_a V_a (x) (C S0_a),
 //   dg_a = f_a S0_a : dS,   dS2 = A dS A^T - sum_a dg_a 2 sym(y_a (x) u_a),
 // y_a = Fp^-1_0 R s_a, u_a = A S m_a, f_a = (h_a/g) / (1/sqrt(a^2 + dg^2) +
 // (h_a/g) dchi/ddg), V_a = sym((G^T Gs s_a) (x) m_a).  In the orthonormal
-// basis of kSchmid5 completed by the trace, C^-1 is diagonal and S0_a has no
-// trace: Y is a 5x5 block, close to symmetric positive definite (eliminated
-// without pivoting), and one row for the trace, solved by substitution.
+// basis of kSchmid5 completed by the trace, C is diagonal and S0_a has no trace: Y is a
+// 5x5 block, close to symmetric positive definite up to a diagonal similarity
+// (eliminated without pivoting unless a constant or some f_a is negative), and
+// one row for the trace, solved by substitution.
 // FP64 up to the stress and the flow slopes, the rest in the precision of K.
 //
 // Bound by its instructions (about 2500 per voxel) and 540 B per voxel in
@@ -851,8 +879,10 @@ __device__ __forceinline__ void tangent_voxel(const TangentArgs<TK>& A, int64_t 
     for (int i = 0; i < 9; ++i) Fs[i] = TK(fs[i]);
   }
   // Phi: the basis tensors pushed forward by A (columns), in the order 11,
-  // 22, 33, 23, 13, 12; L starts as Phi and takes the plastic part
+  // 22, 33, 23, 13, 12; L starts as Phi C and takes the plastic part
   TK Phi[6][6], L[6][5], Y[25], yt[5];
+  const TK cd = TK(lp.c11m12), cs = TK(2.0 * lp.c44);
+  bool pivot = !lp.definite;
   {
     constexpr int vi[6] = {0, 1, 2, 1, 0, 0}, vj[6] = {0, 1, 2, 2, 2, 1};
     constexpr double r2 = 0.70710678118654752440, r3 = 0.57735026918962576451,
@@ -869,14 +899,14 @@ __device__ __forceinline__ void tangent_voxel(const TangentArgs<TK>& A, int64_t 
       Phi[I][4] = TK(r2 * (p[0] * q[1] + p[1] * q[0]));
       Phi[I][5] = TK(r3 * (w0 + w1 + w2));
 #pragma unroll
-      for (int k = 0; k < 5; ++k) L[I][k] = Phi[I][k];
+      for (int k = 0; k < 5; ++k) L[I][k] = Phi[I][k] * (k < 2 ? cd : cs);
     }
   }
 #pragma unroll
   for (int i = 0; i < 25; ++i) Y[i] = TK(0);
 #pragma unroll
   for (int i = 0; i < 5; ++i) {
-    Y[6 * i] = TK(i < 2 ? 1.0 / lp.c11m12 : 0.5 / lp.c44);
+    Y[6 * i] = TK(1);
     yt[i] = TK(0);
   }
 #pragma unroll
@@ -910,7 +940,9 @@ __device__ __forceinline__ void tangent_voxel(const TangentArgs<TK>& A, int64_t 
       const TK y0 = gp * Y0[ps[j]] - gm * Y0[ms[j]];
       const TK y1 = gp * Y0[3 + ps[j]] - gm * Y0[3 + ms[j]];
       const TK y2 = gp * Y0[6 + ps[j]] - gm * Y0[6 + ms[j]];
-      const TK fk = f * TK(k6), f12 = fk * TK(0.28867513459481288225);
+      pivot = pivot || f < TK(0);
+      const TK f12 = f * TK(k6 * 0.28867513459481288225);
+      const TK fd = f12 * cd, fs = f12 * cs;
       const TK w0 = g0 * q0, w1 = g1 * q1, w2 = g2 * q2;
       const TK V[5] = {TK(0.70710678118654752440) * (w0 - w1),
                        TK(k6) * (w0 + w1 - TK(2) * w2),
@@ -925,7 +957,7 @@ __device__ __forceinline__ void tangent_voxel(const TangentArgs<TK>& A, int64_t 
         const double c5 = kSchmid5d[j][k] *
                           (k == 2 ? g1 * g2 : (k == 3 ? g0 * g2 : (k == 4 ? g0 * g1 : 1)));
         if (c5 == 0.0) continue;
-        const TK fc = f12 * TK(c5);
+        const TK fc = (k < 2 ? fd : fs) * TK(c5);
 #pragma unroll
         for (int I = 0; I < 5; ++I) Y[5 * I + k] += V[I] * fc;
         yt[k] += Vt * fc;
@@ -935,8 +967,22 @@ __device__ __forceinline__ void tangent_voxel(const TangentArgs<TK>& A, int64_t 
     }
   }
   // eliminate Y (pivots' reciprocals on the diagonal)
+  unsigned swaps = 0;
 #pragma unroll
   for (int k = 0; k < 5; ++k) {
+    if (pivot) {
+#pragma unroll
+      for (int r = k + 1; r < 5; ++r) {
+        const bool s = fabs(Y[5 * r + k]) > fabs(Y[6 * k]);
+        swaps |= (s ? 1u : 0u) << (5 * k + r);
+#pragma unroll
+        for (int J = 0; J < 5; ++J) {
+          const TK a = Y[5 * k + J], b = Y[5 * r + J];
+          Y[5 * k + J] = s ? b : a;
+          Y[5 * r + J] = s ? a : b;
+        }
+      }
+    }
     const TK ip = TK(1) / Y[6 * k];
     Y[6 * k] = ip;
 #pragma unroll
@@ -952,11 +998,22 @@ __device__ __forceinline__ void tangent_voxel(const TangentArgs<TK>& A, int64_t 
   for (int J = 0; J < 6; ++J) {   // strain direction J (engineering shears)
     TK z[5], zt = Phi[J][5];
 #pragma unroll
-    for (int k = 0; k < 5; ++k) {
-      z[k] = Phi[J][k];
+    for (int k = 0; k < 5; ++k) z[k] = Phi[J][k];
+    if (swaps) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int r = k + 1; r < 5; ++r) {
+          const bool s = (swaps >> (5 * k + r)) & 1u;
+          const TK a = z[k], b = z[r];
+          z[k] = s ? b : a;
+          z[r] = s ? a : b;
+        }
+    }
+#pragma unroll
+    for (int k = 1; k < 5; ++k)
 #pragma unroll
       for (int r = 0; r < k; ++r) z[k] -= Y[5 * k + r] * z[r];
-    }
 #pragma unroll
     for (int k = 4; k >= 0; --k) {
 #pragma unroll
