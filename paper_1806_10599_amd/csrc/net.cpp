@@ -1,6 +1,5 @@
 // Warm-start network object: FP32 master parameters with Adam state, bf16
 // MFMA fragments, activation scratch sized for the largest grid seen.
-#include <algorithm>
 #include <cmath>
 
 #include "nn.hpp"
@@ -88,8 +87,7 @@ void Net::ensure_train(int64_t N) {
   d2_ = (uint16_t*)alloc(N * kWidth * sizeof(uint16_t));
   dy_ = (uint16_t*)alloc(N * kOut * sizeof(uint16_t));
   yf_ = (float*)alloc(N * kOut * sizeof(float));
-  // the chunks grow with N up to kMaxChunks, not always steadily
-  const size_t nch = std::min<int64_t>(kMaxChunks, N / 256);
+  const size_t nch = nn_wgrad_max_chunks(N);
   for (int k = 0; k < 4; ++k) {
     part_[k] = (float*)alloc(nch * 27 * kCIN[k] * kCOUT[k] * sizeof(float));
     bpart_[k] = (float*)alloc((k == 3 ? (size_t)kLossBlocks : nch) * kCOUT[k] *

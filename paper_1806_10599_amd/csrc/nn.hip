@@ -253,6 +253,14 @@ __global__ __launch_bounds__(256) void conv_mfma_kernel(
 // 27 x 32 x 32 partials per chunk).
 constexpr int kGroupVox = 256;
 constexpr int kWgThreads = 192;
+// An MFMA accumulator sums up to kRun groups, 64 products of 32 voxels.  A
+// block of more (96^3, 128^3) adds it to a second sum every kFlush groups and
+// starts again, at most 16 times (kMaxGroups), so that a term passes 48
+// roundings before the FP64 sum over the chunks; in one run it would pass 512
+// at 128^3 (a training step there 3.23 ms, with the second sum 3.37).
+constexpr int kRun = 8;
+constexpr int kFlush = 4;
+constexpr int kMaxGroups = 64;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
@@ -267,7 +275,7 @@ __device__ __forceinline__ bf16x8 join(bf16x4 a, bf16x4 b) {
   return __builtin_bit_cast(bf16x8, r);
 }
 
-template <int CIN, int COUT>
+template <int CIN, int COUT, bool LONG>
 __global__ __launch_bounds__(kWgThreads) void conv_wgrad_kernel(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ dZ,
     float* __restrict__ part, float* __restrict__ bpart, int n, unsigned inv_n,
@@ -296,6 +304,18 @@ __global__ __launch_bounds__(kWgThreads) void conv_wgrad_kernel(
     for (int d = 0; d < 3; ++d)
 #pragma unroll
       for (int a = 0; a < KC; ++a) acc[d][a][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  }
+  // LONG: what the accumulators are added to every kFlush groups
+  f32x4 sum[LONG ? 3 : 1][LONG ? KC : 1][LONG ? NT : 1], sumb[LONG ? NT : 1];
+  if constexpr (LONG) {
+#pragma unroll
+    for (int b = 0; b < NT; ++b) {
+      sumb[b] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int a = 0; a < KC; ++a) sum[d][a][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
   }
   const bf16x4 one4 = {0x3F80, 0x3F80, 0x3F80, 0x3F80};
   const bf16x8 ones = join(one4, one4);
@@ -354,6 +374,21 @@ __global__ __launch_bounds__(kWgThreads) void conv_wgrad_kernel(
           accb[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, b[nt], accb[nt],
                                                              0, 0, 0);
     }
+    if constexpr (LONG)
+      if ((g - g0) % kFlush == kFlush - 1 || g == g1 - 1) {
+        auto flush = [](f32x4& t, f32x4& x) {
+          t += x;
+          x = (f32x4){0.f, 0.f, 0.f, 0.f};
+        };
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          if (bias) flush(sumb[nt], accb[nt]);
+#pragma unroll
+          for (int d = 0; d < 3; ++d)
+#pragma unroll
+            for (int kc = 0; kc < KC; ++kc) flush(sum[d][kc][nt], acc[d][kc][nt]);
+        }
+      }
   }
   // D[4 grp + i][row] = dW[16 kc + 4 grp + i][16 nt + row]
 #pragma unroll
@@ -365,12 +400,15 @@ __global__ __launch_bounds__(kWgThreads) void conv_wgrad_kernel(
       for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          out[(16 * kc + 4 * grp + i) * COUT + 16 * nt + row] = acc[d][kc][nt][i];
+          out[(16 * kc + 4 * grp + i) * COUT + 16 * nt + row] =
+              LONG ? sum[LONG ? d : 0][LONG ? kc : 0][LONG ? nt : 0][i]
+                   : acc[d][kc][nt][i];
   }
   if (bias && grp == 0)
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
-      bpart[(size_t)blockIdx.x * COUT + 16 * nt + row] = accb[nt][0];
+      bpart[(size_t)blockIdx.x * COUT + 16 * nt + row] =
+          LONG ? sumb[LONG ? nt : 0][0] : accb[nt][0];
 }
 
 // loss L = mean over N*CREAL of (Y - T)^2 and dY = 2 (Y - T)/count, written
@@ -558,9 +596,16 @@ void nn_conv(int cin, int cout, int epi, const uint16_t* X, const uint16_t* Wf,
   throw Error(-1, "unsupported convolution shape");
 }
 
-// groups of 256 voxels per weight-gradient block, and the chunks that makes
+// groups of 256 voxels per weight-gradient block (as few as leave
+// kChunks chunks, at most kMaxGroups), and the chunks that makes
 static int wgrad_groups(int64_t N) {
-  return (int)((N / kGroupVox + kMaxChunks - 1) / kMaxChunks);
+  const int64_t g = (N / kGroupVox + kChunks - 1) / kChunks;
+  return (int)(g < kMaxGroups ? g : kMaxGroups);
+}
+int64_t nn_wgrad_max_chunks(int64_t N) {
+  const int64_t all = N / kGroupVox, few = all < kChunks ? all : kChunks;
+  const int64_t most = (all + kMaxGroups - 1) / kMaxGroups;
+  return few > most ? few : most;
 }
 int nn_wgrad_chunks(int64_t N) {
   const int g = wgrad_groups(N);
@@ -579,9 +624,13 @@ void nn_wgrad(int cin, int cout, const uint16_t* X, const uint16_t* dZ,
     hipLaunchKernelGGL(kernel, grid, dim3(kWgThreads), lds, s, X, dZ, part, bpart,
                        n, inv_edge(n), nl, wgrad_groups(N));
   };
-  if (cin == 48 && cout == 32) run(&conv_wgrad_kernel<48, 32>);
-  else if (cin == 32 && cout == 32) run(&conv_wgrad_kernel<32, 32>);
-  else if (cin == 32 && cout == 16) run(&conv_wgrad_kernel<32, 16>);
+  const bool lng = wgrad_groups(N) > kRun;
+  if (cin == 48 && cout == 32)
+    lng ? run(&conv_wgrad_kernel<48, 32, true>) : run(&conv_wgrad_kernel<48, 32, false>);
+  else if (cin == 32 && cout == 32)
+    lng ? run(&conv_wgrad_kernel<32, 32, true>) : run(&conv_wgrad_kernel<32, 32, false>);
+  else if (cin == 32 && cout == 16)
+    lng ? run(&conv_wgrad_kernel<32, 16, true>) : run(&conv_wgrad_kernel<32, 16, false>);
   else throw Error(-1, "unsupported weight-gradient shape");
 }
 

@@ -16,9 +16,11 @@ constexpr int kOutReal = 9, kOut = 16;
 void nn_conv(int cin, int cout, int epi, const uint16_t* X, const uint16_t* Wf,
              const float* b, uint16_t* Yb, float* Yf, const uint16_t* mask,
              int n, int64_t N, int cout_real, hipStream_t s);
-// voxel chunks (partials) of the weight gradient, at most kMaxChunks
-constexpr int kMaxChunks = 128;
+// voxel chunks (partials) of the weight gradient: kChunks, fewer on small
+// grids, more on very large ones; and the most of any grid up to N voxels
+constexpr int kChunks = 128;
 int nn_wgrad_chunks(int64_t N);
+int64_t nn_wgrad_max_chunks(int64_t N);
 void nn_wgrad(int cin, int cout, const uint16_t* X, const uint16_t* dZ,
               float* part, float* bpart, int n, int64_t N, hipStream_t s);
 void nn_mse(const float* Y, const float* T, int creal, int64_t N, uint16_t* dYb,
