@@ -19,6 +19,8 @@ namespace rve {
 
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+// four floats of a caller's array, aligned as floats are
+typedef f32x4 f32x4a __attribute__((aligned(4)));
 
 __device__ __forceinline__ uint16_t f2bf(float f) {
   // round to nearest even
@@ -220,7 +222,7 @@ __global__ __launch_bounds__(256) void conv_mfma_kernel(
 #pragma unroll
       for (int i = 0; i < 4; ++i) val[i] = acc[u][nt][i] + bv[i];
       if constexpr (EPI == 1) {
-        *reinterpret_cast<f32x4*>(Yf + o) = (f32x4){val[0], val[1], val[2], val[3]};
+        *reinterpret_cast<f32x4a*>(Yf + o) = (f32x4){val[0], val[1], val[2], val[3]};
       } else {
         ushort4 m;
         if constexpr (EPI == 2) m = *reinterpret_cast<const ushort4*>(mask_act + o);
@@ -428,7 +430,7 @@ __global__ __launch_bounds__(256) void mse_kernel(
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < N * (kOut / 4);
        i += (int64_t)gridDim.x * 256) {
     const f32x4 y = reinterpret_cast<const f32x4*>(Y)[i];
-    const f32x4 t = reinterpret_cast<const f32x4*>(T)[i];
+    const f32x4 t = reinterpret_cast<const f32x4a*>(T)[i];
     uint16_t r[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
