@@ -91,7 +91,6 @@ Engine::Engine(const rve_config& cfg) : cfg_(cfg) {
   r64_ = (double*)alloc(f9);
   dFt_prev_ = (double*)alloc(f9);
   dFt_pp_ = (double*)alloc(f9);
-  K_ = alloc(kKComp * N_ * tsz);
   rho_ = alloc(3 * N_ * tsz);
   pi_ = alloc(3 * N_ * tsz);
   xi_ = alloc(3 * N_ * tsz);
@@ -112,7 +111,7 @@ Engine::Engine(const rve_config& cfg) : cfg_(cfg) {
   RVE_HIP(hipMemsetAsync(sc_, 0, sizeof(Scalars), st_));
   // the timed iterations of the schedule tuner may read these before the
   // solver writes them: start from zeros
-  RVE_HIP(hipMemsetAsync(K_, 0, kKComp * N_ * tsz, st_));
+  stored_tangent();
   for (void* f : {rho_, pi_, xi_})
     RVE_HIP(hipMemsetAsync(f, 0, 3 * N_ * tsz, st_));
   for (void* f : {p_, Kp_}) RVE_HIP(hipMemsetAsync(f, 0, 9 * N_ * tsz, st_));
@@ -226,6 +225,8 @@ void Engine::set_microstructure(const int32_t* phase, int32_t G,
   if (!(params_[3] > 0 && params_[4] > 0 && params_[5] >= 1 && params_[7] >= 0))
     throw Error(RVE_EINVAL, "bad flow-rule parameters");
   set_preconditioner(cg_preconditioner(params_));
+  release_tangent(Kfull_);
+  stored_tangent();
   std::vector<double> tab = label_table(G, quat, law, params_);
   if (G > labels_) {
     table_ = (double*)alloc(tab.size() * sizeof(double));
@@ -301,6 +302,8 @@ void Engine::set_user_material(rve_umat_fn fn, void* user, int32_t nstatev,
   if (!fn) throw Error(RVE_EINVAL, "null user material");
   if (nstatev < 0 || nstatev > 1024) throw Error(RVE_EINVAL, "nstatev out of [0, 1024]");
   if (nstatev > 0 && !statev0) throw Error(RVE_EINVAL, "null initial state variables");
+  drop_graph();   // it holds the stored tangent
+  release_tangent(K_);
   full_tangent();
   if (!usig_) {
     usig_ = (double*)alloc(6 * N_ * sizeof(double));
@@ -424,7 +427,6 @@ void Engine::tangent(double dt) {
   a.dg = dg_t_;
   a.phase = phase_;
   a.table = table_;
-  a.K = (T*)K_;
   a.lp = law_params(dt);
   a.order = order_;
   a.N = N_;
@@ -433,6 +435,8 @@ void Engine::tangent(double dt) {
     launch_umat_tangent<T>(F_, usig_, udds_, N_, (T*)Kfull_, st_);
     return;
   }
+  stored_tangent();   // gone if a user material could not be set
+  a.K = (T*)K_;
   timer_.begin(5, st_);
   launch_tangent<T>(a, st_);
   timer_.end(5, st_);
@@ -576,6 +580,7 @@ void Engine::autotune() {
       if (schedule_valid(n_, dbl, cpb, cg_tile(n_)) &&
           (n_ <= 16 || (cpb == 1 && !fused)))
         cand.push_back({cpb, cg_tile(n_), fused});
+  if (!umat_fn_) stored_tangent();
   // alpha = 0 in every slot: the timed passes leave the residual unchanged;
   // a solve that broke down may have left an infinite direction, and 0 times
   // that would reach the residual
@@ -621,12 +626,25 @@ void Engine::drop_graph() {
   timer_.recycle(graph_pairs_);
 }
 
-// room for dP/dF (a user material's tangent, the test hook's)
+// Room for the tangent: dP/dF of a user material (and of the test hook), the
+// stored form of a crystal.  A handle holds the one that its material needs.
+void* Engine::tangent_room(int comps) {
+  const size_t bytes = comps * N_ * (fp64_ ? sizeof(double) : sizeof(float));
+  void* p = alloc(bytes);
+  RVE_HIP(hipMemsetAsync(p, 0, bytes, st_));   // the tuner may read it
+  return p;
+}
 void Engine::full_tangent() {
-  if (Kfull_) return;
-  const size_t bytes = kKFull * N_ * (fp64_ ? sizeof(double) : sizeof(float));
-  Kfull_ = alloc(bytes);
-  RVE_HIP(hipMemsetAsync(Kfull_, 0, bytes, st_));   // the tuner may read it
+  if (!Kfull_) Kfull_ = tangent_room(kKFull);
+}
+void Engine::stored_tangent() {
+  if (!K_) K_ = tangent_room(kKComp);
+}
+void Engine::release_tangent(void*& K) {
+  if (!K) return;
+  RVE_HIP(hipStreamSynchronize(st_));
+  release(K);
+  K = nullptr;
 }
 
 void Engine::set_preconditioner(double prec) {

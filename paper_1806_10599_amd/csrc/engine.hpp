@@ -110,7 +110,10 @@ class Engine {
   void swap_trial_sets();
   void reset_macro_state();
   void drop_graph();
+  void* tangent_room(int comps);
   void full_tangent();
+  void stored_tangent();
+  void release_tangent(void*& K);
   void set_preconditioner(double prec);
   // copy of the committed state (device arrays and host macro state) for
   // the rollback of a failed adaptive step
@@ -130,7 +133,8 @@ class Engine {
   double *pcyc_, *pcyc_lit_, *wcyc_;
   // Newton scratch
   double *F_, *P_, *Fpi_t_, *chi_t_, *dg_t_, *r64_;
-  void* K_;      // stored tangent [51][N] float (mixed) or double (fp64)
+  // stored tangent [51][N] of a crystal, float (mixed) or double (fp64)
+  void* K_ = nullptr;
   void* Kfull_ = nullptr;   // dP/dF [81][N] of a user material
   // CG vectors in Fourier space ([3][n][n][n/2] complex T): residual,
   // direction, iterate; the direction and K : p in real space
