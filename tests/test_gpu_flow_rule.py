@@ -133,3 +133,12 @@ def test_back_stress_beyond_saturation(n):
     """A committed back stress above c/d relaxes: the slips' slopes are
     negative although every constant is positive."""
     _compare(n, material_params(), 150.0, -3.2, 29, 1 if n == 16 else 13)
+
+
+@pytest.mark.parametrize("n", [16, 32, 40])   # 32^3: the last of a launch rule
+@pytest.mark.parametrize("n_exp", [1.0, 3.0, 12.5, 50.0])
+def test_state_and_tangent_over_exponents(n, n_exp):
+    """P, slips and consistent tangent from a state with plastic strain and
+    back stress, for exponents by products and by logarithms; on 32^3 and 40^3
+    grains and particles share wavefronts."""
+    _compare(n, material_params(n_exp=n_exp), 60.0, -3.2, 31, 1 if n == 16 else 13)
