@@ -76,8 +76,7 @@ inline void launch(F kernel, dim3 grid, dim3 block, uint32_t lds,
 
 // Device-side scalars of one CG solve (and the residual norms).
 struct Scalars {
-  double rr;        // r.r of the current CG residual
-  double rr_new;
+  double rr_new;    // r.r of the current CG residual
   double pAp;
   double alpha;
   double beta;
@@ -90,11 +89,9 @@ struct Scalars {
   int32_t breakdown;
   int32_t iters;
   int32_t max_iters;
-  int32_t first;    // next pass-A call starts a new direction p = r
   int32_t fails;    // return-mapping failures of the last evaluation
   int32_t inactive;  // batch: this RVE takes no part in the current work
   int32_t commit;    // batch: commit this RVE's trial state
-  int32_t pad;
   double pbar[9];   // <P> of the last residual evaluation
   // CG iteration k has parity k & 1; slot q holds r.r and the number of
   // completed updates published by the direction kernel of parity q

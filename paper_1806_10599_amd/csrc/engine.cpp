@@ -865,13 +865,12 @@ int Engine::increment(const double Fbar_new[9], double dt,
     }
     if (res <= cfg_.newton_tol * pn) {
       commit(dt);
-      double s2 = 0.0, dot = 0.0;
+      double s2 = 0.0;
       for (int i = 0; i < 9; ++i) s2 += dF[i] * dF[i];
       for (int i = 0; i < 9; ++i) {
         Fbar_[i] = Fbar_new[i];
         dFbar_pp_[i] = dFbar_prev_[i];
         dFbar_prev_[i] = dF[i];
-        (void)dot;
       }
       s_pp_ = s_prev_;
       s_prev_ = std::sqrt(s2);

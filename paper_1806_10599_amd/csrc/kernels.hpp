@@ -240,12 +240,11 @@ void batch_allow_lds(size_t slab, size_t pencil);
 // ---------------------------------------------------------- constitutive
 // Per-label table, kTableStride doubles per label:
 //   [0] law (0 crystal, 1 isotropic SVK)
-//   crystal: s[12][3] at kTabS, m[12][3] at kTabM, Nsym[12][6] at kTabN
-//            (C : sym(S0) in Voigt order 11,22,33,23,13,12), Cv[6][6] at
-//            kTabC (C_IJ in the same order), orientation R[3][3] at kTabR
+//   crystal: s[12][3] at kTabS, m[12][3] at kTabM, Cv[6][6] at kTabC (C_IJ in
+//            Voigt order 11,22,33,23,13,12), orientation R[3][3] at kTabR
 //   SVK: lambda at kTabLam, mu at kTabMu
-constexpr int kTableStride = 200;
-constexpr int kTabS = 8, kTabM = 44, kTabN = 80, kTabC = 152, kTabR = 188;
+constexpr int kTableStride = 128;
+constexpr int kTabS = 8, kTabM = 44, kTabC = 80, kTabR = 116;
 constexpr int kTabLam = 8, kTabMu = 9;
 
 struct LawParams {

@@ -40,9 +40,6 @@ constexpr double LOCAL_RTOL = 1e-10;
 constexpr double LOCAL_ATOL = 1e-18;
 constexpr double LOCAL_RFLOOR = 1e-10;
 
-// Voigt order 11, 22, 33, 23, 13, 12
-__device__ constexpr double VW[6] = {1, 1, 1, 2, 2, 2};
-
 // Hides an offset of zero from the optimizer so that table entries are
 // re-read (from cache) at each use instead of being hoisted out of the local
 // Newton loop into registers, which would exhaust the register file.  The

@@ -125,13 +125,12 @@ std::vector<double> label_table(int G, const double* quat, const int32_t* law,
     quat_rotation(qn, R);
     for (int i = 0; i < 3; ++i)
       for (int j = 0; j < 3; ++j) t[kTabR + 3 * i + j] = R[i][j];
-    double s[12][3], m[12][3];
     for (int a = 0; a < 12; ++a)
       for (int i = 0; i < 3; ++i) {
-        s[a][i] = R[i][0] * s0[a][0] + R[i][1] * s0[a][1] + R[i][2] * s0[a][2];
-        m[a][i] = R[i][0] * m0[a][0] + R[i][1] * m0[a][1] + R[i][2] * m0[a][2];
-        t[kTabS + 3 * a + i] = s[a][i];
-        t[kTabM + 3 * a + i] = m[a][i];
+        t[kTabS + 3 * a + i] =
+            R[i][0] * s0[a][0] + R[i][1] * s0[a][1] + R[i][2] * s0[a][2];
+        t[kTabM + 3 * a + i] =
+            R[i][0] * m0[a][0] + R[i][1] * m0[a][1] + R[i][2] * m0[a][2];
       }
     // sample-frame stiffness C_ijkl = R_ia R_jb R_kc R_ld Cl_abcd
     double Cs[3][3][3][3];
@@ -151,16 +150,6 @@ std::vector<double> label_table(int G, const double* quat, const int32_t* law,
       for (int J = 0; J < 6; ++J)
         t[kTabC + 6 * I + J] =
             Cs[kVoigt[I][0]][kVoigt[I][1]][kVoigt[J][0]][kVoigt[J][1]];
-    // N_a = C : sym(s_a (x) m_a), Voigt
-    for (int a = 0; a < 12; ++a)
-      for (int I = 0; I < 6; ++I) {
-        const int i = kVoigt[I][0], j = kVoigt[I][1];
-        double acc = 0.0;
-        for (int k = 0; k < 3; ++k)
-          for (int l = 0; l < 3; ++l)
-            acc += Cs[i][j][k][l] * 0.5 * (s[a][k] * m[a][l] + s[a][l] * m[a][k]);
-        t[kTabN + 6 * a + I] = acc;
-      }
   }
   return tab;
 }
