@@ -595,8 +595,8 @@ rve_status rve_batch_debug_apply_G(rve_batch_t h, const double* in,
                                    double* out);
 /* Per-grid-edge schedule of the batched CG matvec (Sec. 2.1, Eqs. 15-16):
    cpb components per slab block (1 or 3) and tt kz columns per pencil block
-   (4, 8 or 16), as for a single RVE (K : p is always formed inside the
-   forward transform in a batch).  Unless forced, every edge of the batch is
+   (4, 8 or 16), as for a single RVE (K : p always runs in its own kernel in
+   a batch).  Unless forced, every edge of the batch is
    tuned at the first increment (or by rve_batch_tune_fft_schedule): each
    candidate times one CG iteration of that edge's RVEs alone through the
    batched passes, and the fastest is kept.  rve_batch_set_fft_schedule

@@ -1,8 +1,8 @@
 // Device-side CG scalar logic (text after Eq. 16: alpha = r.z / p.Ap,
 // beta = r_new.z_new / r.z, z the preconditioned residual, stop at
-// ||r|| <= eta ||b|| or p.Ap <= 0; the single-RVE path forms p.Ap as
-// p.(K:p), see cg_alpha_publish) and the fixed-order reductions of the
-// per-block partial sums.
+// ||r|| <= eta ||b|| or p.Ap <= 0; p.Ap is formed as p.(K:p), see
+// cg_alpha_publish and cg_alpha_consume) and the fixed-order reductions of
+// the per-block partial sums.
 #pragma once
 
 #include "common.hpp"

@@ -551,11 +551,11 @@ namespace {
 // on there are enough of them and a staged weight serves four tiles (86 / 73
 // us at 48^3, 154 / 119 us at 64^3, 1500 / 820 us at 128^3).
 constexpr int kConvSmall = 32;
-// largest grid edge: the staged lines of 48 channels fit in LDS
+// largest grid edge that is taken: the fragments and staged lines of 48
+// channels take 144 KB of a CU's 160 there
 constexpr int kConvMaxEdge = 304;
 
-// dynamic LDS above 64 KiB is allowed per kernel (the attribute only raises
-// the cap)
+// dynamic LDS above 64 KiB is allowed per kernel before its launch
 void allow_lds(const void* f, size_t lds) {
   if (lds > 64 * 1024)
     RVE_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -1,25 +1,26 @@
 // The linear map G(A) = F^-1{ Ghat : F(A) } of Sec. 2.1, Eqs. 10-11, and the
-// CG matvec G(K : p) of Eqs. 15-16, as three passes over a cubic grid of N^3
-// voxels:
+// CG iteration on G(K : p) of Eqs. 15-16 over a cubic grid of N^3 voxels:
 //
-//   pass A (one block per x-slab and component group): build the real plane
-//     (the field itself, or K:p with the CG direction update fused in), pack
-//     rows y and y + N/2 as one complex line, FFT along z, unpack the two
-//     half spectra in place (kz < N/2; the kz = N/2 Nyquist plane is zeroed
-//     by the operator, so its slots hold the kz = 0 column's second half),
-//     FFT along y, store the spectrum [c][x][ky][kz] (kz < N/2).
-//   pass B (one block per ky and a tile of kz, for one tensor row i): FFT
-//     along x of the three components of row i, apply the projection
-//     Bhat_ij = v_j (sum_l Ahat_il v_l) / |v|^2 (zero at the null frequency
-//     and wherever a component is Nyquist; Sec. 2.2, Eqs. 18-21), fold in
-//     the 1/N^3 of the inverse transform, inverse FFT along x.
-//   pass C (one block per x-slab and component group): inverse of pass A,
-//     writing the real field and a per-block FP64 partial (||out||^2, or the
-//     batched CG's dot p . Ap), or, in a single-RVE CG iteration, applying
-//     r -= alpha G(K:p) in place with the partials of the new r . r.
+//   forward slabs, pass A (one block per x-slab and component group): the
+//     field, or K:p formed on the spot (SRC_KROW); rows y and y + N/2 packed
+//     as one complex line, FFT along z, the two half spectra unpacked in
+//     place (kz < N/2; the kz = N/2 Nyquist plane is zeroed by the operator,
+//     so its slots hold the kz = 0 column's second half), FFT along y, the
+//     spectrum stored as [c][x][ky][kz] (kz < N/2);
+//   inverse slabs, pass C: the inverse, from two planes per tensor row;
+//     writes the real field, or adds it to F at the end of a solve.
+//   Between them, for a field (pencil_body, one block per ky, tile of kz and
+//   tensor row): FFT along x, the projection Bhat_ij = v_j (sum_l Ahat_il
+//   v_l) / |v|^2 (zero at the null frequency and wherever a component is
+//   Nyquist; Sec. 2.2, Eqs. 18-21) with the 1/N^3 of the inverse transform,
+//   inverse FFT along x.
+//   A CG iteration, whose vectors stay in Fourier space, runs
+//     direction pencils (pencil_inv_body: x += alpha p, p = z + beta p,
+//     inverse FFT along x), inverse slabs (p), K:p, forward slabs, residual
+//     pencils (pencil_fwd_body: FFT along x, r -= alpha G(K:p), r.r, r.z).
 //
 // Only the delta_ik structure of the operator is used: row i of the output
-// depends on row i of the input, so pass B never needs all nine components.
+// depends on row i of the input.
 #include "cg_scalars.hpp"
 #include "common.hpp"
 #include "fft.hpp"
@@ -876,8 +877,7 @@ __global__ __launch_bounds__(kBlock) void pencil_proj_kernel(PencilArgs<T> a) {
 // twiddles that it needs, block 0 also writes them and the wave vectors
 // (Sec. 2.2, Eq. 18; continuous Eq. 19: v = q n / L, discrete Eqs. 20-21:
 // v = tan(q / 2) n / L; the Nyquist entry is never used and is set to 0) for
-// the passes that follow.  A launch of its own for them cost 4 us of the 18
-// of a 16^3 projection.
+// the passes that follow: three launches instead of four.
 template <int N>
 __global__ __launch_bounds__((kSlabThreads<double, N>)) void slab_fwd_tables_kernel(
     SlabFwdArgs<double> a, ProjTables p) {
@@ -955,7 +955,10 @@ __global__ __launch_bounds__((kSlabThreads<T, N>)) void slab_inv_kernel(
                                         tw, red, a.sc);
 }
 
-// three component planes per slab block fit the LDS budget of one block
+// The schedules that exist (rve_set_fft_schedule): three component planes per
+// slab block up to 64 KiB of LDS, so that two blocks share a CU; sixteen kz
+// columns per pencil block where three lines of them stay below 64 KiB, which
+// gives the six of a CG pencil at most 107 KB of a CU's 160 (128^3 FP32).
 template <typename T, int N>
 constexpr bool cpb3_fits() {
   return 3 * SlabGeom<N>::PLANE * (int)sizeof(cplx<T>) <= 64 * 1024;
@@ -989,6 +992,9 @@ __device__ __forceinline__ int batch_item(const BatchSpec<T>& b, int pass,
   return __builtin_amdgcn_readfirstlane(r);
 }
 
+// Blocks of 256 threads at every edge, since one launch holds several: the
+// 512 of a single RVE's slabs at 48^3 (kSlabThreads) are too many for its
+// smaller neighbours; not timed in a batch of 48^3 alone.
 // Each pass as a block body (blk: the block it plays, a launch's blockIdx.x
 // or a virtual block of the persistent CG kernel) and a one-launch kernel.
 // CPBS: the slab schedules compiled in (bit 0: one component per block,
