@@ -329,7 +329,7 @@ void Engine::set_user_material(rve_umat_fn fn, void* user, int32_t nstatev,
   RVE_HIP(hipGetLastError());
   RVE_HIP(hipStreamSynchronize(st_));
   reset_macro_state();
-  set_preconditioner(0.0);   // nothing is known of the material: plain CG
+  set_preconditioner(kPrecUnknown);
   umat_fn_ = fn;
   umat_user_ = user;
   nsv_ = nstatev;
