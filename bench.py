@@ -79,7 +79,7 @@ def live_classes(fused):
 # capacitance matrix, its elimination, the Woodbury solve; FP64 step and
 # convergence tests), per crystal voxel (set-up, final Fp^-1 and P) and per
 # particle voxel
-RM_FLOPS = {"eval64": 770, "eval32": 130, "step64": 60, "step32": 1380,
+RM_FLOPS = {"eval64": 970, "eval32": 85, "step64": 60, "step32": 1320,
             "crystal64": 825, "particle64": 90}
 # kernel classes timed live in the timed region: the K:p kernel
 # (the dominant kernel, on a sample of its launches) and the return mapping

@@ -65,7 +65,7 @@ __device__ __forceinline__ void kp_apply(const T* K, const T* p, T* y) {
 // materials); else the stored form of the crystal tangent (kp_apply.hpp).
 // The stop flag of the run is tested once the voxel's loads are issued.
 // Bound by HBM, at 64^3 by the last-level cache: 276 B per voxel in FP32 take
-// 12.4 us at 64^3 (5.8 TB/s) and 119 us at 128^3 (4.9 TB/s); 81 components
+// 12.8 us at 64^3 (5.7 TB/s) and 116 us at 128^3 (5.0 TB/s); 81 components
 // took 17.5 and 167 us.
 template <typename T, bool FULL>
 __device__ __forceinline__ double kp_voxel(const T* __restrict__ K,

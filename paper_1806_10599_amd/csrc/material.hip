@@ -19,9 +19,9 @@
 //
 // The 12x12 Jacobian is diag(D) + U W^T with low-rank factors (the resolved
 // stresses depend on the slips only through the symmetric elastic strain,
-// and not on its trace), so each Newton step costs one 5x5 solve and each
-// tangent column one 6x6 solve (Sherman-Morrison-Woodbury) instead of a
-// 12x12 one.
+// and not on its trace), so each Newton step costs one 5x5 solve and the
+// tangent one 5x5 factorisation (Sherman-Morrison-Woodbury) instead of 12x12
+// ones.
 //
 // Work order: crystal voxels first, then the particle voxels (an index list
 // built with the microstructure), so that wavefronts iterating the local
@@ -579,9 +579,9 @@ __device__ __forceinline__ bool pr_local_solve(const double* Gs,
 
 // Bound by the issue of the local iteration (about 1000 vector instructions
 // per Newton step and residual, a third of them FP64, for the sixteen voxels
-// of a wavefront): 64^3, 5.6 evaluations per voxel, 665 us in the sample frame
-// with tables -> 246 us; 32^3 122 -> 57, 16^3 82 -> 34 us.  The 178 MB of a
-// 64^3 launch would take 35 us.
+// of a wavefront): after three tensile increments of 3e-4, in the sample frame
+// with tables / now: 128^3 5350 / 1745 us, 64^3 719 / 250, 32^3 115 / 50, 16^3
+// 86 / 34.  The 178 MB of a 64^3 launch would take 35 us.
 template <bool INTN, int BLK, int WAVES>
 __global__ __launch_bounds__(BLK, WAVES) void return_map_kernel(ConstArgs A) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -757,16 +757,18 @@ __global__ __launch_bounds__(256) void rm_count_kernel(
 //   dg_a = f_a S0_a : dS,   dS2 = A dS A^T - sum_a dg_a 2 sym(y_a (x) u_a),
 // y_a = Fp^-1_0 R s_a, u_a = A S m_a, f_a = (h_a/g) / (1/sqrt(a^2 + dg^2) +
 // (h_a/g) dchi/ddg), V_a = sym((G^T Gs s_a) (x) m_a).  In the orthonormal
-// basis of kSchmid5 completed by the trace, C is diagonal and S0_a has no trace: Y is a
-// 5x5 block, close to symmetric positive definite up to a diagonal similarity
-// (eliminated without pivoting unless a constant or some f_a is negative), and
-// one row for the trace, solved by substitution.
-// FP64 up to the stress and the flow slopes, the rest in the precision of K.
+// basis of kSchmid5 completed by the trace, C is diagonal and S0_a has no
+// trace: Y is a 5x5 block, close to symmetric positive definite up to a
+// diagonal similarity (eliminated without pivoting unless a constant or some
+// f_a is negative), and one row for the trace, solved by substitution.
+// Frames, stresses, the basis pushed forward and f_a in FP64, the rest in the
+// precision of K.
 //
 // Bound by its instructions (about 2500 per voxel) and 540 B per voxel in
-// FP32.  64^3: 330 us with nine Woodbury solves per voxel on table entries
-// (448 B of scratch per lane) -> 52 us, 128^3 2430 -> 435 us; three wavefronts
-// per SIMD need 464 B of scratch per lane and take 115 us at 64^3.
+// FP32.  64^3: 307 us with nine Woodbury solves per voxel on table entries
+// (448 B of scratch per lane) -> 44 us, 128^3 2350 -> 431 us, 64^3 in FP64 401
+// -> 71 us; three wavefronts per SIMD need 464 B of scratch per lane and took
+// 115 us where two took 52.
 constexpr int kPlaneSign[4][3] = {{1, 1, 1}, {-1, 1, 1}, {1, -1, 1}, {1, 1, -1}};
 constexpr int kPlaneSlip[4][3] = {{0, 1, 2}, {4, 5, 3}, {7, 6, 8}, {9, 10, 11}};
 constexpr int kPlaneFlip[4][3] = {{1, 1, 1}, {-1, -1, 1}, {1, 1, -1}, {1, 1, 1}};
@@ -1058,11 +1060,13 @@ __global__ __launch_bounds__(256) void expand_tangent_kernel(
   }
 }
 
-// Three wavefronts per SIMD at 72 bytes of scratch beat two without once the
-// grid fills them (64^3 242 against 255 us, four with 208 bytes 318 us); up
-// to 32^3, whose wavefronts are two per SIMD in all, two without scratch are
-// faster (32^3 55 against 57.5 us, 16^3 34 against 39 us), in blocks of one
-// wavefront so that the smallest grids reach every CU.
+// Three wavefronts per SIMD (166 registers) beat two once the grid fills them
+// (64^3 253 against 279 us, 40^3 89 against 96 us); up to 32^3, whose
+// wavefronts are two per SIMD in all, they bring nothing (32^3 49.3 against
+// 50.6 us, 24^3 44.6 against 43.4, 16^3 35.8 against 34.9), and blocks of one
+// wavefront let the smallest grids reach every CU.  For an exponent that is no
+// integer two are faster by a fifth up to 32^3 (32^3 89 against 105 us), three,
+// with 168 bytes of scratch, slower by a tenth above (64^3 488 against 450 us).
 template <bool INTN>
 static void return_map_sized(const ConstArgs& a, hipStream_t s) {
   if (a.N <= 32768)
